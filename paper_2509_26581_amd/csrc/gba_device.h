@@ -255,6 +255,60 @@ __device__ __forceinline__ T wave_sum(T v) {
     return lane63(v);
 }
 
+// Sums over the wavefront (every lane active) of N values per lane, each
+// left in one lane: value u ends in register u / 64 of lane rev6(u % 64).
+// Every step halves the number of values: of a pair, one half of the lanes
+// goes on with the first and the other half with the second (permlane swaps
+// across 32 and 16 lanes, DPP moves inside a row of 16), so N sums take about
+// 2 N additions' worth of instructions where N separate wave_sum take 12 N.
+__device__ __forceinline__ int rev6(int l) { return (int)(__brev((unsigned)l) >> 26); }
+
+template <int kHalf>
+__device__ __forceinline__ float swap_add(float a, float b) {
+    const auto r = kHalf == 32
+                       ? __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false)
+                       : __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <int kHalf>
+__device__ __forceinline__ double swap_add(double a, double b) {
+    const unsigned al = (unsigned)__double2loint(a), ah = (unsigned)__double2hiint(a);
+    const unsigned bl = (unsigned)__double2loint(b), bh = (unsigned)__double2hiint(b);
+    const auto lo = kHalf == 32 ? __builtin_amdgcn_permlane32_swap(al, bl, false, false)
+                                : __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+    const auto hi = kHalf == 32 ? __builtin_amdgcn_permlane32_swap(ah, bh, false, false)
+                                : __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+// within a row: lanes with `second` go on with b, the others with a
+template <int kCtrl, typename T>
+__device__ __forceinline__ T pair_add(T a, T b, bool second) {
+    return (second ? b : a) + SegScan::move<kCtrl, 0xF>(second ? a : b);
+}
+
+template <typename T, int N>
+__device__ __forceinline__ void wave_sum_scatter(T (&v)[N]) {
+    const int l = lane_id();
+    constexpr int n1 = (N + 1) / 2, n2 = (n1 + 1) / 2, n3 = (n2 + 1) / 2, n4 = (n3 + 1) / 2,
+                  n5 = (n4 + 1) / 2, n6 = (n5 + 1) / 2;
+#pragma unroll
+    for (int k = 0; k < n1; ++k) v[k] = swap_add<32>(v[2 * k], 2 * k + 1 < N ? v[2 * k + 1] : (T)0);
+#pragma unroll
+    for (int k = 0; k < n2; ++k) v[k] = swap_add<16>(v[2 * k], 2 * k + 1 < n1 ? v[2 * k + 1] : (T)0);
+#pragma unroll
+    for (int k = 0; k < n3; ++k)   // row_ror:8
+        v[k] = pair_add<0x128>(v[2 * k], 2 * k + 1 < n2 ? v[2 * k + 1] : (T)0, (l & 8) != 0);
+#pragma unroll
+    for (int k = 0; k < n4; ++k)   // row_half_mirror
+        v[k] = pair_add<0x141>(v[2 * k], 2 * k + 1 < n3 ? v[2 * k + 1] : (T)0, (l & 4) != 0);
+#pragma unroll
+    for (int k = 0; k < n5; ++k)   // quad_perm [2,3,0,1]
+        v[k] = pair_add<0x4E>(v[2 * k], 2 * k + 1 < n4 ? v[2 * k + 1] : (T)0, (l & 2) != 0);
+#pragma unroll
+    for (int k = 0; k < n6; ++k)   // quad_perm [1,0,3,2]
+        v[k] = pair_add<0xB1>(v[2 * k], 2 * k + 1 < n5 ? v[2 * k + 1] : (T)0, (l & 1) != 0);
+}
+
 // Block-wide sum; every thread gets the result.  `red` holds >= 16 values.
 template <typename T>
 __device__ __forceinline__ T block_sum(T v, T* red) {

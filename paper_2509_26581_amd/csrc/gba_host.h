@@ -37,7 +37,12 @@ struct HostProblem {
 struct ImageCounts {
     int nc = 0, np = 0, ne = 0, n_tiles = 0, n_runs = 0, n_chunks = 0;
     bool info = false;
+    bool reduced = false;   // the PCG runs on the explicit reduced system
 };
+
+// Whether a problem's explicit reduced system is formed (see gba_host.hip)
+struct Tuning;
+bool reduced_rule(const ImageCounts& n, const Tuning& tune);
 
 // Sorted image of one problem, problem-local indices.  Edge arrays are
 // point-major (by point, then camera, then insertion) unless prefixed cm_
@@ -98,6 +103,12 @@ struct UnionPlan {
     bool cam_blocks = false;   // the camera-blocked product pass (one problem)
     int bo_nblk = 0, bo_chunk_cap = 0;   // its blocks, and a bound on its chunks
     int bo_target = 1;         // edges per chunk aimed at
+    // explicit reduced systems: offsets of S (entries, negative: none) and of
+    // the rank bitmaps per problem, totals, cameras of the largest
+    std::vector<long long> xs_off, xs_rank_off;
+    long long xs_total = 0, xs_rank_total = 0;
+    int xs_cams = 0;
+    bool xs_all = false;
     std::vector<int> cam_prob, pt_prob;   // problem of each union camera / point
 };
 
@@ -172,6 +183,8 @@ struct Batch {
     int jacobian = 0;               // GBA_JACOBIAN_* of the linearisation (options)
     // Hpp / bp of the current layout cleared once (points without edges keep 0)
     bool blocks_zeroed = false;
+    bool reduced_built = false;     // rank bitmaps of the current layout filled
+    bool launched_products = false; // keep to the launched PCG iterations (gba_eval_step)
     // pinned host mirrors of the per-problem device arrays (capacity h_cap)
     int h_cap = 0;
     TrialScalars* h_scal = nullptr;

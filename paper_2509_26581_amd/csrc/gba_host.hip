@@ -246,6 +246,18 @@ gba_status make_image(const HostProblem& h, HostImage& img, std::string& msg) {
 }
 
 // ---------------------------------------------------------------- planning
+// The explicit reduced system (gba_reduced.hip): when the camera sums are
+// left to the library, the points are eliminated, no camera observes a point
+// twice (the rank bitmaps hold one edge per camera and point) and S has at
+// most kReducedMax rows.  A launched PCG iteration takes 14-16 us for small
+// problems whatever their size; one workgroup's iteration on S takes 1.3 us at
+// 10 cameras and about 4 us at 40 (S then comes from the L2 in part), and
+// forming S 7-14 us once per step.
+bool reduced_rule(const ImageCounts& n, const Tuning& tune) {
+    if (tune.accumulation != GBA_ACC_AUTO || tune.deterministic || tune.solver == GBA_SOLVER_FULL) return false;
+    return n.nc > 0 && n.ne > 0 && n.n_runs == n.ne && 9 * n.nc <= kReducedMax;
+}
+
 namespace {
 
 // Problem-aligned decomposition of item ranges [off[p], off[p+1]) into
@@ -404,6 +416,21 @@ gba_status plan_union(const std::vector<const ImageCounts*>& probs, const Tuning
         return GBA_ERR_UNSUPPORTED;
     }
     u.part_total = part;
+    u.xs_off.assign(P, -1);
+    u.xs_rank_off.assign(P, 0);
+    u.xs_all = true;
+    for (int p = 0; p < P; ++p) {
+        const ImageCounts& n = *probs[p];
+        if (!n.reduced) {
+            u.xs_all = false;
+            continue;
+        }
+        u.xs_off[p] = u.xs_total;
+        u.xs_rank_off[p] = u.xs_rank_total;
+        u.xs_total += 9LL * n.nc * reduced_ld(9 * n.nc);
+        u.xs_rank_total += (long long)n.nc * rank_words(n.np);
+        u.xs_cams = std::max(u.xs_cams, n.nc);
+    }
     u.cam_prob.resize(sc);
     u.pt_prob.resize(sp);
     for (int p = 0; p < P; ++p) {
@@ -501,6 +528,20 @@ size_t layout_union(const UnionPlan& u, int precision, void* base, DeviceGraph* 
     L.add(d.red_partial, sizeof(double) * 4 * std::max(1, u.pp.nblk()));
     L.add(d.cost_partial, sizeof(double) * std::max(1, u.edges.nblk()));
     L.add(d.damp_partial, sizeof(double) * std::max(1, u.pts.nblk()));
+    if (u.xs_total > 0) {
+        L.add(d.xs_off, sizeof(long long) * P);
+        L.add(d.xs_rank_off, sizeof(long long) * P);
+        L.add(d.prob_pt_off, sizeof(int) * (P + 1));
+        L.add(d.xs_S, tsz * (size_t)u.xs_total);
+        L.add(d.xs_diag, sizeof(double) * 45 * NC);
+        L.add(d.xs_rank, sizeof(RankWord) * (size_t)u.xs_rank_total);
+    } else if (dptr) {
+        d.xs_off = d.xs_rank_off = nullptr;
+        d.prob_pt_off = nullptr;
+        d.xs_S = nullptr;
+        d.xs_diag = nullptr;
+        d.xs_rank = nullptr;
+    }
     L.add(d.gbar, sizeof(unsigned int) * kGbarWords);
     L.add(d.red_count, sizeof(unsigned int) * u.P);
     if (u.full) {
@@ -531,6 +572,8 @@ void set_union_scalars(Batch& b, int precision, int loss, double delta) {
     d.mode = precision;
     d.pcg_host = b.d_pcg_host;
     d.scal_host = b.d_scal_host;
+    d.lam_host = b.h_lam;
+    d.accept_host = b.h_accept;
     d.jac_bytes = precision == GBA_FP64 ? 8 : (precision == GBA_MIXED_FP32 ? 4 : 2);
     d.block_pp = kPointPassBlock;
     d.cam_pass = u.cam_pass ? 1 : 0;
@@ -539,6 +582,9 @@ void set_union_scalars(Batch& b, int precision, int loss, double delta) {
     d.dynamic = u.dynamic ? 1 : 0;
     d.lds_pp = u.lds_pp;
     d.fuse_apply = !u.full && u.max_cams <= kFuseApplyCams ? 1 : 0;
+    d.xs_on = u.xs_total > 0 ? 1 : 0;
+    d.xs_all = d.xs_on && u.xs_all ? 1 : 0;
+    d.xs_cams = u.xs_cams;
     d.dc_pp.nblk = u.pp.nblk();
     d.dc_red.nblk = u.red.nblk();
     d.dc_cam.nblk = u.cam.nblk();
@@ -570,6 +616,11 @@ gba_status upload_plan(Batch& b, std::string& msg) {
     HIP_OR(msg, up(d.cam_prob, u.cam_prob.data(), sizeof(int) * u.cam_prob.size()));
     HIP_OR(msg, up(d.pt_prob, u.pt_prob.data(), sizeof(int) * u.pt_prob.size()));
     HIP_OR(msg, up(d.prob_cam_off, u.cam_off.data(), sizeof(int) * u.cam_off.size()));
+    if (u.xs_total > 0) {
+        HIP_OR(msg, up(d.xs_off, u.xs_off.data(), sizeof(long long) * u.xs_off.size()));
+        HIP_OR(msg, up(d.xs_rank_off, u.xs_rank_off.data(), sizeof(long long) * u.xs_rank_off.size()));
+        HIP_OR(msg, up(d.prob_pt_off, u.pt_off.data(), sizeof(int) * u.pt_off.size()));
+    }
     return GBA_OK;
 }
 
@@ -586,6 +637,7 @@ gba_status build_batch(const std::vector<const HostProblem*>& probs, int precisi
     for (int p = 0; p < P; ++p) {
         gba_status st = make_image(*probs[p], imgs[p], msg);
         if (st != GBA_OK) return st;
+        imgs[p].n.reduced = reduced_rule(imgs[p].n, tune);
         counts[p] = &imgs[p].n;
     }
     gba_status st = plan_union(counts, tune, dev, precision, b.plan, msg);
@@ -602,6 +654,7 @@ gba_status build_batch(const std::vector<const HostProblem*>& probs, int precisi
     b.arena_bytes = bytes;
     b.dg = DeviceGraph{};
     b.blocks_zeroed = false;
+    b.reduced_built = false;
     b.persistent_ok = -1;
     layout_union(u, precision, arena, &b.dg);
     set_union_scalars(b, precision, loss, delta);
@@ -659,7 +712,6 @@ gba_status build_batch(const std::vector<const HostProblem*>& probs, int precisi
     run_off[u.tot.n_runs] = (int)NE;
     chunk_run_off[u.tot.n_chunks] = u.tot.n_runs;
     cam_chunk_off[NC] = u.tot.n_chunks;
-    std::vector<int> accept0(P, 0);
     auto up = [&](const void* dst, const void* src, size_t n) -> hipError_t {
         if (!n) return hipSuccess;
         return hipMemcpyAsync((void*)dst, src, n, hipMemcpyHostToDevice, stream);
@@ -728,7 +780,6 @@ gba_status build_batch(const std::vector<const HostProblem*>& probs, int precisi
     HIP_OR(msg, up(d.cam_chunk_off, cam_chunk_off.data(), sizeof(int) * cam_chunk_off.size()));
     HIP_OR(msg, up(d.cam_fixed, cfix.data(), NC));
     HIP_OR(msg, up(d.pt_fixed, pfix.data(), NP));
-    HIP_OR(msg, up(d.accept, accept0.data(), sizeof(int) * P));
     HIP_OR(msg, up(d.cam, cams.data(), sizeof(double) * 9 * NC));
     HIP_OR(msg, up(d.cam_init, cams0.data(), sizeof(double) * 9 * NC));
     HIP_OR(msg, up(d.pt, pts.data(), sizeof(double) * 3 * NP));
@@ -773,7 +824,6 @@ gba_status batch_damped_step(Batch& b, const gba_options& o, const Tuning& tune,
     const DeviceGraph& d = b.dg;
     hipStream_t s = b.stream;
     const bool timing = tm && tm->on;
-    HIP_OR(msg, hipMemcpyAsync(d.lam, b.h_lam, sizeof(double) * b.P, hipMemcpyHostToDevice, s));
     if (timing) HIP_OR(msg, hipEventRecord(tm->ev[0], s));
     HIP_OR(msg, launch_damp(d, s, o.min_diag, o.max_diag));
     // the block-Jacobi pass forms the reduced RHS on its way (one-pass scheme)
@@ -782,7 +832,26 @@ gba_status batch_damped_step(Batch& b, const gba_options& o, const Tuning& tune,
     if (!d.full && !precond_forms_rhs(d, block_jacobi)) HIP_OR(msg, launch_rhs(d, s));
     HIP_OR(msg, launch_precond(d, s, o.min_diag, o.max_diag, block_jacobi, o.jacobi_scaling));
     if (timing) HIP_OR(msg, hipEventRecord(tm->ev[1], s));
-    HIP_OR(msg, launch_pcg_init(d, s, o.pcg_tol, o.pcg_tol_relative));
+    // explicit reduced systems: S, and the whole PCG of those problems in one
+    // launch; with no other problem in the batch the trial runs to its end
+    // without a host check (phase timing and a forced schedule keep the
+    // launched iterations, the identity preconditioner has no diagonal blocks)
+    const bool reduced = d.xs_on && block_jacobi && !timing && o.pcg_schedule == GBA_PCG_AUTO &&
+                         !b.launched_products;
+    if (!reduced || !d.xs_all) HIP_OR(msg, launch_pcg_init(d, s, o.pcg_tol, o.pcg_tol_relative));
+    if (reduced) {
+        if (!b.reduced_built) HIP_OR(msg, launch_reduced_build(d, (size_t)b.plan.xs_rank_total, s));
+        b.reduced_built = true;
+        HIP_OR(msg, launch_reduced_form(d, s));
+        HIP_OR(msg, launch_pcg_reduced(d, s, o.pcg_tol, o.pcg_tol_relative, o.pcg_max_iters,
+                                       o.pcg_rejection_ratio));
+    }
+    if (reduced && d.xs_all) {
+        HIP_OR(msg, launch_backsub(d, s));
+        HIP_OR(msg, launch_cost(d, s, d.cam_c, d.pt_c));
+        HIP_OR(msg, launch_finish(d, s));
+        return read_scal(b, msg);
+    }
     // one cooperative launch for every PCG iteration (the trial then runs to
     // its end without a host check), or chunks of launched iterations
     bool persistent = false;
@@ -932,7 +1001,6 @@ gba_status batch_time_matvec(Batch& b, const gba_options& o, int launches, doubl
     b.dg.max_diag = o.max_diag;
     const DeviceGraph& d = b.dg;
     hipStream_t s = b.stream;
-    HIP_OR(msg, hipMemcpyAsync(d.lam, b.h_lam, sizeof(double) * b.P, hipMemcpyHostToDevice, s));
     HIP_OR(msg, launch_damp(d, s, o.min_diag, o.max_diag));
     // the block-Jacobi pass forms the reduced RHS on its way (one-pass scheme)
     const int block_jacobi = o.precond == GBA_PRECOND_BLOCK_JACOBI ? 1 : 0;
@@ -1062,8 +1130,6 @@ gba_status batch_trial(Batch& b, std::vector<ProblemLM>& lm, const gba_options& 
             std::swap(b.dg.cam, b.dg.cam_c);
             std::swap(b.dg.pt, b.dg.pt_c);
         } else {
-            HIP_OR(msg, hipMemcpyAsync(b.dg.accept, b.h_accept, sizeof(int) * b.P,
-                                       hipMemcpyHostToDevice, b.stream));
             HIP_OR(msg, launch_commit(b.dg, b.stream));
         }
         if (any_running) return batch_linearize(b, nullptr, tm, msg);

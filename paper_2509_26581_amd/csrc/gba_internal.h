@@ -41,6 +41,20 @@ __host__ __device__ constexpr int sym3(int r, int c) {
     return r <= c ? r * 3 - (r * (r - 1)) / 2 + (c - r) : c * 3 - (c * (c - 1)) / 2 + (r - c);
 }
 
+// The explicit reduced system of small problems (gba_reduced.hip): at most
+// kReducedMax unknowns (8 row wavefronts and at least two column groups of a
+// 16-wavefront workgroup), columns padded to whole wavefronts.
+constexpr int kReducedMax = 512;
+__host__ __device__ constexpr int reduced_ld(int n) { return (n + kWave - 1) / kWave * kWave; }
+// One word of a camera's rank bitmap: the observed points among 64
+// consecutive ones, and the camera-major edge of the first of them.
+struct RankWord {
+    unsigned long long mask;
+    int base;
+    int pad_;
+};
+__host__ __device__ constexpr int rank_words(int n_pts) { return (n_pts + 63) / 64; }
+
 enum Mode { kModeFP64 = 0, kModeFP32 = 1, kModeBF16 = 2 };
 
 // Per-problem scalars of one LM trial, read back by the host.
@@ -154,6 +168,8 @@ struct DeviceGraph {
     PcgState* pcg_dec;        // [P] decision of the current PCG iteration (from the product)
     PcgState* pcg_host;       // [P] mapped host copies of pcg (at the start and once stopped), or null
     TrialScalars* scal_host;  // [P]
+    const double* lam_host;   // [P] host memory: the trial's dampings and accept flags, for the
+    const int* accept_host;   // [P] launchers only (they pass them as arguments or copy them)
 
     // parameters (FP64 master copies and candidates)
     double* cam;              // [nc][9]
@@ -226,6 +242,15 @@ struct DeviceGraph {
     // full-Hessian PCG (the solver form without point elimination)
     int full;                 // 1: PCG on the whole damped system
     int dynamic;              // 1: no stored Jacobian; products recompute it from the parameters
+    // explicit reduced systems (xs_on: some problem has one, xs_all: every one)
+    int xs_on, xs_all;
+    int xs_cams;              // cameras of the largest such problem
+    const long long* xs_off;       // [P] offset of S in xs_S (entries), negative: products stay implicit
+    const long long* xs_rank_off;  // [P] offset of the rank bitmaps in xs_rank
+    const int* prob_pt_off;        // [P + 1] point range of each problem
+    void* xs_S;               // per problem a dense symmetric matrix, columns of reduced_ld(9 nc_p)
+    double* xs_diag;          // [nc][45] diagonal blocks of S (zero in xs_S)
+    RankWord* xs_rank;        // per problem [nc_p][rank_words(np_p)]
     void* w_x;                // [np][3] point parts of the PCG vectors (vector type)
     void* w_r;
     void* w_z;
@@ -329,6 +354,13 @@ hipError_t launch_pcg_persistent(const DeviceGraph& g, hipStream_t s, double min
                                  int max_iters, double reject_ratio);
 // whether launch_pcg_persistent can run this graph on the current device
 bool pcg_persistent_ok(const DeviceGraph& g);
+// Explicit reduced systems: the rank bitmaps (once per device graph), S of
+// the damped step (after launch_precond, which writes its diagonal blocks),
+// and the whole PCG of the problems that have one (start to stop).
+hipError_t launch_reduced_build(const DeviceGraph& g, size_t rank_total, hipStream_t s);
+hipError_t launch_reduced_form(const DeviceGraph& g, hipStream_t s);
+hipError_t launch_pcg_reduced(const DeviceGraph& g, hipStream_t s, double tol, int relative, int max_iters,
+                              double reject_ratio);
 hipError_t launch_backsub(const DeviceGraph& g, hipStream_t s);
 hipError_t launch_finish(const DeviceGraph& g, hipStream_t s);
 hipError_t launch_commit(const DeviceGraph& g, hipStream_t s);

@@ -248,13 +248,29 @@ __global__ __launch_bounds__(256) void k_jacobian_autodiff(DeviceGraph g, RawOut
 // Cholesky; fixed points get a zero inverse (no unknowns).  Also initialises the candidate points and
 // the |x|^2 partial sums over free points.
 // ==========================================================================
+// Per-problem values of a small batch as kernel arguments, instead of a copy
+// in the queue before each trial (a copy dispatch and its gaps cost a small
+// problem's trial about 12 us of 150).
+constexpr int kArgProblems = 64;
+struct LamArgs {
+    double v[kArgProblems];
+    int n;   // 0: the dampings are in g.lam
+};
+
 template <typename T>
-__global__ __launch_bounds__(256) void k_damp_points(DeviceGraph g, double min_diag, double max_diag) {
+__global__ __launch_bounds__(256) void k_damp_points(DeviceGraph g, LamArgs lams, double min_diag,
+                                                     double max_diag) {
     if (!vec_type_ok<T>(g)) return;   // instantiated for another mode
     __shared__ double red[16];
+    // the trial's dampings as kernel arguments: the workgroup after the point
+    // blocks stores them for the later kernels
+    if ((int)blockIdx.x == g.dc_pts.nblk) {
+        if ((int)threadIdx.x < lams.n) g.lam[threadIdx.x] = lams.v[threadIdx.x];
+        return;
+    }
     int pb, pe;
     const int prob = decomp_block(g.dc_pts, blockIdx.x, pb, pe);
-    const double lambda = fabs(g.lam[prob]);   // negative: problem idle this trial
+    const double lambda = fabs(lams.n ? lams.v[prob] : g.lam[prob]);   // negative: problem idle this trial
     const T* Hpp = (const T*)g.hpp;
     double x2 = 0.0;
     for (int j = pb + (int)threadIdx.x; j < pe; j += blockDim.x) {
@@ -525,6 +541,20 @@ __global__ __launch_bounds__(64) void k_cam_finalize(DeviceGraph g, double min_d
     }
     T* Minv = (T*)g.minv;
     const bool fixed = g.cam_fixed[i] != 0;
+    // an explicit reduced system's diagonal block (a fixed camera's stays
+    // zero: its residual and preconditioner are)
+    const long long xs = g.xs_on ? g.xs_off[g.cam_prob[i]] : -1;
+    T* S = nullptr;
+    int ld = 0;
+    if (xs >= 0) {
+        const int c0 = g.prob_cam_off[g.cam_prob[i]];
+        ld = reduced_ld(9 * (g.prob_cam_off[g.cam_prob[i] + 1] - c0));
+        S = (T*)g.xs_S + xs + (size_t)(9 * (i - c0)) * ld + 9 * (i - c0);
+    }
+    if (S) {
+        for (int e = k; e < 81; e += 64) S[(size_t)(e / 9) * ld + e % 9] = (T)0;
+        if (fixed && k < 45) g.xs_diag[45 * (size_t)i + k] = 0.0;
+    }
     if (fixed || !block_jacobi) {
         // identity, or with column scaling s_k = 1 / (1 + sqrt(H_kk)) the
         // preconditioner diag(s)^2 (PCG on the column-scaled system)
@@ -566,6 +596,7 @@ __global__ __launch_bounds__(64) void k_cam_finalize(DeviceGraph g, double min_d
     if (e0 < 81) A[e0] = Ms[sym9(e0 / 9, e0 % 9)];
     if (e1 < 81) A[e1] = Ms[sym9(e1 / 9, e1 % 9)];
     if (k == 0) s_bad = 0;
+    if (S && k < 45) g.xs_diag[45 * (size_t)i + k] = Ms[k];
     __syncthreads();
     for (int q = 0; q < 9; ++q) {
         const double piv = A[q * 9 + q];
@@ -1888,12 +1919,14 @@ __global__ __launch_bounds__(1024) void k_cost_finish(DeviceGraph g) {
 }
 
 // Accepted problems: the candidate parameters become the current ones.
-__global__ __launch_bounds__(256) void k_commit(DeviceGraph g) {
+// The accept flags of a small batch are an argument (bit p: problem p).
+__global__ __launch_bounds__(256) void k_commit(DeviceGraph g, unsigned long long mask, int from_mask) {
+    auto accepted = [&](int p) { return from_mask ? ((mask >> p) & 1ull) != 0 : g.accept[p] != 0; };
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < 9 * (size_t)g.nc; k += stride)
-        if (g.accept[g.cam_prob[k / 9]]) g.cam[k] = g.cam_c[k];
+        if (accepted(g.cam_prob[k / 9])) g.cam[k] = g.cam_c[k];
     for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < 3 * (size_t)g.np; k += stride)
-        if (g.accept[g.pt_prob[k / 3]]) g.pt[k] = g.pt_c[k];
+        if (accepted(g.pt_prob[k / 3])) g.pt[k] = g.pt_c[k];
 }
 
 // ==========================================================================
@@ -2298,11 +2331,20 @@ hipError_t launch_cost_finish(const DeviceGraph& g, hipStream_t s) {
 }
 
 hipError_t launch_damp(const DeviceGraph& g, hipStream_t s, double min_diag, double max_diag) {
-    if (g.dc_pts.nblk == 0) return hipSuccess;
+    LamArgs lams{};
+    if (g.n_probs <= kArgProblems) {
+        lams.n = g.n_probs;
+        for (int p = 0; p < g.n_probs; ++p) lams.v[p] = g.lam_host[p];
+    } else {
+        const hipError_t e = hipMemcpyAsync(g.lam, g.lam_host, sizeof(double) * g.n_probs,
+                                            hipMemcpyHostToDevice, s);
+        if (e != hipSuccess) return e;
+    }
+    const dim3 grid(g.dc_pts.nblk + 1);
     if (g.mode == kModeFP64)
-        hipLaunchKernelGGL(k_damp_points<double>, dim3(g.dc_pts.nblk), dim3(256), 0, s, g, min_diag, max_diag);
+        hipLaunchKernelGGL(k_damp_points<double>, grid, dim3(256), 0, s, g, lams, min_diag, max_diag);
     else
-        hipLaunchKernelGGL(k_damp_points<float>, dim3(g.dc_pts.nblk), dim3(256), 0, s, g, min_diag, max_diag);
+        hipLaunchKernelGGL(k_damp_points<float>, grid, dim3(256), 0, s, g, lams, min_diag, max_diag);
     GBA_CHECK_LAUNCH();
     return hipSuccess;
 }
@@ -2666,7 +2708,16 @@ hipError_t launch_commit(const DeviceGraph& g, hipStream_t s) {
     size_t n = 9 * (size_t)g.nc > 3 * (size_t)g.np ? 9 * (size_t)g.nc : 3 * (size_t)g.np;
     int grid = (int)((n + 255) / 256);
     grid = grid < 1 ? 1 : (grid > 2048 ? 2048 : grid);
-    hipLaunchKernelGGL(k_commit, dim3(grid), dim3(256), 0, s, g);
+    unsigned long long mask = 0;
+    const int from_mask = g.n_probs <= kArgProblems ? 1 : 0;
+    if (from_mask) {
+        for (int p = 0; p < g.n_probs; ++p) mask |= g.accept_host[p] ? 1ull << p : 0ull;
+    } else {
+        const hipError_t e = hipMemcpyAsync(g.accept, g.accept_host, sizeof(int) * g.n_probs,
+                                            hipMemcpyHostToDevice, s);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_commit, dim3(grid), dim3(256), 0, s, g, mask, from_mask);
     GBA_CHECK_LAUNCH();
     return hipSuccess;
 }

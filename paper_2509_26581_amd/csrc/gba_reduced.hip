@@ -1,0 +1,525 @@
+// The explicit reduced camera system of small problems: S = Hcc_lambda -
+// sum_j W_j Hpp_lambda,j^-1 W_j^T formed once per damped step as a dense
+// matrix, and the whole preconditioned conjugate-gradient solve on it in one
+// workgroup per problem.  The implicit products (gba_kernels.hip) stream the
+// stored Jacobian once per PCG iteration and take two or three launches for
+// it; with few cameras S is smaller than that Jacobian, and an iteration on it
+// needs no launch.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "gba.h"
+#include "gba_device.h"
+#include "gba_internal.h"
+
+namespace gba {
+
+// ==========================================================================
+// Rank bitmaps, once per device graph: per camera one bit per point of its
+// problem (set when the camera observes the point) in 64-bit words, each with
+// the camera-major position of the word's first edge, so that the edge of
+// (camera, point) is found by one 16-byte load and a population count.
+// ==========================================================================
+__global__ __launch_bounds__(256) void k_rank_set(DeviceGraph g) {
+    for (int e = blockIdx.x * (int)blockDim.x + (int)threadIdx.x; e < g.ne;
+         e += (int)(gridDim.x * blockDim.x)) {
+        const int a = g.e_cam[e], prob = g.cam_prob[a];
+        if (g.xs_off[prob] < 0) continue;
+        const int p0 = g.prob_pt_off[prob], nw = rank_words(g.prob_pt_off[prob + 1] - p0);
+        const int j = g.e_pt[e] - p0;
+        RankWord* w = g.xs_rank + g.xs_rank_off[prob] + (size_t)(a - g.prob_cam_off[prob]) * nw + (j >> 6);
+        atomicOr((unsigned long long*)&w->mask, 1ull << (j & 63));
+    }
+}
+
+__global__ __launch_bounds__(64) void k_rank_clear(DeviceGraph g, size_t words) {
+    for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < words;
+         k += (size_t)gridDim.x * blockDim.x)
+        g.xs_rank[k] = RankWord{0ull, 0, 0};
+}
+
+// first camera-major edge of camera a
+__device__ __forceinline__ int cam_edge_begin(const DeviceGraph& g, int a) {
+    return g.cm_run_off[g.chunk_run_off[g.cam_chunk_off[a]]];
+}
+
+// One wavefront per camera: the words' first edges, a running sum of their
+// population counts.
+__global__ __launch_bounds__(64) void k_rank_base(DeviceGraph g) {
+    const int a = blockIdx.x, prob = g.cam_prob[a];
+    if (g.xs_off[prob] < 0) return;
+    const int nw = rank_words(g.prob_pt_off[prob + 1] - g.prob_pt_off[prob]);
+    RankWord* w = g.xs_rank + g.xs_rank_off[prob] + (size_t)(a - g.prob_cam_off[prob]) * nw;
+    int base = cam_edge_begin(g, a);
+    const int l = lane_id();
+    for (int k0 = 0; k0 < nw; k0 += kWave) {
+        const int c = k0 + l < nw ? __popcll(w[k0 + l].mask) : 0;
+        int s = c;
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int t = __shfl_up(s, off, kWave);
+            if (l >= off) s += t;
+        }
+        if (k0 + l < nw) w[k0 + l].base = base + s - c;
+        base += __shfl(s, kWave - 1, kWave);
+    }
+}
+
+// ==========================================================================
+// Off-diagonal blocks of S: S_ik = -sum over the points j that cameras i and
+// k both observe of W_ij Hpp_lambda,j^-1 W_kj^T = J_c,i^T (J_p,i Hpp^-1
+// J_p,k^T) J_c,k, one workgroup per camera pair i < k (and per kRows rows of
+// the block: three workgroups in FP64, whose 81 sums would not leave room for
+// a second wavefront per SIMD).  Its four wavefronts share camera i's edges;
+// each looks its edges' points up in camera k's rank bitmap and queues the matches, so that
+// every lane of the arithmetic holds a common point; per match it reads both
+// edges' stored Jacobians (camera-major copy) and the point's inverse block,
+// and keeps the block's sums in registers: no atomics, and an order that
+// depends on the problem alone.  Bound by the gathers of the two Jacobians
+// (192 B a match in FP32, mostly from the L2).  The diagonal blocks come with
+// the preconditioner (k_cam_finalize).
+// ==========================================================================
+template <typename T, typename JS, int kRows>
+__global__ __launch_bounds__(256) void k_reduced_blocks(DeviceGraph g) {
+    const int a = blockIdx.x, prob = g.cam_prob[a];
+    const long long off = g.xs_off[prob];
+    if (off < 0 || g.lam[prob] < 0.0) return;
+    if ((sizeof(T) == 8) != (g.mode == kModeFP64) || sizeof(JS) != (size_t)g.jac_bytes) return;
+    constexpr int kSums = 9 * kRows, kRegsOut = (kSums + kWave - 1) / kWave;
+    __shared__ int qa_s[4][2 * kWave], qb_s[4][2 * kWave];
+    __shared__ T red[4][kRegsOut * kWave];
+    const int l = lane_id(), w = (int)threadIdx.x >> 6;
+    const int c0 = g.prob_cam_off[prob], nc = g.prob_cam_off[prob + 1] - c0, i = a - c0;
+    const int p0 = g.prob_pt_off[prob], nw = rank_words(g.prob_pt_off[prob + 1] - p0);
+    const int n = 9 * nc, ld = reduced_ld(n);
+    constexpr int kSplit = 9 / kRows;
+    const int q0 = cam_edge_begin(g, a), q1 = cam_edge_begin(g, a + 1);
+    const T* __restrict__ Hinv = (const T*)g.hpp_inv;
+    T* __restrict__ S = (T*)g.xs_S + off;
+    int* qa = qa_s[w];
+    int* qb = qb_s[w];
+    for (int t = (int)blockIdx.y; t < (nc - 1 - i) * kSplit; t += (int)gridDim.y) {   // uniform
+        const int k = i + 1 + t / kSplit, rb = (t % kSplit) * kRows;
+        const RankWord* __restrict__ rank = g.xs_rank + g.xs_rank_off[prob] + (size_t)k * nw;
+        T acc[kSums];
+#pragma unroll
+        for (int u = 0; u < kSums; ++u) acc[u] = (T)0;
+        auto add = [&](int ea, int eb) {
+            T ja[2][9], pa[2][3], jb[2][9], pb[2][3];
+            jac_load<JS>(g.jst_cm, ea, ja, pa);
+            jac_load<JS>(g.jst_cm, eb, jb, pb);
+            const T* H = Hinv + kHinvStride * (size_t)g.cm_pt[ea];
+            const T h[6] = {H[0], H[1], H[2], H[3], H[4], H[5]};
+            T A[2][2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const T t0 = pa[r][0] * h[0] + pa[r][1] * h[1] + pa[r][2] * h[2];
+                const T t1 = pa[r][0] * h[1] + pa[r][1] * h[3] + pa[r][2] * h[4];
+                const T t2 = pa[r][0] * h[2] + pa[r][1] * h[4] + pa[r][2] * h[5];
+#pragma unroll
+                for (int c = 0; c < 2; ++c) A[r][c] = t0 * pb[c][0] + t1 * pb[c][1] + t2 * pb[c][2];
+            }
+            T m[2][9];
+#pragma unroll
+            for (int c = 0; c < 9; ++c) {
+                m[0][c] = A[0][0] * jb[0][c] + A[0][1] * jb[1][c];
+                m[1][c] = A[1][0] * jb[0][c] + A[1][1] * jb[1][c];
+            }
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                // rows rb .. rb + kRows - 1 of camera i (rb is uniform)
+                T u0, u1;
+                if constexpr (kSplit == 1) {
+                    u0 = ja[0][r];
+                    u1 = ja[1][r];
+                } else {
+                    u0 = rb == 0 ? ja[0][r] : rb == kRows ? ja[0][kRows + r] : ja[0][2 * kRows + r];
+                    u1 = rb == 0 ? ja[1][r] : rb == kRows ? ja[1][kRows + r] : ja[1][2 * kRows + r];
+                }
+#pragma unroll
+                for (int c = 0; c < 9; ++c) acc[9 * r + c] += u0 * m[0][c] + u1 * m[1][c];
+            }
+        };
+        int queued = 0;   // uniform per wavefront
+        for (int base = q0 + w * kWave; base < q1; base += 4 * kWave) {
+            const int q = base + l;
+            bool hit = false;
+            int other = 0;
+            if (q < q1) {
+                const int j = g.cm_pt[q] - p0;
+                const RankWord r = rank[j >> 6];
+                hit = (r.mask >> (j & 63)) & 1ull;
+                other = r.base + __popcll(r.mask & ((1ull << (j & 63)) - 1ull));
+            }
+            const uint64_t hits = __ballot(hit);
+            if (!hits) continue;
+            if (hit) {
+                const int at = queued + __popcll(hits & ((1ull << l) - 1ull));
+                qa[at] = q;
+                qb[at] = other;
+            }
+            queued += __popcll(hits);
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            if (queued >= kWave) {
+                const int ea = qa[l], eb = qb[l];
+                const bool more = l < queued - kWave;
+                const int na = more ? qa[kWave + l] : 0, nb = more ? qb[kWave + l] : 0;
+                add(ea, eb);
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                if (more) {
+                    qa[l] = na;
+                    qb[l] = nb;
+                }
+                queued -= kWave;
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            }
+        }
+        if (l < queued) add(qa[l], qb[l]);
+        __builtin_amdgcn_wave_barrier();
+        wave_sum_scatter(acc);   // sum u in lane rev6(u % 64), register u / 64
+        __syncthreads();         // the previous block's sums have been read
+#pragma unroll
+        for (int v = 0; v < kRegsOut; ++v) red[w][v * kWave + rev6(l)] = acc[v];
+        __syncthreads();
+        for (int u = (int)threadIdx.x; u < kSums; u += (int)blockDim.x) {
+            const T sum = -((red[0][u] + red[1][u]) + (red[2][u] + red[3][u]));
+            const int row = 9 * i + rb + u / 9, col = 9 * k + u % 9;
+            S[(size_t)col * ld + row] = sum;
+            S[(size_t)row * ld + col] = sum;
+        }
+    }
+}
+
+// ==========================================================================
+// PCG on the explicit S, one workgroup of 16 wavefronts per problem from the
+// start to the stop.  The product: a wavefront takes 128 rows (two per lane)
+// of one column group and keeps the first kRegs columns of the group in
+// registers (the rest are read from the L2 every iteration); the direction is
+// read from LDS four columns at a time, each value used for two rows, which
+// balances the LDS reads (2 cycles a value and wavefront) with the products.
+// In the mixed modes the off-diagonal blocks and their products are FP32 (as
+// the launched products are), the diagonal blocks and the vectors FP64: a
+// diagonal block rounded to FP32 perturbs the system the same way in every
+// iteration, and a step at tolerance 1e-6 was 1.3 times as far from the exact
+// one as the launched products' (7e-5 against 5e-5 over 12 scenes of 8 to 48
+// cameras); with FP64 diagonals it is nearer (4e-5).
+// The vectors live in the registers of the row owners (63 rows, whole
+// cameras, per wavefront, so that the preconditioner's exchange stays inside
+// a wavefront) and an iteration is three workgroup barriers: direction,
+// partial products with p^T q, residual dots.  Arithmetic and decisions are
+// those of the launched kernels (pcg_decision, apply_body); q = S p is formed
+// directly.  The order of every sum depends on the problem alone.  Bound by
+// the latency of its serial chain (LDS exchanges, cross-lane sums, two FP64
+// divisions): 1.3 us an iteration at 90 rows in FP64 and 2.0 us at 162 rows in
+// FP32, where the launched iteration takes 14.2 us (two kernels).
+// ==========================================================================
+constexpr int kOwnRows = 63;   // rows owned per wavefront
+
+// four columns of the product for the two rows of a lane
+template <typename T>
+__device__ __forceinline__ void fma4(const T* __restrict__ p4, const T* __restrict__ a, const T* __restrict__ b,
+                                     T (&qa)[4], T (&qb)[4]) {
+    using V = typename std::conditional<sizeof(T) == 8, double4, float4>::type;
+    const V v = *(const V*)p4;   // 16-byte aligned: columns start at multiples of four
+    qa[0] = fma(a[0], v.x, qa[0]);
+    qb[0] = fma(b[0], v.x, qb[0]);
+    qa[1] = fma(a[1], v.y, qa[1]);
+    qb[1] = fma(b[1], v.y, qb[1]);
+    qa[2] = fma(a[2], v.z, qa[2]);
+    qb[2] = fma(b[2], v.z, qb[2]);
+    qa[3] = fma(a[3], v.w, qa[3]);
+    qb[3] = fma(b[3], v.w, qb[3]);
+}
+
+// One problem's PCG in the first kWaves wavefronts of the workgroup (the
+// others have returned): kR row wavefronts (128 kR rows at least n), kWaves /
+// kR column groups.  kStream: groups may be wider than kRegs columns.
+template <typename T, int kWaves, int kR, int kRegs, bool kStream>
+__device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int prob, double tol, int relative) {
+    static_assert(kRegs % 4 == 0 && kWaves <= 16, "columns are taken four at a time");
+    constexpr int kG = kWaves / kR, kRows = kR * 2 * kWave;
+    constexpr int kOwners = (kRows + kOwnRows - 1) / kOwnRows < kWaves ? (kRows + kOwnRows - 1) / kOwnRows : kWaves;
+    __shared__ __align__(32) T p_s[kRows + kRegs + 4];
+    __shared__ double r_s[kOwners * kWave], x_s[kOwners * kWave];
+    __shared__ T part[kG][kRows];
+    __shared__ __align__(16) double red_q[16], red_z[16], red_r[16];
+    const int c0 = g.prob_cam_off[prob], n = 9 * (g.prob_cam_off[prob + 1] - c0);
+    const int ld = reduced_ld(n);
+    const int W = (n + kOwnRows - 1) / kOwnRows;   // owner wavefronts, at most kOwners
+    const int tid = (int)threadIdx.x, l = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform, and known to be
+    const int grp = w / kR, row0 = (w % kR) * 2 * kWave + l, row1 = row0 + kWave;
+    // columns of this wavefront's group, four at a time: columns past n are
+    // column n - 1 against zeros of the direction, rows past n are row n - 1
+    // and their sums meet zeros of the direction and no owner
+    const int cpg = ((n + kG - 1) / kG + 3) & ~3;
+    const int cb = min(grp * cpg, (n + 3) & ~3), ce = grp < kG ? min(n, cb + cpg) : cb;
+    const T* __restrict__ S = (const T*)g.xs_S + g.xs_off[prob];
+    // byte offsets of the lane's rows in a column, whose address is uniform
+    const unsigned o0 = (unsigned)(min(row0, n - 1) * sizeof(T)), o1 = (unsigned)(min(row1, n - 1) * sizeof(T));
+    auto entry = [&](int c, unsigned o) {
+        return *(const T*)((const char*)(S + (size_t)(min(c, n - 1) * ld)) + o);
+    };
+    T s0[kRegs], s1[kRegs];
+#pragma unroll
+    for (int u = 0; u < kRegs; u += 4) {
+        if (cb + u < ce) {
+#pragma unroll
+            for (int v = u; v < u + 4; ++v) {
+                s0[v] = entry(cb + v, o0);
+                s1[v] = entry(cb + v, o1);
+            }
+        }
+    }
+    const int own = w * kOwnRows + l;
+    const bool owner = w < W && l < kOwnRows && own < n;
+    const int a9 = l % 9, base9 = tid - a9;
+    T m[9];
+    double h[9];   // the owner's row of its camera's diagonal block
+    double r = 0, p = 0, z = 0;
+    T* __restrict__ best = (T*)g.v_best + 9 * (size_t)c0 + own;   // the owner's entry
+#pragma unroll
+    for (int b = 0; b < 9; ++b) {
+        m[b] = 0;
+        h[b] = 0.0;
+    }
+    if (owner) {
+        const T* __restrict__ Minv = (const T*)g.minv + 45 * (size_t)(c0 + own / 9);
+#pragma unroll
+        for (int b = 0; b < 9; ++b) m[b] = Minv[sym9(a9, b)];
+        const double* __restrict__ D = g.xs_diag + 45 * (size_t)(c0 + own / 9);
+#pragma unroll
+        for (int b = 0; b < 9; ++b) h[b] = D[sym9(a9, b)];
+        r = ((const T*)g.v_r)[9 * (size_t)c0 + own];
+        *best = 0;
+    }
+    if (w < kOwners) x_s[tid] = 0;
+    for (int k = tid; k < kRows + kRegs + 4; k += kWaves * kWave) p_s[k] = (T)0;
+    if (grp < kG && cb >= ce) part[grp][row0] = part[grp][row1] = (T)0;   // a group without columns
+    if (tid < 16) red_q[tid] = red_z[tid] = red_r[tid] = 0.0;
+    __syncthreads();
+    // sum of the wavefronts' values (of 16, by rotations inside a row of 16
+    // lanes)
+    auto sum_waves = [&](const double* v) {
+        if constexpr (kWaves == 4) return (v[0] + v[1]) + (v[2] + v[3]);
+        double t = v[l & 15];
+        t += SegScan::move<0x128, 0xF>(t);
+        t += SegScan::move<0x124, 0xF>(t);
+        t += SegScan::move<0x122, 0xF>(t);
+        t += SegScan::move<0x121, 0xF>(t);
+        return lane63(t);
+    };
+    // z = M^-1 r and the dots r.z, r.r over the owners
+    double rz = 0.0, rr = 0.0;
+    auto precondition = [&]() {
+        if (w < W) {
+            r_s[tid] = r;
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            double z0 = 0, z1 = 0, z2 = 0;
+#pragma unroll
+            for (int b = 0; b < 9; b += 3) {   // (lane 63 reads its neighbours' entries against m = 0)
+                z0 += m[b] * r_s[base9 + b];
+                z1 += m[b + 1] * r_s[base9 + b + 1];
+                z2 += m[b + 2] * r_s[base9 + b + 2];
+            }
+            z = (z0 + z1) + z2;
+            // both dots in one chain: the low half of the lanes goes on with
+            // r.z, the high half with r.r
+            double d = swap_add<32>(r * z, r * r);
+            d += SegScan::move<0x128, 0xF>(d);
+            d += SegScan::move<0x124, 0xF>(d);
+            d += SegScan::move<0x122, 0xF>(d);
+            d += SegScan::move<0x121, 0xF>(d);
+            d = swap_add<16>(d, d);   // rows 0 and 1 (2 and 3) added
+            if (l == 0) red_z[w] = d;
+            if (l == 32) red_r[w] = d;
+        }
+        __syncthreads();
+        rz = sum_waves(red_z);
+        rr = sum_waves(red_r);
+    };
+    precondition();
+    const double rr0 = rr, thresh = relative ? tol * tol * rr : tol * tol, ratio = g.pcg_ratio;
+    const bool track = ratio > 0.0 && isfinite(ratio);
+    double min_rr = rr, beta = 0.0;
+    int iters = 0, use_best = 0;
+    // every thread holds the same scalars; the decisions are made uniform
+    auto yes = [](bool b) { return __builtin_amdgcn_readfirstlane((int)b) != 0; };
+    int done = yes(g.lam[prob] < 0.0) ? 5 : (yes(rr <= thresh || !(rz > 0.0)) ? 1 : 0);
+    while (!done) {
+        p = iters ? fma(beta, p, z) : z;
+        p = (double)(T)p;   // the direction as the product reads it
+        if (owner) p_s[own] = (T)p;
+        __syncthreads();
+        double pq_part = 0.0;
+        if (cb < ce) {
+            const T p0 = p_s[row0], p1 = p_s[row1];
+            T qa[4] = {0, 0, 0, 0}, qb[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int u = 0; u < kRegs; u += 4)
+                if (cb + u < ce) fma4(p_s + cb + u, s0 + u, s1 + u, qa, qb);   // uniform per wavefront
+#pragma unroll 1
+            for (int c = cb + kRegs; kStream && c < ce; c += 4) {
+                T a[4], b[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    a[u] = entry(c + u, o0);
+                    b[u] = entry(c + u, o1);
+                }
+                fma4(p_s + c, a, b, qa, qb);
+            }
+            const T ta = (qa[0] + qa[1]) + (qa[2] + qa[3]), tb = (qb[0] + qb[1]) + (qb[2] + qb[3]);
+            part[grp][row0] = ta;
+            part[grp][row1] = tb;
+            // p^T q from the partial products
+            pq_part = (double)p0 * (double)ta + (double)p1 * (double)tb;
+        }
+        double q = 0;
+        if (w < W && owner) {
+            const int b0 = own - a9;
+#pragma unroll
+            for (int b = 0; b < 9; ++b) q += h[b] * (double)p_s[b0 + b];
+            pq_part += p * q;
+        }
+        {
+            const double d = wave_sum(pq_part);
+            if (l == 0) red_q[w] = d;
+        }
+        __syncthreads();
+        if (w < W) {
+            T t[kG];
+#pragma unroll
+            for (int k = 0; k < kG; ++k) t[k] = part[k][min(own, kRows - 1)];
+#pragma unroll
+            for (int k = 0; k < kG; ++k) q += (double)t[k];
+        }
+        const double pq = sum_waves(red_q);
+        if (yes(!(pq > 0.0 && isfinite(pq)))) {   // breakdown: x stays the last iterate
+            done = 3;
+            break;
+        }
+        const double alpha = rz / pq;
+        if (owner) {
+            x_s[tid] = fma(alpha, p, x_s[tid]);
+            r = fma(-alpha, q, r);
+        }
+        const double rz_old = rz;
+        precondition();
+        iters += 1;
+        if (track) {
+            if (yes(rr < min_rr)) {
+                min_rr = rr;
+                use_best = 1;
+                if (owner) *best = (T)x_s[tid];
+            } else if (yes(rr > ratio * ratio * min_rr)) {
+                done = 4;
+                if (owner) x_s[tid] = *best;
+            }
+        }
+        if (!done && yes(rr <= thresh)) done = 1;
+        if (!done && iters >= g.pcg_max_iters) done = 2;
+        beta = rz_old > 0.0 ? rz / rz_old : 0.0;
+    }
+    if (owner) ((T*)g.v_x)[9 * (size_t)c0 + own] = (T)x_s[tid];
+    if (tid == 0) {
+        PcgState st;
+        st.rz = rz;
+        st.rr = rr;
+        st.rr0 = rr0;
+        st.min_rr = min_rr;
+        st.thresh = thresh;
+        st.iters = iters;
+        st.done = done;
+        st.use_best = use_best;
+        st.act = 0;
+        st.beta = beta;
+        st.fresh = iters == 0 ? 1 : 0;
+        st.pad_ = 0;
+        g.pcg[prob] = st;
+        g.pcg_dec[prob] = st;
+        if (g.pcg_host) g.pcg_host[prob] = st;
+    }
+}
+
+// A problem's class follows its own size: up to 128 rows four wavefronts
+// (one per SIMD: the scalar steps between the products, which every wavefront
+// repeats, then issue once per SIMD), up to 256 rows in FP32 twelve with every
+// column in registers, above that twelve (FP64: eight, with twice the
+// registers) with the rest of the columns streamed from the L2.  kBig: the
+// batch holds a problem above the first class.
+template <typename T>
+constexpr int big_waves() { return sizeof(T) == 8 ? 8 : 12; }
+
+template <typename T, bool kBig>
+__global__ __launch_bounds__(kBig ? big_waves<T>() * kWave : 4 * kWave) void k_pcg_reduced(DeviceGraph g,
+                                                                                          double tol,
+                                                                                          int relative) {
+    const int prob = blockIdx.x;
+    if (g.xs_off[prob] < 0 || (sizeof(T) == 8) != (g.mode == kModeFP64)) return;
+    const int n = 9 * (g.prob_cam_off[prob + 1] - g.prob_cam_off[prob]);
+    constexpr bool kF64 = sizeof(T) == 8;
+    if (n <= 2 * kWave) {
+        if (kBig && threadIdx.x >= 4 * kWave) return;
+        pcg_reduced_body<T, 4, 1, 32, false>(g, prob, tol, relative);
+    } else if constexpr (kBig) {
+        constexpr int kW = big_waves<T>();
+        if (n <= 4 * kWave)
+            pcg_reduced_body<T, kW, 2, kF64 ? 24 : 40, true>(g, prob, tol, relative);
+        else if (n <= 6 * kWave)
+            pcg_reduced_body<T, kW, kF64 ? 4 : 3, kF64 ? 24 : 36, true>(g, prob, tol, relative);
+        else
+            pcg_reduced_body<T, kW, 4, kF64 ? 24 : 36, true>(g, prob, tol, relative);
+    }
+}
+
+// ==========================================================================
+// launchers
+// ==========================================================================
+hipError_t launch_reduced_build(const DeviceGraph& g, size_t rank_total, hipStream_t s) {
+    if (!g.xs_on) return hipSuccess;
+    const int eg = std::max(1, std::min(4096, (g.ne + 255) / 256));
+    hipLaunchKernelGGL(k_rank_clear, dim3((unsigned)std::min<size_t>(4096, (rank_total + 63) / 64)), dim3(64),
+                       0, s, g, rank_total);
+    hipLaunchKernelGGL(k_rank_set, dim3(eg), dim3(256), 0, s, g);
+    hipLaunchKernelGGL(k_rank_base, dim3(g.nc), dim3(64), 0, s, g);
+    return hipGetLastError();
+}
+
+hipError_t launch_reduced_form(const DeviceGraph& g, hipStream_t s) {
+    if (!g.xs_on || g.nc == 0) return hipSuccess;
+    const int split = g.mode == kModeFP64 ? 3 : 1;
+    // one workgroup per block (or part) of the longest row
+    const dim3 grid(g.nc, (unsigned)std::max(1, split * (g.xs_cams - 1)));
+    if (g.mode == kModeFP64)
+        hipLaunchKernelGGL((k_reduced_blocks<double, double, 3>), grid, dim3(256), 0, s, g);
+    else if (g.mode == kModeFP32)
+        hipLaunchKernelGGL((k_reduced_blocks<float, float, 9>), grid, dim3(256), 0, s, g);
+    else
+        hipLaunchKernelGGL((k_reduced_blocks<float, bf16, 9>), grid, dim3(256), 0, s, g);
+    return hipGetLastError();
+}
+
+hipError_t launch_pcg_reduced(const DeviceGraph& g0, hipStream_t s, double tol, int relative, int max_iters,
+                              double ratio) {
+    if (!g0.xs_on) return hipSuccess;
+    DeviceGraph g = g0;
+    g.pcg_max_iters = max_iters;
+    g.pcg_ratio = ratio;
+    const bool big = 9 * g.xs_cams > 2 * kWave;
+    const dim3 grid(g.n_probs), block(!big ? 256 : g.mode == kModeFP64 ? 64 * big_waves<double>() : 64 * big_waves<float>());
+    if (g.mode == kModeFP64) {
+        if (big) hipLaunchKernelGGL((k_pcg_reduced<double, true>), grid, block, 0, s, g, tol, relative);
+        else hipLaunchKernelGGL((k_pcg_reduced<double, false>), grid, block, 0, s, g, tol, relative);
+    } else {
+        if (big) hipLaunchKernelGGL((k_pcg_reduced<float, true>), grid, block, 0, s, g, tol, relative);
+        else hipLaunchKernelGGL((k_pcg_reduced<float, false>), grid, block, 0, s, g, tol, relative);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace gba

@@ -369,6 +369,7 @@ gba_status gba_server::repack() {
     if ((st = batch.ensure_mirrors(std::max<int>(cfg.max_slots, (int)order.size()), err)) != GBA_OK) return st;
     batch.dg = DeviceGraph{};
     batch.blocks_zeroed = false;
+    batch.reduced_built = false;
     batch.persistent_ok = -1;
     batch.jacobian = cfg.options.jacobian;
     layout_union(u, cfg.precision, (char*)arena + uo, &batch.dg);
@@ -740,7 +741,15 @@ gba_status gba_server_submit(gba_server* s, const gba_problem* q, uint64_t* tick
         r->counts = img.n;
         r->lay = image_layout(img.n);
         std::vector<const ImageCounts*> one{&r->counts};
+        // the explicit reduced system only where the request fits the budget
+        // with it (decided by the request alone, so that its arithmetic does
+        // not depend on its batch mates)
+        r->counts.reduced = reduced_rule(r->counts, s->tune);
         need = r->lay.bytes + s->union_bytes_for(one);
+        if (need > s->cfg.hbm_budget_bytes && r->counts.reduced) {
+            r->counts.reduced = false;
+            need = r->lay.bytes + s->union_bytes_for(one);
+        }
         if (need > s->cfg.hbm_budget_bytes) {
             bad = GBA_ERR_BUDGET;
             why = "request needs " + std::to_string(need) + " device bytes, budget " +
