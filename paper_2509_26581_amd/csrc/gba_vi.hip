@@ -18,6 +18,7 @@
 #include "gba.h"
 #include "gba_autodiff.h"
 #include "gba_device.h"
+#include "gba_vi_order.h"
 
 namespace gba {
 namespace vi {
@@ -450,6 +451,24 @@ struct VIDev {
     const int* lslot;      // [nlslot] the point-order slots of their observations
     long long nlslot;
     double* sm;            // [36 K] sum over a keyframe's observations of W C^-1 W^T
+    // explicit off-diagonal blocks of the Schur complement's visual part
+    // (null when the products stay implicit): the covisible keyframes of each
+    // keyframe in ascending order, their 6 x 6 blocks -sum W C^-1 W^T, and for
+    // the blocks of a later keyframe the pairs of point-order slots they sum
+    const int* kslot;      // [M] point-order slot of each keyframe-order observation
+    const int* kinv;       // [Mp] and back
+    const int* kfoff;      // [K + 1] keyframe-order range of each keyframe
+    int* nrow;             // [K + 1]
+    int* nitem;            // [K + 1] first pair of each keyframe
+    int* ncol;             // [nnz]
+    int* noff;             // [nnz] first pair of each block (later keyframes; the others unused)
+    int* nkf;              // [nnz] the block's own keyframe
+    int nnz;
+    int2* items;           // pairs of keyframe-order observations
+    double* vblk;          // [36 nnz]
+    double* ad;            // [225 K] damped diagonal blocks of S
+    double* cb;            // [225 (K - 1)] cross blocks of consecutive keyframes (inertial and
+    double* cbt;           // bias terms), and transposed
     double* icx;           // [135 (K - 1)] inertial cross blocks J_i^T Omega J_j (15 x 9)
     double fx, fy, cx, cy, base, inv_sigma, delta2, wg, wa;   // wg, wa: 1 / sigma_w^2
     long long n() const { return 15LL * K + 3 * N; }
@@ -923,6 +942,7 @@ __global__ __launch_bounds__(256) void k_vi_precond_kf(VIDev d, double lam, doub
             v += lam * dd;
         }
         if (d.sm && a < 6 && c < 6) v -= d.sm[36 * (size_t)k + 6 * a + c];
+        if (d.ad) d.ad[225 * (size_t)k + e] = v;   // the explicit products' diagonal block
         A[e] = v;
     }
     __builtin_amdgcn_wave_barrier();
@@ -1378,6 +1398,585 @@ __global__ void k_vi_schur_blocks(VIDev d) {
         }
 }
 
+// ---- the visual blocks of S explicitly.  S's keyframe-keyframe blocks from
+// the points are sparse on a trajectory (a point is seen by a few keyframes
+// near each other): 2,000 keyframes with 2.07M observations have 24k blocks of
+// 6 x 6 (7 MB), where an implicit product streams W and its indices (212 MB, 43 us).
+// They are formed once per step from the same stored W and C^-1 in FP64, and an
+// iteration reads them from the L2.
+
+// The run of a point-order slot (its point's other observations) as [lo, hi)
+__device__ __forceinline__ void vi_run(const VIDev& d, int q, int& lo, int& hi) {
+    const int j = d.qpt[q];
+    lo = q;
+    while (lo > 0 && d.qpt[lo - 1] == j) --lo;
+    hi = q + 1;
+    while (hi < d.Mp && d.qpt[hi] == j) ++hi;
+}
+
+// One workgroup per keyframe: its covisible keyframes counted in LDS (hist,
+// K ints).  kFill = false: the number of blocks and of pairs with later
+// keyframes; true (after the scan): the columns, the blocks' first pairs and
+// the pairs.
+template <bool kFill>
+__global__ __launch_bounds__(256) void k_vi_pattern(VIDev d) {
+    extern __shared__ int hist[];
+    __shared__ int wsum[2][4];
+    const int k = blockIdx.x, tid = (int)threadIdx.x;
+    for (int c = tid; c < d.K; c += 256) hist[c] = 0;
+    __syncthreads();
+    for (int e = d.kfoff[k] + tid; e < d.kfoff[k + 1]; e += 256) {
+        const int q = d.kslot[e];
+        int lo, hi;
+        vi_run(d, q, lo, hi);
+        for (int u = lo; u < hi; ++u)
+            if (u != q) atomicAdd(&hist[d.qkf[u]], 1);
+    }
+    __syncthreads();
+    // running counts over the columns, 256 at a time
+    const int l = tid & 63, w = tid >> 6;
+    int nb = 0, ni = 0;
+    for (int c0 = 0; c0 < d.K; c0 += 256) {
+        const int c = c0 + tid;
+        const int h = c < d.K ? hist[c] : 0;
+        int b = h > 0 ? 1 : 0, it = c > k ? h : 0;
+        const int bown = b, iown = it;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int tb = __shfl_up(b, off, 64), ti = __shfl_up(it, off, 64);
+            if (l >= off) {
+                b += tb;
+                it += ti;
+            }
+        }
+        if (l == 63) {
+            wsum[0][w] = b;
+            wsum[1][w] = it;
+        }
+        __syncthreads();
+        int pb = nb, pi = ni;
+        for (int v = 0; v < 4; ++v) {
+            if (v < w) {
+                pb += wsum[0][v];
+                pi += wsum[1][v];
+            }
+            nb += wsum[0][v];
+            ni += wsum[1][v];
+        }
+        if (kFill && bown) {
+            const int at = d.nrow[k] + pb + b - 1;
+            const int first = d.nitem[k] + pi + it - iown;
+            d.ncol[at] = c;
+            d.nkf[at] = k;
+            d.noff[at] = first;
+            hist[c] = first;   // the cursor of the fill
+        }
+        __syncthreads();
+    }
+    if (!kFill) {
+        if (tid == 0) {
+            d.nrow[k] = nb;
+            d.nitem[k] = ni;
+        }
+        return;
+    }
+    // the pairs, by one wavefront in keyframe order (64 observations at a
+    // time, a partner each), so that a block's pairs ascend in both
+    // observations: lanes of one block are ranked by ballots
+    if (w > 0) return;
+    for (int e = d.kfoff[k] + l; e - l < d.kfoff[k + 1]; e += 64) {
+        const bool in = e < d.kfoff[k + 1];
+        const int q = in ? d.kslot[e] : 0, j = in ? d.qpt[q] : -2;
+        for (int u = q + 1; ; ++u) {   // a run is in keyframe order
+            const bool pair = in && u < d.Mp && d.qpt[u] == j;
+            uint64_t left = __ballot(pair);
+            if (!left) break;
+            const int c = pair ? d.qkf[u] : -1;
+            while (left) {
+                const int lead = __ffsll((long long)left) - 1;
+                const int m = __builtin_amdgcn_readlane(c, lead);
+                const uint64_t same = __ballot(c == m);
+                if (c == m) d.items[hist[m] + __popcll(same & ((1ull << l) - 1ull))] = make_int2(e, d.kinv[u]);
+                __builtin_amdgcn_wave_barrier();
+                if (l == lead) hist[m] += __popcll(same);
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                left &= ~same;
+            }
+        }
+    }
+}
+
+// counts -> offsets of both arrays (exclusive, the totals last), one workgroup
+__global__ __launch_bounds__(1024) void k_vi_pattern_scan(VIDev d) {
+    __shared__ int wsum[2][16];
+    const int tid = (int)threadIdx.x, l = tid & 63, w = tid >> 6;
+    int nb = 0, ni = 0;
+    for (int k0 = 0; k0 < d.K; k0 += 1024) {
+        const int k = k0 + tid;
+        int b = k < d.K ? d.nrow[k] : 0, it = k < d.K ? d.nitem[k] : 0;
+        const int bown = b, iown = it;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int tb = __shfl_up(b, off, 64), ti = __shfl_up(it, off, 64);
+            if (l >= off) {
+                b += tb;
+                it += ti;
+            }
+        }
+        if (l == 63) {
+            wsum[0][w] = b;
+            wsum[1][w] = it;
+        }
+        __syncthreads();
+        int pb = nb, pi = ni;
+        for (int v = 0; v < 16; ++v) {
+            if (v < w) {
+                pb += wsum[0][v];
+                pi += wsum[1][v];
+            }
+            nb += wsum[0][v];
+            ni += wsum[1][v];
+        }
+        if (k < d.K) {
+            d.nrow[k] = pb + b - bown;
+            d.nitem[k] = pi + it - iown;
+        }
+        __syncthreads();
+    }
+    if (tid == 0) {
+        d.nrow[d.K] = nb;
+        d.nitem[d.K] = ni;
+    }
+}
+
+// V_kk' = -sum W_a C^-1 W_b^T over the block's pairs, stored at (k, k') and,
+// transposed, at (k', k).  kWaves wavefronts share a block's pairs (four
+// where few blocks would leave the chip idle).  Bound by the reads of W in
+// keyframe order, where a block's observations on both sides ascend together
+// (in point order the same reads took a line for each lane: 634 us a step at
+// 2,000 keyframes).
+template <typename WT, int kWaves>
+__global__ __launch_bounds__(64 * kWaves) void k_vi_form_blocks(VIDev d) {
+    __shared__ double red[kWaves][64];
+    const int i = blockIdx.x, k = d.nkf[i], kk = d.ncol[i];
+    if (kk <= k) return;
+    const int l = lane_id(), w = (int)threadIdx.x >> 6;
+    const int last = i + 1 < d.nrow[k + 1] ? d.noff[i + 1] : d.nitem[k + 1];
+    double acc[36];
+#pragma unroll
+    for (int u = 0; u < 36; ++u) acc[u] = 0.0;
+    for (int t = d.noff[i] + (int)threadIdx.x; t < last; t += 64 * kWaves) {
+        const int2 it = d.items[t];
+        const double* Mi = d.mp + 9 * (size_t)d.pt[it.x];
+        double A[18], B[18], M[9];
+        load_w<WT>(d.wk, it.x, A);
+        load_w<WT>(d.wk, it.y, B);
+#pragma unroll
+        for (int c = 0; c < 9; ++c) M[c] = Mi[c];
+#pragma unroll
+        for (int a = 0; a < 6; ++a) {
+            const double g0 = A[3 * a] * M[0] + A[3 * a + 1] * M[3] + A[3 * a + 2] * M[6];
+            const double g1 = A[3 * a] * M[1] + A[3 * a + 1] * M[4] + A[3 * a + 2] * M[7];
+            const double g2 = A[3 * a] * M[2] + A[3 * a + 1] * M[5] + A[3 * a + 2] * M[8];
+#pragma unroll
+            for (int b = 0; b < 6; ++b) acc[6 * a + b] += g0 * B[3 * b] + g1 * B[3 * b + 1] + g2 * B[3 * b + 2];
+        }
+    }
+    wave_sum_scatter(acc);   // sum u in lane rev6(u)
+    red[w][rev6(l)] = acc[0];
+    __syncthreads();
+    const int u = (int)threadIdx.x;
+    if (u >= 36) return;
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) v -= red[q][u];
+    d.vblk[36 * (size_t)i + u] = v;
+    // the transposed block's place in row k' (its columns ascend)
+    int lo = d.nrow[kk], hi = d.nrow[kk + 1] - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (d.ncol[mid] < k) lo = mid + 1;
+        else hi = mid;
+    }
+    d.vblk[36 * (size_t)lo + 6 * (u % 6) + u / 6] = v;
+}
+
+// S p for the 15 rows of a keyframe by one wavefront.  The lanes are used
+// twice: rows of 16 lanes take the diagonal block and the two cross blocks
+// (lane 16 part + row, part 0..2; columns of ad, cbt and cb, so consecutive
+// lanes read consecutive entries), and eights of lanes the visual blocks'
+// rows (lane 8 s + r, r < 6, of eight neighbours at a time).  Both are summed
+// across the lanes without LDS; lane r < 15 returns row r.
+__device__ __forceinline__ const double* vi_s_block(const VIDev& d, int k, int part, int& kk) {
+    kk = part == 0 ? k : part == 1 ? k + 1 : part == 2 ? k - 1 : -1;
+    if (kk < 0 || kk >= d.K) {
+        kk = -1;
+        return d.ad;
+    }
+    return part == 0 ? d.ad + 225 * (size_t)k : part == 1 ? d.cbt + 225 * (size_t)k : d.cb + 225 * (size_t)(k - 1);
+}
+
+__device__ __forceinline__ double vi_s_total(double u, double v) {
+    // u: the parts' rows (lanes 16 apart); v: the neighbours' rows (8 apart)
+    u = swap_add<16>(u, u);
+    u = swap_add<32>(u, u);
+    v += SegScan::move<0x128, 0xF>(v);
+    v = swap_add<16>(v, v);
+    v = swap_add<32>(v, v);
+    return u + (lane_id() < 6 ? v : 0.0);
+}
+
+// p(kk, c): entry c of keyframe kk's part, read from memory by one lane each
+// and shared through buf (128 doubles of LDS of this wavefront).
+template <typename P>
+__device__ __forceinline__ double vi_s_rows(const VIDev& d, int k, const P& p, double* buf) {
+    const int l = lane_id(), part = l >> 4, row = l & 15;
+    const int n0 = d.nrow[k], n1 = d.nrow[k + 1];
+    int kk;
+    const double* M = vi_s_block(d, k, part, kk);
+    double m[15];
+#pragma unroll
+    for (int c = 0; c < 15; ++c) m[c] = M[15 * c + min(row, 14)];
+    buf[l] = kk >= 0 && row < 15 ? p(kk, row) : 0.0;
+    const int s = l >> 3, r = l & 7;
+    double v = 0.0;
+    for (int i0 = n0; i0 < n1; i0 += 8) {   // uniform
+        const bool nb = i0 + s < n1 && r < 6;
+        const int i = nb ? i0 + s : n0;
+        const double2* B = (const double2*)(d.vblk + 36 * (size_t)i + 6 * min(r, 5));
+        const double2 b0 = B[0], b1 = B[1], b2 = B[2];
+        __builtin_amdgcn_wave_barrier();
+        buf[64 + l] = nb ? p(d.ncol[i], r) : 0.0;
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        const double* ps = buf + 64 + 8 * s;
+        const double t = b0.x * ps[0] + b0.y * ps[1] + b1.x * ps[2] + b1.y * ps[3] + b2.x * ps[4] + b2.y * ps[5];
+        v += nb ? t : 0.0;
+    }
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    double u = 0.0;
+    const double* ps = buf + 16 * part;
+#pragma unroll
+    for (int c = 0; c < 15; ++c) u += m[c] * ps[c];
+    return vi_s_total(u, v);
+}
+
+// One PCG step in two launches.  First: the decisions about the step before
+// (k_vi_pcg_dir's, from slot `prev_slot`; none at the first step), the
+// direction p = z + beta p_old formed as it is read (p_old and the new p are
+// separate buffers), q = S p and p.q into slot `slot`; one wavefront per
+// keyframe.  last: only the decisions about the last step.
+// At 2,000 keyframes it takes 9.4 us and the update 5.2 us, where the
+// three kernels around the implicit product took 60 (the solve from 87 to 21 ms).
+__global__ __launch_bounds__(256) void k_vi_s_prod(VIDev d, double* __restrict__ ps, int slot,
+                                                  int prev_slot, int first, int last,
+                                                  const double* __restrict__ z,
+                                                  const double* __restrict__ p_old, double* __restrict__ p_new,
+                                                  double* __restrict__ q, double* __restrict__ x,
+                                                  double* __restrict__ xb) {
+    __shared__ double red[16];
+    __shared__ double sums[2];
+    __shared__ double buf[4][128];
+    if (ps[kDone] != 0.0) return;   // set by the update kernel only
+    const int l = lane_id(), w = (int)threadIdx.x >> 6;
+    const int k = (int)blockIdx.x * 4 + w;
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    const size_t own = 15 * (size_t)k + l;
+    const bool mine = k < d.K && l < 15;
+    double beta = 0.0;
+    if (!first) {
+        double* acc = ps + kAccN * prev_slot;
+        const double* prev = ps + kAccN * ((prev_slot + kSlots - 1) % kSlots);
+        const double a = block_sum_vi(threadIdx.x < kPqParts ? acc[kAccRrP + threadIdx.x] : 0.0, red);
+        __syncthreads();
+        const double b = block_sum_vi(threadIdx.x < kPqParts ? acc[kAccRzP + threadIdx.x] : 0.0, red);
+        if (threadIdx.x == 0) {
+            sums[0] = a;
+            sums[1] = b;
+        }
+        __syncthreads();
+        const double rr = sums[0], least = prev[kAccMin], ratio2 = ps[kRatio2];
+        double nmin = least;
+        bool stop = acc[kAccBreak] != 0.0;
+        if (!stop && ratio2 > 0.0) {
+            if (rr < least) {
+                nmin = rr;
+                if (mine) xb[own] = x[own];
+            } else if (rr > ratio2 * least) {
+                if (mine) x[own] = xb[own];
+                stop = true;
+            }
+        }
+        if (!stop && rr <= ps[kThr]) stop = true;
+        if (lead) {
+            acc[kAccRr] = rr;
+            acc[kAccRz] = sums[1];
+            acc[kAccMin] = nmin;
+            if (stop) acc[kAccStop] = 1.0;   // the update kernel sets the stop flag from it
+        }
+        if (stop || last) return;
+        beta = sums[1] / prev[kAccRz];
+    }
+    double pq = 0.0;
+    if (k < d.K) {   // whole wavefronts
+        auto p = [&](int kk, int c) { return z[15 * (size_t)kk + c] + beta * p_old[15 * (size_t)kk + c]; };
+        const double qv = vi_s_rows(d, k, p, buf[w]);
+        if (mine) {
+            const double pv = p(k, l);
+            p_new[own] = pv;
+            q[own] = qv;
+            pq = pv * qv;
+        }
+    }
+    pq = block_sum_vi(pq, red);
+    if (threadIdx.x == 0) atomic_add(ps + kAccN * slot + kAccPq + blockIdx.x % kPqParts, pq);
+}
+
+// Second: alpha, x, r, z = M^-1 r and the parts of r.r and r.z (as
+// k_vi_pcg_update); the stop decided by the first kernel becomes the stop
+// flag, and the next step's slot is cleared (no kernel in flight reads it).
+__global__ __launch_bounds__(256) void k_vi_s_update(VIDev d, double* __restrict__ ps, int slot, int prev_slot,
+                                                    const double* __restrict__ p, const double* __restrict__ q,
+                                                    double* __restrict__ x, double* __restrict__ r,
+                                                    double* __restrict__ z) {
+    __shared__ double rs[256];
+    __shared__ double red[16];
+    __shared__ double pq_s;
+    if (ps[kDone] != 0.0) return;
+    double* acc = ps + kAccN * slot;
+    if (ps[kAccN * prev_slot + kAccStop] != 0.0) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) ps[kDone] = 1.0;
+        return;
+    }
+    if (blockIdx.x == 0)
+        for (int e = threadIdx.x; e < kAccN; e += blockDim.x) ps[kAccN * ((slot + 1) % kSlots) + e] = 0.0;
+    const long long k = blockIdx.x * 16LL + (threadIdx.x >> 4);
+    const int row = (int)(threadIdx.x & 15);
+    const bool act = k < d.K && row < 15;
+    const size_t i = 15 * (size_t)k + row;
+    const double part = block_sum_vi(threadIdx.x < kPqParts ? acc[kAccPq + threadIdx.x] : 0.0, red);
+    if (threadIdx.x == 0) pq_s = part;
+    __syncthreads();
+    const double pq = pq_s;
+    if (!(pq > 0.0)) {   // breakdown: decided by every workgroup alike
+        if (blockIdx.x == 0 && threadIdx.x == 0) acc[kAccBreak] = 1.0;
+        return;
+    }
+    const double alpha = ps[kAccN * prev_slot + kAccRz] / pq;
+    double rr = 0.0, rz = 0.0, rn = 0.0;
+    if (act) {
+        x[i] += alpha * p[i];
+        rn = r[i] - alpha * q[i];
+        r[i] = rn;
+    }
+    rs[threadIdx.x] = rn;
+    __syncthreads();
+    if (act) {
+        const double* Mi = d.mki + 225 * (size_t)k + 15 * row;
+        const double* rk = rs + (threadIdx.x & ~15u);
+        double u = 0.0;
+#pragma unroll
+        for (int c = 0; c < 15; ++c) u += Mi[c] * rk[c];
+        z[i] = u;
+        rr = rn * rn;
+        rz = rn * u;
+    }
+    rr = block_sum_vi(rr, red);
+    __syncthreads();
+    rz = block_sum_vi(rz, red);
+    if (threadIdx.x == 0) {
+        atomic_add(acc + kAccRrP + blockIdx.x % kPqParts, rr);
+        atomic_add(acc + kAccRzP + blockIdx.x % kPqParts, rz);
+        if (blockIdx.x == 0) ps[kSteps] += 1.0;
+    }
+}
+
+// The whole PCG of a short trajectory (at most kOneKf keyframes) in one
+// workgroup of eight wavefronts: keyframe w + 8 t is wavefront w's t-th.  Its
+// diagonal, cross and preconditioner blocks stay in registers (two wavefronts
+// per SIMD leave 256 VGPRs), the vectors too (a lane per entry: 16 lanes a
+// keyframe), the direction and the visual blocks in LDS (their upper half: at
+// most 496 of 288 bytes, read along rows or columns); three barriers an
+// iteration.  Rules and arithmetic as the two kernels above; r, z from the
+// start kernels, x out.  Bound by the chain of LDS reads, sums and barriers
+// of an iteration; with the visual blocks requested from the L2 instead it
+// took 4.5 us an iteration, and as three launches of the implicit product 14
+// (31 keyframes, 5 steps of 200 iterations: the solve from 19.0 to 5.1 ms).
+constexpr int kOneKf = 32;
+constexpr int kOneBlock = 512;
+__global__ __launch_bounds__(kOneBlock) void k_vi_s_pcg_one(VIDev d, double* __restrict__ ps,
+                                                           int max_iters, const double* __restrict__ r_in,
+                                                           const double* __restrict__ z_in,
+                                                           double* __restrict__ x_out) {
+    constexpr int kWaves = kOneBlock / 64, kN = 16 * kOneKf, kPer = kOneKf / kWaves, kPre = 4;
+    static_assert(kPer == 4 && 8 * kPre >= kOneKf - 1, "a keyframe per 16 lanes; every neighbour in a group");
+    extern __shared__ __align__(16) double blocks[];   // 36 doubles per upper block
+    __shared__ __align__(16) double p_s[kN], r_s[kN], q_s[kN];
+    __shared__ __align__(16) double red[3][kWaves];
+    __shared__ int low_s[kOneKf];   // lower blocks in the rows up to this one
+    const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int part = l >> 4, row = l & 15, s = l >> 3, r8 = l & 7;
+    const double* a = ps + kAccN * (kSlots - 1);
+    double rz = a[kAccRz], rr = a[kAccRr], least = rr;
+    const double thr = ps[kThr], ratio2 = ps[kRatio2];
+    auto yes = [](bool b) { return __builtin_amdgcn_readfirstlane((int)b) != 0; };
+    const bool idle = yes(ps[kDone] != 0.0);
+    // first index in [lo, hi) of a row's ascending columns that is >= c
+    auto lower = [&](int lo, int hi, int c) {
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (d.ncol[mid] < c) lo = mid + 1;
+            else hi = mid;
+        }
+        return lo;
+    };
+    if (w == 0) {
+        int c = l < d.K ? lower(d.nrow[l], d.nrow[l + 1], l) - d.nrow[l] : 0;
+        for (int off = 1; off < kOneKf; off <<= 1) {
+            const int t = __shfl_up(c, off, 64);
+            if (l >= off) c += t;
+        }
+        if (l < kOneKf) low_s[l] = c;
+    }
+    __syncthreads();
+    for (int i = w; i < d.nnz; i += kWaves) {   // uniform
+        const int k = d.nkf[i];
+        if (d.ncol[i] > k && l < 36) blocks[36 * (i - low_s[k]) + l] = d.vblk[36 * (size_t)i + l];
+    }
+    // lane 16 t + c owns entry c of the wavefront's keyframe t
+    const int k_own = w + kWaves * part, i_own = 16 * k_own + row;
+    const bool mine = k_own < d.K && row < 15;
+    double x = 0.0, xb = 0.0, z = mine ? z_in[15 * k_own + row] : 0.0, r = mine ? r_in[15 * k_own + row] : 0.0;
+    double p = z;
+    r_s[i_own] = r;
+    p_s[i_own] = p;
+    double m[kPer][15], mi[15];
+#pragma unroll
+    for (int c = 0; c < 15; ++c)   // symmetric: read by columns
+        mi[c] = mine ? d.mki[225 * (size_t)k_own + 15 * c + row] : 0.0;
+    // nb: a neighbour's block (entry 36 u + r8 or 6 r8 of blocks), whether it
+    // is read by columns, and its keyframe
+    int pb[kPer], nn[kPer], nb[kPer][kPre];
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) {
+        const int k = w + kWaves * t;
+        const bool on = k < d.K;
+        int kk = -1;
+        const double* M = on ? vi_s_block(d, k, part, kk) : d.ad;
+        pb[t] = 16 * max(kk, 0);
+#pragma unroll
+        for (int c = 0; c < 15; ++c) m[t][c] = kk >= 0 && row < 15 ? M[15 * c + min(row, 14)] : 0.0;
+        const int n0 = on ? __builtin_amdgcn_readfirstlane(d.nrow[k]) : 0;
+        nn[t] = on ? __builtin_amdgcn_readfirstlane(d.nrow[k + 1]) - n0 : 0;
+#pragma unroll
+        for (int g = 0; g < kPre; ++g) {
+            nb[t][g] = -1;
+            if (8 * g + s < nn[t] && r8 < 6) {
+                const int i = n0 + 8 * g + s, c = d.ncol[i];
+                const int u = c > k ? i - low_s[k] : lower(d.nrow[c], d.nrow[c + 1], k) - low_s[c];
+                nb[t][g] = (36 * u + (c > k ? 6 * r8 : r8)) << 8 | (c > k ? 0 : 128) | c;
+            }
+        }
+    }
+    auto total = [&](int c) {   // the wavefronts' sums
+        const double* v = red[c];
+        return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+    };
+    int steps = 0;
+    while (!idle && steps < max_iters) {   // uniform: every thread holds the same scalars
+        __syncthreads();   // the direction is complete
+#pragma unroll
+        for (int t = 0; t < kPer; ++t) {
+            if (w + kWaves * t >= d.K) break;   // uniform
+            double v = 0.0;
+#pragma unroll
+            for (int g = 0; g < kPre; ++g) {
+                if (8 * g >= nn[t]) break;   // uniform
+                int at = nb[t][g];
+                asm volatile("" : "+v"(at));   // its addresses are made here, not kept: registers
+                if (at >= 0) {
+                    const double* B = blocks + (at >> 8);
+                    const double* q6 = p_s + 16 * (at & 31);
+                    const int st = (at & 128) ? 6 : 1;
+                    double h0 = 0.0, h1 = 0.0;
+#pragma unroll
+                    for (int c = 0; c < 6; c += 2) {
+                        h0 += B[st * c] * q6[c];
+                        h1 += B[st * (c + 1)] * q6[c + 1];
+                    }
+                    v += h0 + h1;
+                }
+            }
+            double u0 = 0.0, u1 = 0.0, u2 = 0.0;
+            const double* pk = p_s + pb[t];
+#pragma unroll
+            for (int c = 0; c < 15; c += 3) {
+                u0 += m[t][c] * pk[c];
+                u1 += m[t][c + 1] * pk[c + 1];
+                u2 += m[t][c + 2] * pk[c + 2];
+            }
+            const double q = vi_s_total((u0 + u1) + u2, v);
+            if (l < 16) q_s[16 * (w + kWaves * t) + l] = q;   // (entry 15 is not used)
+        }
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        const double q = mine ? q_s[i_own] : 0.0;
+        const double pql = wave_sum(p * q);
+        if (l == 0) red[0][w] = pql;
+        __syncthreads();
+        const double pq = total(0);
+        if (yes(!(pq > 0.0))) break;   // breakdown: x stays the last iterate
+        const double alpha = rz / pq;
+        x += alpha * p;
+        r -= alpha * q;
+        r_s[i_own] = r;
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        {
+            const double* rk = r_s + 16 * k_own;
+            double u0 = 0.0, u1 = 0.0, u2 = 0.0;
+#pragma unroll
+            for (int c = 0; c < 15; c += 3) {
+                u0 += mi[c] * rk[c];
+                u1 += mi[c + 1] * rk[c + 1];
+                u2 += mi[c + 2] * rk[c + 2];
+            }
+            z = (u0 + u1) + u2;
+        }
+        double both = swap_add<32>(r * r, r * z);   // r.r in the low lanes, r.z in the high ones
+        both += SegScan::move<0x128, 0xF>(both);
+        both += SegScan::move<0x124, 0xF>(both);
+        both += SegScan::move<0x122, 0xF>(both);
+        both += SegScan::move<0x121, 0xF>(both);
+        both = swap_add<16>(both, both);
+        if (l == 0) red[1][w] = both;
+        if (l == 32) red[2][w] = both;
+        __syncthreads();
+        rr = total(1);
+        const double rz_new = total(2);
+        steps += 1;
+        if (ratio2 > 0.0) {
+            if (yes(rr < least)) {
+                least = rr;
+                xb = x;
+            } else if (yes(rr > ratio2 * least)) {
+                x = xb;
+                break;
+            }
+        }
+        if (yes(rr <= thr)) break;
+        const double beta = rz_new / rz;
+        rz = rz_new;
+        p = z + beta * p;
+        p_s[i_own] = p;
+    }
+    if (mine) x_out[15 * k_own + row] = x;
+    if (threadIdx.x == 0) {
+        ps[kSteps] = (double)steps;
+        ps[kDone] = 1.0;
+    }
+}
+
 // the inertial cross blocks of the damped system, once per linearisation:
 // icx_f = J_i^T Omega J_j over keyframe i's 15 columns and keyframe j's first
 // 9 (one lane per entry)
@@ -1395,6 +1994,19 @@ __global__ void k_vi_cross(VIDev d) {
         u += J[24 * m + a] * w;
     }
     d.icx[t] = u;
+}
+
+// the same as whole 15 x 15 blocks with the bias random walk's -Omega_b, and
+// transposed, for the explicit products (one lane per entry)
+__global__ void k_vi_cross_full(VIDev d) {
+    const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+    if (t >= 225LL * (d.K - 1)) return;
+    const long long f = t / 225;
+    const int a = (int)(t % 225) / 15, c = (int)(t % 15);
+    double u = c < 9 ? d.icx[135 * f + 9 * a + c] : 0.0;
+    if (a == c && a >= 9 && f != 0) u -= (a < 12 ? d.wg : d.wa) / d.pre[(size_t)kPreStride * f + kDt];
+    d.cb[225 * f + 15 * a + c] = u;
+    d.cbt[225 * f + 15 * c + a] = u;
 }
 
 // q_k = A_k v: (hk_k + lambda diag(D_k)) v_k plus the cross blocks to
@@ -1702,21 +2314,43 @@ __global__ void k_vi_xnorm(VIDev d, const double* __restrict__ st, const double*
 // ------------------------------------------------------------------ C ABI
 namespace {
 
-// Device buffers of one call, released on every return path.
+// Device buffers of one call, carved from a few allocations (an allocation
+// and its release cost 20-200 us each; a solve takes about 50 buffers) and
+// released on every return path.
 struct DevBufs {
-    std::vector<void*> p;
-    size_t bytes = 0;
+    std::vector<void*> chunks;
+    char* at = nullptr;
+    size_t left = 0, next, bytes = 0;
+    explicit DevBufs(size_t expect) : next(expect) {}
+    DevBufs(const DevBufs&) = delete;
+    DevBufs& operator=(const DevBufs&) = delete;
     ~DevBufs() {
-        for (void* q : p) (void)hipFree(q);
+        for (void* q : chunks) (void)hipFree(q);
     }
     template <typename T>
     bool up(T** dst, const T* src, size_t n) {
-        void* q = nullptr;
-        if (hipMalloc(&q, n * sizeof(T) + 16) != hipSuccess) return false;
-        p.push_back(q);
-        bytes += n * sizeof(T) + 16;
-        *dst = (T*)q;
-        return !src || hipMemcpy(q, src, n * sizeof(T), hipMemcpyHostToDevice) == hipSuccess;
+        const size_t need = (n * sizeof(T) + 16 + 255) & ~(size_t)255;
+        if (need > left) {
+            const size_t size = std::max(need, next);
+            void* q = nullptr;
+            if (hipMalloc(&q, size) != hipSuccess) {
+                // the expected size may be more than what is left needs
+                const bool ok = size > need && hipMalloc(&q, need) == hipSuccess;
+                (void)hipGetLastError();   // a failed allocation is the caller's to handle
+                if (!ok) return false;
+                left = need;
+            } else {
+                left = size;
+            }
+            chunks.push_back(q);
+            bytes += left;
+            at = (char*)q;
+            next = std::max<size_t>(next / 8, 1 << 20);
+        }
+        *dst = (T*)at;
+        at += need;
+        left -= need;
+        return !src || n == 0 || hipMemcpy(*dst, src, n * sizeof(T), hipMemcpyHostToDevice) == hipSuccess;
     }
 };
 
@@ -1735,11 +2369,11 @@ gba_status gba_vi_preintegrate(int device, int n, const int64_t* sample_off, con
     const size_t ns = (size_t)sample_off[n];
     if (ns > 0 && (!gyro || !acc)) return GBA_ERR_INVALID_ARG;
     if (hipSetDevice(device) != hipSuccess) return GBA_ERR_HIP;
-    DevBufs b;
+    DevBufs b(sizeof(double) * (6 * ns + (gba::vi::kPreStride + 8) * (size_t)n) + 8192);
     long long* doff = nullptr;
     double *dg = nullptr, *da = nullptr, *db = nullptr, *dout = nullptr;
-    if (!b.up(&doff, (const long long*)sample_off, (size_t)n + 1) || !b.up(&dg, gyro, 3 * ns + 3) ||
-        !b.up(&da, acc, 3 * ns + 3) || !b.up(&db, bias0, 6 * (size_t)n) ||
+    if (!b.up(&doff, (const long long*)sample_off, (size_t)n + 1) || !b.up(&dg, gyro, 3 * ns) ||
+        !b.up(&da, acc, 3 * ns) || !b.up(&db, bias0, 6 * (size_t)n) ||
         !b.up(&dout, (const double*)nullptr, (size_t)gba::vi::kPreStride * n))
         return GBA_ERR_HIP;
     hipLaunchKernelGGL(gba::vi::k_preintegrate, dim3((n + 63) / 64), dim3(64), 0, nullptr, n, doff, dg,
@@ -1756,7 +2390,7 @@ gba_status gba_vi_eval_inertial(int device, int n_kf, const double* states, cons
     const int n = n_kf > 1 ? n_kf - 1 : 0;
     if (n == 0) return GBA_OK;
     if (hipSetDevice(device) != hipSuccess) return GBA_ERR_HIP;
-    DevBufs b;
+    DevBufs b(sizeof(double) * (15 + gba::vi::kPreStride + 225) * (size_t)n_kf + 8192);
     double *ds = nullptr, *dp = nullptr, *dr = nullptr, *dj = nullptr;
     if (!b.up(&ds, states, 15 * (size_t)n_kf) || !b.up(&dp, pre, (size_t)gba::vi::kPreStride * n) ||
         !b.up(&dr, (const double*)nullptr, 9 * (size_t)n) || !b.up(&dj, (const double*)nullptr, 216 * (size_t)n))
@@ -1780,7 +2414,7 @@ gba_status gba_vi_eval_stereo(int device, int n_kf, const double* states, int64_
     for (int64_t e = 0; e < n_obs; ++e)
         if (kf[e] < 0 || kf[e] >= n_kf || pt[e] < 0 || pt[e] >= n_pts) return GBA_ERR_UNKNOWN_ID;
     if (hipSetDevice(device) != hipSuccess) return GBA_ERR_HIP;
-    DevBufs b;
+    DevBufs b(sizeof(double) * (15 * (size_t)n_kf + 3 * (size_t)n_pts + 35 * (size_t)n_obs) + 8192);
     double *ds = nullptr, *dpts = nullptr, *dobs = nullptr, *dr = nullptr, *dj = nullptr;
     long long *dkf = nullptr, *dpt = nullptr;
     if (!b.up(&ds, states, 15 * (size_t)n_kf) || !b.up(&dpts, pts, 3 * (size_t)n_pts) ||
@@ -1835,96 +2469,142 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
 
         !(o.min_diag > 0.0) || !(o.max_diag >= o.min_diag))
         return GBA_ERR_INVALID_ARG;
-    // observations in keyframe order (a stable counting sort), so that the
-    // keyframe terms of a wavefront sum across it before their atomic add
-    std::vector<int> hkf((size_t)P.n_obs + 1, 0), hpt((size_t)P.n_obs + 1, 0);   // + 1: uploaded with a pad
-    std::vector<double> hobs(3 * (size_t)P.n_obs + 1, 0.0);
-    {
-        std::vector<int64_t> cnt((size_t)P.n_kf + 1, 0);
-        for (int64_t e = 0; e < P.n_obs; ++e) {
-            if (P.kf[e] < 0 || P.kf[e] >= P.n_kf || P.pt[e] < 0 || P.pt[e] >= P.n_pts)
-                return GBA_ERR_UNKNOWN_ID;
-            ++cnt[(size_t)P.kf[e] + 1];
-        }
-        for (int k = 0; k < P.n_kf; ++k) cnt[(size_t)k + 1] += cnt[(size_t)k];
-        for (int64_t e = 0; e < P.n_obs; ++e) {
-            const size_t q = (size_t)cnt[(size_t)P.kf[e]]++;
-            hkf[q] = (int)P.kf[e];
-            hpt[q] = (int)P.pt[e];
-            for (int c = 0; c < 3; ++c) hobs[3 * q + c] = P.obs[3 * e + c];
-        }
-    }
-    // points renumbered by the first keyframe that observes them (stable;
-    // unobserved points last), so that a keyframe's observations and a run
-    // of consecutive points touch nearby points and keyframes: the point
-    // and keyframe gathers of the products stay within a narrow window
-    std::vector<int> pt_new((size_t)P.n_pts), pt_old((size_t)P.n_pts);
-    {
-        std::vector<int> first((size_t)P.n_pts, P.n_kf);
-        for (int64_t e = 0; e < P.n_obs; ++e) first[hpt[e]] = std::min(first[hpt[e]], hkf[e]);
-        std::vector<int64_t> cnt((size_t)P.n_kf + 2, 0);
-        for (int64_t j = 0; j < P.n_pts; ++j) ++cnt[(size_t)first[j] + 1];
-        for (int k = 0; k <= P.n_kf; ++k) cnt[(size_t)k + 1] += cnt[(size_t)k];
-        for (int64_t j = 0; j < P.n_pts; ++j) {
-            const int q = (int)cnt[(size_t)first[j]]++;
-            pt_new[j] = q;
-            pt_old[q] = (int)j;
-        }
-        for (int64_t e = 0; e < P.n_obs; ++e) hpt[e] = pt_new[hpt[e]];
-    }
-    std::vector<double> hX(3 * (size_t)P.n_pts + 1, 0.0);
-    for (int64_t q = 0; q < P.n_pts; ++q)
-        for (int c = 0; c < 3; ++c) hX[3 * q + c] = P.pts[3 * (size_t)pt_old[q] + c];
-    const bool schur = o.solver == GBA_SOLVER_SCHUR;
-    // the same observations in point order (stable in the keyframe order),
-    // padded so that a point's observations sit in one wavefront (64 slots)
-    // unless it has more than 64 of them
-    std::vector<int> hqkf, hqpt, hlong, hlslot;
-    std::vector<double> hqobs;
-    long long Mp = 0;
-    {
-        std::vector<int64_t> cnt((size_t)P.n_pts, 0), at((size_t)P.n_pts, 0);
-        for (int64_t e = 0; e < P.n_obs; ++e) ++cnt[(size_t)hpt[e]];
-        for (int64_t j = 0; j < P.n_pts; ++j) {
-            const int64_t c = cnt[(size_t)j];
-            if (c == 0) continue;
-            if (c > 64) hlong.push_back((int)j);
-            else if (Mp % 64 + c > 64) Mp = (Mp + 63) / 64 * 64;
-            at[(size_t)j] = Mp;
-            Mp += c;
-        }
-        Mp = (Mp + 63) / 64 * 64;
-        if (Mp > INT32_MAX / 18) return GBA_ERR_UNSUPPORTED;
-        hqkf.assign((size_t)Mp + 1, 0);
-        hqpt.assign((size_t)Mp + 1, -1);
-        hqobs.assign(3 * (size_t)Mp + 1, 0.0);
-        for (int64_t e = 0; e < P.n_obs; ++e) {
-            const size_t q = (size_t)at[(size_t)hpt[e]]++;
-            hqkf[q] = hkf[e];
-            hqpt[q] = hpt[e];
-            for (int c = 0; c < 3; ++c) hqobs[3 * q + c] = hobs[3 * e + c];
-        }
-        for (const int j : hlong)
-            for (int64_t q = at[(size_t)j] - cnt[(size_t)j]; q < at[(size_t)j]; ++q) hlslot.push_back((int)q);
-    }
+    for (int64_t e = 0; e < P.n_obs; ++e)
+        if (P.kf[e] < 0 || P.kf[e] >= P.n_kf || P.pt[e] < 0 || P.pt[e] >= P.n_pts) return GBA_ERR_UNKNOWN_ID;
     if (hipSetDevice(device) != hipSuccess) return GBA_ERR_HIP;
+    const bool schur = o.solver == GBA_SOLVER_SCHUR;
     const int K = P.n_kf;
     const long long N = P.n_pts, M = P.n_obs, n = 15LL * K + 3 * N;
-    DevBufs B;
+    const bool f32 = o.precision == GBA_MIXED_FP32;
+    // one allocation for nearly everything (about this much, see below)
+    DevBufs B((size_t)(8.0 * (8200.0 * K + 46.0 * N) + (double)M * (170.0 + (f32 ? 4.0 : 8.0) * (schur ? 37 : 28)) +
+                       (1 << 20)));
     VIDev d{};
     d.K = K;
     d.N = N;
     d.M = M;
+    auto grid = [](long long cnt) { return dim3((unsigned)std::max(1LL, (cnt + 255) / 256)); };
+    const dim3 blk(256);
+    hipError_t err = hipSuccess;
+    auto chk = [&]() {
+        if (err == hipSuccess) err = hipGetLastError();
+        return err == hipSuccess;
+    };
+    const int* no_in = nullptr;
+    // items sorted by key (0 .. nkeys - 1, stable; negative keys left out),
+    // 12 bits a pass; tmp: as many items
+    auto sort_by = [&](int items, int kept, const int* key, int nkeys, int* out, int* tmp) {
+        int passes = 1;
+        while (((nkeys - 1) >> (kSortBits * passes)) > 0) ++passes;
+        int *counts = nullptr, *total = nullptr;
+        const int nblk = (items + kSortItems - 1) / kSortItems, nb = std::min(nkeys, kSortBins);
+        if (!B.up(&counts, no_in, (size_t)nblk * nb) || !B.up(&total, no_in, (size_t)nb)) return false;
+        int left = items;
+        const int* in = no_in;
+        for (int p = 0; p < passes; ++p) {
+            int* to = (passes - 1 - p) % 2 == 0 ? out : tmp;
+            const int nbl = (left + kSortItems - 1) / kSortItems, shift = kSortBits * p;
+            hipLaunchKernelGGL(k_sort_count, dim3(nbl), blk, 0, nullptr, left, in, key, shift, nb, counts);
+            hipLaunchKernelGGL(k_sort_rows, dim3(nb), dim3(64), 0, nullptr, nbl, counts, total);
+            hipLaunchKernelGGL(k_sort_base, dim3(1), dim3(64), 0, nullptr, nb, total);
+            hipLaunchKernelGGL(k_sort_place, dim3(nbl), dim3(64), 0, nullptr, left, in, key, shift, nb,
+                               (const int*)counts, (const int*)total, to);
+            in = to;
+            left = kept;   // negative keys are gone after the first pass
+        }
+        return chk();
+    };
     double *s15 = nullptr, *pre = nullptr, *x = nullptr, *r = nullptr, *z = nullptr, *pv = nullptr,
-           *q = nullptr, *xb = nullptr;
-    int *dkf = nullptr, *dpt = nullptr;
-    double* obs = nullptr;
-    if (!B.up(&s15, P.states, 15 * (size_t)K) || !B.up(&d.st, (const double*)nullptr, kSt * (size_t)K) ||
+           *q = nullptr, *xb = nullptr, *p2 = nullptr, *Xraw = nullptr;
+    int* pt_old = nullptr;
+    std::vector<int> hlong, hlslot;
+    long long Mp = 0, pairs = 0;   // padded point order; pairs of observations of one point
+    bool twice = false;            // a keyframe observes a point more than once
+    if (!B.up(&s15, P.states, 15 * (size_t)K) || !B.up(&pre, P.pre, (size_t)kPreStride * (K - 1)) ||
+        !B.up(&Xraw, P.pts, 3 * (size_t)N) || !B.up(&d.X, (const double*)nullptr, 3 * (size_t)N) ||
+        !B.up(&d.X_c, (const double*)nullptr, 3 * (size_t)N + 1) || !B.up(&pt_old, no_in, (size_t)N + 1))
+        return GBA_ERR_OOM;
+    {
+        // The orders, on the device (gba_vi_order.h).  Points are renumbered
+        // by the first keyframe that observes them (stable; unobserved points
+        // last), so that a keyframe's observations and a run of consecutive
+        // points touch nearby points and keyframes.
+        const long long *kf64 = nullptr, *pt64 = nullptr;
+        const double* raw = nullptr;
+        int *kf = nullptr, *pt = nullptr, *first = nullptr, *cnt = nullptr, *cntn = nullptr, *renum = nullptr,
+            *at = nullptr, *used = nullptr, *flag = nullptr, *tmp = nullptr;
+        if (!B.up((long long**)&kf64, (const long long*)P.kf, (size_t)M) ||
+            !B.up((long long**)&pt64, (const long long*)P.pt, (size_t)M) ||
+            !B.up((double**)&raw, P.obs, 3 * (size_t)M) || !B.up(&kf, no_in, (size_t)M) || !B.up(&pt, no_in, (size_t)M) ||
+            !B.up(&first, no_in, (size_t)N) || !B.up(&cnt, no_in, (size_t)N) || !B.up(&cntn, no_in, (size_t)N) ||
+            !B.up(&renum, no_in, (size_t)N) || !B.up(&used, no_in, (size_t)N) || !B.up(&flag, no_in, 1) ||
+            !B.up(&tmp, no_in, (size_t)std::max(N, M)))
+            return GBA_ERR_OOM;
+        std::vector<int> hcnt((size_t)N), hat((size_t)N + 1, 0);
+        if (N > 0) {
+            hipLaunchKernelGGL(k_vo_fill, grid(N), blk, 0, nullptr, N, first, K);
+            hipLaunchKernelGGL(k_vo_fill, grid(N), blk, 0, nullptr, N, cnt, 0);
+            hipLaunchKernelGGL(k_vo_fill, grid(N), blk, 0, nullptr, N, used, 0);
+            if (M > 0) hipLaunchKernelGGL(k_vo_raw, grid(M), blk, 0, nullptr, M, kf64, pt64, kf, pt, first, cnt);
+            if (!sort_by((int)N, (int)N, first, K + 1, pt_old, tmp)) return GBA_ERR_HIP;
+            hipLaunchKernelGGL(k_vo_points, grid(N), blk, 0, nullptr, (int)N, (const int*)pt_old, (const int*)cnt,
+                               (const double*)Xraw, renum, cntn, d.X);
+            if (!chk() || hipMemcpy(hcnt.data(), cntn, sizeof(int) * N, hipMemcpyDeviceToHost) != hipSuccess)
+                return GBA_ERR_HIP;
+        }
+        // the padded point order: a point's observations sit in one wavefront
+        // (64 slots) unless it has more than 64 of them
+        for (long long j = 0; j < N; ++j) {
+            const long long c = hcnt[(size_t)j];
+            if (c > 64) hlong.push_back((int)j);
+            else if (Mp % 64 + c > 64) Mp = (Mp + 63) / 64 * 64;
+            hat[(size_t)j] = (int)Mp;
+            pairs += c * (c - 1) / 2;
+            Mp += c;
+            if (Mp > INT32_MAX / 18) return GBA_ERR_UNSUPPORTED;
+        }
+        Mp = (Mp + 63) / 64 * 64;
+        for (const int j : hlong)
+            for (int c = 0; c < hcnt[(size_t)j]; ++c) hlslot.push_back(hat[(size_t)j] + c);
+        int *qe = nullptr, *qs = nullptr, *qkf = nullptr, *qpt = nullptr, *key = nullptr, *dkf = nullptr, *dpt = nullptr,
+            *ks = nullptr, *ko = nullptr;
+        double *qobs = nullptr, *obs = nullptr;
+        if (!B.up(&at, (const int*)hat.data(), (size_t)N) || !B.up(&qe, no_in, (size_t)Mp) ||
+            !B.up(&qs, no_in, (size_t)Mp) || !B.up(&qkf, no_in, (size_t)Mp + 1) || !B.up(&qpt, no_in, (size_t)Mp + 1) ||
+            !B.up(&key, no_in, (size_t)Mp) || !B.up(&qobs, (const double*)nullptr, 3 * (size_t)Mp + 1) ||
+            !B.up(&dkf, no_in, (size_t)M + 1) || !B.up(&dpt, no_in, (size_t)M + 1) ||
+            !B.up(&obs, (const double*)nullptr, 3 * (size_t)M + 1) || !B.up(&ks, no_in, (size_t)M) ||
+            !B.up(&ko, no_in, (size_t)K + 1))
+            return GBA_ERR_OOM;
+        if (M > 0) {
+            hipLaunchKernelGGL(k_vo_fill, grid(Mp + 1), blk, 0, nullptr, Mp + 1, qpt, -1);
+            hipLaunchKernelGGL(k_vo_fill, dim3(1), blk, 0, nullptr, 1LL, flag, 0);
+            hipLaunchKernelGGL(k_vo_place, grid(M), blk, 0, nullptr, M, (const int*)pt, (const int*)renum,
+                               (const int*)at, used, qe, qpt);
+            hipLaunchKernelGGL(k_vo_rank, grid(Mp), blk, 0, nullptr, Mp, (const int*)qpt, (const int*)at,
+                               (const int*)cntn, (const int*)kf, (const int*)qe, qs);
+            hipLaunchKernelGGL(k_vo_slots, grid(Mp), blk, 0, nullptr, Mp, (const int*)qs, (const int*)qpt,
+                               (const int*)kf, raw, qkf, key, qobs, flag);
+            if (!sort_by((int)Mp, (int)M, key, K, ks, tmp)) return GBA_ERR_HIP;
+            hipLaunchKernelGGL(k_vo_kf, grid(M), blk, 0, nullptr, (int)M, K, (const int*)ks, (const int*)qkf,
+                               (const int*)qpt, (const double*)qobs, dkf, dpt, obs, key, ko);
+            int h = 0;
+            if (!chk() || hipMemcpy(&h, flag, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess) return GBA_ERR_HIP;
+            twice = h != 0;
+        }
+        d.Mp = Mp;
+        d.qkf = qkf;
+        d.qpt = qpt;
+        d.qobs = qobs;
+        d.kf = dkf;
+        d.pt = dpt;
+        d.obs = obs;
+        d.kslot = ks;
+        d.kinv = key;
+        d.kfoff = ko;
+    }
+    if (!B.up(&d.st, (const double*)nullptr, kSt * (size_t)K) ||
         !B.up(&d.st_c, (const double*)nullptr, kSt * (size_t)K) ||
-        !B.up(&d.X, (const double*)hX.data(), 3 * (size_t)N) || !B.up(&d.X_c, (const double*)nullptr, 3 * (size_t)N + 1) ||
-        !B.up(&dkf, hkf.data(), (size_t)M + 1) || !B.up(&dpt, hpt.data(), (size_t)M + 1) ||
-        !B.up(&obs, hobs.data(), 3 * (size_t)M + 1) ||
-        !B.up(&pre, P.pre, (size_t)kPreStride * (K - 1)) ||
         !B.up(&d.info, (const double*)nullptr, 81 * (size_t)(K - 1)) ||
         !B.up(&d.ji, (const double*)nullptr, 216 * (size_t)(K - 1)) ||
         !B.up(&d.ri, (const double*)nullptr, 9 * (size_t)(K - 1)) ||
@@ -1934,19 +2614,8 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         !B.up(&d.scal, (const double*)nullptr, (size_t)kScalN) || !B.up(&x, (const double*)nullptr, (size_t)n) ||
         !B.up(&r, (const double*)nullptr, (size_t)n) || !B.up(&z, (const double*)nullptr, (size_t)n) ||
         !B.up(&pv, (const double*)nullptr, (size_t)n) || !B.up(&q, (const double*)nullptr, (size_t)n) ||
-        !B.up(&xb, (const double*)nullptr, (size_t)n))
+        !B.up(&xb, (const double*)nullptr, (size_t)n) || !B.up(&p2, (const double*)nullptr, 15 * (size_t)K))
         return GBA_ERR_OOM;
-    {   // the padded point order (both forms)
-        int *qkf = nullptr, *qpt = nullptr;
-        double* qobs = nullptr;
-        if (!B.up(&qkf, hqkf.data(), (size_t)Mp + 1) || !B.up(&qpt, hqpt.data(), (size_t)Mp + 1) ||
-            !B.up(&qobs, hqobs.data(), 3 * (size_t)Mp + 1))
-            return GBA_ERR_OOM;
-        d.qkf = qkf;
-        d.qpt = qpt;
-        d.qobs = qobs;
-        d.Mp = Mp;
-    }
     if (!schur) {   // the point-order J (FP32: half the doubles, rounded up)
         d.w32 = o.precision == GBA_MIXED_FP32 ? 1 : 0;
         double* jp = nullptr;
@@ -1965,8 +2634,8 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
             !B.up(&d.icx, (const double*)nullptr, 135 * (size_t)(K - 1)) ||
             !B.up(&d.sm, (const double*)nullptr, 36 * (size_t)K) ||
             !B.up(&zb, (const double*)nullptr, 3 * (size_t)N + 1) ||
-            !B.up(&lp, hlong.empty() ? (const int*)nullptr : hlong.data(), hlong.size() + 1) ||
-            !B.up(&ls, hlslot.empty() ? (const int*)nullptr : hlslot.data(), hlslot.size() + 1) ||
+            !B.up(&lp, hlong.empty() ? (const int*)nullptr : hlong.data(), hlong.size()) ||
+            !B.up(&ls, hlslot.empty() ? (const int*)nullptr : hlslot.data(), hlslot.size()) ||
             !B.up(&d.tb, (const double*)nullptr, 3 * (size_t)N + 1))
             return GBA_ERR_OOM;
         if (hipMemset(d.tb, 0, sizeof(double) * (3 * (size_t)N + 1)) != hipSuccess) return GBA_ERR_HIP;
@@ -1977,9 +2646,38 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         d.lslot = ls;
         d.nlslot = (long long)hlslot.size();
     }
-    d.kf = dkf;
-    d.pt = dpt;
-    d.obs = obs;
+    // The visual blocks of S explicitly: when no keyframe observes a point
+    // twice (the diagonal blocks are then exact), tracks are short enough
+    // that forming them (about 20 ps a pair and step) stays below a few
+    // implicit products (about 20 ps an observation and PCG iteration), and a
+    // keyframe's counts fit in LDS.
+    bool explicit_s = schur && M > 0 && !twice && pairs > 0 && pairs <= 16 * M && K <= 16000;
+    if (explicit_s) {
+        (void)hipFuncSetAttribute((const void*)k_vi_s_pcg_one, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  144 * kOneKf * (kOneKf - 1));
+        if (!B.up(&d.nrow, no_in, (size_t)K + 1) || !B.up(&d.nitem, no_in, (size_t)K + 1) ||
+            !B.up(&d.items, (const int2*)nullptr, (size_t)pairs) || !B.up(&d.ad, (const double*)nullptr, 225 * (size_t)K) ||
+            !B.up(&d.cb, (const double*)nullptr, 225 * (size_t)(K - 1)) ||
+            !B.up(&d.cbt, (const double*)nullptr, 225 * (size_t)(K - 1)))
+            explicit_s = false;   // no room for them: the implicit product needs none
+    }
+    if (explicit_s) {
+        const int lds = K * (int)sizeof(int);
+        hipLaunchKernelGGL(k_vi_pattern<false>, dim3(K), dim3(256), lds, nullptr, d);
+        hipLaunchKernelGGL(k_vi_pattern_scan, dim3(1), dim3(1024), 0, nullptr, d);
+        if (hipGetLastError() != hipSuccess ||
+            hipMemcpy(&d.nnz, d.nrow + K, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess)
+            return GBA_ERR_HIP;
+        if (!B.up(&d.ncol, (const int*)nullptr, (size_t)d.nnz) || !B.up(&d.noff, (const int*)nullptr, (size_t)d.nnz) ||
+            !B.up(&d.nkf, (const int*)nullptr, (size_t)d.nnz) ||
+            !B.up(&d.vblk, (const double*)nullptr, 36 * (size_t)d.nnz))
+            explicit_s = false;
+    }
+    if (explicit_s) {
+        const int lds = K * (int)sizeof(int);
+        hipLaunchKernelGGL(k_vi_pattern<true>, dim3(K), dim3(256), lds, nullptr, d);
+        if (hipGetLastError() != hipSuccess) return GBA_ERR_HIP;
+    }
     d.pre = pre;
     d.fx = P.intr[0];
     d.fy = P.intr[1];
@@ -1990,13 +2688,6 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
     d.delta2 = P.huber_delta2;
     d.wg = 1.0 / (P.sigma_gw * P.sigma_gw);
     d.wa = 1.0 / (P.sigma_aw * P.sigma_aw);
-    auto grid = [](long long cnt) { return dim3((unsigned)std::max(1LL, (cnt + 255) / 256)); };
-    const dim3 blk(256);
-    hipError_t err = hipSuccess;
-    auto chk = [&]() {
-        if (err == hipSuccess) err = hipGetLastError();
-        return err == hipSuccess;
-    };
     hipLaunchKernelGGL(k_vi_states_in, grid(K), blk, 0, nullptr, K, s15, d.st);
     hipLaunchKernelGGL(k_vi_info, grid(K - 1), blk, 0, nullptr, K - 1, pre, d.info);
     if (!chk()) return GBA_ERR_HIP;
@@ -2049,6 +2740,7 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         hipLaunchKernelGGL(k_vi_lin_inertial, grid(24LL * (K - 1)), blk, 0, nullptr, d);
         hipLaunchKernelGGL(k_vi_acc_inertial, grid(64LL * (K - 1)), blk, 0, nullptr, d);
         if (schur) hipLaunchKernelGGL(k_vi_cross, grid(135LL * (K - 1)), blk, 0, nullptr, d);
+        if (explicit_s) hipLaunchKernelGGL(k_vi_cross_full, grid(225LL * (K - 1)), blk, 0, nullptr, d);
         return chk();
     };
     auto schur_kf = [&](const double* zz, double* out, const double* g) {
@@ -2142,10 +2834,47 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         hipLaunchKernelGGL(k_vi_fill, grid(nn), blk, 0, nullptr, nn, xb, none);   // the best iterate: x0 = 0
         if (schur) hipLaunchKernelGGL(k_vi_fill, grid(nn), blk, 0, nullptr, nn, q, none);   // the products add into q
         hipLaunchKernelGGL(k_vi_pcg_init, dim3(1), dim3(1), 0, nullptr, ps, o.pcg_tol, ratio2);
+        if (explicit_s) {
+            // the blocks of this step, then the PCG on them: one launch for a
+            // short trajectory, else two per step (p and its successor in pv
+            // and q2 in turn)
+            const dim3 fg((unsigned)d.nnz);
+            if (d.nnz < 4096) {   // few blocks: four wavefronts each
+                if (d.w32) hipLaunchKernelGGL((k_vi_form_blocks<float, 4>), fg, dim3(256), 0, nullptr, d);
+                else hipLaunchKernelGGL((k_vi_form_blocks<double, 4>), fg, dim3(256), 0, nullptr, d);
+            } else {
+                if (d.w32) hipLaunchKernelGGL((k_vi_form_blocks<float, 1>), fg, dim3(64), 0, nullptr, d);
+                else hipLaunchKernelGGL((k_vi_form_blocks<double, 1>), fg, dim3(64), 0, nullptr, d);
+            }
+            if (K <= kOneKf) {
+                hipLaunchKernelGGL(k_vi_s_pcg_one, dim3(1), dim3(kOneBlock), 144 * d.nnz, nullptr, d, ps,
+                                   o.pcg_max_iters, (const double*)r, (const double*)z, x);
+            } else {
+                const dim3 pg((unsigned)((K + 3) / 4)), ug((unsigned)((K + 15) / 16));
+                double* dir[2] = {pv, p2};
+                hipLaunchKernelGGL(k_vi_fill, grid(nn), blk, 0, nullptr, nn, p2, none);
+                int it = 0;
+                for (; it < o.pcg_max_iters; ++it) {
+                    const int slot = it % kSlots, prev = (it + kSlots - 1) % kSlots;
+                    hipLaunchKernelGGL(k_vi_s_prod, pg, blk, 0, nullptr, d, ps, slot, prev, it == 0 ? 1 : 0, 0,
+                                       (const double*)z, (const double*)dir[(it + 1) & 1], dir[it & 1], q, x, xb);
+                    hipLaunchKernelGGL(k_vi_s_update, ug, blk, 0, nullptr, d, ps, slot, prev,
+                                       (const double*)dir[it & 1], (const double*)q, x, r, z);
+                    const int first_read = std::max(kPcgSync, prev_iters - kPcgSync);
+                    if (it + 1 >= first_read && (it + 1 - first_read) % kPcgSync == 0 && it + 1 < o.pcg_max_iters) {
+                        if (!chk() || !read_scal()) return false;
+                        if (hs[8 + kDone] != 0.0) break;
+                    }
+                }
+                if (it == o.pcg_max_iters)   // the decisions about the last step
+                    hipLaunchKernelGGL(k_vi_s_prod, pg, blk, 0, nullptr, d, ps, 0, (it + kSlots - 1) % kSlots, 0,
+                                       1, (const double*)z, (const double*)pv, p2, q, x, xb);
+            }
+        }
         const long long npt = schur ? 0 : N;
         const dim3 upd((unsigned)((K + 15) / 16 + (npt + kUpdPts - 1) / kUpdPts));
         const dim3 dirg((unsigned)std::max(1LL, std::min<long long>(1024, (nn + 255) / 256)));
-        for (int it = 0; it < o.pcg_max_iters; ++it) {
+        for (int it = 0; !explicit_s && it < o.pcg_max_iters; ++it) {
             const int slot = it % kSlots;
             if (schur) {
                 schur_product(pv, q, lam, ps, ps + kAccN * slot + kAccPq);   // p . q summed inside
@@ -2261,11 +2990,13 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
     rep.final_lambda = lam;
     hipLaunchKernelGGL(k_vi_states_out, grid(K), blk, 0, nullptr, K, d.st, s15);
     if (!chk()) return GBA_ERR_HIP;
+    if (N > 0)
+        hipLaunchKernelGGL(k_vo_points_out, grid(N), blk, 0, nullptr, (int)N, (const int*)pt_old, (const double*)d.X,
+                           Xraw);
+    if (!chk()) return GBA_ERR_HIP;
     if (hipMemcpy(P.states, s15, sizeof(double) * 15 * K, hipMemcpyDeviceToHost) != hipSuccess ||
-        (N > 0 && hipMemcpy(hX.data(), d.X, sizeof(double) * 3 * N, hipMemcpyDeviceToHost) != hipSuccess))
+        (N > 0 && hipMemcpy(P.pts, Xraw, sizeof(double) * 3 * N, hipMemcpyDeviceToHost) != hipSuccess))
         return GBA_ERR_HIP;
-    for (int64_t q = 0; q < N; ++q)
-        for (int c = 0; c < 3; ++c) P.pts[3 * (size_t)pt_old[q] + c] = hX[3 * q + c];
     rep.ms_total = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count();
     if (report) *report = rep;
     if (n_log) *n_log = nl;

@@ -1,0 +1,138 @@
+"""The explicit keyframe blocks of the visual-inertial Schur form and the
+device-side observation orders: truncated PCG steps against the oracle's
+Schur PCG at the keyframe counts where the PCG changes its form (one
+workgroup up to 32 keyframes, two launches a step above), with observations
+in any order, unobserved points and tracks of more than 64 observations; a
+keyframe that observes a point twice takes the implicit products and gives
+the oracle's step too."""
+import numpy as np
+import pytest
+
+from oracle import imu, vi
+from paper_2509_26581_amd import gba, synth_vi
+
+pytestmark = pytest.mark.gpu
+
+SIG_G, SIG_A, SIG_GW, SIG_AW = 1.7e-4, 2e-3, 2e-5, 3e-3
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    gba.load()
+
+
+def _problem(n_kf, n_pts, seed, window=None, extra=0, twice=0):
+    """Scene, oracle problem, start, GPU arguments; observations shuffled,
+    extra unobserved points among the others, twice observations repeated."""
+    sc = synth_vi.make_vi_scene(seed=seed, n_kf=n_kf, n_pts=n_pts, window=window)
+    rng = np.random.default_rng(seed + 7)
+    R0 = np.stack([sc.R_true[k] @ imu.so3_exp(rng.normal(0, 0.01, 3) if k else np.zeros(3))
+                   for k in range(n_kf)])
+    dp, dv = rng.normal(0, 0.05, (2, n_kf, 3))
+    dp[0] = dv[0] = 0.0
+    n = sc.pts.shape[0] + extra
+    place = rng.permutation(n)
+    X0 = rng.normal(0.0, 3.0, (n, 3))
+    X0[place[:sc.pts.shape[0]]] = sc.pts + rng.normal(0, 0.05, sc.pts.shape)
+    order = rng.permutation(len(sc.st_kf))
+    order = np.concatenate([order, order[:twice]])
+    kf, pt, obs = sc.st_kf[order], place[sc.st_pt[order]], sc.st_obs[order]
+    x0 = vi.VIState(R0, sc.p_true + dp, sc.v_true + dv, sc.bg_true.copy(), sc.ba_true.copy(), X0)
+    pre_o = [imu.preintegrate(sc.gyro[f], sc.acc[f], sc.imu_dt, sc.bg_true[f], sc.ba_true[f], SIG_G, SIG_A)
+             for f in range(n_kf - 1)]
+    prob = vi.VIProblem(kf, pt, obs, sc.intr, pre_o, sigma_px=1.0, delta2=7.815, sigma_gw=SIG_GW,
+                        sigma_aw=SIG_AW)
+    off = np.arange(n_kf, dtype=np.int64) * sc.gyro.shape[1]
+    pre_g = gba.gba_vi_preintegrate(0, off, sc.gyro.reshape(-1, 3), sc.acc.reshape(-1, 3), sc.imu_dt,
+                                    np.concatenate([sc.bg_true[:-1], sc.ba_true[:-1]], axis=1), SIG_G, SIG_A)
+    states = np.concatenate([np.array([imu.so3_log(R) for R in R0]), x0.p, x0.v, x0.bg, x0.ba], axis=1)
+
+    def run(trials, **opt):
+        return gba.gba_vi_solve(0, states, X0, kf, pt, obs, sc.intr, pre_g, trials, sigma_px=1.0,
+                                huber_delta2=7.815, sigma_gw=SIG_GW, sigma_aw=SIG_AW,
+                                options=gba.vi_options(solver=gba.GBA_SOLVER_SCHUR, **opt))
+    return prob, x0, run
+
+
+# keyframes, points, window, unobserved points, repeated observations
+CASES = [(2, 40, None, 3, 0), (9, 90, None, 0, 0), (31, 120, 4, 0, 0), (32, 130, None, 2, 0),
+         (33, 130, None, 2, 0), (33, 150, 3, 0, 0), (70, 60, None, 1, 0)]
+
+
+@pytest.mark.parametrize("k", [1, 6])
+@pytest.mark.parametrize("n_kf,n_pts,window,extra,twice", CASES)
+def test_vi_block_steps_match_the_oracle(n_kf, n_pts, window, extra, twice, k):
+    # tolerances as for the implicit products: FP64 sums in another order
+    prob, x0, run = _problem(n_kf, n_pts, 20 + n_kf, window, extra, twice)
+    _, _, _, log = run(1, pcg_tol=0.0, pcg_max_iters=k)
+    lin = prob.linearize(x0)
+    dx, steps = prob.schur_pcg_step(lin, 1e-4, 1e-6, 1e32, 0.0, k)
+    t = log[0]
+    assert t["pcg_iters"] == steps == k
+    F1, L = prob.cost(prob.step(x0, dx)), prob.model_decrease(lin, dx)
+    assert abs(t["candidate_cost"] - F1) <= 1e-9 * F1, (t, F1)
+    assert abs(t["model_decrease"] - L) <= 1e-8 * abs(L), (t, L)
+    assert abs(t["step_norm"] - np.linalg.norm(dx)) <= 1e-8 * np.linalg.norm(dx)
+
+
+@pytest.mark.parametrize("n_kf,n_pts,window", [(9, 90, None), (33, 150, 3)])
+def test_vi_repeated_observations_match_the_oracle(n_kf, n_pts, window):
+    # (the preconditioner is then not the exact diagonal block: converged)
+    prob, x0, run = _problem(n_kf, n_pts, 20 + n_kf, window, 2, 5)
+    _, _, _, log = run(1, pcg_tol=1e-12, pcg_max_iters=4000)
+    lin = prob.linearize(x0)
+    dx, _ = prob.schur_pcg_step(lin, 1e-4, 1e-6, 1e32, 1e-12, 4000)
+    t = log[0]
+    F1, L = prob.cost(prob.step(x0, dx)), prob.model_decrease(lin, dx)
+    assert abs(t["candidate_cost"] - F1) <= 1e-8 * F1, (t, F1)
+    assert abs(t["model_decrease"] - L) <= 1e-6 * abs(L), (t, L)
+    assert abs(t["step_norm"] - np.linalg.norm(dx)) <= 1e-6 * np.linalg.norm(dx)
+
+
+@pytest.mark.parametrize("n_kf", [32, 33])
+def test_vi_block_stop_rules_match_the_oracle(n_kf):
+    # the tolerance ends the PCG at the oracle's step; a ratio just above 1
+    # ends it at the first rise of |r| with the best iterate
+    prob, x0, run = _problem(n_kf, 130, 3, None, 0)
+    lin = prob.linearize(x0)
+    for tol, ratio in [(1e-2, 0.0), (0.0, 1.001)]:
+        _, _, _, log = run(1, pcg_tol=tol, pcg_max_iters=60, pcg_rejection_ratio=ratio)
+        dx, steps = prob.schur_pcg_step(lin, 1e-4, 1e-6, 1e32, tol, 60, ratio if ratio else np.inf)
+        assert log[0]["pcg_iters"] == steps, (tol, ratio)
+        assert abs(log[0]["step_norm"] - np.linalg.norm(dx)) <= 1e-6 * np.linalg.norm(dx)
+
+
+def test_vi_order_is_independent_of_the_input_order():
+    # more keys than one sorting pass takes (12 bits) and several workgroups'
+    # worth of items: 4,500 keyframes with one observation run each; the
+    # caller's order of the observations does not change the first cost, and
+    # a PCG-converged step is the same to rounding
+    n_kf, per = 4500, 2
+    rng = np.random.default_rng(5)
+    sc = synth_vi.make_vi_scene(seed=2, n_kf=6, n_pts=40)
+    rep = n_kf // 6
+    kf = np.concatenate([sc.st_kf + 6 * b for b in range(rep)])
+    pt = np.concatenate([sc.st_pt + sc.pts.shape[0] * b for b in range(rep)])
+    obs = np.tile(sc.st_obs, (rep, 1))
+    keep = rng.random(len(kf)) < per / 6
+    kf, pt, obs = kf[keep], pt[keep], obs[keep]
+    X0 = np.tile(sc.pts, (rep, 1))
+    st6 = np.concatenate([np.array([imu.so3_log(R) for R in sc.R_true]), sc.p_true, sc.v_true, sc.bg_true,
+                          sc.ba_true], axis=1)
+    states = np.tile(st6, (rep, 1))
+    off = np.arange(n_kf, dtype=np.int64) * sc.gyro.shape[1]
+    g = np.tile(np.concatenate([sc.gyro, sc.gyro[:1]]).reshape(-1, 3), (rep, 1))[:off[-1]]
+    a = np.tile(np.concatenate([sc.acc, sc.acc[:1]]).reshape(-1, 3), (rep, 1))[:off[-1]]
+    pre = gba.gba_vi_preintegrate(0, off, g, a, sc.imu_dt, states[:-1, 9:15], SIG_G, SIG_A)
+    outs = []
+    for perm in (np.arange(len(kf)), rng.permutation(len(kf))):
+        outs.append(gba.gba_vi_solve(0, states, X0, kf[perm], pt[perm], obs[perm], sc.intr, pre, 1, sigma_px=1.0,
+                                     huber_delta2=7.815, sigma_gw=SIG_GW, sigma_aw=SIG_AW,
+                                     options=gba.vi_options(pcg_tol=0.0, pcg_max_iters=3)))
+    (s0, X_0, r0, l0), (s1, X_1, r1, l1) = outs
+    assert abs(r0["initial_cost"] - r1["initial_cost"]) <= 1e-12 * r0["initial_cost"]
+    assert abs(l0[0]["candidate_cost"] - l1[0]["candidate_cost"]) <= 1e-9 * l0[0]["candidate_cost"]
+    assert abs(l0[0]["step_norm"] - l1[0]["step_norm"]) <= 1e-9 * l0[0]["step_norm"]
