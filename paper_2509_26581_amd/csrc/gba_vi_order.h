@@ -12,9 +12,8 @@
 namespace gba {
 namespace vi {
 
-// ---- stable counting sort of item indices by a key's digit, kSortItems
-// items per workgroup, at most kSortBins digits
-constexpr int kSortItems = 4096;
+// ---- stable counting sort of item indices by a key's digit, `per` items per
+// workgroup, at most kSortBins digits
 constexpr int kSortBits = 12, kSortBins = 1 << kSortBits;
 
 __device__ __forceinline__ int sort_digit(const int* __restrict__ key, int item, int shift) {
@@ -23,12 +22,12 @@ __device__ __forceinline__ int sort_digit(const int* __restrict__ key, int item,
 }
 
 // counts per (digit, workgroup); in: the items in order (null: 0, 1, ...)
-__global__ __launch_bounds__(256) void k_sort_count(int n, const int* __restrict__ in, const int* __restrict__ key,
-                                                   int shift, int nb, int* __restrict__ counts) {
+__global__ __launch_bounds__(256) void k_sort_count(int n, int per, const int* __restrict__ in,
+                                                   const int* __restrict__ key, int shift, int nb, int* __restrict__ counts) {
     __shared__ int hist[kSortBins];
     for (int b = (int)threadIdx.x; b < nb; b += 256) hist[b] = 0;
     __syncthreads();
-    const int i0 = (int)blockIdx.x * kSortItems, i1 = min(n, i0 + kSortItems);
+    const int i0 = (int)blockIdx.x * per, i1 = (int)min((long long)n, i0 + (long long)per);
     for (int i = i0 + (int)threadIdx.x; i < i1; i += 256) {
         const int b = sort_digit(key, in ? in[i] : i, shift);
         if (b >= 0) atomicAdd(&hist[b], 1);
@@ -71,16 +70,16 @@ __global__ __launch_bounds__(64) void k_sort_base(int nb, int* __restrict__ tota
     }
 }
 
-// the items to their places: one wavefront per kSortItems items, 64 at a time
+// the items to their places: one wavefront per `per` items, 64 at a time
 // in order; lanes of one digit are ranked by ballots
-__global__ __launch_bounds__(64) void k_sort_place(int n, const int* __restrict__ in, const int* __restrict__ key,
-                                                  int shift, int nb, const int* __restrict__ offset,
+__global__ __launch_bounds__(64) void k_sort_place(int n, int per, const int* __restrict__ in,
+                                                  const int* __restrict__ key, int shift, int nb, const int* __restrict__ offset,
                                                   const int* __restrict__ base, int* __restrict__ out) {
     __shared__ int at[kSortBins];
     const int l = lane_id();
     for (int b = l; b < nb; b += 64) at[b] = base[b] + offset[(size_t)b * gridDim.x + blockIdx.x];
     __syncthreads();
-    const int i0 = (int)blockIdx.x * kSortItems, i1 = min(n, i0 + kSortItems);
+    const int i0 = (int)blockIdx.x * per, i1 = (int)min((long long)n, i0 + (long long)per);
     for (int i = i0 + l; i - l < i1; i += 64) {
         const int item = i < i1 ? (in ? in[i] : i) : 0;
         const int b = i < i1 ? sort_digit(key, item, shift) : -1;
@@ -105,13 +104,18 @@ __global__ __launch_bounds__(256) void k_vo_fill(long long n, int* __restrict__ 
     if (i < n) a[i] = v;
 }
 
-// 32-bit indices; per point the first keyframe and the observation count
-__global__ __launch_bounds__(256) void k_vo_raw(long long n, const long long* __restrict__ kf64,
+// 32-bit indices; per point the first keyframe and the observation count;
+// unknown is set by an id outside [0, K) or [0, N)
+__global__ __launch_bounds__(256) void k_vo_raw(long long n, int K, int N, const long long* __restrict__ kf64,
                                                const long long* __restrict__ pt64, int* __restrict__ kf,
                                                int* __restrict__ pt, int* __restrict__ first,
-                                               int* __restrict__ cnt) {
+                                               int* __restrict__ cnt, int* __restrict__ unknown) {
     const long long e = blockIdx.x * 256LL + threadIdx.x;
     if (e >= n) return;
+    if (kf64[e] < 0 || kf64[e] >= K || pt64[e] < 0 || pt64[e] >= N) {
+        *unknown = 1;
+        return;
+    }
     const int k = (int)kf64[e], j = (int)pt64[e];
     kf[e] = k;
     pt[e] = j;
