@@ -422,9 +422,9 @@ struct VIDev {
     const double* obs;     // [3 M]
     const double* pre;     // [kPreStride (K - 1)]
     double* info;          // [81 (K - 1)] Omega of the inertial terms
-    void* jsp;             // whole-system form: whitened stereo J (dtheta, dp | dX), padded
-                           // point-order tiles (js_at), double or float when w32; null in
-                           // the Schur form
+    double* jsp;           // whole-system form: what the stereo Jacobians are made of, the
+                           // point in the camera and the whitening factor, in point-order
+                           // tiles (js_at); null in the Schur form
     double* ji;            // [216 (K - 1)] inertial Jacobians
     double* ri;            // [9 (K - 1)]
     double* b;             // [n] gradient J^T Omega r
@@ -471,7 +471,6 @@ struct VIDev {
     double* cbt;           // bias terms), and transposed
     double* icx;           // [135 (K - 1)] inertial cross blocks J_i^T Omega J_j (15 x 9)
     double fx, fy, cx, cy, base, inv_sigma, delta2, wg, wa;   // wg, wa: 1 / sigma_w^2
-    long long n() const { return 15LL * K + 3 * N; }
 };
 
 // PCG scalars on the device: three slots of dot accumulators {p.q parts,
@@ -608,8 +607,8 @@ __global__ void k_vi_info(int n, const double* __restrict__ pre, double* __restr
 template <bool kJac>
 __device__ __forceinline__ void vi_stereo(const VIDev& d, const double* __restrict__ s,
                                           const double* __restrict__ X, long long e, double (&r)[3],
-                                          double (&J)[3][9]) {
-    double q[3], Xc[3];
+                                          double (&J)[3][9], double (&Xc)[3]) {
+    double q[3];
     for (int k = 0; k < 3; ++k) q[k] = X[k] - s[9 + k];
     for (int k = 0; k < 3; ++k) Xc[k] = s[k] * q[0] + s[3 + k] * q[1] + s[6 + k] * q[2];
     const double iz = 1.0 / Xc[2];
@@ -644,16 +643,21 @@ __device__ __forceinline__ void vi_huber(double s, double delta2, double& rho, d
 }
 
 // whitened residual and Jacobian of observation (k, j) with the observed
-// pixels ob (zero when !valid; the first keyframe's columns zero)
+// pixels ob (zero when !valid; the first keyframe's columns zero); jc: the
+// point in the camera and the whitening factor
 __device__ __forceinline__ void vi_stereo_whitened(const VIDev& d, const double* __restrict__ ob, int k, int j,
-                                                   bool valid, double (&r)[3], double (&J)[3][9]) {
+                                                   bool valid, double (&r)[3], double (&J)[3][9],
+                                                   double (&jc)[4]) {
     VIDev dd = d;
     dd.obs = ob;
-    vi_stereo<true>(dd, d.st + (size_t)kSt * k, d.X + 3 * (size_t)j, 0, r, J);
+    double Xc[3];
+    vi_stereo<true>(dd, d.st + (size_t)kSt * k, d.X + 3 * (size_t)j, 0, r, J, Xc);
     const double s = (r[0] * r[0] + r[1] * r[1] + r[2] * r[2]) * d.inv_sigma * d.inv_sigma;
     double rho, w;
     vi_huber(s, d.delta2, rho, w);
     const double sc = valid ? sqrt(w) * d.inv_sigma : 0.0;
+    for (int a = 0; a < 3; ++a) jc[a] = Xc[a];
+    jc[3] = sc;
     for (int a = 0; a < 3; ++a) {
         r[a] *= sc;
         for (int c = 0; c < 9; ++c) J[a][c] = (k == 0 && c < 6) ? 0.0 : J[a][c] * sc;
@@ -676,8 +680,8 @@ __global__ void k_vi_lin_stereo(VIDev d) {
     const SegScan seg(start);
     int head, end;
     segment_of(__ballot(start), l, head, end);
-    double r[3], J[3][9];
-    vi_stereo_whitened(d, d.obs + 3 * e, k, j, valid, r, J);
+    double r[3], J[3][9], jc[4];
+    vi_stereo_whitened(d, d.obs + 3 * e, k, j, valid, r, J, jc);
     if (valid && d.wk)
         for (int a = 0; a < 6; ++a)
             for (int c = 0; c < 3; ++c) {
@@ -701,13 +705,13 @@ __global__ void k_vi_lin_stereo(VIDev d) {
         }
 }
 
-// whitened J (3 x 9) of the whole-system form in padded point-order tiles:
-// entry c of slot i at (27 tile + c) 64 + lane
+// the whole-system form's stereo terms in padded point-order tiles: entry c of
+// slot i at (4 tile + c) 64 + lane
 __device__ __forceinline__ size_t js_at(long long i, int c) {
-    return ((size_t)(i >> 6) * 27 + c) * 64 + (size_t)(i & 63);
+    return ((size_t)(i >> 6) * 4 + c) * 64 + (size_t)(i & 63);
 }
 
-// the same terms in point order: W (Schur form) or the whitened J
+// the same terms in point order: W (Schur form) or the Jacobian's terms
 // (whole-system form) stored in point-order tiles,
 // the point's gradient b_p and block H_pp summed across its run of the
 // wavefront; a point whose observations all sit in one wavefront is stored,
@@ -728,16 +732,17 @@ __global__ void k_vi_lin_stereo_pts(VIDev d) {
     const bool first = i == 0 || d.qpt[i - 1] != jq;
     const bool lastp = i == d.Mp - 1 || d.qpt[i + 1] != jq;
     const bool whole = (__shfl(first ? 1 : 0, head, 64) != 0) && lastp;
-    double r[3], J[3][9];
-    vi_stereo_whitened(d, d.qobs + 3 * i, k, j, valid, r, J);
+    double r[3], J[3][9], jc[4];
+    vi_stereo_whitened(d, d.qobs + 3 * i, k, j, valid, r, J, jc);
     if (valid && d.wp)
         for (int a = 0; a < 6; ++a)
             for (int c = 0; c < 3; ++c)
                 ((WT*)d.wp)[w_at<WT>(i, 3 * a + c)] =
                     (WT)(J[0][a] * J[0][6 + c] + J[1][a] * J[1][6 + c] + J[2][a] * J[2][6 + c]);
-    if (valid && d.jsp)
-        for (int a = 0; a < 3; ++a)
-            for (int c = 0; c < 9; ++c) ((WT*)d.jsp)[js_at(i, 9 * a + c)] = (WT)J[a][c];
+    if (d.jsp && i0 < d.Mp) {
+        const double pad[4] = {0.0, 0.0, 1.0, 0.0};
+        for (int c = 0; c < 4; ++c) d.jsp[js_at(i, c)] = valid ? jc[c] : pad[c];
+    }
     const bool out = valid && l == end;
     double* bp = d.b + 15 * (size_t)d.K + 3 * (size_t)j;
     for (int c = 0; c < 3; ++c) {
@@ -862,8 +867,8 @@ __global__ void k_vi_cost(VIDev d, const double* __restrict__ st, const double* 
     const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
     double c = 0.0;
     if (t < d.M) {
-        double r[3], J[3][9];
-        vi_stereo<false>(d, st + (size_t)kSt * d.kf[t], X + 3 * (size_t)d.pt[t], t, r, J);
+        double r[3], J[3][9], Xc[3];
+        vi_stereo<false>(d, st + (size_t)kSt * d.kf[t], X + 3 * (size_t)d.pt[t], t, r, J, Xc);
         double rho, w;
         vi_huber((r[0] * r[0] + r[1] * r[1] + r[2] * r[2]) * d.inv_sigma * d.inv_sigma, d.delta2, rho, w);
         c = 0.5 * rho;
@@ -1068,111 +1073,6 @@ __global__ __launch_bounds__(256) void k_vi_apply_m(VIDev d, long long npt, cons
     if (threadIdx.x == 0) {
         atomic_add(acc + kAccRrP + blockIdx.x % kPqParts, rr);
         atomic_add(acc + kAccRzP + blockIdx.x % kPqParts, rz);
-    }
-}
-
-// q += (stereo part of H) v, whole-system form: one pass over the padded
-// point-order J.  Per observation u = J_k v_k + J_p v_j; the point rows
-// J_p^T u are summed across the point's run of the wavefront (added by its
-// last lane: whole runs own the point's rows, parts of a point split across
-// wavefronts add atomically), the keyframe rows J_k^T u go to the
-// workgroup's LDS partials of its keyframe window (as in k_vi_schur_pts) and
-// to q with one atomic add per entry.  q holds lambda D v on entry.
-template <typename JT>
-__global__ __launch_bounds__(512) void k_vi_prod_stereo(VIDev d, const double* __restrict__ v,
-                                                       double* __restrict__ q, const double* __restrict__ ps) {
-    if (pcg_done(ps)) return;
-    __shared__ double part[kKfWin * 6];
-    __shared__ int kmin_w[16];
-    const long long i0 = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    const long long i = i0 < d.Mp ? i0 : d.Mp - 1;
-    const int jq = d.qpt[i];
-    const bool valid = i0 < d.Mp && jq >= 0;
-    const int j = valid ? jq : 0, k = valid ? d.qkf[i] : 0;
-    const int l = (int)(threadIdx.x & 63);
-    const int jprev = __shfl_up(jq, 1, 64);
-    const bool start = !valid || l == 0 || jprev != jq;
-    const SegScan seg(start);
-    int head, end;
-    segment_of(__ballot(start), l, head, end);
-    const bool first = i == 0 || d.qpt[i - 1] != jq;
-    const bool lastp = i == d.Mp - 1 || d.qpt[i + 1] != jq;
-    const bool whole = (__shfl(first ? 1 : 0, head, 64) != 0) && lastp;   // at the run's last lane
-    const size_t ok = 15 * (size_t)k, op = 15 * (size_t)d.K + 3 * (size_t)j;
-    double in[9];
-    for (int c = 0; c < 6; ++c) in[c] = v[ok + c];
-    for (int c = 0; c < 3; ++c) in[6 + c] = v[op + c];
-    double J[27];
-    for (int c = 0; c < 27; ++c) J[c] = (double)((const JT*)d.jsp)[js_at(i, c)];
-    double u[3];
-    for (int a = 0; a < 3; ++a) {
-        double t = 0.0;
-        for (int c = 0; c < 9; ++c) t += J[9 * a + c] * in[c];
-        u[a] = valid ? t : 0.0;
-    }
-    for (int c = 0; c < 3; ++c) {
-        const double sy = seg.sum(J[6 + c] * u[0] + J[15 + c] * u[1] + J[24 + c] * u[2]);
-        if (valid && l == end) {
-            if (whole) q[op + c] += sy;
-            else atomic_add(q + op + c, sy);
-        }
-    }
-    int km = valid ? k : 0x7fffffff;
-    for (int off = 32; off > 0; off >>= 1) km = min(km, __shfl_xor(km, off, 64));
-    if (l == 0) kmin_w[threadIdx.x >> 6] = km;
-    for (int e = threadIdx.x; e < kKfWin * 6; e += blockDim.x) part[e] = 0.0;
-    __syncthreads();
-    int kbase = 0x7fffffff;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) kbase = min(kbase, kmin_w[w]);
-    if (valid && k != 0) {
-        const int kk = k - kbase;
-        for (int c = 0; c < 6; ++c) {
-            const double y = J[c] * u[0] + J[9 + c] * u[1] + J[18 + c] * u[2];
-            if (kk < kKfWin) atomicAdd(part + 6 * kk + c, y);
-            else atomic_add(q + ok + c, y);
-        }
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; kbase != 0x7fffffff && e < kKfWin * 6; e += blockDim.x) {
-        const int kf = kbase + e / 6;
-        const double val = part[e];
-        if (val != 0.0 && kf < d.K && kf != 0) atomic_add(q + 15 * (size_t)kf + e % 6, val);
-    }
-}
-
-// q += (inertial and bias parts of H) v: one wavefront per term; lane c < 24
-// holds column c (keyframe i's 15 entries, then keyframe j's first 9)
-__global__ __launch_bounds__(256) void k_vi_prod_inertial(VIDev d, const double* __restrict__ v,
-                                                          double* __restrict__ q,
-                                                          const double* __restrict__ ps) {
-    if (pcg_done(ps)) return;
-    const int f = (int)((blockIdx.x * (long long)blockDim.x + threadIdx.x) >> 6);
-    const int l = (int)(threadIdx.x & 63);
-    if (f >= d.K - 1) return;   // whole wavefronts
-    const size_t oi = 15 * (size_t)f, oj = 15 * (size_t)(f + 1);
-    const double* J = d.ji + (size_t)216 * f;
-    const double* O = d.info + 81 * (size_t)f;
-    const bool col = l < 24;
-    const double vc = col ? v[l < 15 ? oi + l : oj + (l - 15)] : 0.0;
-    double jc[9];
-    for (int a = 0; a < 9; ++a) jc[a] = col ? J[24 * a + l] : 0.0;
-    // u = J v (sums over the 24 columns), w = Omega u, y_c = sum_a J[a][c] w[a]
-    double u[9];
-    for (int a = 0; a < 9; ++a) u[a] = wave_sum(jc[a] * vc);
-    double y = 0.0;
-    for (int a = 0; a < 9; ++a) {
-        double w = 0.0;
-        for (int b = 0; b < 9; ++b) w += O[9 * a + b] * u[b];
-        y += jc[a] * w;
-    }
-    if (col) atomic_add(q + (l < 15 ? oi + l : oj + (l - 15)), y);
-    if (l < 6) {
-        const double dt = d.pre[(size_t)kPreStride * f + kDt];
-        const double wb = (l < 3 ? d.wg : d.wa) / dt;
-        const double vi_k = f != 0 ? v[oi + 9 + l] : 0.0;
-        const double yb = wb * (v[oj + 9 + l] - vi_k);
-        atomic_add(q + oj + 9 + l, yb);
-        if (f != 0) atomic_add(q + oi + 9 + l, -yb);
     }
 }
 
@@ -1684,6 +1584,46 @@ __device__ __forceinline__ double vi_s_rows(const VIDev& d, int k, const P& p, d
     return vi_s_total(u, v);
 }
 
+// The decisions about the PCG step before this one (k_vi_pcg_dir's rules, from
+// slot prev_slot), taken alike by every workgroup and recorded by `lead`:
+// false when the PCG ends; save and restore act on the caller's own entries.
+template <typename Save, typename Restore>
+__device__ __forceinline__ bool vi_pcg_go_on(double* __restrict__ ps, int prev_slot, bool lead, double* red,
+                                             double* sums, const Save& save, const Restore& restore,
+                                             double& beta) {
+    double* acc = ps + kAccN * prev_slot;
+    const double* prev = ps + kAccN * ((prev_slot + kSlots - 1) % kSlots);
+    const double a = block_sum_vi(threadIdx.x < kPqParts ? acc[kAccRrP + threadIdx.x] : 0.0, red);
+    __syncthreads();
+    const double b = block_sum_vi(threadIdx.x < kPqParts ? acc[kAccRzP + threadIdx.x] : 0.0, red);
+    if (threadIdx.x == 0) {
+        sums[0] = a;
+        sums[1] = b;
+    }
+    __syncthreads();
+    const double rr = sums[0], least = prev[kAccMin], ratio2 = ps[kRatio2];
+    double nmin = least;
+    bool stop = acc[kAccBreak] != 0.0;
+    if (!stop && ratio2 > 0.0) {
+        if (rr < least) {
+            nmin = rr;
+            save();
+        } else if (rr > ratio2 * least) {
+            restore();
+            stop = true;
+        }
+    }
+    if (!stop && rr <= ps[kThr]) stop = true;
+    if (lead) {
+        acc[kAccRr] = rr;
+        acc[kAccRz] = sums[1];
+        acc[kAccMin] = nmin;
+        if (stop) acc[kAccStop] = 1.0;   // the update kernel sets the stop flag from it
+    }
+    beta = sums[1] / prev[kAccRz];
+    return !stop;
+}
+
 // One PCG step in two launches.  First: the decisions about the step before
 // (k_vi_pcg_dir's, from slot `prev_slot`; none at the first step), the
 // direction p = z + beta p_old formed as it is read (p_old and the new p are
@@ -1708,37 +1648,9 @@ __global__ __launch_bounds__(256) void k_vi_s_prod(VIDev d, double* __restrict__
     const bool mine = k < d.K && l < 15;
     double beta = 0.0;
     if (!first) {
-        double* acc = ps + kAccN * prev_slot;
-        const double* prev = ps + kAccN * ((prev_slot + kSlots - 1) % kSlots);
-        const double a = block_sum_vi(threadIdx.x < kPqParts ? acc[kAccRrP + threadIdx.x] : 0.0, red);
-        __syncthreads();
-        const double b = block_sum_vi(threadIdx.x < kPqParts ? acc[kAccRzP + threadIdx.x] : 0.0, red);
-        if (threadIdx.x == 0) {
-            sums[0] = a;
-            sums[1] = b;
-        }
-        __syncthreads();
-        const double rr = sums[0], least = prev[kAccMin], ratio2 = ps[kRatio2];
-        double nmin = least;
-        bool stop = acc[kAccBreak] != 0.0;
-        if (!stop && ratio2 > 0.0) {
-            if (rr < least) {
-                nmin = rr;
-                if (mine) xb[own] = x[own];
-            } else if (rr > ratio2 * least) {
-                if (mine) x[own] = xb[own];
-                stop = true;
-            }
-        }
-        if (!stop && rr <= ps[kThr]) stop = true;
-        if (lead) {
-            acc[kAccRr] = rr;
-            acc[kAccRz] = sums[1];
-            acc[kAccMin] = nmin;
-            if (stop) acc[kAccStop] = 1.0;   // the update kernel sets the stop flag from it
-        }
-        if (stop || last) return;
-        beta = sums[1] / prev[kAccRz];
+        const bool go = vi_pcg_go_on(ps, prev_slot, lead, red, sums, [&] { if (mine) xb[own] = x[own]; },
+                                     [&] { if (mine) x[own] = xb[own]; }, beta);
+        if (!go || last) return;
     }
     double pq = 0.0;
     if (k < d.K) {   // whole wavefronts
@@ -1758,10 +1670,14 @@ __global__ __launch_bounds__(256) void k_vi_s_prod(VIDev d, double* __restrict__
 // Second: alpha, x, r, z = M^-1 r and the parts of r.r and r.z (as
 // k_vi_pcg_update); the stop decided by the first kernel becomes the stop
 // flag, and the next step's slot is cleared (no kernel in flight reads it).
-__global__ __launch_bounds__(256) void k_vi_s_update(VIDev d, double* __restrict__ ps, int slot, int prev_slot,
-                                                    const double* __restrict__ p, const double* __restrict__ q,
-                                                    double* __restrict__ x, double* __restrict__ r,
-                                                    double* __restrict__ z) {
+// full (the whole-system form): the points are unknowns too (three lanes per
+// point in the workgroups after the keyframe ones), and q is cleared for the
+// next product.
+constexpr int kUpdPts = 85;   // points per 256-lane workgroup of the update
+__global__ __launch_bounds__(256) void k_vi_s_update(VIDev d, int full, double* __restrict__ ps, int slot,
+                                                    int prev_slot, const double* __restrict__ p,
+                                                    double* __restrict__ q, double* __restrict__ x,
+                                                    double* __restrict__ r, double* __restrict__ z) {
     __shared__ double rs[256];
     __shared__ double red[16];
     __shared__ double pq_s;
@@ -1773,10 +1689,12 @@ __global__ __launch_bounds__(256) void k_vi_s_update(VIDev d, double* __restrict
     }
     if (blockIdx.x == 0)
         for (int e = threadIdx.x; e < kAccN; e += blockDim.x) ps[kAccN * ((slot + 1) % kSlots) + e] = 0.0;
-    const long long k = blockIdx.x * 16LL + (threadIdx.x >> 4);
-    const int row = (int)(threadIdx.x & 15);
-    const bool act = k < d.K && row < 15;
-    const size_t i = 15 * (size_t)k + row;
+    const long long kf_blocks = (d.K + 15) / 16;
+    const bool pts = blockIdx.x >= kf_blocks;
+    const int t = (int)threadIdx.x, sub = pts ? t / 3 : t >> 4, row = pts ? t - 3 * sub : t & 15;
+    const long long k = pts ? (blockIdx.x - kf_blocks) * (long long)kUpdPts + sub : blockIdx.x * 16LL + sub;
+    const bool act = pts ? sub < kUpdPts && k < d.N : k < d.K && row < 15;
+    const size_t i = pts ? 15 * (size_t)d.K + 3 * (size_t)k + row : 15 * (size_t)k + row;
     const double part = block_sum_vi(threadIdx.x < kPqParts ? acc[kAccPq + threadIdx.x] : 0.0, red);
     if (threadIdx.x == 0) pq_s = part;
     __syncthreads();
@@ -1791,15 +1709,22 @@ __global__ __launch_bounds__(256) void k_vi_s_update(VIDev d, double* __restrict
         x[i] += alpha * p[i];
         rn = r[i] - alpha * q[i];
         r[i] = rn;
+        if (full) q[i] = 0.0;
     }
     rs[threadIdx.x] = rn;
     __syncthreads();
     if (act) {
-        const double* Mi = d.mki + 225 * (size_t)k + 15 * row;
-        const double* rk = rs + (threadIdx.x & ~15u);
         double u = 0.0;
+        if (pts) {
+            const double* M = d.mp + 9 * (size_t)k + 3 * row;
+            const double* rk = rs + 3 * sub;
+            u = M[0] * rk[0] + M[1] * rk[1] + M[2] * rk[2];
+        } else {
+            const double* Mi = d.mki + 225 * (size_t)k + 15 * row;
+            const double* rk = rs + 16 * sub;
 #pragma unroll
-        for (int c = 0; c < 15; ++c) u += Mi[c] * rk[c];
+            for (int c = 0; c < 15; ++c) u += Mi[c] * rk[c];
+        }
         z[i] = u;
         rr = rn * rn;
         rz = rn * u;
@@ -1812,6 +1737,177 @@ __global__ __launch_bounds__(256) void k_vi_s_update(VIDev d, double* __restrict
         atomic_add(acc + kAccRzP + blockIdx.x % kPqParts, rz);
         if (blockIdx.x == 0) ps[kSteps] += 1.0;
     }
+}
+
+// The whole-system form's PCG step in two launches, this one and the update
+// above: the decisions about the step before and the direction p = z + beta
+// p_old as in k_vi_s_prod, then q = (H + lambda D) p (q is zero on entry) and
+// p.q.  Workgroups over the padded point-order observations, then over the
+// inertial terms, then over the rows (p itself and the damping).
+//
+// An observation's Jacobian is (P [Xc]x, -P R^T | P R^T), so with w = Xc x'
+// v_theta + R^T (v_X - v_p) its part of H p is u = P w, g = P^T u and R g, -R
+// g, [Xc]x^T g: 32 bytes an observation (Xc and the whitening factor) in
+// place of the 216 of a stored Jacobian, and fewer operations.  The keyframes
+// of a workgroup lie close together (points are numbered by first observing
+// keyframe): those of a window of kKfWin keep rotation, direction and partial
+// sums in LDS, one further out goes through memory.  The point rows are
+// summed across the point's run of the wavefront and stored by its last lane
+// (parts of a point split across wavefronts are added).
+//
+// quad: only v.H v into the parts of quad (v in z; lambda 0).
+//
+// At 300 keyframes and 0.31M observations it takes 15.7 us, the update 7.0,
+// where the stored Jacobian's product (18.9), the inertial product (6.8), the
+// damping, dot and direction kernels (12.2) and the update took 45.
+enum { kFullFirst = 0, kFullNext, kFullLast, kFullQuad };
+__global__ __launch_bounds__(kFuseBlock) void k_vi_full_prod(VIDev d, double lam, double* __restrict__ ps, int slot,
+                                                            int prev_slot, int mode, const double* __restrict__ z,
+                                                            const double* __restrict__ p_old,
+                                                            double* __restrict__ p_new, double* __restrict__ q,
+                                                            double* __restrict__ x, double* __restrict__ xb,
+                                                            double* __restrict__ quad) {
+    __shared__ double red[16];
+    __shared__ double sums[2];
+    __shared__ double part[kKfWin * 6];
+    __shared__ double win[kKfWin * 15];   // direction (6) and rotation (9)
+    __shared__ int kmin_w[16];
+    const bool only_quad = mode == kFullQuad;
+    if (!only_quad && ps[kDone] != 0.0) return;   // set by the update kernel only
+    const long long n = 15LL * d.K + 3 * d.N, st_blocks = (d.Mp + kFuseBlock - 1) / kFuseBlock, in_blocks = (d.K + 6) / 8;
+    const int tid = (int)threadIdx.x, l = tid & 63;
+    const long long rb = blockIdx.x - st_blocks - in_blocks;
+    const size_t own = (size_t)(rb * kFuseBlock + tid);
+    const bool mine = rb >= 0 && (long long)own < n;
+    const bool next = mode == kFullNext;
+    double beta = 0.0;
+    if (next || mode == kFullLast) {
+        const bool go = vi_pcg_go_on(ps, prev_slot, blockIdx.x == 0 && tid == 0, red, sums,
+                                     [&] { if (mine) xb[own] = x[own]; }, [&] { if (mine) x[own] = xb[own]; }, beta);
+        if (!go || !next) return;
+    }
+    auto p = [&](size_t i) { return next ? z[i] + beta * p_old[i] : z[i]; };
+    double pq = 0.0;
+    if (blockIdx.x < st_blocks) {
+        const long long i = blockIdx.x * (long long)kFuseBlock + tid < d.Mp
+                                ? blockIdx.x * (long long)kFuseBlock + tid : d.Mp - 1;
+        const int jq = d.qpt[i];
+        const bool valid = blockIdx.x * (long long)kFuseBlock + tid < d.Mp && jq >= 0;
+        const int j = valid ? jq : 0, k = valid ? d.qkf[i] : 0;
+        const size_t op = 15 * (size_t)d.K + 3 * (size_t)j;
+        double jc[4], vx[3];
+        for (int c = 0; c < 4; ++c) jc[c] = d.jsp[js_at(i, c)];
+        for (int c = 0; c < 3; ++c) vx[c] = p(op + c);
+        const int jprev = __shfl_up(jq, 1, 64);
+        const bool start = !valid || l == 0 || jprev != jq;
+        const SegScan seg(start);
+        int head, end;
+        segment_of(__ballot(start), l, head, end);
+        const bool first = i == 0 || d.qpt[i - 1] != jq;
+        const bool lastp = i == d.Mp - 1 || d.qpt[i + 1] != jq;
+        const bool has_first = __shfl(first ? 1 : 0, head, 64) != 0;
+        const bool whole = has_first && lastp;   // at the run's last lane
+        int km = valid ? k : 0x7fffffff;
+        for (int off = 32; off > 0; off >>= 1) km = min(km, __shfl_xor(km, off, 64));
+        if (l == 0) kmin_w[tid >> 6] = km;
+        __syncthreads();
+        int kbase = 0x7fffffff;
+        for (int w = 0; w < kFuseBlock / 64; ++w) kbase = min(kbase, kmin_w[w]);
+        const bool any = kbase != 0x7fffffff;
+        for (int e = tid; e < kKfWin * 15; e += kFuseBlock) {
+            const int kf = kbase + e / 15, c = e % 15;   // (no further than K when any)
+            if (any && kf < d.K) win[e] = c < 6 ? p(15 * (size_t)kf + c) : d.st[(size_t)kSt * kf + c - 6];
+        }
+        for (int e = tid; e < kKfWin * 6; e += kFuseBlock) part[e] = 0.0;
+        __syncthreads();
+        double yx[3] = {0.0, 0.0, 0.0};
+        if (valid) {
+            const int kk = k - kbase;
+            double v[6], R[9];
+            if (kk < kKfWin) {
+                for (int c = 0; c < 6; ++c) v[c] = win[15 * kk + c];
+                for (int c = 0; c < 9; ++c) R[c] = win[15 * kk + 6 + c];
+            } else {
+                for (int c = 0; c < 6; ++c) v[c] = p(15 * (size_t)k + c);
+                for (int c = 0; c < 9; ++c) R[c] = d.st[(size_t)kSt * k + c];
+            }
+            const double X = jc[0], Y = jc[1], Z = jc[2], sc = jc[3], iz = 1.0 / Z;
+            const double e0 = vx[0] - v[3], e1 = vx[1] - v[4], e2 = vx[2] - v[5];
+            const double w0 = R[0] * e0 + R[3] * e1 + R[6] * e2 + (Y * v[2] - Z * v[1]);
+            const double w1 = R[1] * e0 + R[4] * e1 + R[7] * e2 + (Z * v[0] - X * v[2]);
+            const double w2 = R[2] * e0 + R[5] * e1 + R[8] * e2 + (X * v[1] - Y * v[0]);
+            const double fx = sc * d.fx * iz, fy = sc * d.fy * iz, xz = X * iz, yz = Y * iz,
+                         bz = (X - d.base) * iz;
+            const double u0 = fx * (w0 - xz * w2), u1 = fy * (w1 - yz * w2), u2 = fx * (w0 - bz * w2);
+            pq = u0 * u0 + u1 * u1 + u2 * u2;
+            const double g0 = fx * (u0 + u2), g1 = fy * u1, g2 = -(fx * (xz * u0 + bz * u2) + yz * g1);
+            for (int c = 0; c < 3; ++c) yx[c] = R[3 * c] * g0 + R[3 * c + 1] * g1 + R[3 * c + 2] * g2;
+            if (k != 0 && !only_quad) {
+                const double y[6] = {Z * g1 - Y * g2, X * g2 - Z * g0, Y * g0 - X * g1, -yx[0], -yx[1], -yx[2]};
+                for (int c = 0; c < 6; ++c) {
+                    if (kk < kKfWin) atomicAdd(part + 6 * kk + c, y[c]);
+                    else atomic_add(q + 15 * (size_t)k + c, y[c]);
+                }
+            }
+        }
+        if (!only_quad) {
+            for (int c = 0; c < 3; ++c) {
+                const double sy = seg.sum(yx[c]);
+                if (valid && l == end) {
+                    const double damp = has_first ? lam * d.dg[op + c] * vx[c] : 0.0;
+                    if (whole) q[op + c] = sy + damp;
+                    else atomic_add(q + op + c, sy + damp);
+                }
+            }
+            __syncthreads();
+            for (int e = tid; any && e < kKfWin * 6; e += kFuseBlock) {
+                const int kf = kbase + e / 6;
+                const double val = part[e];
+                if (val != 0.0 && kf < d.K && kf != 0) atomic_add(q + 15 * (size_t)kf + e % 6, val);
+            }
+        }
+    } else if (rb < 0) {
+        // the inertial and bias terms: one wavefront per term; lane c < 24
+        // holds column c (keyframe i's 15 entries, then keyframe j's first 9)
+        const int f = (int)((blockIdx.x - st_blocks) * (kFuseBlock / 64)) + (tid >> 6);
+        if (f < d.K - 1) {   // whole wavefronts
+            const size_t oi = 15 * (size_t)f, oj = 15 * (size_t)(f + 1);
+            const double* J = d.ji + (size_t)216 * f;
+            const double* O = d.info + 81 * (size_t)f;
+            const bool col = l < 24;
+            const double vc = col ? p(l < 15 ? oi + l : oj + (l - 15)) : 0.0;
+            double jc[9], u[9];
+            for (int a = 0; a < 9; ++a) jc[a] = col ? J[24 * a + l] : 0.0;
+            // u = J v (sums over the 24 columns), w = Omega u, y_c = sum_a J[a][c] w[a]
+            for (int a = 0; a < 9; ++a) u[a] = wave_sum(jc[a] * vc);
+            double y = 0.0, uw = 0.0;
+            for (int a = 0; a < 9; ++a) {
+                double w = 0.0;
+                for (int b = 0; b < 9; ++b) w += O[9 * a + b] * u[b];
+                y += jc[a] * w;
+                uw += u[a] * w;
+            }
+            if (l == 0) pq += uw;
+            if (col && !only_quad) atomic_add(q + (l < 15 ? oi + l : oj + (l - 15)), y);
+            if (l < 6) {
+                const double dt = d.pre[(size_t)kPreStride * f + kDt];
+                const double wb = (l < 3 ? d.wg : d.wa) / dt;
+                const double diff = p(oj + 9 + l) - (f != 0 ? p(oi + 9 + l) : 0.0);
+                pq += wb * diff * diff;
+                if (!only_quad) {
+                    atomic_add(q + oj + 9 + l, wb * diff);
+                    if (f != 0) atomic_add(q + oi + 9 + l, -(wb * diff));
+                }
+            }
+        }
+    } else if (mine && !only_quad) {
+        const double v = p(own), damp = lam * d.dg[own] * v;
+        p_new[own] = v;
+        pq = damp * v;
+        if (own < 15 * (size_t)d.K) atomic_add(q + own, damp);
+    }
+    pq = block_sum_vi(pq, red);
+    if (tid == 0) atomic_add((only_quad ? quad : ps + kAccN * slot + kAccPq) + blockIdx.x % kPqParts, pq);
 }
 
 // The whole PCG of a short trajectory (at most kOneKf keyframes) in one
@@ -2024,15 +2120,6 @@ __global__ void k_vi_cross(VIDev d, int full) {
     d.cbt[225 * f + 15 * c + a] = u;
 }
 
-// q = lambda diag(D) v (the first term of the product; the others add)
-__global__ void k_vi_prod_damp(long long n, double lam, const double* __restrict__ dg,
-                               const double* __restrict__ v, double* __restrict__ q,
-                               const double* __restrict__ ps) {
-    if (pcg_done(ps)) return;
-    const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (i < n) q[i] = lam * dg[i] * v[i];
-}
-
 // the start: threshold tol^2 r0.r0 (r0.r0 and r0.z0 in the last slot, summed
 // from their parts by one workgroup of kPqParts);
 // nothing to do when r0 is already below it or r0.z0 <= 0.  ratio2: the
@@ -2057,12 +2144,10 @@ __global__ __launch_bounds__(kPqParts) void k_vi_pcg_init(double* __restrict__ p
 
 // step `slot`: alpha = r.z / p.q (a step with p.q <= 0 ends the iteration at
 // the current iterate), x += alpha p, r -= alpha q, z = M^-1 r and the new
-// r.r, r.z.  Keyframe rows: 16 lanes per keyframe (15 used), the residual
-// block through LDS for the 15 x 15 inverse; point rows (the whole-system
-// form): three lanes per point in the workgroups after the keyframe ones.
-constexpr int kUpdPts = 85;   // points per 256-lane workgroup of the update
-__global__ __launch_bounds__(256) void k_vi_pcg_update(VIDev d, long long npt, double* __restrict__ ps,
-                                                      int slot, const double* __restrict__ p,
+// r.r, r.z.  16 lanes per keyframe (15 used), the residual block through LDS
+// for the 15 x 15 inverse.
+__global__ __launch_bounds__(256) void k_vi_pcg_update(VIDev d, double* __restrict__ ps, int slot,
+                                                      const double* __restrict__ p,
                                                       const double* __restrict__ q, double* __restrict__ x,
                                                       double* __restrict__ r, double* __restrict__ z) {
     __shared__ double rs[256];
@@ -2081,54 +2166,26 @@ __global__ __launch_bounds__(256) void k_vi_pcg_update(VIDev d, long long npt, d
         return;
     }
     const double alpha = ps[kAccN * ((slot + kSlots - 1) % kSlots) + kAccRz] / pq;
-    const long long kf_blocks = (d.K + 15) / 16;
-    double rr = 0.0, rz = 0.0;
-    if (blockIdx.x < kf_blocks) {
-        const long long k = blockIdx.x * 16LL + (threadIdx.x >> 4);
-        const int row = (int)(threadIdx.x & 15);
-        const bool act = k < d.K && row < 15;
-        const size_t i = 15 * (size_t)k + row;
-        double rn = 0.0;
-        if (act) {
-            x[i] += alpha * p[i];
-            rn = r[i] - alpha * q[i];
-            r[i] = rn;
-        }
-        rs[threadIdx.x] = rn;
-        __syncthreads();
-        if (act) {
-            const double* Mi = d.mki + 225 * (size_t)k + 15 * row;
-            const double* rk = rs + (threadIdx.x & ~15u);
-            double u = 0.0;
-            for (int c = 0; c < 15; ++c) u += Mi[c] * rk[c];
-            z[i] = u;
-            rr = rn * rn;
-            rz = rn * u;
-        }
-    } else {
-        // point rows: three lanes per point (kUpdPts points per workgroup),
-        // so consecutive lanes take consecutive rows; the point's residual
-        // through LDS for its 3 x 3 inverse
-        const int pl = (int)threadIdx.x / 3, a = (int)threadIdx.x - 3 * pl;
-        const long long j = (blockIdx.x - kf_blocks) * (long long)kUpdPts + pl;
-        const bool act = pl < kUpdPts && j < npt;
-        const size_t i = 15 * (size_t)d.K + 3 * (size_t)j + a;
-        double rn = 0.0;
-        if (act) {
-            x[i] += alpha * p[i];
-            rn = r[i] - alpha * q[i];
-            r[i] = rn;
-        }
-        rs[threadIdx.x] = rn;
-        __syncthreads();
-        if (act) {
-            const double* M = d.mp + 9 * (size_t)j + 3 * a;
-            const double* rk = rs + 3 * pl;
-            const double u = M[0] * rk[0] + M[1] * rk[1] + M[2] * rk[2];
-            z[i] = u;
-            rr = rn * rn;
-            rz = rn * u;
-        }
+    const long long k = blockIdx.x * 16LL + (threadIdx.x >> 4);
+    const int row = (int)(threadIdx.x & 15);
+    const bool act = k < d.K && row < 15;
+    const size_t i = 15 * (size_t)k + row;
+    double rr = 0.0, rz = 0.0, rn = 0.0;
+    if (act) {
+        x[i] += alpha * p[i];
+        rn = r[i] - alpha * q[i];
+        r[i] = rn;
+    }
+    rs[threadIdx.x] = rn;
+    __syncthreads();
+    if (act) {
+        const double* Mi = d.mki + 225 * (size_t)k + 15 * row;
+        const double* rk = rs + (threadIdx.x & ~15u);
+        double u = 0.0;
+        for (int c = 0; c < 15; ++c) u += Mi[c] * rk[c];
+        z[i] = u;
+        rr = rn * rn;
+        rz = rn * u;
     }
     rr = block_sum_vi(rr, red);
     __syncthreads();
@@ -2215,20 +2272,6 @@ __global__ void k_vi_pcg_dir(long long n, double* __restrict__ ps, int slot, con
         if (qz) qz[i] = 0.0;   // the next product adds into q
     }
     if (lead) acc[kAccMin] = nmin;
-}
-
-// out[blockIdx % parts] += the workgroup's part of a . b (parts > 1 spreads
-// the additions over addresses that the reader sums)
-__global__ void k_vi_dot(long long n, const double* __restrict__ a, const double* __restrict__ b,
-                         double* __restrict__ out, const double* __restrict__ ps = nullptr, int parts = 1) {
-    if (pcg_done(ps)) return;
-    __shared__ double red[16];
-    double s = 0.0;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x)
-        s += a[i] * b[i];
-    s = block_sum_vi(s, red);
-    if (threadIdx.x == 0) atomic_add(out + blockIdx.x % parts, s);
 }
 
 // The candidate (R Exp(dtheta), p + dp, v + dv, b + db; X + dX) and the sums
@@ -2458,7 +2501,7 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
     const long long N = P.n_pts, M = P.n_obs, n = 15LL * K + 3 * N;
     const bool f32 = o.precision == GBA_MIXED_FP32;
     // one allocation for nearly everything (about this much, see below)
-    DevBufs B((size_t)(8.0 * (8200.0 * K + 46.0 * N) + (double)M * (170.0 + (f32 ? 4.0 : 8.0) * (schur ? 37 : 28)) +
+    DevBufs B((size_t)(8.0 * (8200.0 * K + 46.0 * N) + (double)M * (170.0 + (schur ? (f32 ? 4.0 : 8.0) * 37 : 32.0)) +
                        (1 << 20)));
     VIDev d{};
     d.K = K;
@@ -2603,14 +2646,9 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         !B.up(&d.scal, (const double*)nullptr, (size_t)kScalN) || !B.up(&x, (const double*)nullptr, (size_t)n) ||
         !B.up(&r, (const double*)nullptr, (size_t)n) || !B.up(&z, (const double*)nullptr, (size_t)n) ||
         !B.up(&pv, (const double*)nullptr, (size_t)n) || !B.up(&q, (const double*)nullptr, (size_t)n) ||
-        !B.up(&xb, (const double*)nullptr, (size_t)n) || !B.up(&p2, (const double*)nullptr, 15 * (size_t)K))
+        !B.up(&xb, (const double*)nullptr, (size_t)n) || !B.up(&p2, (const double*)nullptr, schur ? 15 * (size_t)K : (size_t)n))
         return GBA_ERR_OOM;
-    if (!schur) {   // the point-order J (FP32: half the doubles, rounded up)
-        d.w32 = o.precision == GBA_MIXED_FP32 ? 1 : 0;
-        double* jp = nullptr;
-        if (!B.up(&jp, (const double*)nullptr, (27 * 64 * (size_t)(Mp / 64) + 2) / (d.w32 ? 2 : 1))) return GBA_ERR_OOM;
-        d.jsp = jp;
-    }
+    if (!schur && !B.up(&d.jsp, (const double*)nullptr, 4 * (size_t)Mp + 1)) return GBA_ERR_OOM;
     double* zb = nullptr;   // Schur form: the point vector of a product
     if (schur) {
         // W in FP32 takes half the doubles of FP64 (rounded up)
@@ -2714,16 +2752,6 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         if (schur) hipLaunchKernelGGL(k_vi_cross, grid(225LL * (K - 1)), blk, 0, nullptr, d, explicit_s ? 1 : 0);
         return chk();
     };
-    // q = (H + lam diag(D)) v, the whole system (nothing once g's stop flag is set)
-    auto product = [&](const double* v, double* out, double lam, const double* g) {
-        hipLaunchKernelGGL(k_vi_prod_damp, grid(n), blk, 0, nullptr, n, lam, d.dg, v, out, g);
-        if (M > 0) {
-            const dim3 pg((unsigned)((Mp + kFuseBlock - 1) / kFuseBlock));
-            if (d.w32) hipLaunchKernelGGL(k_vi_prod_stereo<float>, pg, dim3(kFuseBlock), 0, nullptr, d, v, out, g);
-            else hipLaunchKernelGGL(k_vi_prod_stereo<double>, pg, dim3(kFuseBlock), 0, nullptr, d, v, out, g);
-        }
-        hipLaunchKernelGGL(k_vi_prod_inertial, grid(64LL * (K - 1)), blk, 0, nullptr, d, v, out, g);
-    };
     // z = sign C^-1 (B^T v + add) over the points (acc: -t . z added)
     auto schur_pts = [&](const double* v, const double* add, double sign, double* out, const double* g,
                          double* acc) {
@@ -2757,7 +2785,6 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
             else hipLaunchKernelGGL(k_vi_long_kf<double>, grid(d.nlslot), blk, 0, nullptr, d, (const double*)zb, out, g);
         }
     };
-    auto dot_blocks = [](long long len) { return dim3((unsigned)std::min<long long>(1024, (len + 255) / 256)); };
     // PCG from 0 to |r| <= pcg_tol |r0|: on (H + lam D) x = -b (full form),
     // or on S x_k = v followed by the point back-substitution (Schur form)
     const long long nn = schur ? 15LL * K : n;          // PCG unknowns
@@ -2767,6 +2794,15 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
     // previous solve's count, as the next solve usually takes about as many
     constexpr int kPcgSync = 8;
     int prev_iters = 0;
+    auto sync = [&](int it, bool& done) {
+        const int first_read = std::max(kPcgSync, prev_iters - kPcgSync);
+        if (it + 1 >= first_read && (it + 1 - first_read) % kPcgSync == 0 && it + 1 < o.pcg_max_iters) {
+            if (!chk() || !read_scal(8 + kPcgScalars)) return false;
+            done = hs[8 + kDone] != 0.0;
+        }
+        return true;
+    };
+    const dim3 full_grid((unsigned)((Mp + kFuseBlock - 1) / kFuseBlock + (K + 6) / 8 + (n + kFuseBlock - 1) / kFuseBlock));
     const double ratio2 = (o.pcg_rejection_ratio > 0.0 && std::isfinite(o.pcg_rejection_ratio))
                               ? o.pcg_rejection_ratio * o.pcg_rejection_ratio : 0.0;
     auto pcg = [&](double lam) {
@@ -2775,8 +2811,8 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         zero.add(x, n);
         zero.add(xb, nn);   // the best iterate: x0 = 0
         zero.add(d.scal, kScalN);
+        zero.add(q, nn);   // the products add into q
         if (schur) {
-            zero.add(q, nn);   // the products add into q
             zero.add(d.sm, 36LL * K);
             zero.add(p2, nn);
         }
@@ -2792,9 +2828,7 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
                            ps + kAccN * (kSlots - 1));
         hipLaunchKernelGGL(k_vi_pcg_init, dim3(1), dim3(kPqParts), 0, nullptr, ps, o.pcg_tol, ratio2);
         if (explicit_s) {
-            // the blocks of this step, then the PCG on them: one launch for a
-            // short trajectory, else two per step (p and its successor in pv
-            // and p2 in turn)
+            // the blocks of this step
             const dim3 fg((unsigned)d.nnz);
             if (d.nnz < 4096) {   // few blocks: four wavefronts each
                 if (d.w32) hipLaunchKernelGGL((k_vi_form_blocks<float, 4>), fg, dim3(256), 0, nullptr, d);
@@ -2803,49 +2837,48 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
                 if (d.w32) hipLaunchKernelGGL((k_vi_form_blocks<float, 1>), fg, dim3(64), 0, nullptr, d);
                 else hipLaunchKernelGGL((k_vi_form_blocks<double, 1>), fg, dim3(64), 0, nullptr, d);
             }
-            if (K <= kOneKf) {
-                hipLaunchKernelGGL(k_vi_s_pcg_one, dim3(1), dim3(kOneBlock), 144 * d.nnz, nullptr, d, ps,
-                                   o.pcg_max_iters, (const double*)r, (const double*)z, x);
-            } else {
-                const dim3 pg((unsigned)((K + 3) / 4)), ug((unsigned)((K + 15) / 16));
-                double* dir[2] = {pv, p2};
-                int it = 0;
-                for (; it < o.pcg_max_iters; ++it) {
-                    const int slot = it % kSlots, prev = (it + kSlots - 1) % kSlots;
-                    hipLaunchKernelGGL(k_vi_s_prod, pg, blk, 0, nullptr, d, ps, slot, prev, it == 0 ? 1 : 0, 0,
-                                       (const double*)z, (const double*)dir[(it + 1) & 1], dir[it & 1], q, x, xb);
-                    hipLaunchKernelGGL(k_vi_s_update, ug, blk, 0, nullptr, d, ps, slot, prev,
-                                       (const double*)dir[it & 1], (const double*)q, x, r, z);
-                    const int first_read = std::max(kPcgSync, prev_iters - kPcgSync);
-                    if (it + 1 >= first_read && (it + 1 - first_read) % kPcgSync == 0 && it + 1 < o.pcg_max_iters) {
-                        if (!chk() || !read_scal(8 + kPcgScalars)) return false;
-                        if (hs[8 + kDone] != 0.0) break;
-                    }
-                }
-                if (it == o.pcg_max_iters)   // the decisions about the last step
-                    hipLaunchKernelGGL(k_vi_s_prod, pg, blk, 0, nullptr, d, ps, 0, (it + kSlots - 1) % kSlots, 0,
-                                       1, (const double*)z, (const double*)pv, p2, q, x, xb);
-            }
         }
-        const dim3 upd((unsigned)((K + 15) / 16 + (npt + kUpdPts - 1) / kUpdPts));
-        const dim3 dirg((unsigned)std::max(1LL, std::min<long long>(1024, (nn + 255) / 256)));
-        for (int it = 0; !explicit_s && it < o.pcg_max_iters; ++it) {
-            const int slot = it % kSlots;
-            if (schur) {
-                schur_product(pv, q, lam, ps, ps + kAccN * slot + kAccPq);   // p . q summed inside
-            } else {
-                product(pv, q, lam, ps);
-                hipLaunchKernelGGL(k_vi_dot, dot_blocks(nn), blk, 0, nullptr, nn, (const double*)pv,
-                                   (const double*)q, ps + kAccN * slot + kAccPq, (const double*)ps, kPqParts);
+        if (explicit_s && K <= kOneKf) {
+            hipLaunchKernelGGL(k_vi_s_pcg_one, dim3(1), dim3(kOneBlock), 144 * d.nnz, nullptr, d, ps, o.pcg_max_iters,
+                               (const double*)r, (const double*)z, x);
+        } else if (explicit_s || !schur) {
+            // two launches per step: the product, with the decisions about
+            // the step before, and the update
+            const dim3 ug((unsigned)((K + 15) / 16 + (npt + kUpdPts - 1) / kUpdPts));
+            double* dir[2] = {pv, p2};
+            auto prod = [&](int it, bool last) {
+                const int slot = it % kSlots, prev = (it + kSlots - 1) % kSlots;
+                if (schur)
+                    hipLaunchKernelGGL(k_vi_s_prod, dim3((unsigned)((K + 3) / 4)), blk, 0, nullptr, d, ps, slot, prev,
+                                       it == 0 ? 1 : 0, last ? 1 : 0, (const double*)z,
+                                       (const double*)dir[(it + 1) & 1], dir[it & 1], q, x, xb);
+                else
+                    hipLaunchKernelGGL(k_vi_full_prod, full_grid, dim3(kFuseBlock), 0, nullptr, d, lam, ps, slot, prev,
+                                       last ? (int)kFullLast : it == 0 ? (int)kFullFirst : (int)kFullNext,
+                                       (const double*)z, (const double*)dir[(it + 1) & 1], dir[it & 1], q, x, xb,
+                                       (double*)nullptr);
+            };
+            int it = 0;
+            for (; it < o.pcg_max_iters; ++it) {
+                prod(it, false);
+                hipLaunchKernelGGL(k_vi_s_update, ug, blk, 0, nullptr, d, schur ? 0 : 1, ps, it % kSlots,
+                                   (it + kSlots - 1) % kSlots, (const double*)dir[it & 1], q, x, r, z);
+                bool done = false;
+                if (!sync(it, done)) return false;
+                if (done) break;
             }
-            hipLaunchKernelGGL(k_vi_pcg_update, upd, blk, 0, nullptr, d, npt, ps, slot, (const double*)pv,
-                               (const double*)q, x, r, z);
-            hipLaunchKernelGGL(k_vi_pcg_dir, dirg, blk, 0, nullptr, nn, ps, slot, (const double*)z, pv, x, xb,
-                               schur ? q : nullptr);
-            const int first_read = std::max(kPcgSync, prev_iters - kPcgSync);
-            if (it + 1 >= first_read && (it + 1 - first_read) % kPcgSync == 0 && it + 1 < o.pcg_max_iters) {
-                if (!chk() || !read_scal(8 + kPcgScalars)) return false;
-                if (hs[8 + kDone] != 0.0) break;
+            if (it == o.pcg_max_iters) prod(it, true);   // the decisions about the last step
+        } else {
+            const dim3 dirg((unsigned)std::max(1LL, std::min<long long>(1024, (nn + 255) / 256)));
+            for (int it = 0; it < o.pcg_max_iters; ++it) {
+                const int slot = it % kSlots;
+                schur_product(pv, q, lam, ps, ps + kAccN * slot + kAccPq);   // p . q summed inside
+                hipLaunchKernelGGL(k_vi_pcg_update, dim3((unsigned)((K + 15) / 16)), blk, 0, nullptr, d, ps, slot,
+                                   (const double*)pv, (const double*)q, x, r, z);
+                hipLaunchKernelGGL(k_vi_pcg_dir, dirg, blk, 0, nullptr, nn, ps, slot, (const double*)z, pv, x, xb, q);
+                bool done = false;
+                if (!sync(it, done)) return false;
+                if (done) break;
             }
         }
         if (schur) {
@@ -2882,10 +2915,9 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
             // from the back-substitution's (b_p + B^T dx_k) . dx_p; then the
             // candidate, its cost and |x|: one readback per trial
             if (!schur) {
-                const double* cnone = nullptr;
-                product(x, q, 0.0, nullptr);
-                hipLaunchKernelGGL(k_vi_dot, dot_blocks(n), blk, 0, nullptr, n, (const double*)x, (const double*)q,
-                                   red_parts(kRedQuad), cnone, kPqParts);
+                hipLaunchKernelGGL(k_vi_full_prod, full_grid, dim3(kFuseBlock), 0, nullptr, d, 0.0, ps, 0, 0,
+                                   (int)kFullQuad, (const double*)x, (const double*)nullptr, (double*)nullptr,
+                                   (double*)nullptr, (double*)nullptr, (double*)nullptr, red_parts(kRedQuad));
             }
             hipLaunchKernelGGL(k_vi_step, grid(16LL * K + N), blk, 0, nullptr, d, (const double*)x, schur ? 1 : 0);
             cost_of(d.st_c, d.X_c);
