@@ -309,6 +309,39 @@ __device__ __forceinline__ void wave_sum_scatter(T (&v)[N]) {
         v[k] = pair_add<0xB1>(v[2 * k], 2 * k + 1 < n5 ? v[2 * k + 1] : (T)0, (l & 1) != 0);
 }
 
+// The same over groups of kLanes consecutive lanes (16 or 32): value u ends in
+// register u / kLanes of lane rev6(u % kLanes) >> (64 / kLanes == 2 ? 1 : 2)
+// of the group.
+template <int kLanes>
+__device__ __forceinline__ int group_rev(int u) { return rev6(u) >> (kLanes == 32 ? 1 : kLanes == 16 ? 2 : 0); }
+template <int kLanes, typename T, int N>
+__device__ __forceinline__ void group_sum_scatter(T (&v)[N]) {
+    static_assert(kLanes == 64 || kLanes == 32 || kLanes == 16, "whole rows of 16 lanes");
+    if constexpr (kLanes == 64) {
+        wave_sum_scatter(v);
+    } else {
+        const int l = lane_id();
+        constexpr int n2 = kLanes == 32 ? (N + 1) / 2 : N, n3 = (n2 + 1) / 2, n4 = (n3 + 1) / 2, n5 = (n4 + 1) / 2,
+                      n6 = (n5 + 1) / 2;
+        if constexpr (kLanes == 32) {
+#pragma unroll
+            for (int k = 0; k < n2; ++k) v[k] = swap_add<16>(v[2 * k], 2 * k + 1 < N ? v[2 * k + 1] : (T)0);
+        }
+#pragma unroll
+        for (int k = 0; k < n3; ++k)   // row_ror:8
+            v[k] = pair_add<0x128>(v[2 * k], 2 * k + 1 < n2 ? v[2 * k + 1] : (T)0, (l & 8) != 0);
+#pragma unroll
+        for (int k = 0; k < n4; ++k)   // row_half_mirror
+            v[k] = pair_add<0x141>(v[2 * k], 2 * k + 1 < n3 ? v[2 * k + 1] : (T)0, (l & 4) != 0);
+#pragma unroll
+        for (int k = 0; k < n5; ++k)   // quad_perm [2,3,0,1]
+            v[k] = pair_add<0x4E>(v[2 * k], 2 * k + 1 < n4 ? v[2 * k + 1] : (T)0, (l & 2) != 0);
+#pragma unroll
+        for (int k = 0; k < n6; ++k)   // quad_perm [1,0,3,2]
+            v[k] = pair_add<0xB1>(v[2 * k], 2 * k + 1 < n5 ? v[2 * k + 1] : (T)0, (l & 1) != 0);
+    }
+}
+
 // Block-wide sum; every thread gets the result.  `red` holds >= 16 values.
 template <typename T>
 __device__ __forceinline__ T block_sum(T v, T* red) {

@@ -38,11 +38,14 @@ struct ImageCounts {
     int nc = 0, np = 0, ne = 0, n_tiles = 0, n_runs = 0, n_chunks = 0;
     bool info = false;
     bool reduced = false;   // the PCG runs on the explicit reduced system
+    bool wide = false;      // launched PCG iterations multiply by it
+    long long pairs = 0;    // pairs of edges of one point
 };
 
 // Whether a problem's explicit reduced system is formed (see gba_host.hip)
 struct Tuning;
 bool reduced_rule(const ImageCounts& n, const Tuning& tune);
+bool reduced_wide_rule(const ImageCounts& n, const Tuning& tune, int precision);
 
 // Sorted image of one problem, problem-local indices.  Edge arrays are
 // point-major (by point, then camera, then insertion) unless prefixed cm_
@@ -106,9 +109,9 @@ struct UnionPlan {
     // explicit reduced systems: offsets of S (entries, negative: none) and of
     // the rank bitmaps per problem, totals, cameras of the largest
     std::vector<long long> xs_off, xs_rank_off;
-    long long xs_total = 0, xs_rank_total = 0;
+    long long xs_total = 0, xs_rank_total = 0, xs_pairs = 0;
     int xs_cams = 0;
-    bool xs_all = false;
+    bool xs_all = false, xs_wide = false;
     std::vector<int> cam_prob, pt_prob;   // problem of each union camera / point
 };
 
@@ -174,6 +177,7 @@ struct Batch {
         double min_diag = 0, max_diag = 0, ratio = 0;
         const double* cam = nullptr;
         const double* pt = nullptr;
+        bool wide = false;
     } pcg_graph[kMaxPcgChunk + 1][2];   // by chunk length and parameter orientation
     void drop_graphs();
     // PCG iterations of the last damped step (the largest over the problems):

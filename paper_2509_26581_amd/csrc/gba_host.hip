@@ -156,6 +156,7 @@ gba_status make_image(const HostProblem& h, HostImage& img, std::string& msg) {
         for (int j = 0; j < np; ++j) {
             const int c = cnt[j + 1] - cnt[j];
             if (c == 0) continue;
+            img.n.pairs += (long long)c * (c - 1) / 2;
             if (c > kTileEdges) {
                 if (cur > 0) {
                     img.tile_off.push_back(img.tile_off.back() + cur);
@@ -256,6 +257,21 @@ gba_status make_image(const HostProblem& h, HostImage& img, std::string& msg) {
 bool reduced_rule(const ImageCounts& n, const Tuning& tune) {
     if (tune.accumulation != GBA_ACC_AUTO || tune.deterministic || tune.solver == GBA_SOLVER_FULL) return false;
     return n.nc > 0 && n.ne > 0 && n.n_runs == n.ne && 9 * n.nc <= kReducedMax;
+}
+
+// The same for a single larger problem, whose launched PCG iterations then
+// multiply by S instead of taking the point pass and its reduction.  Whole
+// solves (10 trials of about 38 iterations, FP32 and FP64) against the point
+// passes: 1.6 and 1.7 times as fast at 60 and 90 cameras, 1.5 and 1.4 at 203,
+// 1.26 and 1.07 at 320 (35 and 70 MB of S), 0.85-1.14 at 440 in FP32: S is read
+// in every iteration, so it is bounded to 40 MB.  Forming it takes about 60 ps
+// (FP32) and 160 ps (FP64) a pair of a point's edges and step (FP64, 260
+// cameras, 2M pairs: 0.32 ms, and no gain left), so the pairs are too.
+bool reduced_wide_rule(const ImageCounts& n, const Tuning& tune, int precision) {
+    if (tune.accumulation != GBA_ACC_AUTO || tune.deterministic || tune.solver == GBA_SOLVER_FULL) return false;
+    if (n.nc <= 0 || n.ne <= 0 || n.n_runs != n.ne || 9 * n.nc <= kReducedMax) return false;
+    const long long word = precision == GBA_FP64 ? 8 : 4;
+    return 9LL * n.nc * reduced_ld(9 * n.nc) * word <= 40'000'000 && n.pairs * word <= 12'000'000;
 }
 
 namespace {
@@ -421,10 +437,12 @@ gba_status plan_union(const std::vector<const ImageCounts*>& probs, const Tuning
     u.xs_all = true;
     for (int p = 0; p < P; ++p) {
         const ImageCounts& n = *probs[p];
-        if (!n.reduced) {
+        if (!n.reduced && !(P == 1 && n.wide)) {
             u.xs_all = false;
             continue;
         }
+        u.xs_wide = !n.reduced;
+        if (u.xs_wide) u.xs_pairs = n.pairs;
         u.xs_off[p] = u.xs_total;
         u.xs_rank_off[p] = u.xs_rank_total;
         u.xs_total += 9LL * n.nc * reduced_ld(9 * n.nc);
@@ -521,7 +539,7 @@ size_t layout_union(const UnionPlan& u, int precision, void* base, DeviceGraph* 
     decomp(d.dc_pts, u.pts);
     L.add(d.pp_part_off, sizeof(int) * u.part_off.size());
     L.add(d.cam_partial, sizeof(double) * std::max<long long>(1, u.part_total));
-    L.add(d.pq_partial, sizeof(double) * std::max(1, u.red.nblk()));
+    L.add(d.pq_partial, sizeof(double) * std::max({1, u.red.nblk(), u.xs_wide ? reduced_row_blocks(9 * (int)NC) : 0}));
     L.add(d.dot_partial, sizeof(double) * 2 * std::max(1, u.cam.nblk()));
     L.add(d.camupd_partial, sizeof(double) * 3 * std::max(1, u.cam.nblk()));
     L.add(d.chunk_partial, sizeof(double) * 54 * std::max(1, u.tot.n_chunks));
@@ -535,6 +553,11 @@ size_t layout_union(const UnionPlan& u, int precision, void* base, DeviceGraph* 
         L.add(d.xs_S, tsz * (size_t)u.xs_total);
         L.add(d.xs_diag, sizeof(double) * 45 * NC);
         L.add(d.xs_rank, sizeof(RankWord) * (size_t)u.xs_rank_total);
+        if (u.xs_wide) {
+            L.add(d.xs_pair_off, sizeof(int) * (NC * NC + 1));
+            L.add(d.xs_pairs, sizeof(int2) * (size_t)u.xs_pairs);
+            L.add(d.xs_edge, tsz * 24 * NE);
+        }
     } else if (dptr) {
         d.xs_off = d.xs_rank_off = nullptr;
         d.prob_pt_off = nullptr;
@@ -585,6 +608,9 @@ void set_union_scalars(Batch& b, int precision, int loss, double delta) {
     d.xs_on = u.xs_total > 0 ? 1 : 0;
     d.xs_all = d.xs_on && u.xs_all ? 1 : 0;
     d.xs_cams = u.xs_cams;
+    d.xs_wide = u.xs_wide ? 1 : 0;
+    d.xs_pair_total = u.xs_pairs;
+    d.xs_rows = 0;
     d.dc_pp.nblk = u.pp.nblk();
     d.dc_red.nblk = u.red.nblk();
     d.dc_cam.nblk = u.cam.nblk();
@@ -638,6 +664,7 @@ gba_status build_batch(const std::vector<const HostProblem*>& probs, int precisi
         gba_status st = make_image(*probs[p], imgs[p], msg);
         if (st != GBA_OK) return st;
         imgs[p].n.reduced = reduced_rule(imgs[p].n, tune);
+        imgs[p].n.wide = P == 1 && reduced_wide_rule(imgs[p].n, tune, precision);
         counts[p] = &imgs[p].n;
     }
     gba_status st = plan_union(counts, tune, dev, precision, b.plan, msg);
@@ -838,15 +865,18 @@ gba_status batch_damped_step(Batch& b, const gba_options& o, const Tuning& tune,
     // launched iterations, the identity preconditioner has no diagonal blocks)
     const bool reduced = d.xs_on && block_jacobi && !timing && o.pcg_schedule == GBA_PCG_AUTO &&
                          !b.launched_products;
-    if (!reduced || !d.xs_all) HIP_OR(msg, launch_pcg_init(d, s, o.pcg_tol, o.pcg_tol_relative));
+    const bool wide = reduced && d.xs_wide;
+    if (!reduced || !d.xs_all || wide) HIP_OR(msg, launch_pcg_init(d, s, o.pcg_tol, o.pcg_tol_relative));
     if (reduced) {
-        if (!b.reduced_built) HIP_OR(msg, launch_reduced_build(d, (size_t)b.plan.xs_rank_total, s));
+        if (!b.reduced_built)
+            HIP_OR(msg, launch_reduced_build(d, (size_t)b.plan.xs_rank_total, (size_t)b.plan.xs_total, s));
         b.reduced_built = true;
         HIP_OR(msg, launch_reduced_form(d, s));
-        HIP_OR(msg, launch_pcg_reduced(d, s, o.pcg_tol, o.pcg_tol_relative, o.pcg_max_iters,
-                                       o.pcg_rejection_ratio));
+        if (!wide)
+            HIP_OR(msg, launch_pcg_reduced(d, s, o.pcg_tol, o.pcg_tol_relative, o.pcg_max_iters,
+                                           o.pcg_rejection_ratio));
     }
-    if (reduced && d.xs_all) {
+    if (reduced && d.xs_all && !wide) {
         HIP_OR(msg, launch_backsub(d, s));
         HIP_OR(msg, launch_cost(d, s, d.cam_c, d.pt_c));
         HIP_OR(msg, launch_finish(d, s));
@@ -883,6 +913,8 @@ gba_status batch_damped_step(Batch& b, const gba_options& o, const Tuning& tune,
         b.last_pcg_iters = iters;
         return GBA_OK;
     }
+    DeviceGraph di = d;   // of the launched iterations
+    di.xs_rows = wide ? reduced_row_blocks(9 * d.nc) : 0;
     const int chunk = std::max(1, std::min(kMaxPcgChunk, tune.pcg_sync_every));
     // A PCG of k steps takes k + 1 launched iterations: an iteration decides
     // at its start whether the previous step ended the PCG.  The first chunk
@@ -911,7 +943,7 @@ gba_status batch_damped_step(Batch& b, const gba_options& o, const Tuning& tune,
             const bool moved = d.dynamic && (pg.cam != d.cam || pg.pt != d.pt);
             if (pg.exec && (pg.iters != c || pg.max_iters != o.pcg_max_iters ||
                             pg.min_diag != o.min_diag || pg.max_diag != o.max_diag ||
-                            pg.ratio != o.pcg_rejection_ratio || moved)) {
+                            pg.ratio != o.pcg_rejection_ratio || pg.wide != wide || moved)) {
                 (void)hipGraphExecDestroy(pg.exec);
                 pg = Batch::PcgGraph{};
             }
@@ -924,7 +956,7 @@ gba_status batch_damped_step(Batch& b, const gba_options& o, const Tuning& tune,
                 HIP_OR(msg, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
                 hipError_t r = hipSuccess;
                 for (int k = 0; k < c && r == hipSuccess; ++k)
-                    r = launch_pcg_iter(d, cs, o.min_diag, o.max_diag, o.pcg_max_iters,
+                    r = launch_pcg_iter(di, cs, o.min_diag, o.max_diag, o.pcg_max_iters,
                                         o.pcg_rejection_ratio, nullptr, nullptr);
                 hipError_t r2 = hipStreamEndCapture(cs, &graph);
                 HIP_OR(msg, r);
@@ -937,6 +969,7 @@ gba_status batch_damped_step(Batch& b, const gba_options& o, const Tuning& tune,
                 pg.min_diag = o.min_diag;
                 pg.max_diag = o.max_diag;
                 pg.ratio = o.pcg_rejection_ratio;
+                pg.wide = wide;
                 pg.cam = d.cam;
                 pg.pt = d.pt;
             }
@@ -945,7 +978,7 @@ gba_status batch_damped_step(Batch& b, const gba_options& o, const Tuning& tune,
             for (int k = 0; k < c; ++k) {
                 hipEvent_t e0 = timing ? tm->ev[4 + 2 * k] : nullptr;
                 hipEvent_t e1 = timing ? tm->ev[5 + 2 * k] : nullptr;
-                HIP_OR(msg, launch_pcg_iter(d, s, o.min_diag, o.max_diag, o.pcg_max_iters,
+                HIP_OR(msg, launch_pcg_iter(di, s, o.min_diag, o.max_diag, o.pcg_max_iters,
                                             o.pcg_rejection_ratio, e0, e1));
             }
             b.pcg_warm = true;

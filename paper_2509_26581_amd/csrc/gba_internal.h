@@ -244,6 +244,8 @@ struct DeviceGraph {
     int dynamic;              // 1: no stored Jacobian; products recompute it from the parameters
     // explicit reduced systems (xs_on: some problem has one, xs_all: every one)
     int xs_on, xs_all;
+    int xs_wide;              // the only problem's S is larger: launched PCG iterations multiply by it
+    int xs_rows;              // launched product on S: its workgroups (set by launch_pcg_iter, else 0)
     int xs_cams;              // cameras of the largest such problem
     const long long* xs_off;       // [P] offset of S in xs_S (entries), negative: products stay implicit
     const long long* xs_rank_off;  // [P] offset of the rank bitmaps in xs_rank
@@ -251,6 +253,13 @@ struct DeviceGraph {
     void* xs_S;               // per problem a dense symmetric matrix, columns of reduced_ld(9 nc_p)
     double* xs_diag;          // [nc][45] diagonal blocks of S (zero in xs_S)
     RankWord* xs_rank;        // per problem [nc_p][rank_words(np_p)]
+    // xs_wide: the common points of every camera pair i < k, by i nc + k:
+    // camera-major edges of both, in point order
+    int* xs_pair_off;         // [nc nc + 1]
+    int2* xs_pairs;
+    void* xs_edge;            // [ne][24] per camera-major edge J_c (2 x 9) and J_p L (2 x 3),
+                              // L L^T = Hpp^-1, vector type
+    long long xs_pair_total;
     void* w_x;                // [np][3] point parts of the PCG vectors (vector type)
     void* w_r;
     void* w_z;
@@ -357,8 +366,13 @@ bool pcg_persistent_ok(const DeviceGraph& g);
 // Explicit reduced systems: the rank bitmaps (once per device graph), S of
 // the damped step (after launch_precond, which writes its diagonal blocks),
 // and the whole PCG of the problems that have one (start to stop).
-hipError_t launch_reduced_build(const DeviceGraph& g, size_t rank_total, hipStream_t s);
+hipError_t launch_reduced_build(const DeviceGraph& g, size_t rank_total, size_t s_total, hipStream_t s);
 hipError_t launch_reduced_form(const DeviceGraph& g, hipStream_t s);
+// rows of S per workgroup of the launched product, and the product itself (a
+// PCG iteration's decision, q, p and the p^T q partials) for one problem
+constexpr int kReducedRows = 8;
+inline int reduced_row_blocks(int n) { return (n + kReducedRows - 1) / kReducedRows; }
+hipError_t launch_reduced_product(const DeviceGraph& g, hipStream_t s, int max_iters, double reject_ratio);
 hipError_t launch_pcg_reduced(const DeviceGraph& g, hipStream_t s, double tol, int relative, int max_iters,
                               double reject_ratio);
 hipError_t launch_backsub(const DeviceGraph& g, hipStream_t s);

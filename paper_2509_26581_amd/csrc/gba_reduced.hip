@@ -1,7 +1,8 @@
 // The explicit reduced camera system of small problems: S = Hcc_lambda -
 // sum_j W_j Hpp_lambda,j^-1 W_j^T formed once per damped step as a dense
 // matrix, and the whole preconditioned conjugate-gradient solve on it in one
-// workgroup per problem.  The implicit products (gba_kernels.hip) stream the
+// workgroup per problem, or (one larger problem) the products of launched
+// iterations.  The implicit products (gba_kernels.hip) stream the
 // stored Jacobian once per PCG iteration and take two or three launches for
 // it; with few cameras S is smaller than that Jacobian, and an iteration on it
 // needs no launch.
@@ -13,6 +14,7 @@
 #include "gba.h"
 #include "gba_device.h"
 #include "gba_internal.h"
+#include "gba_pcg.h"
 
 namespace gba {
 
@@ -80,6 +82,46 @@ __global__ __launch_bounds__(64) void k_rank_base(DeviceGraph g) {
 // (192 B a match in FP32, mostly from the L2).  The diagonal blocks come with
 // the preconditioner (k_cam_finalize).
 // ==========================================================================
+
+// rows rb .. rb + kRows - 1 of one match's J_c,i^T (J_p,i Hpp^-1 J_p,k^T) J_c,k
+// added to acc; ea, eb: the camera-major edges of both cameras
+template <typename T, typename JS, int kRows>
+__device__ __forceinline__ void reduced_term(const DeviceGraph& g, int ea, int eb, int rb, T (&acc)[9 * kRows]) {
+    T ja[2][9], pa[2][3], jb[2][9], pb[2][3];
+    jac_load<JS>(g.jst_cm, ea, ja, pa);
+    jac_load<JS>(g.jst_cm, eb, jb, pb);
+    const T* H = (const T*)g.hpp_inv + kHinvStride * (size_t)g.cm_pt[ea];
+    const T h[6] = {H[0], H[1], H[2], H[3], H[4], H[5]};
+    T A[2][2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const T t0 = pa[r][0] * h[0] + pa[r][1] * h[1] + pa[r][2] * h[2];
+        const T t1 = pa[r][0] * h[1] + pa[r][1] * h[3] + pa[r][2] * h[4];
+        const T t2 = pa[r][0] * h[2] + pa[r][1] * h[4] + pa[r][2] * h[5];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) A[r][c] = t0 * pb[c][0] + t1 * pb[c][1] + t2 * pb[c][2];
+    }
+    T m[2][9];
+#pragma unroll
+    for (int c = 0; c < 9; ++c) {
+        m[0][c] = A[0][0] * jb[0][c] + A[0][1] * jb[1][c];
+        m[1][c] = A[1][0] * jb[0][c] + A[1][1] * jb[1][c];
+    }
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        T u0, u1;
+        if constexpr (kRows == 9) {
+            u0 = ja[0][r];
+            u1 = ja[1][r];
+        } else {   // rb is uniform
+            u0 = rb == 0 ? ja[0][r] : rb == kRows ? ja[0][kRows + r] : ja[0][2 * kRows + r];
+            u1 = rb == 0 ? ja[1][r] : rb == kRows ? ja[1][kRows + r] : ja[1][2 * kRows + r];
+        }
+#pragma unroll
+        for (int c = 0; c < 9; ++c) acc[9 * r + c] += u0 * m[0][c] + u1 * m[1][c];
+    }
+}
+
 template <typename T, typename JS, int kRows>
 __global__ __launch_bounds__(256) void k_reduced_blocks(DeviceGraph g) {
     const int a = blockIdx.x, prob = g.cam_prob[a];
@@ -95,7 +137,6 @@ __global__ __launch_bounds__(256) void k_reduced_blocks(DeviceGraph g) {
     const int n = 9 * nc, ld = reduced_ld(n);
     constexpr int kSplit = 9 / kRows;
     const int q0 = cam_edge_begin(g, a), q1 = cam_edge_begin(g, a + 1);
-    const T* __restrict__ Hinv = (const T*)g.hpp_inv;
     T* __restrict__ S = (T*)g.xs_S + off;
     int* qa = qa_s[w];
     int* qb = qb_s[w];
@@ -105,42 +146,7 @@ __global__ __launch_bounds__(256) void k_reduced_blocks(DeviceGraph g) {
         T acc[kSums];
 #pragma unroll
         for (int u = 0; u < kSums; ++u) acc[u] = (T)0;
-        auto add = [&](int ea, int eb) {
-            T ja[2][9], pa[2][3], jb[2][9], pb[2][3];
-            jac_load<JS>(g.jst_cm, ea, ja, pa);
-            jac_load<JS>(g.jst_cm, eb, jb, pb);
-            const T* H = Hinv + kHinvStride * (size_t)g.cm_pt[ea];
-            const T h[6] = {H[0], H[1], H[2], H[3], H[4], H[5]};
-            T A[2][2];
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const T t0 = pa[r][0] * h[0] + pa[r][1] * h[1] + pa[r][2] * h[2];
-                const T t1 = pa[r][0] * h[1] + pa[r][1] * h[3] + pa[r][2] * h[4];
-                const T t2 = pa[r][0] * h[2] + pa[r][1] * h[4] + pa[r][2] * h[5];
-#pragma unroll
-                for (int c = 0; c < 2; ++c) A[r][c] = t0 * pb[c][0] + t1 * pb[c][1] + t2 * pb[c][2];
-            }
-            T m[2][9];
-#pragma unroll
-            for (int c = 0; c < 9; ++c) {
-                m[0][c] = A[0][0] * jb[0][c] + A[0][1] * jb[1][c];
-                m[1][c] = A[1][0] * jb[0][c] + A[1][1] * jb[1][c];
-            }
-#pragma unroll
-            for (int r = 0; r < kRows; ++r) {
-                // rows rb .. rb + kRows - 1 of camera i (rb is uniform)
-                T u0, u1;
-                if constexpr (kSplit == 1) {
-                    u0 = ja[0][r];
-                    u1 = ja[1][r];
-                } else {
-                    u0 = rb == 0 ? ja[0][r] : rb == kRows ? ja[0][kRows + r] : ja[0][2 * kRows + r];
-                    u1 = rb == 0 ? ja[1][r] : rb == kRows ? ja[1][kRows + r] : ja[1][2 * kRows + r];
-                }
-#pragma unroll
-                for (int c = 0; c < 9; ++c) acc[9 * r + c] += u0 * m[0][c] + u1 * m[1][c];
-            }
-        };
+        auto add = [&](int ea, int eb) { reduced_term<T, JS, kRows>(g, ea, eb, rb, acc); };
         int queued = 0;   // uniform per wavefront
         for (int base = q0 + w * kWave; base < q1; base += 4 * kWave) {
             const int q = base + l;
@@ -190,6 +196,189 @@ __global__ __launch_bounds__(256) void k_reduced_blocks(DeviceGraph g) {
             const int row = 9 * i + rb + u / 9, col = 9 * k + u % 9;
             S[(size_t)col * ld + row] = sum;
             S[(size_t)row * ld + col] = sum;
+        }
+    }
+}
+
+// ==========================================================================
+// The common points of every camera pair of a larger problem, once per device
+// graph (the lookups above in every step would take 180 us at 203 cameras).
+// One wavefront per pair: counts, then (after the scan) the matches in point
+// order.
+// ==========================================================================
+template <bool kFill>
+__global__ __launch_bounds__(256) void k_pair_lists(DeviceGraph g) {
+    const int l = lane_id(), i = (int)blockIdx.x;
+    const int k = (int)blockIdx.y * 4 + ((int)threadIdx.x >> 6);
+    if (k >= g.nc) return;
+    const size_t at = (size_t)i * g.nc + k;
+    if (k <= i) {
+        if (!kFill && l == 0) g.xs_pair_off[at] = 0;
+        return;
+    }
+    const int nw = rank_words(g.np);
+    const RankWord* __restrict__ rank = g.xs_rank + (size_t)k * nw;
+    const int q0 = cam_edge_begin(g, i), q1 = cam_edge_begin(g, i + 1);
+    int n = 0;
+    const int first = kFill ? g.xs_pair_off[at] : 0;
+    for (int base = q0; base < q1; base += kWave) {
+        const int q = base + l;
+        bool hit = false;
+        int other = 0;
+        if (q < q1) {
+            const int j = g.cm_pt[q];
+            const RankWord r = rank[j >> 6];
+            hit = (r.mask >> (j & 63)) & 1ull;
+            other = r.base + __popcll(r.mask & ((1ull << (j & 63)) - 1ull));
+        }
+        const uint64_t hits = __ballot(hit);
+        if (kFill && hit) g.xs_pairs[first + n + __popcll(hits & ((1ull << l) - 1ull))] = make_int2(q, other);
+        n += __popcll(hits);
+    }
+    if (!kFill && l == 0) g.xs_pair_off[at] = n;
+}
+
+// counts -> offsets (exclusive, the total last), one workgroup
+__global__ __launch_bounds__(1024) void k_pair_scan(DeviceGraph g) {
+    __shared__ int wsum[16];
+    const int tid = (int)threadIdx.x, l = tid & 63, w = tid >> 6, n = g.nc * g.nc;
+    int base = 0;
+    for (int k0 = 0; k0 < n; k0 += 1024) {
+        const int c = k0 + tid < n ? g.xs_pair_off[k0 + tid] : 0;
+        int s = c;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int t = __shfl_up(s, off, 64);
+            if (l >= off) s += t;
+        }
+        if (l == 63) wsum[w] = s;
+        __syncthreads();
+        int before = base;
+        for (int v = 0; v < 16; ++v) {
+            if (v < w) before += wsum[v];
+            base += wsum[v];
+        }
+        if (k0 + tid < n) g.xs_pair_off[k0 + tid] = before + s - c;
+        __syncthreads();
+    }
+    if (tid == 0) g.xs_pair_off[n] = base;
+}
+
+// One record per camera-major edge, contiguous: the matches of a pair are a
+// few of its cameras' edges, and from the stored Jacobian's tiles each 16
+// bytes of one came with a line of their own (68 us a step at 203 cameras in
+// FP32, 276 in FP64; 30 and 99 from the records, which take 11 and 18 to
+// write).  With Hpp^-1 = L L^T a match needs no point block.
+template <typename T, typename JS>
+__global__ __launch_bounds__(256) void k_reduced_edges(DeviceGraph g) {
+    if ((sizeof(T) == 8) != (g.mode == kModeFP64) || sizeof(JS) != (size_t)g.jac_bytes) return;
+    const int e = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (e >= g.ne) return;
+    T jc[2][9], jp[2][3];
+    jac_load<JS>(g.jst_cm, e, jc, jp);
+    const T* H = (const T*)g.hpp_inv + kHinvStride * (size_t)g.cm_pt[e];
+    const double h00 = H[0], h01 = H[1], h02 = H[2], h11 = H[3], h12 = H[4], h22 = H[5];
+    const double l00 = sqrt(fmax(h00, 0.0)), i0 = l00 > 0.0 ? 1.0 / l00 : 0.0;
+    const double l10 = h01 * i0, l20 = h02 * i0;
+    const double l11 = sqrt(fmax(h11 - l10 * l10, 0.0)), i1 = l11 > 0.0 ? 1.0 / l11 : 0.0;
+    const double l21 = (h12 - l20 * l10) * i1;
+    const double l22 = sqrt(fmax(h22 - l20 * l20 - l21 * l21, 0.0));
+    T out[24];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+#pragma unroll
+        for (int c = 0; c < 9; ++c) out[9 * r + c] = jc[r][c];
+        const double a = jp[r][0], b = jp[r][1], c = jp[r][2];
+        out[18 + 3 * r] = (T)(a * l00 + b * l10 + c * l20);
+        out[19 + 3 * r] = (T)(b * l11 + c * l21);
+        out[20 + 3 * r] = (T)(c * l22);
+    }
+    typedef T V __attribute__((ext_vector_type(16 / sizeof(T))));
+    constexpr int kV = 16 / (int)sizeof(T);
+    V* dst = (V*)((T*)g.xs_edge + 24 * (size_t)e);
+#pragma unroll
+    for (int k = 0; k < 24 / kV; ++k) {
+        V v;
+#pragma unroll
+        for (int u = 0; u < kV; ++u) v[u] = out[kV * k + u];
+        dst[k] = v;
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void edge_record(const DeviceGraph& g, int e, T (&v)[24]) {
+    typedef T V __attribute__((ext_vector_type(16 / sizeof(T))));
+    constexpr int kV = 16 / (int)sizeof(T);
+    const V* src = (const V*)((const T*)g.xs_edge + 24 * (size_t)e);
+#pragma unroll
+    for (int k = 0; k < 24 / kV; ++k) {
+        const V x = src[k];
+#pragma unroll
+        for (int u = 0; u < kV; ++u) v[kV * k + u] = x[u];
+    }
+}
+
+// Off-diagonal blocks of S from the lists, kLanes lanes per camera pair (and
+// kRows rows of its block; about a pair's mean number of common points, as the
+// sums over the lanes cost more than the terms of one match); pairs without a
+// common point keep the zeros of the build.
+template <typename T, int kRows, int kLanes>
+__global__ __launch_bounds__(256) void k_reduced_pairs(DeviceGraph g) {
+    if ((sizeof(T) == 8) != (g.mode == kModeFP64)) return;
+    constexpr int kSums = 9 * kRows, kGroups = 256 / kLanes;
+    const int l = (int)threadIdx.x % kLanes, i = (int)blockIdx.x, rb = (int)blockIdx.z * kRows;
+    const int k = i + 1 + (int)blockIdx.y * kGroups + (int)threadIdx.x / kLanes;
+    if (i + 1 + (int)blockIdx.y * kGroups >= g.nc || g.lam[0] < 0.0) return;   // uniform
+    int m0 = 0, m1 = 0;
+    if (k < g.nc) {
+        const size_t at = (size_t)i * g.nc + k;
+        m0 = g.xs_pair_off[at];
+        m1 = g.xs_pair_off[at + 1];
+    }
+    if (__ballot(m0 < m1) == 0) return;   // whole wavefronts
+    T acc[kSums];
+#pragma unroll
+    for (int u = 0; u < kSums; ++u) acc[u] = (T)0;
+    for (int m = m0 + l; m < m1; m += kLanes) {
+        const int2 e = g.xs_pairs[m];
+        T a[24], b[24];
+        edge_record(g, e.x, a);
+        edge_record(g, e.y, b);
+        T A[2][2], M[2][9];
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                A[r][c] = a[18 + 3 * r] * b[18 + 3 * c] + a[19 + 3 * r] * b[19 + 3 * c] + a[20 + 3 * r] * b[20 + 3 * c];
+#pragma unroll
+        for (int c = 0; c < 9; ++c) {
+            M[0][c] = A[0][0] * b[c] + A[0][1] * b[9 + c];
+            M[1][c] = A[1][0] * b[c] + A[1][1] * b[9 + c];
+        }
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            T u0, u1;
+            if constexpr (kRows == 9) {
+                u0 = a[r];
+                u1 = a[9 + r];
+            } else {   // rb is uniform
+                u0 = rb == 0 ? a[r] : rb == kRows ? a[kRows + r] : a[2 * kRows + r];
+                u1 = rb == 0 ? a[9 + r] : rb == kRows ? a[9 + kRows + r] : a[9 + 2 * kRows + r];
+            }
+#pragma unroll
+            for (int c = 0; c < 9; ++c) acc[9 * r + c] += u0 * M[0][c] + u1 * M[1][c];
+        }
+    }
+    group_sum_scatter<kLanes>(acc);   // sum u in lane group_rev(u % kLanes), register u / kLanes
+    if (m0 == m1) return;
+    const int ld = reduced_ld(9 * g.nc);
+    T* __restrict__ S = (T*)g.xs_S;
+#pragma unroll
+    for (int v = 0; v < (kSums + kLanes - 1) / kLanes; ++v) {
+        const int u = v * kLanes + group_rev<kLanes>(l);
+        if (u < kSums) {
+            const int row = 9 * i + rb + u / 9, col = 9 * k + u % 9;
+            S[(size_t)col * ld + row] = -acc[v];
+            S[(size_t)row * ld + col] = -acc[v];
         }
     }
 }
@@ -478,21 +667,127 @@ __global__ __launch_bounds__(kBig ? big_waves<T>() * kWave : 4 * kWave) void k_p
 }
 
 // ==========================================================================
+// A launched PCG iteration's product on S (one problem): the iteration's
+// decision, then q = S p = S z + beta q_old, p = z + beta p_old and partial
+// p^T q, kReducedRows rows per workgroup.  Four wavefronts share the columns
+// (16 bytes a lane and row, every row's loads in flight together), the fifth
+// takes the decision and the rows' other operands meanwhile.  Sums in FP64.
+// Bound by the reads of S: 5.0 us at 203 cameras in FP32 (13 MB), 7.4 at 320
+// (33 MB), where the point pass and its reduction take 12.6 and 14; 16 rows a
+// workgroup and half the bytes in flight took 9.5 at 203.
+// ==========================================================================
+constexpr int kReducedProductBlock = 5 * kWave;
+template <typename T>
+__global__ __launch_bounds__(kReducedProductBlock) void k_reduced_product(DeviceGraph g) {
+    if ((sizeof(T) == 8) != (g.mode == kModeFP64)) return;
+    constexpr int kWaves = 4;
+    __shared__ double tot_s[kWaves][kReducedRows];
+    const int n = 9 * g.nc, ld = reduced_ld(n), k0 = (int)blockIdx.x * kReducedRows;
+    const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const T* __restrict__ z = (const T*)g.v_z;
+    if (w == kWaves) {
+        // lanes l < kReducedRows own a row each
+        const int k = k0 + l, i = k / 9, r = k % 9;
+        const bool own = l < kReducedRows && k < n;
+        double diag = 0.0;
+        T zk = 0, pold = 0, qold = 0;
+        if (own) {
+            zk = z[k];
+            pold = ((const T*)g.v_p)[k];
+            qold = ((const T*)g.v_q)[k];
+#pragma unroll
+            for (int c = 0; c < 9; ++c) diag += g.xs_diag[45 * (size_t)i + sym9(r, c)] * (double)z[9 * i + c];
+        }
+        const PcgState d = pcg_decision(g, 0);
+        if (blockIdx.x == 0 && l == 0) g.pcg_dec[0] = d;
+        __syncthreads();   // the products
+        if (!(d.act & kActStep)) return;
+        double dot = 0.0;
+        if (own) {
+            double s = diag;
+#pragma unroll
+            for (int v = 0; v < kWaves; ++v) s += tot_s[v][l];
+            const T beta = (T)d.beta, sz = (T)s;
+            const T q = (d.act & kActRun) ? fma(beta, qold, sz) : sz;
+            const T p = (d.act & kActRun) ? fma(beta, pold, zk) : zk;
+            ((T*)g.v_q)[k] = q;
+            ((T*)g.v_p)[k] = p;
+            dot = (double)p * (double)q;
+        }
+        dot = wave_sum(dot);
+        if (l == 0) g.pq_partial[blockIdx.x] = dot;
+        return;
+    }
+    constexpr int kV = 16 / (int)sizeof(T);
+    typedef T V __attribute__((ext_vector_type(16 / sizeof(T))));
+    const T* __restrict__ S = (const T*)g.xs_S + g.xs_off[0];
+    double acc[kReducedRows];
+#pragma unroll
+    for (int u = 0; u < kReducedRows; ++u) acc[u] = 0.0;
+    if (!g.pcg[0].done) {   // (uniform; a stopped PCG only takes the decision)
+        for (int c = kV * (int)threadIdx.x; c < n; c += kV * kWaves * kWave) {
+            V s[kReducedRows];
+#pragma unroll
+            for (int u = 0; u < kReducedRows; ++u)   // rows are padded to whole vectors
+                s[u] = *(const V*)(S + (size_t)min(k0 + u, n - 1) * ld + c);
+#pragma unroll
+            for (int v = 0; v < kV; ++v) {
+                const bool in = c + v < n;
+                const double zv = in ? (double)z[c + v] : 0.0;
+#pragma unroll
+                for (int u = 0; u < kReducedRows; ++u) acc[u] += (in ? (double)s[u][v] : 0.0) * zv;
+            }
+        }
+    }
+    wave_sum_scatter(acc);   // row u in lane rev6(u)
+    if (rev6(l) < kReducedRows) tot_s[w][rev6(l)] = acc[0];
+    __syncthreads();
+}
+
+// ==========================================================================
 // launchers
 // ==========================================================================
-hipError_t launch_reduced_build(const DeviceGraph& g, size_t rank_total, hipStream_t s) {
+hipError_t launch_reduced_build(const DeviceGraph& g, size_t rank_total, size_t s_total, hipStream_t s) {
     if (!g.xs_on) return hipSuccess;
     const int eg = std::max(1, std::min(4096, (g.ne + 255) / 256));
     hipLaunchKernelGGL(k_rank_clear, dim3((unsigned)std::min<size_t>(4096, (rank_total + 63) / 64)), dim3(64),
                        0, s, g, rank_total);
     hipLaunchKernelGGL(k_rank_set, dim3(eg), dim3(256), 0, s, g);
     hipLaunchKernelGGL(k_rank_base, dim3(g.nc), dim3(64), 0, s, g);
+    if (g.xs_wide) {
+        const dim3 grid(g.nc, (unsigned)((g.nc + 3) / 4));
+        hipLaunchKernelGGL(k_pair_lists<false>, grid, dim3(256), 0, s, g);
+        hipLaunchKernelGGL(k_pair_scan, dim3(1), dim3(1024), 0, s, g);
+        hipLaunchKernelGGL(k_pair_lists<true>, grid, dim3(256), 0, s, g);
+        const hipError_t e = launch_fill_f64((double*)g.xs_S, 0.0, s_total * (g.mode == kModeFP64 ? 1 : 0) +
+                                             (g.mode == kModeFP64 ? 0 : s_total / 2), s);
+        if (e != hipSuccess) return e;
+    }
     return hipGetLastError();
+}
+
+template <typename T, typename JS, int kRows>
+static void reduced_pairs(const DeviceGraph& g, hipStream_t s) {
+    const long long mean = g.xs_pair_total / std::max(1LL, (long long)g.nc * (g.nc - 1) / 2);
+    auto grid = [&](int lanes) {
+        const int groups = 256 / lanes;
+        return dim3(g.nc, (unsigned)std::max(1, (g.nc - 1 + groups - 1) / groups), 9 / kRows);
+    };
+    hipLaunchKernelGGL((k_reduced_edges<T, JS>), dim3((unsigned)((g.ne + 255) / 256)), dim3(256), 0, s, g);
+    if (mean > 40) hipLaunchKernelGGL((k_reduced_pairs<T, kRows, 64>), grid(64), dim3(256), 0, s, g);
+    else if (mean > 12) hipLaunchKernelGGL((k_reduced_pairs<T, kRows, 32>), grid(32), dim3(256), 0, s, g);
+    else hipLaunchKernelGGL((k_reduced_pairs<T, kRows, 16>), grid(16), dim3(256), 0, s, g);
 }
 
 hipError_t launch_reduced_form(const DeviceGraph& g, hipStream_t s) {
     if (!g.xs_on || g.nc == 0) return hipSuccess;
     const int split = g.mode == kModeFP64 ? 3 : 1;
+    if (g.xs_wide) {
+        if (g.mode == kModeFP64) reduced_pairs<double, double, 3>(g, s);
+        else if (g.mode == kModeFP32) reduced_pairs<float, float, 9>(g, s);
+        else reduced_pairs<float, bf16, 9>(g, s);
+        return hipGetLastError();
+    }
     // one workgroup per block (or part) of the longest row
     const dim3 grid(g.nc, (unsigned)std::max(1, split * (g.xs_cams - 1)));
     if (g.mode == kModeFP64)
@@ -501,6 +796,15 @@ hipError_t launch_reduced_form(const DeviceGraph& g, hipStream_t s) {
         hipLaunchKernelGGL((k_reduced_blocks<float, float, 9>), grid, dim3(256), 0, s, g);
     else
         hipLaunchKernelGGL((k_reduced_blocks<float, bf16, 9>), grid, dim3(256), 0, s, g);
+    return hipGetLastError();
+}
+
+hipError_t launch_reduced_product(const DeviceGraph& g0, hipStream_t s, int max_iters, double ratio) {
+    DeviceGraph g = g0;
+    g.pcg_max_iters = max_iters;
+    g.pcg_ratio = ratio;
+    if (g.mode == kModeFP64) hipLaunchKernelGGL(k_reduced_product<double>, dim3(g.xs_rows), dim3(kReducedProductBlock), 0, s, g);
+    else hipLaunchKernelGGL(k_reduced_product<float>, dim3(g.xs_rows), dim3(kReducedProductBlock), 0, s, g);
     return hipGetLastError();
 }
 
