@@ -424,7 +424,7 @@ struct VIDev {
     double* info;          // [81 (K - 1)] Omega of the inertial terms
     double* jsp;           // whole-system form: what the stereo Jacobians are made of, the
                            // point in the camera and the whitening factor, in point-order
-                           // tiles (js_at); null in the Schur form
+                           // tiles (js_tile); null in the Schur form
     double* ji;            // [216 (K - 1)] inertial Jacobians
     double* ri;            // [9 (K - 1)]
     double* b;             // [n] gradient J^T Omega r
@@ -705,10 +705,25 @@ __global__ void k_vi_lin_stereo(VIDev d) {
         }
 }
 
-// the whole-system form's stereo terms in padded point-order tiles: entry c of
-// slot i at (4 tile + c) 64 + lane
-__device__ __forceinline__ size_t js_at(long long i, int c) {
-    return ((size_t)(i >> 6) * 4 + c) * 64 + (size_t)(i & 63);
+// the whole-system form's stereo terms in padded point-order tiles of 64
+// slots: the point in the camera (3 x 64 doubles), then the whitening factors
+// (64 doubles, or floats when w32: a row of the Jacobian then carries one FP32
+// rounding, as each of its entries did when it was stored)
+__device__ __forceinline__ double* js_tile(const VIDev& d, long long i) {
+    return d.jsp + (size_t)(i >> 6) * (d.w32 ? 224 : 256);
+}
+__device__ __forceinline__ void js_save(const VIDev& d, long long i, const double (&jc)[4]) {
+    double* t = js_tile(d, i);
+    const int l = (int)(i & 63);
+    for (int c = 0; c < 3; ++c) t[64 * c + l] = jc[c];
+    if (d.w32) ((float*)(t + 192))[l] = (float)jc[3];
+    else t[192 + l] = jc[3];
+}
+__device__ __forceinline__ void js_load(const VIDev& d, long long i, double (&jc)[4]) {
+    const double* t = js_tile(d, i);
+    const int l = (int)(i & 63);
+    for (int c = 0; c < 3; ++c) jc[c] = t[64 * c + l];
+    jc[3] = d.w32 ? (double)((const float*)(t + 192))[l] : t[192 + l];
 }
 
 // the same terms in point order: W (Schur form) or the Jacobian's terms
@@ -741,7 +756,9 @@ __global__ void k_vi_lin_stereo_pts(VIDev d) {
                     (WT)(J[0][a] * J[0][6 + c] + J[1][a] * J[1][6 + c] + J[2][a] * J[2][6 + c]);
     if (d.jsp && i0 < d.Mp) {
         const double pad[4] = {0.0, 0.0, 1.0, 0.0};
-        for (int c = 0; c < 4; ++c) d.jsp[js_at(i, c)] = valid ? jc[c] : pad[c];
+        double js[4];
+        for (int c = 0; c < 4; ++c) js[c] = valid ? jc[c] : pad[c];
+        js_save(d, i, js);
     }
     const bool out = valid && l == end;
     double* bp = d.b + 15 * (size_t)d.K + 3 * (size_t)j;
@@ -1796,7 +1813,7 @@ __global__ __launch_bounds__(kFuseBlock) void k_vi_full_prod(VIDev d, double lam
         const int j = valid ? jq : 0, k = valid ? d.qkf[i] : 0;
         const size_t op = 15 * (size_t)d.K + 3 * (size_t)j;
         double jc[4], vx[3];
-        for (int c = 0; c < 4; ++c) jc[c] = d.jsp[js_at(i, c)];
+        js_load(d, i, jc);
         for (int c = 0; c < 3; ++c) vx[c] = p(op + c);
         const int jprev = __shfl_up(jq, 1, 64);
         const bool start = !valid || l == 0 || jprev != jq;
@@ -2648,7 +2665,10 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         !B.up(&pv, (const double*)nullptr, (size_t)n) || !B.up(&q, (const double*)nullptr, (size_t)n) ||
         !B.up(&xb, (const double*)nullptr, (size_t)n) || !B.up(&p2, (const double*)nullptr, schur ? 15 * (size_t)K : (size_t)n))
         return GBA_ERR_OOM;
-    if (!schur && !B.up(&d.jsp, (const double*)nullptr, 4 * (size_t)Mp + 1)) return GBA_ERR_OOM;
+    if (!schur) {
+        d.w32 = f32 ? 1 : 0;
+        if (!B.up(&d.jsp, (const double*)nullptr, 4 * (size_t)Mp + 1)) return GBA_ERR_OOM;
+    }
     double* zb = nullptr;   // Schur form: the point vector of a product
     if (schur) {
         // W in FP32 takes half the doubles of FP64 (rounded up)
