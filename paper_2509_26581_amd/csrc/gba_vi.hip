@@ -1622,41 +1622,69 @@ __device__ __forceinline__ double vi_s_total(double u, double v) {
     return u + (lane_id() < 6 ? v : 0.0);
 }
 
-// p(kk, c): entry c of keyframe kk's part, read from memory by one lane each
-// and shared through buf (128 doubles of LDS of this wavefront).
-template <typename P>
-__device__ __forceinline__ double vi_s_rows(const VIDev& d, int k, const P& p, double* buf) {
-    const int l = lane_id(), part = l >> 4, row = l & 15;
-    const int n0 = d.nrow[k], n1 = d.nrow[k + 1];
-    int kk;
-    const double* M = vi_s_block(d, k, part, kk);
-    double m[15];
-#pragma unroll
-    for (int c = 0; c < 15; ++c) m[c] = M[15 * c + min(row, 14)];
-    buf[l] = kk >= 0 && row < 15 ? p(kk, row) : 0.0;
-    const int s = l >> 3, r = l & 7;
-    double v = 0.0;
-    for (int i0 = n0; i0 < n1; i0 += 8) {   // uniform
+// The row's operands that do not depend on the decision (requested before it):
+// the dense blocks, the parts' entries of z and p_old (one lane each), and the
+// first eight neighbours' blocks and entries.
+struct VISRow {
+    double m[15], za, pa, zn, pn;
+    double2 b0, b1, b2;
+    int n0, n1;
+    __device__ __forceinline__ void neighbour(const VIDev& d, const double* __restrict__ z,
+                                              const double* __restrict__ p_old, int i0) {
+        const int s = lane_id() >> 3, r = lane_id() & 7;
         const bool nb = i0 + s < n1 && r < 6;
         const int i = nb ? i0 + s : n0;
-        const double2* B = (const double2*)(d.vblk + 36 * (size_t)i + 6 * min(r, 5));
-        const double2 b0 = B[0], b1 = B[1], b2 = B[2];
-        __builtin_amdgcn_wave_barrier();
-        buf[64 + l] = nb ? p(d.ncol[i], r) : 0.0;
+        zn = pn = 0.0;
+        if (n0 < n1) {   // uniform
+            const double2* B = (const double2*)(d.vblk + 36 * (size_t)i + 6 * min(r, 5));
+            b0 = B[0];
+            b1 = B[1];
+            b2 = B[2];
+            const size_t e = 15 * (size_t)d.ncol[i] + min(r, 5);
+            zn = nb ? z[e] : 0.0;
+            pn = nb ? p_old[e] : 0.0;
+        }
+    }
+    __device__ __forceinline__ void load(const VIDev& d, int k, const double* __restrict__ z,
+                                         const double* __restrict__ p_old) {
+        const int l = lane_id(), part = l >> 4, row = l & 15;
+        n0 = d.nrow[k];
+        n1 = d.nrow[k + 1];
+        int kk;
+        const double* M = vi_s_block(d, k, part, kk);
+#pragma unroll
+        for (int c = 0; c < 15; ++c) m[c] = M[15 * c + min(row, 14)];
+        const bool in = kk >= 0 && row < 15;
+        za = in ? z[15 * (size_t)kk + row] : 0.0;
+        pa = in ? p_old[15 * (size_t)kk + row] : 0.0;
+        neighbour(d, z, p_old, n0);
+    }
+    // row r < 15 of S (z + beta p_old) in lane r; buf: 128 doubles of LDS of
+    // this wavefront
+    __device__ __forceinline__ double product(const VIDev& d, const double* __restrict__ z,
+                                              const double* __restrict__ p_old, double beta, double* buf) {
+        const int l = lane_id(), part = l >> 4, s = l >> 3, r = l & 7;
+        buf[l] = za + beta * pa;
+        double v = 0.0;
+        for (int i0 = n0; i0 < n1; i0 += 8) {   // uniform
+            if (i0 > n0) neighbour(d, z, p_old, i0);
+            __builtin_amdgcn_wave_barrier();
+            buf[64 + l] = zn + beta * pn;
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            const double* ps = buf + 64 + 8 * s;
+            const double t = b0.x * ps[0] + b0.y * ps[1] + b1.x * ps[2] + b1.y * ps[3] + b2.x * ps[4] + b2.y * ps[5];
+            v += i0 + s < n1 && r < 6 ? t : 0.0;
+        }
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        const double* ps = buf + 64 + 8 * s;
-        const double t = b0.x * ps[0] + b0.y * ps[1] + b1.x * ps[2] + b1.y * ps[3] + b2.x * ps[4] + b2.y * ps[5];
-        v += nb ? t : 0.0;
-    }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    double u = 0.0;
-    const double* ps = buf + 16 * part;
+        double u = 0.0;
+        const double* ps = buf + 16 * part;
 #pragma unroll
-    for (int c = 0; c < 15; ++c) u += m[c] * ps[c];
-    return vi_s_total(u, v);
-}
+        for (int c = 0; c < 15; ++c) u += m[c] * ps[c];
+        return vi_s_total(u, v);
+    }
+};
 
 // The decisions about the PCG step before this one (k_vi_pcg_dir's rules, from
 // slot prev_slot), taken alike by every workgroup and recorded by `lead`:
@@ -1714,12 +1742,20 @@ __global__ __launch_bounds__(256) void k_vi_s_prod(VIDev d, double* __restrict__
     __shared__ double red[16];
     __shared__ double sums[2];
     __shared__ double buf[4][128];
-    if (ps[kDone] != 0.0) return;   // set by the update kernel only
-    const int l = lane_id(), w = (int)threadIdx.x >> 6;
+    const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int k = (int)blockIdx.x * 4 + w;
     const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
     const size_t own = 15 * (size_t)k + l;
     const bool mine = k < d.K && l < 15;
+    // (the rows are requested before the decision's two dependent sums)
+    VISRow rows;
+    double zo = 0.0, po = 0.0;
+    if (k < d.K && !last) {
+        rows.load(d, k, z, p_old);
+        zo = mine ? z[own] : 0.0;
+        po = mine ? p_old[own] : 0.0;
+    }
+    if (ps[kDone] != 0.0) return;   // set by the update kernel only
     double beta = 0.0;
     if (!first) {
         const bool go = vi_pcg_go_on(ps, prev_slot, lead, red, sums, [&] { if (mine) xb[own] = x[own]; },
@@ -1728,10 +1764,9 @@ __global__ __launch_bounds__(256) void k_vi_s_prod(VIDev d, double* __restrict__
     }
     double pq = 0.0;
     if (k < d.K) {   // whole wavefronts
-        auto p = [&](int kk, int c) { return z[15 * (size_t)kk + c] + beta * p_old[15 * (size_t)kk + c]; };
-        const double qv = vi_s_rows(d, k, p, buf[w]);
+        const double qv = rows.product(d, z, p_old, beta, buf[w]);
         if (mine) {
-            const double pv = p(k, l);
+            const double pv = zo + beta * po;
             p_new[own] = pv;
             q[own] = qv;
             pq = pv * qv;
@@ -1755,6 +1790,23 @@ __global__ __launch_bounds__(256) void k_vi_s_update(VIDev d, int full, double* 
     __shared__ double rs[256];
     __shared__ double red[16];
     __shared__ double pq_s;
+    const long long kf_blocks = (d.K + 15) / 16;
+    const bool pts = blockIdx.x >= kf_blocks;
+    const int t = (int)threadIdx.x, sub = pts ? t / 3 : t >> 4, row = pts ? t - 3 * sub : t & 15;
+    const long long k = pts ? (blockIdx.x - kf_blocks) * (long long)kUpdPts + sub : blockIdx.x * 16LL + sub;
+    const bool act = pts ? sub < kUpdPts && k < d.N : k < d.K && row < 15;
+    const size_t i = pts ? 15 * (size_t)d.K + 3 * (size_t)k + row : 15 * (size_t)k + row;
+    // (requested before the sum of p.q)
+    double xi = 0.0, pi = 0.0, qi = 0.0, ri = 0.0, m[15];
+    if (act) {
+        xi = x[i];
+        pi = p[i];
+        qi = q[i];
+        ri = r[i];
+        const double* M = pts ? d.mp + 9 * (size_t)k + 3 * row : d.mki + 225 * (size_t)k + 15 * row;
+#pragma unroll
+        for (int c = 0; c < 15; ++c) m[c] = c < 3 || !pts ? M[c] : 0.0;
+    }
     if (ps[kDone] != 0.0) return;
     double* acc = ps + kAccN * slot;
     if (ps[kAccN * prev_slot + kAccStop] != 0.0) {
@@ -1763,12 +1815,6 @@ __global__ __launch_bounds__(256) void k_vi_s_update(VIDev d, int full, double* 
     }
     if (blockIdx.x == 0)
         for (int e = threadIdx.x; e < kAccN; e += blockDim.x) ps[kAccN * ((slot + 1) % kSlots) + e] = 0.0;
-    const long long kf_blocks = (d.K + 15) / 16;
-    const bool pts = blockIdx.x >= kf_blocks;
-    const int t = (int)threadIdx.x, sub = pts ? t / 3 : t >> 4, row = pts ? t - 3 * sub : t & 15;
-    const long long k = pts ? (blockIdx.x - kf_blocks) * (long long)kUpdPts + sub : blockIdx.x * 16LL + sub;
-    const bool act = pts ? sub < kUpdPts && k < d.N : k < d.K && row < 15;
-    const size_t i = pts ? 15 * (size_t)d.K + 3 * (size_t)k + row : 15 * (size_t)k + row;
     const double part = block_sum_vi(threadIdx.x < kPqParts ? acc[kAccPq + threadIdx.x] : 0.0, red);
     if (threadIdx.x == 0) pq_s = part;
     __syncthreads();
@@ -1780,8 +1826,8 @@ __global__ __launch_bounds__(256) void k_vi_s_update(VIDev d, int full, double* 
     const double alpha = ps[kAccN * prev_slot + kAccRz] / pq;
     double rr = 0.0, rz = 0.0, rn = 0.0;
     if (act) {
-        x[i] += alpha * p[i];
-        rn = r[i] - alpha * q[i];
+        x[i] = xi + alpha * pi;
+        rn = ri - alpha * qi;
         r[i] = rn;
         if (full) q[i] = 0.0;
     }
@@ -1789,15 +1835,12 @@ __global__ __launch_bounds__(256) void k_vi_s_update(VIDev d, int full, double* 
     __syncthreads();
     if (act) {
         double u = 0.0;
+        const double* rk = rs + (pts ? 3 : 16) * sub;
         if (pts) {
-            const double* M = d.mp + 9 * (size_t)k + 3 * row;
-            const double* rk = rs + 3 * sub;
-            u = M[0] * rk[0] + M[1] * rk[1] + M[2] * rk[2];
+            u = m[0] * rk[0] + m[1] * rk[1] + m[2] * rk[2];
         } else {
-            const double* Mi = d.mki + 225 * (size_t)k + 15 * row;
-            const double* rk = rs + 16 * sub;
 #pragma unroll
-            for (int c = 0; c < 15; ++c) u += Mi[c] * rk[c];
+            for (int c = 0; c < 15; ++c) u += m[c] * rk[c];
         }
         z[i] = u;
         rr = rn * rn;
@@ -1991,10 +2034,11 @@ __global__ __launch_bounds__(kFuseBlock) void k_vi_full_prod(VIDev d, double lam
 // keyframe), the direction and the visual blocks in LDS (their upper half: at
 // most 496 of 288 bytes, read along rows or columns); three barriers an
 // iteration.  Rules and arithmetic as the two kernels above; r, z from the
-// start kernels, x out.  Bound by instruction issue (two wavefronts a SIMD,
-// about 1,000 vector instructions each an iteration): 3.2 us at 31 keyframes;
-// 4.5 with the visual blocks requested from the L2, 14 as three launches of
-// the implicit product (5 steps of 200 iterations: the solve from 19.0 to 5.1 ms).
+// start kernels, x out.  Bound by the iteration's chain of sums, divisions and
+// barriers: 3.2 us at 31 keyframes (reading each pair's block once for both
+// rows, or taking the direction by DPP instead of from LDS, left it there); 4.5
+// with the visual blocks requested from the L2, 14 as three launches of the
+// implicit product (5 steps of 200 iterations: the solve from 19.0 to 5.1 ms).
 constexpr int kOneKf = 32;
 constexpr int kOneBlock = 512;
 __global__ __launch_bounds__(kOneBlock) void k_vi_s_pcg_one(VIDev d, double* __restrict__ ps,
@@ -2453,6 +2497,38 @@ struct DevBufs {
     }
 };
 
+// A recorded run of PCG steps of one solve (its stream is only captured on).
+struct StepGraph {
+    hipStream_t stream = nullptr;
+    hipGraphExec_t exec = nullptr;
+    bool failed = false;   // steps are then launched one by one
+    StepGraph() = default;
+    StepGraph(const StepGraph&) = delete;
+    StepGraph& operator=(const StepGraph&) = delete;
+    ~StepGraph() {
+        if (exec) (void)hipGraphExecDestroy(exec);
+        if (stream) (void)hipStreamDestroy(stream);
+    }
+    template <typename Launch>
+    bool record(const Launch& launch) {
+        hipGraph_t graph = nullptr;
+        bool ok = hipStreamCreateWithFlags(&stream, hipStreamNonBlocking) == hipSuccess &&
+                  hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
+        if (ok) {
+            launch(stream);
+            ok = hipStreamEndCapture(stream, &graph) == hipSuccess && graph &&
+                 hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) == hipSuccess;
+        }
+        if (graph) (void)hipGraphDestroy(graph);
+        if (!ok) {
+            exec = nullptr;
+            failed = true;
+            (void)hipGetLastError();
+        }
+        return ok;
+    }
+};
+
 }  // namespace
 
 extern "C" {
@@ -2879,6 +2955,15 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         }
         return true;
     };
+    // Two launches a step take the host about 12 us, more than the kernels of a
+    // short trajectory: after the first steps of a solve the Schur form replays
+    // kGraphSteps steps as one graph.  The slots and the direction buffers of a
+    // step repeat every six, so one recording from a multiple of six serves all.
+    // (33 keyframes, 1,000 steps: 14.9 to 13.8 ms with the kernels' operands
+    // requested ahead of their sums.)
+    constexpr int kGraphSteps = 12, kGraphAfter = 24;
+    static_assert(kGraphSteps % (2 * kSlots) == 0 && kGraphAfter % (2 * kSlots) == 0, "whole periods");
+    StepGraph graph;
     const dim3 full_grid((unsigned)((Mp + kFuseBlock - 1) / kFuseBlock + (K + 6) / 8 + (n + kFuseBlock - 1) / kFuseBlock));
     const double ratio2 = (o.pcg_rejection_ratio > 0.0 && std::isfinite(o.pcg_rejection_ratio))
                               ? o.pcg_rejection_ratio * o.pcg_rejection_ratio : 0.0;
@@ -2923,10 +3008,10 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
             // the step before, and the update
             const dim3 ug((unsigned)((K + 15) / 16 + (npt + kUpdPts - 1) / kUpdPts));
             double* dir[2] = {pv, p2};
-            auto prod = [&](int it, bool last) {
+            auto prod = [&](int it, bool last, hipStream_t on = nullptr) {
                 const int slot = it % kSlots, prev = (it + kSlots - 1) % kSlots;
                 if (schur)
-                    hipLaunchKernelGGL(k_vi_s_prod, dim3((unsigned)((K + 3) / 4)), blk, 0, nullptr, d, ps, slot, prev,
+                    hipLaunchKernelGGL(k_vi_s_prod, dim3((unsigned)((K + 3) / 4)), blk, 0, on, d, ps, slot, prev,
                                        it == 0 ? 1 : 0, last ? 1 : 0, (const double*)z,
                                        (const double*)dir[(it + 1) & 1], dir[it & 1], q, x, xb);
                 else
@@ -2935,16 +3020,34 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
                                        (const double*)z, (const double*)dir[(it + 1) & 1], dir[it & 1], q, x, xb,
                                        (double*)nullptr);
             };
-            int it = 0;
-            for (; it < o.pcg_max_iters; ++it) {
-                prod(it, false);
-                hipLaunchKernelGGL(k_vi_s_update, ug, blk, 0, nullptr, d, schur ? 0 : 1, ps, it % kSlots,
+            auto step = [&](int it, hipStream_t on) {
+                prod(it, false, on);
+                hipLaunchKernelGGL(k_vi_s_update, ug, blk, 0, on, d, schur ? 0 : 1, ps, it % kSlots,
                                    (it + kSlots - 1) % kSlots, (const double*)dir[it & 1], q, x, r, z);
+            };
+            int it = 0;
+            while (it < o.pcg_max_iters) {
+                const bool whole = schur && it > 0 && it % (2 * kSlots) == 0 && it + kGraphSteps <= o.pcg_max_iters;
+                if (whole && !graph.exec && !graph.failed && it >= kGraphAfter)
+                    graph.record([&](hipStream_t on) {
+                        for (int k = 0; k < kGraphSteps; ++k) step(2 * kSlots + k, on);
+                    });
                 bool done = false;
-                if (!sync(it, done)) return false;
+                if (whole && graph.exec) {
+                    if (err == hipSuccess) err = hipGraphLaunch(graph.exec, nullptr);
+                    it += kGraphSteps;
+                    if (it >= prev_iters && it < o.pcg_max_iters) {   // (near or past the last solve's count)
+                        if (!chk() || !read_scal(8 + kPcgScalars)) return false;
+                        done = hs[8 + kDone] != 0.0;
+                    }
+                } else {
+                    step(it, nullptr);
+                    if (!sync(it, done)) return false;
+                    it += 1;
+                }
                 if (done) break;
             }
-            if (it == o.pcg_max_iters) prod(it, true);   // the decisions about the last step
+            if (it == o.pcg_max_iters) prod(it, true);   // the decisions about the last step (or none: stopped)
         } else {
             const dim3 dirg((unsigned)std::max(1LL, std::min<long long>(1024, (nn + 255) / 256)));
             for (int it = 0; it < o.pcg_max_iters; ++it) {

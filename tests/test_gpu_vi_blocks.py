@@ -136,3 +136,24 @@ def test_vi_order_is_independent_of_the_input_order():
     assert abs(r0["initial_cost"] - r1["initial_cost"]) <= 1e-12 * r0["initial_cost"]
     assert abs(l0[0]["candidate_cost"] - l1[0]["candidate_cost"]) <= 1e-9 * l0[0]["candidate_cost"]
     assert abs(l0[0]["step_norm"] - l1[0]["step_norm"]) <= 1e-9 * l0[0]["step_norm"]
+
+
+def test_vi_long_pcg_trajectory_matches_the_oracle():
+    # PCG runs long enough to be replayed as recorded steps, over trials that
+    # reuse the recording
+    from oracle import lm
+    prob, x0, run = _problem(33, 150, 53, 3)
+    res = lm.levenberg_marquardt(prob, x0, 3)
+    _, X, rep, log = run(3, pcg_tol=1e-12, pcg_max_iters=4000)
+    assert min(t["pcg_iters"] for t in log) > 36
+    for a, b in zip(log, res.log):
+        assert a["accepted"] == b["accepted"]
+        assert abs(a["cost"] - b["cost"]) <= 1e-8 * b["cost"], (a, b)
+    assert abs(rep["final_cost"] - res.cost) <= 1e-8 * res.cost
+
+
+@pytest.mark.parametrize("limit", [24, 35, 36, 47, 60])
+def test_vi_iteration_limit_is_exact(limit):
+    _, _, run = _problem(33, 150, 53, 3)
+    _, _, _, log = run(2, pcg_tol=0.0, pcg_max_iters=limit)
+    assert [t["pcg_iters"] for t in log] == [limit, limit]
