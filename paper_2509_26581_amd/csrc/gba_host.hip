@@ -401,9 +401,16 @@ gba_status plan_union(const std::vector<const ImageCounts*>& probs, const Tuning
     // automatic: one point-pass workgroup per CU (each flushes one LDS camera
     // partial; the flush grows with the workgroup count, and smaller
     // workgroups measured slower in both schemes)
+    // A workgroup of the Schur passes gets at least 16 tiles; the whole-system
+    // products, with more work per edge (and a Jacobian to recompute when it is
+    // dynamic), spread to four: a wavefront per SIMD on four times the CUs.
+    // Whole solves in FP64 at 16 and at 4 tiles: dynamic 13.3 and 11.4 ms at 120
+    // cameras and 1,000 tiles, 8.7 and 7.0 at 20 and 170; stored 11.0 and 10.5,
+    // and 9.3 and 8.7 at 60 cameras.  Two tiles: 16.2, 6.8; 14.0, 11.5 ms.
+    const long long least = u.full ? 4 : 16;
     const long long tpb = tune.tiles_per_block > 0
                               ? tune.tiles_per_block
-                              : std::max<long long>(16, (st + dev.n_cu - 1) / std::max(1, dev.n_cu));
+                              : std::max<long long>(least, (st + dev.n_cu - 1) / std::max(1, dev.n_cu));
     const long long epb = tune.edges_per_block > 0 ? tune.edges_per_block
                                                    : std::max<long long>(256, (se + 2047) / 2048);
     const long long ppb = tune.pts_per_block > 0 ? tune.pts_per_block
