@@ -261,17 +261,18 @@ bool reduced_rule(const ImageCounts& n, const Tuning& tune) {
 
 // The same for a single larger problem, whose launched PCG iterations then
 // multiply by S instead of taking the point pass and its reduction.  Whole
-// solves (10 trials of about 38 iterations, FP32 and FP64) against the point
-// passes: 1.6 and 1.7 times as fast at 60 and 90 cameras, 1.5 and 1.4 at 203,
-// 1.26 and 1.07 at 320 (35 and 70 MB of S), 0.85-1.14 at 440 in FP32: S is read
-// in every iteration, so it is bounded to 40 MB.  Forming it takes about 60 ps
-// (FP32) and 160 ps (FP64) a pair of a point's edges and step (FP64, 260
-// cameras, 2M pairs: 0.32 ms, and no gain left), so the pairs are too.
+// solves (8 trials of about 35 iterations, mixed FP32 and FP64) against the
+// point passes: 1.5 and 1.6 times as fast at 60 and 90 cameras, 1.4 and 1.5 at
+// 130, 1.3 and 1.4 at 203, 1.13 and 1.2 at 240, 0.95 and 0.98 at 300: S is read
+// in every iteration, FP64 in every mode, so it is bounded to 40 MB (248
+// cameras).  Forming it takes about 60 ps (mixed) and 120 ps (FP64) a pair of a
+// point's edges and step (FP64, 260 cameras, 2M pairs: no gain left), so the
+// pairs are bounded too.
 bool reduced_wide_rule(const ImageCounts& n, const Tuning& tune, int precision) {
     if (tune.accumulation != GBA_ACC_AUTO || tune.deterministic || tune.solver == GBA_SOLVER_FULL) return false;
     if (n.nc <= 0 || n.ne <= 0 || n.n_runs != n.ne || 9 * n.nc <= kReducedMax) return false;
     const long long word = precision == GBA_FP64 ? 8 : 4;
-    return 9LL * n.nc * reduced_ld(9 * n.nc) * word <= 40'000'000 && n.pairs * word <= 12'000'000;
+    return 9LL * n.nc * reduced_ld(9 * n.nc) * (long long)sizeof(double) <= 40'000'000 && n.pairs * word <= 12'000'000;
 }
 
 namespace {
@@ -557,7 +558,7 @@ size_t layout_union(const UnionPlan& u, int precision, void* base, DeviceGraph* 
         L.add(d.xs_off, sizeof(long long) * P);
         L.add(d.xs_rank_off, sizeof(long long) * P);
         L.add(d.prob_pt_off, sizeof(int) * (P + 1));
-        L.add(d.xs_S, tsz * (size_t)u.xs_total);
+        L.add(d.xs_S, sizeof(double) * (size_t)u.xs_total);
         L.add(d.xs_diag, sizeof(double) * 45 * NC);
         L.add(d.xs_rank, sizeof(RankWord) * (size_t)u.xs_rank_total);
         if (u.xs_wide) {

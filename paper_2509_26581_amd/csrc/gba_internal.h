@@ -250,7 +250,7 @@ struct DeviceGraph {
     const long long* xs_off;       // [P] offset of S in xs_S (entries), negative: products stay implicit
     const long long* xs_rank_off;  // [P] offset of the rank bitmaps in xs_rank
     const int* prob_pt_off;        // [P + 1] point range of each problem
-    void* xs_S;               // per problem a dense symmetric matrix, columns of reduced_ld(9 nc_p)
+    double* xs_S;             // per problem a dense symmetric matrix, columns of reduced_ld(9 nc_p)
     double* xs_diag;          // [nc][45] diagonal blocks of S (zero in xs_S)
     RankWord* xs_rank;        // per problem [nc_p][rank_words(np_p)]
     // xs_wide: the common points of every camera pair i < k, by i nc + k:

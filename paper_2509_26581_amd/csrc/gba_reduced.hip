@@ -78,44 +78,52 @@ __global__ __launch_bounds__(64) void k_rank_base(DeviceGraph g) {
 // every lane of the arithmetic holds a common point; per match it reads both
 // edges' stored Jacobians (camera-major copy) and the point's inverse block,
 // and keeps the block's sums in registers: no atomics, and an order that
-// depends on the problem alone.  Bound by the gathers of the two Jacobians
-// (192 B a match in FP32, mostly from the L2).  The diagonal blocks come with
-// the preconditioner (k_cam_finalize).
+// depends on the problem alone.  Terms, sums and S are FP64 in the mixed modes
+// too, as the launched products' camera sums are.  Bound by the gathers of the
+// two Jacobians (192 B a match in FP32, mostly from the L2).  The diagonal
+// blocks come with the preconditioner (k_cam_finalize).
 // ==========================================================================
 
 // rows rb .. rb + kRows - 1 of one match's J_c,i^T (J_p,i Hpp^-1 J_p,k^T) J_c,k
 // added to acc; ea, eb: the camera-major edges of both cameras
 template <typename T, typename JS, int kRows>
-__device__ __forceinline__ void reduced_term(const DeviceGraph& g, int ea, int eb, int rb, T (&acc)[9 * kRows]) {
-    T ja[2][9], pa[2][3], jb[2][9], pb[2][3];
-    jac_load<JS>(g.jst_cm, ea, ja, pa);
-    jac_load<JS>(g.jst_cm, eb, jb, pb);
+__device__ __forceinline__ void reduced_term(const DeviceGraph& g, int ea, int eb, int rb, double (&acc)[9 * kRows]) {
+    T ja[2][9], jb[2][9], pat[2][3], pbt[2][3];
+    jac_load<JS>(g.jst_cm, ea, ja, pat);
+    jac_load<JS>(g.jst_cm, eb, jb, pbt);
     const T* H = (const T*)g.hpp_inv + kHinvStride * (size_t)g.cm_pt[ea];
-    const T h[6] = {H[0], H[1], H[2], H[3], H[4], H[5]};
-    T A[2][2];
+    const double h[6] = {(double)H[0], (double)H[1], (double)H[2], (double)H[3], (double)H[4], (double)H[5]};
+    double A[2][2], pa[2][3], pb[2][3];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            pa[r][c] = (double)pat[r][c];
+            pb[r][c] = (double)pbt[r][c];
+        }
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-        const T t0 = pa[r][0] * h[0] + pa[r][1] * h[1] + pa[r][2] * h[2];
-        const T t1 = pa[r][0] * h[1] + pa[r][1] * h[3] + pa[r][2] * h[4];
-        const T t2 = pa[r][0] * h[2] + pa[r][1] * h[4] + pa[r][2] * h[5];
+        const double t0 = pa[r][0] * h[0] + pa[r][1] * h[1] + pa[r][2] * h[2];
+        const double t1 = pa[r][0] * h[1] + pa[r][1] * h[3] + pa[r][2] * h[4];
+        const double t2 = pa[r][0] * h[2] + pa[r][1] * h[4] + pa[r][2] * h[5];
 #pragma unroll
         for (int c = 0; c < 2; ++c) A[r][c] = t0 * pb[c][0] + t1 * pb[c][1] + t2 * pb[c][2];
     }
-    T m[2][9];
+    double m[2][9];
 #pragma unroll
     for (int c = 0; c < 9; ++c) {
-        m[0][c] = A[0][0] * jb[0][c] + A[0][1] * jb[1][c];
-        m[1][c] = A[1][0] * jb[0][c] + A[1][1] * jb[1][c];
+        m[0][c] = A[0][0] * (double)jb[0][c] + A[0][1] * (double)jb[1][c];
+        m[1][c] = A[1][0] * (double)jb[0][c] + A[1][1] * (double)jb[1][c];
     }
 #pragma unroll
     for (int r = 0; r < kRows; ++r) {
-        T u0, u1;
+        double u0, u1;
         if constexpr (kRows == 9) {
-            u0 = ja[0][r];
-            u1 = ja[1][r];
+            u0 = (double)ja[0][r];
+            u1 = (double)ja[1][r];
         } else {   // rb is uniform
-            u0 = rb == 0 ? ja[0][r] : rb == kRows ? ja[0][kRows + r] : ja[0][2 * kRows + r];
-            u1 = rb == 0 ? ja[1][r] : rb == kRows ? ja[1][kRows + r] : ja[1][2 * kRows + r];
+            u0 = (double)(rb == 0 ? ja[0][r] : rb == kRows ? ja[0][kRows + r] : ja[0][2 * kRows + r]);
+            u1 = (double)(rb == 0 ? ja[1][r] : rb == kRows ? ja[1][kRows + r] : ja[1][2 * kRows + r]);
         }
 #pragma unroll
         for (int c = 0; c < 9; ++c) acc[9 * r + c] += u0 * m[0][c] + u1 * m[1][c];
@@ -130,22 +138,22 @@ __global__ __launch_bounds__(256) void k_reduced_blocks(DeviceGraph g) {
     if ((sizeof(T) == 8) != (g.mode == kModeFP64) || sizeof(JS) != (size_t)g.jac_bytes) return;
     constexpr int kSums = 9 * kRows, kRegsOut = (kSums + kWave - 1) / kWave;
     __shared__ int qa_s[4][2 * kWave], qb_s[4][2 * kWave];
-    __shared__ T red[4][kRegsOut * kWave];
+    __shared__ double red[4][kRegsOut * kWave];
     const int l = lane_id(), w = (int)threadIdx.x >> 6;
     const int c0 = g.prob_cam_off[prob], nc = g.prob_cam_off[prob + 1] - c0, i = a - c0;
     const int p0 = g.prob_pt_off[prob], nw = rank_words(g.prob_pt_off[prob + 1] - p0);
     const int n = 9 * nc, ld = reduced_ld(n);
     constexpr int kSplit = 9 / kRows;
     const int q0 = cam_edge_begin(g, a), q1 = cam_edge_begin(g, a + 1);
-    T* __restrict__ S = (T*)g.xs_S + off;
+    double* __restrict__ S = g.xs_S + off;
     int* qa = qa_s[w];
     int* qb = qb_s[w];
     for (int t = (int)blockIdx.y; t < (nc - 1 - i) * kSplit; t += (int)gridDim.y) {   // uniform
         const int k = i + 1 + t / kSplit, rb = (t % kSplit) * kRows;
         const RankWord* __restrict__ rank = g.xs_rank + g.xs_rank_off[prob] + (size_t)k * nw;
-        T acc[kSums];
+        double acc[kSums];
 #pragma unroll
-        for (int u = 0; u < kSums; ++u) acc[u] = (T)0;
+        for (int u = 0; u < kSums; ++u) acc[u] = 0.0;
         auto add = [&](int ea, int eb) { reduced_term<T, JS, kRows>(g, ea, eb, rb, acc); };
         int queued = 0;   // uniform per wavefront
         for (int base = q0 + w * kWave; base < q1; base += 4 * kWave) {
@@ -192,7 +200,7 @@ __global__ __launch_bounds__(256) void k_reduced_blocks(DeviceGraph g) {
         for (int v = 0; v < kRegsOut; ++v) red[w][v * kWave + rev6(l)] = acc[v];
         __syncthreads();
         for (int u = (int)threadIdx.x; u < kSums; u += (int)blockDim.x) {
-            const T sum = -((red[0][u] + red[1][u]) + (red[2][u] + red[3][u]));
+            const double sum = -((red[0][u] + red[1][u]) + (red[2][u] + red[3][u]));
             const int row = 9 * i + rb + u / 9, col = 9 * k + u % 9;
             S[(size_t)col * ld + row] = sum;
             S[(size_t)row * ld + col] = sum;
@@ -335,34 +343,35 @@ __global__ __launch_bounds__(256) void k_reduced_pairs(DeviceGraph g) {
         m1 = g.xs_pair_off[at + 1];
     }
     if (__ballot(m0 < m1) == 0) return;   // whole wavefronts
-    T acc[kSums];
+    double acc[kSums];
 #pragma unroll
-    for (int u = 0; u < kSums; ++u) acc[u] = (T)0;
+    for (int u = 0; u < kSums; ++u) acc[u] = 0.0;
     for (int m = m0 + l; m < m1; m += kLanes) {
         const int2 e = g.xs_pairs[m];
         T a[24], b[24];
         edge_record(g, e.x, a);
         edge_record(g, e.y, b);
-        T A[2][2], M[2][9];
+        double A[2][2], M[2][9];
 #pragma unroll
         for (int r = 0; r < 2; ++r)
 #pragma unroll
             for (int c = 0; c < 2; ++c)
-                A[r][c] = a[18 + 3 * r] * b[18 + 3 * c] + a[19 + 3 * r] * b[19 + 3 * c] + a[20 + 3 * r] * b[20 + 3 * c];
+                A[r][c] = (double)a[18 + 3 * r] * (double)b[18 + 3 * c] + (double)a[19 + 3 * r] * (double)b[19 + 3 * c] +
+                          (double)a[20 + 3 * r] * (double)b[20 + 3 * c];
 #pragma unroll
         for (int c = 0; c < 9; ++c) {
-            M[0][c] = A[0][0] * b[c] + A[0][1] * b[9 + c];
-            M[1][c] = A[1][0] * b[c] + A[1][1] * b[9 + c];
+            M[0][c] = A[0][0] * (double)b[c] + A[0][1] * (double)b[9 + c];
+            M[1][c] = A[1][0] * (double)b[c] + A[1][1] * (double)b[9 + c];
         }
 #pragma unroll
         for (int r = 0; r < kRows; ++r) {
-            T u0, u1;
+            double u0, u1;
             if constexpr (kRows == 9) {
-                u0 = a[r];
-                u1 = a[9 + r];
+                u0 = (double)a[r];
+                u1 = (double)a[9 + r];
             } else {   // rb is uniform
-                u0 = rb == 0 ? a[r] : rb == kRows ? a[kRows + r] : a[2 * kRows + r];
-                u1 = rb == 0 ? a[9 + r] : rb == kRows ? a[9 + kRows + r] : a[9 + 2 * kRows + r];
+                u0 = (double)(rb == 0 ? a[r] : rb == kRows ? a[kRows + r] : a[2 * kRows + r]);
+                u1 = (double)(rb == 0 ? a[9 + r] : rb == kRows ? a[9 + kRows + r] : a[9 + 2 * kRows + r]);
             }
 #pragma unroll
             for (int c = 0; c < 9; ++c) acc[9 * r + c] += u0 * M[0][c] + u1 * M[1][c];
@@ -371,7 +380,7 @@ __global__ __launch_bounds__(256) void k_reduced_pairs(DeviceGraph g) {
     group_sum_scatter<kLanes>(acc);   // sum u in lane group_rev(u % kLanes), register u / kLanes
     if (m0 == m1) return;
     const int ld = reduced_ld(9 * g.nc);
-    T* __restrict__ S = (T*)g.xs_S;
+    double* __restrict__ S = g.xs_S;
 #pragma unroll
     for (int v = 0; v < (kSums + kLanes - 1) / kLanes; ++v) {
         const int u = v * kLanes + group_rev<kLanes>(l);
@@ -384,18 +393,20 @@ __global__ __launch_bounds__(256) void k_reduced_pairs(DeviceGraph g) {
 }
 
 // ==========================================================================
-// PCG on the explicit S, one workgroup of 16 wavefronts per problem from the
-// start to the stop.  The product: a wavefront takes 128 rows (two per lane)
-// of one column group and keeps the first kRegs columns of the group in
+// PCG on the explicit S, one workgroup of four or eight wavefronts per problem
+// from the start to the stop.  The product: a wavefront takes 128 rows (two per
+// lane) of one column group and keeps the first kRegs columns of the group in
 // registers (the rest are read from the L2 every iteration); the direction is
 // read from LDS four columns at a time, each value used for two rows, which
 // balances the LDS reads (2 cycles a value and wavefront) with the products.
-// In the mixed modes the off-diagonal blocks and their products are FP32 (as
-// the launched products are), the diagonal blocks and the vectors FP64: a
-// diagonal block rounded to FP32 perturbs the system the same way in every
-// iteration, and a step at tolerance 1e-6 was 1.3 times as far from the exact
-// one as the launched products' (7e-5 against 5e-5 over 12 scenes of 8 to 48
-// cameras); with FP64 diagonals it is nearer (4e-5).
+// S, the products, their sums and the vectors are FP64 in every mode; the
+// mixed modes have FP32 where the launched iterations have it in what goes in
+// and out (right-hand side, preconditioner, solution).  With S and its sums in
+// FP32 a damped step of five cameras with 16,000 common points was four times as
+// far from the FP64 one (5.7e-5 against 1.4e-5 of its norm; launched products:
+// 1.2e-4), and over 120 served requests of 5 to 40 keyframes the points of
+// whole solves were 0.94 times as far from a 64-bit solve as the launched
+// products' (geometric mean) where they are 0.88 times now.
 // The vectors live in the registers of the row owners (63 rows, whole
 // cameras, per wavefront, so that the preconditioner's exchange stays inside
 // a wavefront) and an iteration is three workgroup barriers: direction,
@@ -403,17 +414,15 @@ __global__ __launch_bounds__(256) void k_reduced_pairs(DeviceGraph g) {
 // those of the launched kernels (pcg_decision, apply_body); q = S p is formed
 // directly.  The order of every sum depends on the problem alone.  Bound by
 // the latency of its serial chain (LDS exchanges, cross-lane sums, two FP64
-// divisions): 1.3 us an iteration at 90 rows in FP64 and 2.0 us at 162 rows in
-// FP32, where the launched iteration takes 14.2 us (two kernels).
+// divisions): 1.3 us an iteration at 90 rows, where the launched iteration
+// takes 14.2 us (two kernels).
 // ==========================================================================
 constexpr int kOwnRows = 63;   // rows owned per wavefront
 
 // four columns of the product for the two rows of a lane
-template <typename T>
-__device__ __forceinline__ void fma4(const T* __restrict__ p4, const T* __restrict__ a, const T* __restrict__ b,
-                                     T (&qa)[4], T (&qb)[4]) {
-    using V = typename std::conditional<sizeof(T) == 8, double4, float4>::type;
-    const V v = *(const V*)p4;   // 16-byte aligned: columns start at multiples of four
+__device__ __forceinline__ void fma4(const double* __restrict__ p4, const double* __restrict__ a,
+                                     const double* __restrict__ b, double (&qa)[4], double (&qb)[4]) {
+    const double4 v = *(const double4*)p4;   // 16-byte aligned: columns start at multiples of four
     qa[0] = fma(a[0], v.x, qa[0]);
     qb[0] = fma(b[0], v.x, qb[0]);
     qa[1] = fma(a[1], v.y, qa[1]);
@@ -432,9 +441,9 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
     static_assert(kRegs % 4 == 0 && kWaves <= 16, "columns are taken four at a time");
     constexpr int kG = kWaves / kR, kRows = kR * 2 * kWave;
     constexpr int kOwners = (kRows + kOwnRows - 1) / kOwnRows < kWaves ? (kRows + kOwnRows - 1) / kOwnRows : kWaves;
-    __shared__ __align__(32) T p_s[kRows + kRegs + 4];
+    __shared__ __align__(32) double p_s[kRows + kRegs + 4];
     __shared__ double r_s[kOwners * kWave], x_s[kOwners * kWave];
-    __shared__ T part[kG][kRows];
+    __shared__ double part[kG][kRows];
     __shared__ __align__(16) double red_q[16], red_z[16], red_r[16];
     const int c0 = g.prob_cam_off[prob], n = 9 * (g.prob_cam_off[prob + 1] - c0);
     const int ld = reduced_ld(n);
@@ -447,13 +456,13 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
     // and their sums meet zeros of the direction and no owner
     const int cpg = ((n + kG - 1) / kG + 3) & ~3;
     const int cb = min(grp * cpg, (n + 3) & ~3), ce = grp < kG ? min(n, cb + cpg) : cb;
-    const T* __restrict__ S = (const T*)g.xs_S + g.xs_off[prob];
+    const double* __restrict__ S = g.xs_S + g.xs_off[prob];
     // byte offsets of the lane's rows in a column, whose address is uniform
-    const unsigned o0 = (unsigned)(min(row0, n - 1) * sizeof(T)), o1 = (unsigned)(min(row1, n - 1) * sizeof(T));
+    const unsigned o0 = (unsigned)(min(row0, n - 1) * sizeof(double)), o1 = (unsigned)(min(row1, n - 1) * sizeof(double));
     auto entry = [&](int c, unsigned o) {
-        return *(const T*)((const char*)(S + (size_t)(min(c, n - 1) * ld)) + o);
+        return *(const double*)((const char*)(S + (size_t)(min(c, n - 1) * ld)) + o);
     };
-    T s0[kRegs], s1[kRegs];
+    double s0[kRegs], s1[kRegs];
 #pragma unroll
     for (int u = 0; u < kRegs; u += 4) {
         if (cb + u < ce) {
@@ -467,7 +476,7 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
     const int own = w * kOwnRows + l;
     const bool owner = w < W && l < kOwnRows && own < n;
     const int a9 = l % 9, base9 = tid - a9;
-    T m[9];
+    double m[9];
     double h[9];   // the owner's row of its camera's diagonal block
     double r = 0, p = 0, z = 0;
     T* __restrict__ best = (T*)g.v_best + 9 * (size_t)c0 + own;   // the owner's entry
@@ -479,7 +488,7 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
     if (owner) {
         const T* __restrict__ Minv = (const T*)g.minv + 45 * (size_t)(c0 + own / 9);
 #pragma unroll
-        for (int b = 0; b < 9; ++b) m[b] = Minv[sym9(a9, b)];
+        for (int b = 0; b < 9; ++b) m[b] = (double)Minv[sym9(a9, b)];
         const double* __restrict__ D = g.xs_diag + 45 * (size_t)(c0 + own / 9);
 #pragma unroll
         for (int b = 0; b < 9; ++b) h[b] = D[sym9(a9, b)];
@@ -487,8 +496,8 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
         *best = 0;
     }
     if (w < kOwners) x_s[tid] = 0;
-    for (int k = tid; k < kRows + kRegs + 4; k += kWaves * kWave) p_s[k] = (T)0;
-    if (grp < kG && cb >= ce) part[grp][row0] = part[grp][row1] = (T)0;   // a group without columns
+    for (int k = tid; k < kRows + kRegs + 4; k += kWaves * kWave) p_s[k] = 0.0;
+    if (grp < kG && cb >= ce) part[grp][row0] = part[grp][row1] = 0.0;   // a group without columns
     if (tid < 16) red_q[tid] = red_z[tid] = red_r[tid] = 0.0;
     __syncthreads();
     // sum of the wavefronts' values (of 16, by rotations inside a row of 16
@@ -542,19 +551,18 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
     int done = yes(g.lam[prob] < 0.0) ? 5 : (yes(rr <= thresh || !(rz > 0.0)) ? 1 : 0);
     while (!done) {
         p = iters ? fma(beta, p, z) : z;
-        p = (double)(T)p;   // the direction as the product reads it
-        if (owner) p_s[own] = (T)p;
+        if (owner) p_s[own] = p;
         __syncthreads();
         double pq_part = 0.0;
         if (cb < ce) {
-            const T p0 = p_s[row0], p1 = p_s[row1];
-            T qa[4] = {0, 0, 0, 0}, qb[4] = {0, 0, 0, 0};
+            const double p0 = p_s[row0], p1 = p_s[row1];
+            double qa[4] = {0, 0, 0, 0}, qb[4] = {0, 0, 0, 0};
 #pragma unroll
             for (int u = 0; u < kRegs; u += 4)
                 if (cb + u < ce) fma4(p_s + cb + u, s0 + u, s1 + u, qa, qb);   // uniform per wavefront
 #pragma unroll 1
             for (int c = cb + kRegs; kStream && c < ce; c += 4) {
-                T a[4], b[4];
+                double a[4], b[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     a[u] = entry(c + u, o0);
@@ -562,17 +570,17 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
                 }
                 fma4(p_s + c, a, b, qa, qb);
             }
-            const T ta = (qa[0] + qa[1]) + (qa[2] + qa[3]), tb = (qb[0] + qb[1]) + (qb[2] + qb[3]);
+            const double ta = (qa[0] + qa[1]) + (qa[2] + qa[3]), tb = (qb[0] + qb[1]) + (qb[2] + qb[3]);
             part[grp][row0] = ta;
             part[grp][row1] = tb;
             // p^T q from the partial products
-            pq_part = (double)p0 * (double)ta + (double)p1 * (double)tb;
+            pq_part = p0 * ta + p1 * tb;
         }
         double q = 0;
         if (w < W && owner) {
             const int b0 = own - a9;
 #pragma unroll
-            for (int b = 0; b < 9; ++b) q += h[b] * (double)p_s[b0 + b];
+            for (int b = 0; b < 9; ++b) q += h[b] * p_s[b0 + b];
             pq_part += p * q;
         }
         {
@@ -581,11 +589,11 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
         }
         __syncthreads();
         if (w < W) {
-            T t[kG];
+            double t[kG];
 #pragma unroll
             for (int k = 0; k < kG; ++k) t[k] = part[k][min(own, kRows - 1)];
 #pragma unroll
-            for (int k = 0; k < kG; ++k) q += (double)t[k];
+            for (int k = 0; k < kG; ++k) q += t[k];
         }
         const double pq = sum_waves(red_q);
         if (yes(!(pq > 0.0 && isfinite(pq)))) {   // breakdown: x stays the last iterate
@@ -637,32 +645,23 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
 
 // A problem's class follows its own size: up to 128 rows four wavefronts
 // (one per SIMD: the scalar steps between the products, which every wavefront
-// repeats, then issue once per SIMD), up to 256 rows in FP32 twelve with every
-// column in registers, above that twelve (FP64: eight, with twice the
-// registers) with the rest of the columns streamed from the L2.  kBig: the
-// batch holds a problem above the first class.
-template <typename T>
-constexpr int big_waves() { return sizeof(T) == 8 ? 8 : 12; }
+// repeats, then issue once per SIMD), above that eight with what the registers
+// do not hold of the columns streamed from the L2.  kBig: the batch holds a
+// problem above the first class.
+constexpr int kBigWaves = 8;
 
 template <typename T, bool kBig>
-__global__ __launch_bounds__(kBig ? big_waves<T>() * kWave : 4 * kWave) void k_pcg_reduced(DeviceGraph g,
-                                                                                          double tol,
-                                                                                          int relative) {
+__global__ __launch_bounds__(kBig ? kBigWaves * kWave : 4 * kWave) void k_pcg_reduced(DeviceGraph g, double tol,
+                                                                                     int relative) {
     const int prob = blockIdx.x;
     if (g.xs_off[prob] < 0 || (sizeof(T) == 8) != (g.mode == kModeFP64)) return;
     const int n = 9 * (g.prob_cam_off[prob + 1] - g.prob_cam_off[prob]);
-    constexpr bool kF64 = sizeof(T) == 8;
     if (n <= 2 * kWave) {
         if (kBig && threadIdx.x >= 4 * kWave) return;
         pcg_reduced_body<T, 4, 1, 32, false>(g, prob, tol, relative);
     } else if constexpr (kBig) {
-        constexpr int kW = big_waves<T>();
-        if (n <= 4 * kWave)
-            pcg_reduced_body<T, kW, 2, kF64 ? 24 : 40, true>(g, prob, tol, relative);
-        else if (n <= 6 * kWave)
-            pcg_reduced_body<T, kW, kF64 ? 4 : 3, kF64 ? 24 : 36, true>(g, prob, tol, relative);
-        else
-            pcg_reduced_body<T, kW, 4, kF64 ? 24 : 36, true>(g, prob, tol, relative);
+        if (n <= 4 * kWave) pcg_reduced_body<T, kBigWaves, 2, 24, true>(g, prob, tol, relative);
+        else pcg_reduced_body<T, kBigWaves, 4, 24, true>(g, prob, tol, relative);
     }
 }
 
@@ -718,9 +717,9 @@ __global__ __launch_bounds__(kReducedProductBlock) void k_reduced_product(Device
         if (l == 0) g.pq_partial[blockIdx.x] = dot;
         return;
     }
-    constexpr int kV = 16 / (int)sizeof(T);
-    typedef T V __attribute__((ext_vector_type(16 / sizeof(T))));
-    const T* __restrict__ S = (const T*)g.xs_S + g.xs_off[0];
+    constexpr int kV = 2;
+    typedef double V __attribute__((ext_vector_type(kV)));
+    const double* __restrict__ S = g.xs_S + g.xs_off[0];
     double acc[kReducedRows];
 #pragma unroll
     for (int u = 0; u < kReducedRows; ++u) acc[u] = 0.0;
@@ -735,7 +734,7 @@ __global__ __launch_bounds__(kReducedProductBlock) void k_reduced_product(Device
                 const bool in = c + v < n;
                 const double zv = in ? (double)z[c + v] : 0.0;
 #pragma unroll
-                for (int u = 0; u < kReducedRows; ++u) acc[u] += (in ? (double)s[u][v] : 0.0) * zv;
+                for (int u = 0; u < kReducedRows; ++u) acc[u] += (in ? s[u][v] : 0.0) * zv;
             }
         }
     }
@@ -759,8 +758,7 @@ hipError_t launch_reduced_build(const DeviceGraph& g, size_t rank_total, size_t 
         hipLaunchKernelGGL(k_pair_lists<false>, grid, dim3(256), 0, s, g);
         hipLaunchKernelGGL(k_pair_scan, dim3(1), dim3(1024), 0, s, g);
         hipLaunchKernelGGL(k_pair_lists<true>, grid, dim3(256), 0, s, g);
-        const hipError_t e = launch_fill_f64((double*)g.xs_S, 0.0, s_total * (g.mode == kModeFP64 ? 1 : 0) +
-                                             (g.mode == kModeFP64 ? 0 : s_total / 2), s);
+        const hipError_t e = launch_fill_f64(g.xs_S, 0.0, s_total, s);
         if (e != hipSuccess) return e;
     }
     return hipGetLastError();
@@ -815,7 +813,7 @@ hipError_t launch_pcg_reduced(const DeviceGraph& g0, hipStream_t s, double tol, 
     g.pcg_max_iters = max_iters;
     g.pcg_ratio = ratio;
     const bool big = 9 * g.xs_cams > 2 * kWave;
-    const dim3 grid(g.n_probs), block(!big ? 256 : g.mode == kModeFP64 ? 64 * big_waves<double>() : 64 * big_waves<float>());
+    const dim3 grid(g.n_probs), block(!big ? 256 : 64 * kBigWaves);
     if (g.mode == kModeFP64) {
         if (big) hipLaunchKernelGGL((k_pcg_reduced<double, true>), grid, block, 0, s, g, tol, relative);
         else hipLaunchKernelGGL((k_pcg_reduced<double, false>), grid, block, 0, s, g, tol, relative);
