@@ -564,7 +564,7 @@ size_t layout_union(const UnionPlan& u, int precision, void* base, DeviceGraph* 
         if (u.xs_wide) {
             L.add(d.xs_pair_off, sizeof(int) * (NC * NC + 1));
             L.add(d.xs_pairs, sizeof(int2) * (size_t)u.xs_pairs);
-            L.add(d.xs_edge, tsz * 24 * NE);
+            L.add(d.xs_edge, tsz * kEdgeRec * NE);
         }
     } else if (dptr) {
         d.xs_off = d.xs_rank_off = nullptr;

@@ -46,6 +46,17 @@ __host__ __device__ constexpr int sym3(int r, int c) {
 // 16-wavefront workgroup), columns padded to whole wavefronts.
 constexpr int kReducedMax = 512;
 __host__ __device__ constexpr int reduced_ld(int n) { return (n + kWave - 1) / kWave * kWave; }
+constexpr int kEdgeRec = 32;   // entries of an edge's record (DeviceGraph::xs_edge)
+// out = J_p Hpp^-1 (2 x 3); h: the inverse's upper triangle (00 01 02 11 12 22)
+template <typename T>
+__host__ __device__ inline void point_side(const T (&jp)[2][3], const T* h, T* out) {
+    for (int r = 0; r < 2; ++r) {
+        const double a = (double)jp[r][0], b = (double)jp[r][1], c = (double)jp[r][2];
+        out[3 * r] = (T)(a * (double)h[0] + b * (double)h[1] + c * (double)h[2]);
+        out[3 * r + 1] = (T)(a * (double)h[1] + b * (double)h[3] + c * (double)h[4]);
+        out[3 * r + 2] = (T)(a * (double)h[2] + b * (double)h[4] + c * (double)h[5]);
+    }
+}
 // One word of a camera's rank bitmap: the observed points among 64
 // consecutive ones, and the camera-major edge of the first of them.
 struct RankWord {
@@ -257,8 +268,8 @@ struct DeviceGraph {
     // camera-major edges of both, in point order
     int* xs_pair_off;         // [nc nc + 1]
     int2* xs_pairs;
-    void* xs_edge;            // [ne][24] per camera-major edge J_c (2 x 9) and J_p L (2 x 3),
-                              // L L^T = Hpp^-1, vector type
+    void* xs_edge;            // [ne][kEdgeRec] per camera-major edge J_p Hpp^-1 (2 x 3), two pads,
+                              // J_c (2 x 9), J_p (2 x 3), vector type
     long long xs_pair_total;
     void* w_x;                // [np][3] point parts of the PCG vectors (vector type)
     void* w_r;

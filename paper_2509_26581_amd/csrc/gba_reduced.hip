@@ -271,11 +271,14 @@ __global__ __launch_bounds__(1024) void k_pair_scan(DeviceGraph g) {
     if (tid == 0) g.xs_pair_off[n] = base;
 }
 
-// One record per camera-major edge, contiguous: the matches of a pair are a
-// few of its cameras' edges, and from the stored Jacobian's tiles each 16
-// bytes of one came with a line of their own (68 us a step at 203 cameras in
-// FP32, 276 in FP64; 30 and 99 from the records, which take 11 and 18 to
-// write).  With Hpp^-1 = L L^T a match needs no point block.
+// One record per camera-major edge, contiguous (128 bytes in the mixed modes):
+// J_p Hpp^-1, two pads, J_c, J_p.  The matches of a pair are a few of its
+// cameras' edges, and from the stored Jacobian's tiles each 16 bytes of one
+// came with a line of their own.  A match takes J_p Hpp^-1 of one edge and J_p
+// of the other, so that the blocks hold the same point inverses as the diagonal
+// ones (a factor L L^T of an inverse rounded to FP32 is off by up to thousands
+// of roundings where its condition passes 1e8: points far away for their
+// baseline, at a small damping).
 template <typename T, typename JS>
 __global__ __launch_bounds__(256) void k_reduced_edges(DeviceGraph g) {
     if ((sizeof(T) == 8) != (g.mode == kModeFP64) || sizeof(JS) != (size_t)g.jac_bytes) return;
@@ -283,28 +286,21 @@ __global__ __launch_bounds__(256) void k_reduced_edges(DeviceGraph g) {
     if (e >= g.ne) return;
     T jc[2][9], jp[2][3];
     jac_load<JS>(g.jst_cm, e, jc, jp);
-    const T* H = (const T*)g.hpp_inv + kHinvStride * (size_t)g.cm_pt[e];
-    const double h00 = H[0], h01 = H[1], h02 = H[2], h11 = H[3], h12 = H[4], h22 = H[5];
-    const double l00 = sqrt(fmax(h00, 0.0)), i0 = l00 > 0.0 ? 1.0 / l00 : 0.0;
-    const double l10 = h01 * i0, l20 = h02 * i0;
-    const double l11 = sqrt(fmax(h11 - l10 * l10, 0.0)), i1 = l11 > 0.0 ? 1.0 / l11 : 0.0;
-    const double l21 = (h12 - l20 * l10) * i1;
-    const double l22 = sqrt(fmax(h22 - l20 * l20 - l21 * l21, 0.0));
-    T out[24];
+    T out[kEdgeRec];
+    point_side(jp, (const T*)g.hpp_inv + kHinvStride * (size_t)g.cm_pt[e], out);
+    out[6] = out[7] = (T)0;
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
 #pragma unroll
-        for (int c = 0; c < 9; ++c) out[9 * r + c] = jc[r][c];
-        const double a = jp[r][0], b = jp[r][1], c = jp[r][2];
-        out[18 + 3 * r] = (T)(a * l00 + b * l10 + c * l20);
-        out[19 + 3 * r] = (T)(b * l11 + c * l21);
-        out[20 + 3 * r] = (T)(c * l22);
+        for (int c = 0; c < 9; ++c) out[8 + 9 * r + c] = jc[r][c];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) out[26 + 3 * r + c] = jp[r][c];
     }
     typedef T V __attribute__((ext_vector_type(16 / sizeof(T))));
     constexpr int kV = 16 / (int)sizeof(T);
-    V* dst = (V*)((T*)g.xs_edge + 24 * (size_t)e);
+    V* dst = (V*)((T*)g.xs_edge + kEdgeRec * (size_t)e);
 #pragma unroll
-    for (int k = 0; k < 24 / kV; ++k) {
+    for (int k = 0; k < kEdgeRec / kV; ++k) {
         V v;
 #pragma unroll
         for (int u = 0; u < kV; ++u) v[u] = out[kV * k + u];
@@ -312,13 +308,15 @@ __global__ __launch_bounds__(256) void k_reduced_edges(DeviceGraph g) {
     }
 }
 
-template <typename T>
-__device__ __forceinline__ void edge_record(const DeviceGraph& g, int e, T (&v)[24]) {
+// entries kFirst .. kFirst + kN - 1 of edge e's record (whole 16-byte groups)
+template <int kFirst, int kN, typename T>
+__device__ __forceinline__ void edge_record(const DeviceGraph& g, int e, T (&v)[kN]) {
     typedef T V __attribute__((ext_vector_type(16 / sizeof(T))));
     constexpr int kV = 16 / (int)sizeof(T);
-    const V* src = (const V*)((const T*)g.xs_edge + 24 * (size_t)e);
+    static_assert(kFirst % kV == 0 && kN % kV == 0 && kFirst + kN <= kEdgeRec, "whole groups of the record");
+    const V* src = (const V*)((const T*)g.xs_edge + kEdgeRec * (size_t)e + kFirst);
 #pragma unroll
-    for (int k = 0; k < 24 / kV; ++k) {
+    for (int k = 0; k < kN / kV; ++k) {
         const V x = src[k];
 #pragma unroll
         for (int u = 0; u < kV; ++u) v[kV * k + u] = x[u];
@@ -348,16 +346,17 @@ __global__ __launch_bounds__(256) void k_reduced_pairs(DeviceGraph g) {
     for (int u = 0; u < kSums; ++u) acc[u] = 0.0;
     for (int m = m0 + l; m < m1; m += kLanes) {
         const int2 e = g.xs_pairs[m];
-        T a[24], b[24];
-        edge_record(g, e.x, a);
-        edge_record(g, e.y, b);
+        T a[28], b[24];
+        edge_record<0, 28>(g, e.x, a);   // J_p Hpp^-1, the pads, J_c (and two entries of J_p)
+        edge_record<8, 24>(g, e.y, b);   // J_c, J_p
+        const T* ja = a + 8;
         double A[2][2], M[2][9];
 #pragma unroll
         for (int r = 0; r < 2; ++r)
 #pragma unroll
             for (int c = 0; c < 2; ++c)
-                A[r][c] = (double)a[18 + 3 * r] * (double)b[18 + 3 * c] + (double)a[19 + 3 * r] * (double)b[19 + 3 * c] +
-                          (double)a[20 + 3 * r] * (double)b[20 + 3 * c];
+                A[r][c] = (double)a[3 * r] * (double)b[18 + 3 * c] + (double)a[3 * r + 1] * (double)b[19 + 3 * c] +
+                          (double)a[3 * r + 2] * (double)b[20 + 3 * c];
 #pragma unroll
         for (int c = 0; c < 9; ++c) {
             M[0][c] = A[0][0] * (double)b[c] + A[0][1] * (double)b[9 + c];
@@ -367,11 +366,11 @@ __global__ __launch_bounds__(256) void k_reduced_pairs(DeviceGraph g) {
         for (int r = 0; r < kRows; ++r) {
             double u0, u1;
             if constexpr (kRows == 9) {
-                u0 = (double)a[r];
-                u1 = (double)a[9 + r];
+                u0 = (double)ja[r];
+                u1 = (double)ja[9 + r];
             } else {   // rb is uniform
-                u0 = (double)(rb == 0 ? a[r] : rb == kRows ? a[kRows + r] : a[2 * kRows + r]);
-                u1 = (double)(rb == 0 ? a[9 + r] : rb == kRows ? a[9 + kRows + r] : a[9 + 2 * kRows + r]);
+                u0 = (double)(rb == 0 ? ja[r] : rb == kRows ? ja[kRows + r] : ja[2 * kRows + r]);
+                u1 = (double)(rb == 0 ? ja[9 + r] : rb == kRows ? ja[9 + kRows + r] : ja[9 + 2 * kRows + r]);
             }
 #pragma unroll
             for (int c = 0; c < 9; ++c) acc[9 * r + c] += u0 * M[0][c] + u1 * M[1][c];

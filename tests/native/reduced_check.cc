@@ -1,0 +1,88 @@
+// Host-only checks of the explicit reduced systems' parts that run on both
+// sides, built with a plain C++ compiler by tests/test_reduced_host.py.  No GPU
+// is touched.
+#include <hip/hip_runtime.h>
+
+#include <cmath>
+#include <cstdio>
+#include <random>
+
+#include "gba_internal.h"
+
+using namespace gba;
+
+static int g_fail = 0;
+#define CHECK(c)                                                                   \
+    do {                                                                           \
+        if (!(c)) {                                                                \
+            std::fprintf(stderr, "%s:%d: check failed: %s\n", __FILE__, __LINE__, #c); \
+            ++g_fail;                                                              \
+        }                                                                          \
+    } while (0)
+
+// The blocks' point side J_p,i Hpp^-1 J_p,k^T of FP32 inverses up to condition
+// 1e12 equals the product with the stored inverse itself (as the diagonal
+// blocks have it) to the FP32 rounding of J_p Hpp^-1, six terms of at most one
+// rounding each.  (A Cholesky factor of such an inverse is off by thousands of
+// roundings where its condition passes 1e8.)
+static void check_point_side() {
+    std::mt19937_64 rng(1);
+    std::normal_distribution<double> nrm;
+    std::uniform_real_distribution<double> uni(0.0, 1.0);
+    for (int it = 0; it < 20000; ++it) {
+        // H^-1 = Q diag(1, e1, e2) Q^T with e2 <= e1 <= 1
+        double q[3][3];
+        for (auto& r : q)
+            for (double& v : r) v = nrm(rng);
+        for (int a = 0; a < 3; ++a) {   // Gram-Schmidt
+            for (int b = 0; b < a; ++b) {
+                double d = 0.0;
+                for (int c = 0; c < 3; ++c) d += q[a][c] * q[b][c];
+                for (int c = 0; c < 3; ++c) q[a][c] -= d * q[b][c];
+            }
+            double n = 0.0;
+            for (int c = 0; c < 3; ++c) n += q[a][c] * q[a][c];
+            for (int c = 0; c < 3; ++c) q[a][c] /= std::sqrt(n);
+        }
+        const double e[3] = {1.0, std::pow(10.0, -12.0 * uni(rng)), std::pow(10.0, -12.0 * uni(rng))};
+        float h[6];
+        int at = 0;
+        for (int r = 0; r < 3; ++r)
+            for (int c = r; c < 3; ++c) {
+                double v = 0.0;
+                for (int k = 0; k < 3; ++k) v += e[k] * q[k][r] * q[k][c];
+                h[at++] = (float)v;
+            }
+        float ji[2][3], jk[2][3], out[6];
+        for (int r = 0; r < 2; ++r)
+            for (int c = 0; c < 3; ++c) {
+                ji[r][c] = (float)nrm(rng);
+                jk[r][c] = (float)nrm(rng);
+            }
+        point_side(ji, h, out);
+        const int sym[3][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}};
+        for (int r = 0; r < 2; ++r)
+            for (int c = 0; c < 2; ++c) {
+                double got = 0.0, want = 0.0, size = 0.0;
+                for (int k = 0; k < 3; ++k) {
+                    got += (double)out[3 * r + k] * (double)jk[c][k];
+                    for (int m = 0; m < 3; ++m) {
+                        const double t = (double)ji[r][m] * (double)h[sym[m][k]] * (double)jk[c][k];
+                        want += t;
+                        size += std::fabs(t);
+                    }
+                }
+                CHECK(std::fabs(got - want) <= size * std::ldexp(1.0, -23));
+            }
+    }
+}
+
+int main() {
+    check_point_side();
+    if (g_fail) {
+        std::fprintf(stderr, "%d checks failed\n", g_fail);
+        return 1;
+    }
+    std::printf("reduced checks passed\n");
+    return 0;
+}

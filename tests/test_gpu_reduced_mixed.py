@@ -5,6 +5,7 @@ point inverses, right-hand side)."""
 import numpy as np
 import pytest
 
+from oracle import camera
 from paper_2509_26581_amd import gba, synth
 
 pytestmark = pytest.mark.gpu
@@ -44,3 +45,39 @@ def test_sums_over_many_common_points(n_cams, n_pts):
     err = [np.linalg.norm(_cam_step(sc, gba.GBA_MIXED_FP32, acc, 12) - want)
            for acc in (gba.GBA_ACC_AUTO, gba.GBA_ACC_LDS)]
     assert err[0] <= 0.2 * err[1], err
+
+
+def test_points_with_nearly_parallel_rays():
+    # Half of the points are seen by two cameras a 25,000th of the depth apart
+    # only, at a damping of 1e-6: their inverse blocks are known to a few per
+    # cent in FP32 (the launched products' two orders give costs 5e-4 apart).
+    # The off-diagonal blocks hold the same inverses as the diagonal ones, so
+    # the damped system stays definite and the trial ends where the launched
+    # products' does: 1e-2 of the cost allowed.
+    rng = np.random.default_rng(5)
+    n_cams, n_pts = 60, 4000
+    sc = synth.make_scene("small", seed=5, n_cams=n_cams, n_pts=n_pts, layout="sphere")
+    cams = sc.cams_true.copy()
+    cams[1::2] = cams[::2]
+    cams[1::2, 3:6] += rng.normal(0.0, 1e-3, (n_cams // 2, 3))
+    first = 2 * rng.integers(n_cams // 2, size=n_pts // 2)
+    ci = [np.stack([first, first + 1], 1).ravel()]
+    ci += [rng.choice(n_cams, 6, replace=False) for _ in range(n_pts - n_pts // 2)]
+    ci = np.concatenate(ci)
+    pi = np.repeat(np.arange(n_pts), np.where(np.arange(n_pts) < n_pts // 2, 2, 6))
+    X = rng.uniform(-5.0, 5.0, (n_pts, 3))
+    uv = camera.residuals(cams, X, ci, pi, np.zeros((len(ci), 2))) + rng.normal(0.0, 0.5, (len(ci), 2))
+    d = np.repeat(rng.normal(0.0, 1e-3, (n_cams // 2, 3)), 2, axis=0)
+    cams0, pts0 = cams.copy(), X + rng.normal(0.0, 1e-2, X.shape)
+    cams0[:, 3:6] += d
+    reps = []
+    for acc in (gba.GBA_ACC_AUTO, gba.GBA_ACC_LDS):
+        g = gba.Graph.from_arrays(cams0, pts0, ci, pi, uv, loss=gba.GBA_LOSS_HUBER, delta=1.0,
+                                  precision=gba.GBA_MIXED_FP32,
+                                  options=gba.options(pcg_max_iters=6, pcg_tol=0.0, accumulation=acc,
+                                                      initial_lambda=1e-6))
+        reps.append(g.solve(1))
+        g.close()
+    a, b = reps
+    assert a.accepted == b.accepted == 1 and a.pcg_iters_total == b.pcg_iters_total == 6
+    assert abs(a.final_cost - b.final_cost) <= 1e-2 * b.final_cost

@@ -1,0 +1,24 @@
+"""Host build (no GPU) of what the explicit reduced systems share between host
+and device: tests/native/reduced_check.cc holds the checks."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+
+def test_reduced_system_host_checks(tmp_path):
+    cxx = shutil.which("g++")
+    if cxx is None or not os.path.exists(os.path.join(ROCM, "include", "hip", "hip_runtime.h")):
+        pytest.skip("g++ or the HIP headers are missing")
+    exe = str(tmp_path / "reduced_check")
+    cmd = [cxx, "-std=c++17", "-O1", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
+           "-D__HIP_PLATFORM_AMD__", "-I" + os.path.join(ROCM, "include"), "-I" + os.path.join(ROOT, "include"),
+           "-I" + os.path.join(ROOT, "paper_2509_26581_amd", "csrc"),
+           os.path.join(ROOT, "tests", "native", "reduced_check.cc"), "-o", exe]
+    subprocess.run(cmd, check=True, capture_output=True, timeout=600)
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0 and "reduced checks passed" in res.stdout, res.stdout + res.stderr
