@@ -251,9 +251,11 @@ gba_status make_image(const HostProblem& h, HostImage& img, std::string& msg) {
 // left to the library, the points are eliminated, no camera observes a point
 // twice (the rank bitmaps hold one edge per camera and point) and S has at
 // most kReducedMax rows.  A launched PCG iteration takes 14-16 us for small
-// problems whatever their size; one workgroup's iteration on S takes 1.3 us at
-// 10 cameras and about 4 us at 40 (S then comes from the L2 in part), and
-// forming S 7-14 us once per step.
+// problems whatever their size; one workgroup's iteration on S takes 1.6 us at
+// 12 cameras, 4.4 at 18 and 6.6 at 28 (S then comes from the L2 in part).  Past
+// 28 cameras one CU's reads of S set the pace: at 32, 40 and 48 cameras whole
+// solves are 1.0, 0.85 and 0.73 times as fast as with launched iterations,
+// where launched iterations on S (below) make them 1.4 to 1.7 times as fast.
 bool reduced_rule(const ImageCounts& n, const Tuning& tune) {
     if (tune.accumulation != GBA_ACC_AUTO || tune.deterministic || tune.solver == GBA_SOLVER_FULL) return false;
     return n.nc > 0 && n.ne > 0 && n.n_runs == n.ne && 9 * n.nc <= kReducedMax;

