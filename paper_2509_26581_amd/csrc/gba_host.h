@@ -40,6 +40,8 @@ struct ImageCounts {
     bool reduced = false;   // the PCG runs on the explicit reduced system
     bool wide = false;      // launched PCG iterations multiply by it
     long long pairs = 0;    // pairs of edges of one point
+    int free_cams = 0;      // cameras that are not fixed
+    int cam_edges = 0;      // edges of the camera with the most
 };
 
 // Whether a problem's explicit reduced system is formed (see gba_host.hip)

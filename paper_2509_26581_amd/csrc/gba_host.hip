@@ -237,6 +237,10 @@ gba_status make_image(const HostProblem& h, HostImage& img, std::string& msg) {
     }
     img.pm_edge = std::move(pm);
     img.n.nc = nc;
+    for (int i = 0; i < nc; ++i) {
+        if (!h.cam_fixed[i]) ++img.n.free_cams;
+        img.n.cam_edges = std::max(img.n.cam_edges, ccount[i + 1] - ccount[i]);
+    }
     img.n.np = np;
     img.n.ne = ne;
     img.n.n_tiles = (int)img.tile_off.size() - 1;
@@ -256,9 +260,17 @@ gba_status make_image(const HostProblem& h, HostImage& img, std::string& msg) {
 // 28 cameras one CU's reads of S set the pace: at 32, 40 and 48 cameras whole
 // solves are 1.0, 0.85 and 0.73 times as fast as with launched iterations,
 // where launched iterations on S (below) make them 1.4 to 1.7 times as fast.
+// A block of S is one workgroup's walk over its first camera's edges, 6.5 ns
+// (mixed) to 8 ns (FP64) an edge, so few cameras with many edges are bounded
+// too: four-trial solves at 2,000, 10,000, 16,000 and 24,000 edges a camera are
+// 1.9-2.1, 1.2-1.4, 1.0-1.2 and 0.8-0.95 times as fast with 8 iterations a step
+// (2.9-3.6, 1.9-2.7, 1.6-2.6 and 1.2-2.4 with about 25), and with one free
+// camera, whose step takes one iteration, 1.2-1.5 at 2,000, 1.0-1.2 at 5,000 and
+// 0.8-1.0 at 10,000 (0.2 at 200,000).
 bool reduced_rule(const ImageCounts& n, const Tuning& tune) {
     if (tune.accumulation != GBA_ACC_AUTO || tune.deterministic || tune.solver == GBA_SOLVER_FULL) return false;
-    return n.nc > 0 && n.ne > 0 && n.n_runs == n.ne && 9 * n.nc <= kReducedMax;
+    return n.nc > 0 && n.ne > 0 && n.n_runs == n.ne && 9 * n.nc <= kReducedMax &&
+           n.cam_edges <= (n.free_cams > 1 ? 20'000 : 5'000);
 }
 
 // The same for a single larger problem, whose launched PCG iterations then

@@ -105,6 +105,8 @@ static void check_point_side() {
 // there), the launched products where S or its forming costs too much.
 static ImageCounts counts(int nc, int np, int ne, long long pairs) {
     ImageCounts n;
+    n.free_cams = nc - 1;
+    n.cam_edges = ne / nc;
     n.nc = nc;
     n.np = np;
     n.ne = n.n_runs = ne;
@@ -118,6 +120,12 @@ static void check_rules() {
             const ImageCounts n = counts(nc, 20 * nc, 100 * nc, 200 * nc);
             CHECK(reduced_rule(n, t) == (nc <= 28));
             CHECK(reduced_wide_rule(n, t, prec) == (nc > 28 && nc <= 248));
+        }
+    // few cameras with many edges: forming S would cost more than the PCG
+    for (int nc : {2, 3, 8, 28})
+        for (int per : {1'000, 4'000, 6'000, 19'000, 21'000, 200'000}) {
+            const ImageCounts n = counts(nc, per, nc * per, per);
+            CHECK(reduced_rule(n, t) == (per <= (nc == 2 ? 5'000 : 20'000)));
         }
 }
 
