@@ -48,6 +48,8 @@ struct ImageCounts {
 struct Tuning;
 bool reduced_rule(const ImageCounts& n, const Tuning& tune);
 bool reduced_wide_rule(const ImageCounts& n, const Tuning& tune, int precision);
+// Whether forming it pays under these options (one of the rules above holds)
+bool reduced_pays(const ImageCounts& n, int precision, const gba_options& o);
 
 // Sorted image of one problem, problem-local indices.  Edge arrays are
 // point-major (by point, then camera, then insertion) unless prefixed cm_
@@ -114,6 +116,7 @@ struct UnionPlan {
     long long xs_total = 0, xs_rank_total = 0, xs_pairs = 0;
     int xs_cams = 0;
     bool xs_all = false, xs_wide = false;
+    ImageCounts one;           // one problem: its counts
     std::vector<int> cam_prob, pt_prob;   // problem of each union camera / point
 };
 

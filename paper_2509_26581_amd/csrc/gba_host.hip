@@ -289,6 +289,29 @@ bool reduced_wide_rule(const ImageCounts& n, const Tuning& tune, int precision) 
     return 9LL * n.nc * reduced_ld(9 * n.nc) * (long long)sizeof(double) <= 40'000'000 && n.pairs * word <= 12'000'000;
 }
 
+// S pays when forming it takes no longer than a step's PCG iterations save.
+// Iterations of a step: at most the limit, about four a decade of a relative
+// tolerance, 25 where neither says less.  Forming a wide S takes 8 us and 60 ps
+// an edge and 65 ps a pair of a point's edges (FP64: 150 and 130); a launched
+// iteration is 12 us and 17 ps an edge (FP64: 15 and 30) above one on S but for
+// the read of S (4 us, or 5.2 MB a us).  Four-trial solves against the launched
+// products with 3 and 8 iterations a step, mixed / FP64: 29 cameras, 110,000
+// edges 0.95 and 1.16 / 0.88 and 1.06, 550,000 edges 0.75 and 0.98 / 0.63 and
+// 0.84; 240 cameras, 161,000 edges 0.74 and 0.85 / 0.61 and 0.77 (with about 30
+// iterations 1.1 to 1.5 for all of these).  The one-workgroup form also saves a
+// host check, about 50 us.
+bool reduced_pays(const ImageCounts& n, int precision, const gba_options& o) {
+    double its = std::min(25, o.pcg_max_iters);
+    if (o.pcg_tol_relative && o.pcg_tol > 0.0) its = std::min(its, std::max(1.0, -4.0 * std::log10(o.pcg_tol)));
+    const bool f64 = precision == GBA_FP64;
+    const double ne = n.ne;
+    if (9 * n.nc <= kReducedMax) return 0.008 * n.cam_edges <= 50.0 + 12.0 * its;
+    const double form = 8.0 + (f64 ? 150e-6 : 60e-6) * ne + (f64 ? 130e-6 : 65e-6) * (double)n.pairs;
+    const double s_mb = 9.0 * n.nc * reduced_ld(9 * n.nc) * sizeof(double) * 1e-6;
+    const double saved = (f64 ? 15.0 : 12.0) + (f64 ? 30e-6 : 17e-6) * ne - std::max(4.0, s_mb / 5.2);
+    return form <= its * saved;
+}
+
 namespace {
 
 // Problem-aligned decomposition of item ranges [off[p], off[p+1]) into
@@ -457,6 +480,7 @@ gba_status plan_union(const std::vector<const ImageCounts*>& probs, const Tuning
     u.xs_off.assign(P, -1);
     u.xs_rank_off.assign(P, 0);
     u.xs_all = true;
+    if (P == 1) u.one = *probs[0];
     for (int p = 0; p < P; ++p) {
         const ImageCounts& n = *probs[p];
         if (!n.reduced && !(P == 1 && n.wide)) {
@@ -886,7 +910,7 @@ gba_status batch_damped_step(Batch& b, const gba_options& o, const Tuning& tune,
     // without a host check (phase timing and a forced schedule keep the
     // launched iterations, the identity preconditioner has no diagonal blocks)
     const bool reduced = d.xs_on && block_jacobi && !timing && o.pcg_schedule == GBA_PCG_AUTO &&
-                         !b.launched_products;
+                         !b.launched_products && (b.P > 1 || reduced_pays(b.plan.one, d.mode, o));
     const bool wide = reduced && d.xs_wide;
     if (!reduced || !d.xs_all || wide) HIP_OR(msg, launch_pcg_init(d, s, o.pcg_tol, o.pcg_tol_relative));
     if (reduced) {

@@ -129,9 +129,40 @@ static void check_rules() {
         }
 }
 
+// S is formed where a step's iterations pay for it: not at a small iteration
+// limit or with a loose tolerance, and always at those of a tight PCG.
+static void check_pays() {
+    gba_options o{};
+    o.pcg_tol = 1e-6;
+    o.pcg_tol_relative = 1;
+    const int nc[] = {29, 240, 60}, ne[] = {550'000, 161'000, 80'000};
+    const long long pairs[] = {1'380'000, 1'000'000, 760'000};
+    for (int prec : {GBA_FP64, GBA_MIXED_FP32})
+        for (int k = 0; k < 3; ++k) {
+            ImageCounts n = counts(nc[k], 1'000, ne[k], pairs[k]);
+            o.pcg_max_iters = 100;
+            o.pcg_tol = 1e-6;
+            CHECK(reduced_pays(n, prec, o));
+            o.pcg_max_iters = 3;
+            CHECK(!reduced_pays(n, prec, o));
+            o.pcg_max_iters = 100;
+            o.pcg_tol = 0.2;
+            CHECK(!reduced_pays(n, prec, o));
+            o.pcg_tol_relative = 0;   // an absolute tolerance says nothing
+            CHECK(reduced_pays(n, prec, o));
+            o.pcg_tol_relative = 1;
+            o.pcg_tol = 0.0;
+            CHECK(reduced_pays(n, prec, o));
+        }
+    o.pcg_max_iters = 1;
+    CHECK(!reduced_pays(counts(5, 20'000, 90'000, 120'000), GBA_FP64, o));
+    CHECK(reduced_pays(counts(5, 500, 2'000, 3'000), GBA_FP64, o));
+}
+
 int main() {
     check_point_side();
     check_rules();
+    check_pays();
     if (g_fail) {
         std::fprintf(stderr, "%d checks failed\n", g_fail);
         return 1;
