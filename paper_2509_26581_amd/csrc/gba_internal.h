@@ -125,7 +125,7 @@ __device__ __forceinline__ int decomp_block(const Decomp& d, int b, int& begin, 
 // Device view of one graph.  All arrays are device pointers.  Edge arrays are
 // in point-major order (sorted by problem, point, camera) unless prefixed cm_
 // (camera-major order, sorted by camera, then point).
-struct DeviceGraph {
+struct KernelGraph {
     int nc, np, ne;
     int n_tiles;         // point tiles (whole points of one problem, <= 64 edges, or one long point)
     int n_runs;          // camera-major runs of equal (camera, point)
@@ -180,8 +180,6 @@ struct DeviceGraph {
     PcgState* pcg_dec;        // [P] decision of the current PCG iteration (from the product)
     PcgState* pcg_host;       // [P] mapped host copies of pcg (at the start and once stopped), or null
     TrialScalars* scal_host;  // [P]
-    const double* lam_host;   // [P] host memory: the trial's dampings and accept flags, for the
-    const int* accept_host;   // [P] launchers only (they pass them as arguments or copy them)
 
     // parameters (FP64 master copies and candidates)
     double* cam;              // [nc][9]
@@ -254,6 +252,24 @@ struct DeviceGraph {
     // full-Hessian PCG (the solver form without point elimination)
     int full;                 // 1: PCG on the whole damped system
     int dynamic;              // 1: no stored Jacobian; products recompute it from the parameters
+    void* w_x;                // [np][3] point parts of the PCG vectors (vector type)
+    void* w_r;
+    void* w_z;
+    void* w_p;
+    void* w_q;
+    void* w_best;
+    double* pdot_partial;     // [2][dc_pts.nblk] point parts of r^T z, r^T r
+    double* ppq_partial;      // [dc_pp.nblk] point part of p^T q
+    double min_diag, max_diag;  // damping clamp (set by the full system's launchers)
+};
+
+// The same with what few kernels or only the launchers read.  Most kernels take
+// the base: a recorded iteration's nodes carry their arguments in every replay
+// (112 bytes more on each of three kernels an iteration: 70-85 us a solve of
+// 300 iterations).
+struct DeviceGraph : KernelGraph {
+    const double* lam_host;   // [P] host memory: the trial's dampings and accept flags, for the
+    const int* accept_host;   // [P] launchers only (they pass them as arguments or copy them)
     // explicit reduced systems (xs_on: some problem has one, xs_all: every one)
     int xs_on, xs_all;
     int xs_wide;              // the only problem's S is larger: launched PCG iterations multiply by it
@@ -272,26 +288,17 @@ struct DeviceGraph {
     void* xs_edge;            // [ne][kEdgeRec] per camera-major edge J_p Hpp^-1 (2 x 3), two pads,
                               // J_c (2 x 9), J_p (2 x 3), vector type
     long long xs_pair_total;
-    void* w_x;                // [np][3] point parts of the PCG vectors (vector type)
-    void* w_r;
-    void* w_z;
-    void* w_p;
-    void* w_q;
-    void* w_best;
-    double* pdot_partial;     // [2][dc_pts.nblk] point parts of r^T z, r^T r
-    double* ppq_partial;      // [dc_pp.nblk] point part of p^T q
-    double min_diag, max_diag;  // damping clamp (set by the full system's launchers)
 };
 
 // The storage types a kernel is instantiated with must be those of the
 // graph's precision mode (another type would address the buffers with the
 // wrong strides, past their ends); kernels check and return at once.
 template <typename VT>
-__device__ __forceinline__ bool vec_type_ok(const DeviceGraph& g) {
+__device__ __forceinline__ bool vec_type_ok(const KernelGraph& g) {
     return (sizeof(VT) == 8) == (g.mode == kModeFP64);
 }
 template <typename JS>
-__device__ __forceinline__ bool jac_type_ok(const DeviceGraph& g) {
+__device__ __forceinline__ bool jac_type_ok(const KernelGraph& g) {
     return sizeof(JS) == (size_t)g.jac_bytes;
 }
 

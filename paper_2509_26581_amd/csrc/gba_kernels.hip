@@ -71,7 +71,7 @@ __device__ __forceinline__ void edge_eval(const double* __restrict__ cam, const 
 // by forward-mode automatic differentiation.
 // ==========================================================================
 template <typename T, typename JS, bool kRaw, bool kAD>
-__global__ __launch_bounds__(256) void k_linearize(DeviceGraph g, RawOut raw) {
+__global__ __launch_bounds__(256) void k_linearize(KernelGraph g, RawOut raw) {
     if (!vec_type_ok<T>(g) || !jac_type_ok<JS>(g)) return;   // instantiated for another mode
     const int l = lane_id();
     const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(256) void k_linearize(DeviceGraph g, RawOut raw) {
 // Cost F = 1/2 sum_e rho(s_e) (Eq. 1 with the Eq. 7 kernel) in FP64 at the
 // given parameters; per-workgroup partial sums.
 // ==========================================================================
-__global__ __launch_bounds__(256) void k_cost(DeviceGraph g, const double* __restrict__ cam,
+__global__ __launch_bounds__(256) void k_cost(KernelGraph g, const double* __restrict__ cam,
                                               const double* __restrict__ pt) {
     __shared__ double red[16];
     int eb, ee;
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(256) void k_cost(DeviceGraph g, const double* __res
 // seeded and writes that column; the lane of column 0 also writes the
 // residual and the robust weight.
 // ==========================================================================
-__global__ __launch_bounds__(256) void k_jacobian_autodiff(DeviceGraph g, RawOut raw) {
+__global__ __launch_bounds__(256) void k_jacobian_autodiff(KernelGraph g, RawOut raw) {
     const size_t total = 12 * (size_t)g.ne;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < total; t += stride) {
@@ -259,7 +259,7 @@ struct LamArgs {
 };
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_damp_points(DeviceGraph g, LamArgs lams, double min_diag,
+__global__ __launch_bounds__(256) void k_damp_points(KernelGraph g, LamArgs lams, double min_diag,
                                                      double max_diag) {
     if (!vec_type_ok<T>(g)) return;   // instantiated for another mode
     __shared__ double red[16];
@@ -327,7 +327,7 @@ __device__ __forceinline__ void rhs_term(const A (&jc)[2][9], const A (&jp)[2][3
 }
 
 template <typename T, typename JS, int kMode, bool kAD = false>
-__global__ __launch_bounds__(256) void k_cam_accumulate(DeviceGraph g) {
+__global__ __launch_bounds__(256) void k_cam_accumulate(KernelGraph g) {
     if (!vec_type_ok<T>(g) || !jac_type_ok<JS>(g)) return;   // instantiated for another mode
     constexpr int K = 45;
     __shared__ double red[4][54];
@@ -665,7 +665,7 @@ enum { kRhs = 0, kMatvec = 1, kBacksub = 2 };
 // kernels below run one block per workgroup, the persistent PCG kernel loops
 // over blocks.
 template <typename VT, typename JS, typename AT, int kMode>
-__device__ __forceinline__ void pp_body(const DeviceGraph& g, const int bid, const void* __restrict__ J,
+__device__ __forceinline__ void pp_body(const KernelGraph& g, const int bid, const void* __restrict__ J,
                                         const VT* __restrict__ vin, AT* __restrict__ out) {
     if (!vec_type_ok<VT>(g) || !jac_type_ok<JS>(g)) return;   // instantiated for another mode
     // Arithmetic in the vector type (FP32 in the mixed modes); the camera sums
@@ -948,7 +948,7 @@ __device__ __forceinline__ void pp_body(const DeviceGraph& g, const int bid, con
 }
 
 template <typename VT, typename JS, typename AT, int kMode>
-__global__ __launch_bounds__(kPointPassBlock) void k_point_pass(DeviceGraph g, const void* __restrict__ J,
+__global__ __launch_bounds__(kPointPassBlock) void k_point_pass(KernelGraph g, const void* __restrict__ J,
                                                      const VT* __restrict__ vin, AT* __restrict__ out) {
     pp_body<VT, JS, AT, kMode>(g, (int)blockIdx.x, J, vin, out);
 }
@@ -967,7 +967,7 @@ __global__ __launch_bounds__(kPointPassBlock) void k_point_pass(DeviceGraph g, c
 // the storage type so that it equals what would have been stored.
 // ==========================================================================
 template <typename T, typename JS, bool kDyn>
-__device__ __forceinline__ void edge_jacobian(const DeviceGraph& g, int e, int i, int j,
+__device__ __forceinline__ void edge_jacobian(const KernelGraph& g, int e, int i, int j,
                                               T (&jc)[2][9], T (&jp)[2][3]) {
     if constexpr (kDyn) {
         EdgeEval<double> ev;
@@ -988,7 +988,7 @@ __device__ __forceinline__ void edge_jacobian(const DeviceGraph& g, int e, int i
 }
 
 template <typename VT, typename JS, bool kDyn, int kMode>
-__device__ __forceinline__ void full_pp_body(const DeviceGraph& g, const int bid) {
+__device__ __forceinline__ void full_pp_body(const KernelGraph& g, const int bid) {
     if (!vec_type_ok<VT>(g) || !jac_type_ok<JS>(g)) return;   // instantiated for another mode
     using T = VT;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1166,7 +1166,7 @@ __device__ __forceinline__ void full_pp_body(const DeviceGraph& g, const int bid
 }
 
 template <typename VT, typename JS, bool kDyn, int kMode>
-__global__ __launch_bounds__(kPointPassBlock) void k_full_point_pass(DeviceGraph g) {
+__global__ __launch_bounds__(kPointPassBlock) void k_full_point_pass(KernelGraph g) {
     full_pp_body<VT, JS, kDyn, kMode>(g, (int)blockIdx.x);
 }
 
@@ -1177,8 +1177,9 @@ __global__ __launch_bounds__(kPointPassBlock) void k_full_point_pass(DeviceGraph
 //            q = S p = S z + beta q (FP64); partial dots p^T q (FP64)
 // Workgroup: up to 64 components of one problem x 16 partial groups.
 // ==========================================================================
-template <typename T, int kSubs>
-__device__ __forceinline__ void apply_body(const DeviceGraph& g, const int bid0, const int bid_end);
+template <typename T, int kSubs, bool kOnS = false>
+__device__ __forceinline__ void apply_body(const KernelGraph& g, const int bid0, const int bid_end,
+                                           const int s_blocks = 0);
 
 // Every vector-memory access of this wavefront has completed: its stores are
 // in the L2 (s_waitcnt vmcnt(0); the workgroup barrier does not wait for them).
@@ -1191,7 +1192,7 @@ __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70)
 // arrival is a device-scope release by one thread after every wavefront's
 // stores have reached the L2.
 template <typename T, int kBlock>
-__device__ __forceinline__ void fused_update(const DeviceGraph& g, const int prob) {
+__device__ __forceinline__ void fused_update(const KernelGraph& g, const int prob) {
     __shared__ int s_last;
     wait_vmem();
     __syncthreads();
@@ -1216,7 +1217,7 @@ __device__ __forceinline__ void fused_update(const DeviceGraph& g, const int pro
 }
 
 template <typename T, int kMode, int kBlock>
-__device__ __forceinline__ void reduce_body(const DeviceGraph& g, const int bid, double min_diag,
+__device__ __forceinline__ void reduce_body(const KernelGraph& g, const int bid, double min_diag,
                                             double max_diag) {
     if (!vec_type_ok<T>(g)) return;   // instantiated for another mode
     // The partial vectors are read with one 16-byte load per lane: a row of
@@ -1391,7 +1392,7 @@ __device__ __forceinline__ void reduce_body(const DeviceGraph& g, const int bid,
 }
 
 template <typename T, int kMode>
-__global__ __launch_bounds__(1024) void k_reduce(DeviceGraph g, double min_diag, double max_diag) {
+__global__ __launch_bounds__(1024) void k_reduce(KernelGraph g, double min_diag, double max_diag) {
     reduce_body<T, kMode, 1024>(g, (int)blockIdx.x, min_diag, max_diag);
 }
 
@@ -1417,7 +1418,7 @@ __device__ __forceinline__ T minv_row(const T* __restrict__ Minv, const T* r_lds
 // x_best = x = 0 (the start is the first candidate), z = M^{-1} r, partial
 // (r^T z, r^T r) per workgroup.
 template <typename T>
-__global__ __launch_bounds__(kPcgBlock) void k_pcg_start(DeviceGraph g) {
+__global__ __launch_bounds__(kPcgBlock) void k_pcg_start(KernelGraph g) {
     if (!vec_type_ok<T>(g)) return;   // instantiated for another mode
     __shared__ T r_lds[kPcgBlock];
     __shared__ double red[16];
@@ -1452,7 +1453,7 @@ __global__ __launch_bounds__(kPcgBlock) void k_pcg_start(DeviceGraph g) {
 
 // PCG start, scalars: rz0, rr0, threshold per problem (the first direction
 // p = z is formed by the first iteration).
-__global__ __launch_bounds__(1024) void k_pcg_start_finish(DeviceGraph g, double tol, int relative) {
+__global__ __launch_bounds__(1024) void k_pcg_start_finish(KernelGraph g, double tol, int relative) {
     const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     for (int prob = w; prob < g.n_probs; prob += nw) {
         const int q0 = g.dc_cam.prob_blk[prob], q1 = g.dc_cam.prob_blk[prob + 1];
@@ -1496,8 +1497,11 @@ __global__ __launch_bounds__(1024) void k_pcg_start_finish(DeviceGraph g, double
 // kSubs > 1: a workgroup of kSubs x kPcgBlock threads runs camera workgroups
 // bid0 .. bid0 + kSubs - 1 side by side (the persistent kernel), each with
 // the arithmetic of a launched one; every thread then passes every barrier.
-template <typename T, int kSubs>
-__device__ __forceinline__ void apply_body(const DeviceGraph& g, const int bid0, const int bid_end) {
+// kOnS: the product was the one on the explicit S, with s_blocks workgroups and
+// one p^T q partial of each.
+template <typename T, int kSubs, bool kOnS>
+__device__ __forceinline__ void apply_body(const KernelGraph& g, const int bid0, const int bid_end,
+                                           const int s_blocks) {
     if (!vec_type_ok<T>(g)) return;   // instantiated for another mode
     __shared__ T r_lds[kSubs * kPcgBlock];
     __shared__ double red[16];
@@ -1531,9 +1535,12 @@ __device__ __forceinline__ void apply_body(const DeviceGraph& g, const int bid0,
     T* __restrict__ r = (T*)g.v_r;
     double pq = 0.0;
     if (blk) {
-        // (a launched product on S has its own workgroups)
-        const int b0 = g.xs_rows ? 0 : g.dc_red.prob_blk[prob], b1 = g.xs_rows ? g.xs_rows : g.dc_red.prob_blk[prob + 1];
-        for (int b = b0 + tid; b < b1; b += kPcgBlock) pq += g.pq_partial[b];
+        if constexpr (kOnS) {
+            for (int b = tid; b < s_blocks; b += kPcgBlock) pq += g.pq_partial[b];
+        } else {
+            for (int b = g.dc_red.prob_blk[prob] + tid; b < g.dc_red.prob_blk[prob + 1]; b += kPcgBlock)
+                pq += g.pq_partial[b];
+        }
         if (g.full)   // the point part of p^T q, from the product's workgroups
             for (int b = g.dc_pp.prob_blk[prob] + tid; b < g.dc_pp.prob_blk[prob + 1]; b += kPcgBlock)
                 pq += g.ppq_partial[b];
@@ -1617,7 +1624,7 @@ __device__ __forceinline__ void apply_body(const DeviceGraph& g, const int bid0,
 // the best-iterate copy / restore of the rejection ratio.  alpha from the
 // same sums, in the same order, as the camera part.  kSubs as in apply_body.
 template <typename T, int kSubs>
-__device__ __forceinline__ void apply_pts_body(const DeviceGraph& g, const int bid0) {
+__device__ __forceinline__ void apply_pts_body(const KernelGraph& g, const int bid0) {
     __shared__ double red[16];
     const int sub = kSubs > 1 ? (int)threadIdx.x / kPcgBlock : 0;
     const int tid = (int)threadIdx.x - sub * kPcgBlock;
@@ -1684,7 +1691,7 @@ __device__ __forceinline__ void apply_pts_body(const DeviceGraph& g, const int b
 // PCG start, the full system's point part: r = -b_p, z = Hpp_lambda^-1 r,
 // x = best = p = q = 0, partial (r^T z, r^T r) per point workgroup.
 template <typename T>
-__global__ __launch_bounds__(kPcgBlock) void k_pcg_start_pts(DeviceGraph g) {
+__global__ __launch_bounds__(kPcgBlock) void k_pcg_start_pts(KernelGraph g) {
     if (!vec_type_ok<T>(g)) return;   // instantiated for another mode
     __shared__ double red[16];
     int pb, pe;
@@ -1720,7 +1727,7 @@ __global__ __launch_bounds__(kPcgBlock) void k_pcg_start_pts(DeviceGraph g) {
 // The update of one PCG iteration: camera workgroups first, then (full
 // system) the point workgroups.
 template <typename T>
-__global__ __launch_bounds__(kPcgBlock) void k_pcg_apply(DeviceGraph g) {
+__global__ __launch_bounds__(kPcgBlock) void k_pcg_apply(KernelGraph g) {
     const int b = (int)blockIdx.x;
     if (b < g.dc_cam.nblk)
         apply_body<T, 1>(g, b, g.dc_cam.nblk);
@@ -1728,12 +1735,17 @@ __global__ __launch_bounds__(kPcgBlock) void k_pcg_apply(DeviceGraph g) {
         apply_pts_body<T, 1>(g, b - g.dc_cam.nblk);
 }
 
+template <typename T>
+__global__ __launch_bounds__(kPcgBlock) void k_pcg_apply_s(KernelGraph g, int s_blocks) {
+    apply_body<T, 1, true>(g, (int)blockIdx.x, g.dc_cam.nblk, s_blocks);
+}
+
 // ==========================================================================
 // Cameras after PCG: dc = x, candidate cameras; partial b^T dc, |dc|^2 and
 // |c|^2 over free cameras per camera-aligned workgroup.
 // ==========================================================================
 template <typename T>
-__global__ __launch_bounds__(kPcgBlock) void k_cam_update(DeviceGraph g) {
+__global__ __launch_bounds__(kPcgBlock) void k_cam_update(KernelGraph g) {
     if (!vec_type_ok<T>(g)) return;   // instantiated for another mode
     __shared__ double red[16];
     int cb, ce;
@@ -1766,7 +1778,7 @@ __global__ __launch_bounds__(kPcgBlock) void k_cam_update(DeviceGraph g) {
 // Combine the per-workgroup partial sums of the trial, per problem (single
 // workgroup; with fewer problems than wavefronts several wavefronts share a
 // problem's sums).
-__global__ __launch_bounds__(1024) void k_finish(DeviceGraph g) {
+__global__ __launch_bounds__(1024) void k_finish(KernelGraph g) {
     __shared__ double part[16][8];
     const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     // wavefronts per problem: with fixed-order sums one, so that a problem's
@@ -1815,7 +1827,7 @@ __global__ __launch_bounds__(1024) void k_finish(DeviceGraph g) {
 }
 
 // Cost only: combine the cost partials per problem (as k_finish).
-__global__ __launch_bounds__(1024) void k_cost_finish(DeviceGraph g) {
+__global__ __launch_bounds__(1024) void k_cost_finish(KernelGraph g) {
     __shared__ double part[16];
     const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const int wpp = (g.deterministic || g.n_probs >= nw) ? 1 : nw / g.n_probs;
@@ -1841,7 +1853,7 @@ __global__ __launch_bounds__(1024) void k_cost_finish(DeviceGraph g) {
 
 // Accepted problems: the candidate parameters become the current ones.
 // The accept flags of a small batch are an argument (bit p: problem p).
-__global__ __launch_bounds__(256) void k_commit(DeviceGraph g, unsigned long long mask, int from_mask) {
+__global__ __launch_bounds__(256) void k_commit(KernelGraph g, unsigned long long mask, int from_mask) {
     auto accepted = [&](int p) { return from_mask ? ((mask >> p) & 1ull) != 0 : g.accept[p] != 0; };
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < 9 * (size_t)g.nc; k += stride)
@@ -1860,7 +1872,7 @@ __global__ __launch_bounds__(256) void k_commit(DeviceGraph g, unsigned long lon
 //   (v the product's camera vector).
 // ==========================================================================
 template <typename VT, typename JS, int kMode, int kSubs>
-__device__ __forceinline__ void cam_pass_body(const DeviceGraph& g, const int chunk0) {
+__device__ __forceinline__ void cam_pass_body(const KernelGraph& g, const int chunk0) {
     if (!vec_type_ok<VT>(g) || !jac_type_ok<JS>(g)) return;   // instantiated for another mode
     // arithmetic and sums in the vector type (FP32 in the mixed modes)
     using T = VT;
@@ -1908,13 +1920,13 @@ __device__ __forceinline__ void cam_pass_body(const DeviceGraph& g, const int ch
 }
 
 template <typename VT, typename JS, int kMode>
-__global__ __launch_bounds__(kCamPassBlock) void k_cam_pass(DeviceGraph g) {
+__global__ __launch_bounds__(kCamPassBlock) void k_cam_pass(KernelGraph g) {
     cam_pass_body<VT, JS, kMode, 1>(g, (int)blockIdx.x);
 }
 
 // Two-pass scheme, RHS first pass: z_j = Hpp_lambda^-1 bp_j for every point.
 template <typename T>
-__global__ __launch_bounds__(256) void k_rhs_z(DeviceGraph g) {
+__global__ __launch_bounds__(256) void k_rhs_z(KernelGraph g) {
     if (!vec_type_ok<T>(g)) return;   // instantiated for another mode
     using PT = T;
     const T* bp = (const T*)g.bp;
@@ -1939,7 +1951,7 @@ __global__ __launch_bounds__(256) void k_rhs_z(DeviceGraph g) {
 // (k_copy_jac_bo, after each linearisation).
 // ==========================================================================
 template <typename JS>
-__global__ __launch_bounds__(256) void k_copy_jac_bo(DeviceGraph g) {
+__global__ __launch_bounds__(256) void k_copy_jac_bo(KernelGraph g) {
     if (!jac_type_ok<JS>(g)) return;   // instantiated for another mode
     using A = typename std::conditional<std::is_same<JS, double>::value, double, float>::type;
     for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < g.ne;
@@ -1951,7 +1963,7 @@ __global__ __launch_bounds__(256) void k_copy_jac_bo(DeviceGraph g) {
 }
 
 template <typename VT, typename JS>
-__global__ __launch_bounds__(kCamBlockThreads) void k_cam_block_pass(DeviceGraph g) {
+__global__ __launch_bounds__(kCamBlockThreads) void k_cam_block_pass(KernelGraph g) {
     if (!vec_type_ok<VT>(g) || !jac_type_ok<JS>(g)) return;   // instantiated for another mode
     using T = VT;
     // the sums in LDS are FP64 in every mode (FP32 LDS atomics are slower)
@@ -2051,7 +2063,7 @@ __device__ __forceinline__ void grid_barrier(unsigned int* bar, unsigned int nbl
 // kForm: 0 the Schur form, 1 the full system, 2 the full system with
 // dynamic Jacobians
 template <typename VT, typename JS, int kForm>
-__global__ __launch_bounds__(kPersistentBlock) void k_pcg_persistent(DeviceGraph g, double min_diag,
+__global__ __launch_bounds__(kPersistentBlock) void k_pcg_persistent(KernelGraph g, double min_diag,
                                                                     double max_diag, int max_launch) {
     // every workgroup runs the same loop (uniform trip count), so each
     // arrives at every barrier; the type check is uniform too
@@ -2482,8 +2494,10 @@ hipError_t launch_pcg_iter(const DeviceGraph& g, hipStream_t s, double min_diag,
     if (g.xs_rows) {   // on the explicit reduced system: product and update
         hipError_t e = launch_reduced_product(g, s, max_iters, ratio);
         if (e != hipSuccess) return e;
-        if (g.mode == kModeFP64) hipLaunchKernelGGL(k_pcg_apply<double>, dim3(g.dc_cam.nblk), dim3(kPcgBlock), 0, s, g);
-        else hipLaunchKernelGGL(k_pcg_apply<float>, dim3(g.dc_cam.nblk), dim3(kPcgBlock), 0, s, g);
+        if (g.mode == kModeFP64)
+            hipLaunchKernelGGL(k_pcg_apply_s<double>, dim3(g.dc_cam.nblk), dim3(kPcgBlock), 0, s, g, g.xs_rows);
+        else
+            hipLaunchKernelGGL(k_pcg_apply_s<float>, dim3(g.dc_cam.nblk), dim3(kPcgBlock), 0, s, g, g.xs_rows);
         GBA_CHECK_LAUNCH();
         return hipSuccess;
     }

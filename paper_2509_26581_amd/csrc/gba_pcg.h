@@ -38,7 +38,7 @@ __device__ __forceinline__ double wave_sum_blocks(const double* part, int stride
 // iteration is three kernels with no separate scalar pass, and the product
 // gathers one vector.
 // ==========================================================================
-__device__ __forceinline__ PcgState pcg_decision(const DeviceGraph& g, int prob) {
+__device__ __forceinline__ PcgState pcg_decision(const KernelGraph& g, int prob) {
     PcgState st = g.pcg[prob];
     const int q0 = g.dc_cam.prob_blk[prob], q1 = g.dc_cam.prob_blk[prob + 1];
     double rz = wave_sum_blocks(g.dot_partial, 2, 0, q0, q1);

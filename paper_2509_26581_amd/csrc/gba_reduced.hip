@@ -664,7 +664,9 @@ __global__ __launch_bounds__(kBig ? kBigWaves * kWave : 4 * kWave) void k_pcg_re
 // ==========================================================================
 constexpr int kReducedProductBlock = 5 * kWave;
 template <typename T>
-__global__ __launch_bounds__(kReducedProductBlock) void k_reduced_product(DeviceGraph g) {
+__global__ __launch_bounds__(kReducedProductBlock) void k_reduced_product(KernelGraph g,
+                                                                          const double* __restrict__ S,
+                                                                          const double* __restrict__ D) {
     if ((sizeof(T) == 8) != (g.mode == kModeFP64)) return;
     constexpr int kWaves = 4;
     __shared__ double tot_s[kWaves][kReducedRows];
@@ -682,7 +684,7 @@ __global__ __launch_bounds__(kReducedProductBlock) void k_reduced_product(Device
             pold = ((const T*)g.v_p)[k];
             qold = ((const T*)g.v_q)[k];
 #pragma unroll
-            for (int c = 0; c < 9; ++c) diag += g.xs_diag[45 * (size_t)i + sym9(r, c)] * (double)z[9 * i + c];
+            for (int c = 0; c < 9; ++c) diag += D[45 * (size_t)i + sym9(r, c)] * (double)z[9 * i + c];
         }
         const PcgState d = pcg_decision(g, 0);
         if (blockIdx.x == 0 && l == 0) g.pcg_dec[0] = d;
@@ -706,7 +708,6 @@ __global__ __launch_bounds__(kReducedProductBlock) void k_reduced_product(Device
     }
     constexpr int kV = 2;
     typedef double V __attribute__((ext_vector_type(kV)));
-    const double* __restrict__ S = g.xs_S + g.xs_off[0];
     double acc[kReducedRows];
 #pragma unroll
     for (int u = 0; u < kReducedRows; ++u) acc[u] = 0.0;
@@ -784,11 +785,14 @@ hipError_t launch_reduced_form(const DeviceGraph& g, hipStream_t s) {
 }
 
 hipError_t launch_reduced_product(const DeviceGraph& g0, hipStream_t s, int max_iters, double ratio) {
-    DeviceGraph g = g0;
+    KernelGraph g = g0;
     g.pcg_max_iters = max_iters;
     g.pcg_ratio = ratio;
-    if (g.mode == kModeFP64) hipLaunchKernelGGL(k_reduced_product<double>, dim3(g.xs_rows), dim3(kReducedProductBlock), 0, s, g);
-    else hipLaunchKernelGGL(k_reduced_product<float>, dim3(g.xs_rows), dim3(kReducedProductBlock), 0, s, g);
+    // (one problem: its S is the whole of xs_S)
+    const dim3 grid(g0.xs_rows), block(kReducedProductBlock);
+    const double *S = g0.xs_S, *D = g0.xs_diag;
+    if (g.mode == kModeFP64) hipLaunchKernelGGL(k_reduced_product<double>, grid, block, 0, s, g, S, D);
+    else hipLaunchKernelGGL(k_reduced_product<float>, grid, block, 0, s, g, S, D);
     return hipGetLastError();
 }
 

@@ -160,6 +160,8 @@ static void check_pays() {
 }
 
 int main() {
+    // the arguments of a recorded iteration's kernels without the explicit systems' part
+    CHECK(sizeof(KernelGraph) <= 848 && sizeof(DeviceGraph) > sizeof(KernelGraph));
     check_point_side();
     check_rules();
     check_pays();
