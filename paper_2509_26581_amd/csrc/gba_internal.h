@@ -58,6 +58,12 @@ __host__ __device__ inline void point_side(const T (&jp)[2][3], const T* h, T* o
         out[3 * r + 2] = (T)(a * (double)h[2] + b * (double)h[4] + c * (double)h[5]);
     }
 }
+// Rows owned by a wavefront of the one-workgroup PCG (whole cameras), and the
+// first of the nine lanes whose residuals lane l reads: its own camera's, and
+// for the lane without a row the last camera's, so that every entry read is one
+// that the wavefront itself has written.
+constexpr int kOwnRows = kWave / 9 * 9;
+__host__ __device__ constexpr int own_first(int l) { return (l < kOwnRows ? l : kOwnRows - 1) / 9 * 9; }
 // One word of a camera's rank bitmap: the observed points among 64
 // consecutive ones, and the camera-major edge of the first of them.
 struct RankWord {

@@ -402,8 +402,6 @@ __global__ __launch_bounds__(256) void k_reduced_pairs(DeviceGraph g) {
 // divisions): 1.3 us an iteration at 90 rows, where the launched iteration
 // takes 14.2 us (two kernels).
 // ==========================================================================
-constexpr int kOwnRows = 63;   // rows owned per wavefront
-
 // four columns of the product for the two rows of a lane
 __device__ __forceinline__ void fma4(const double* __restrict__ p4, const double* __restrict__ a,
                                      const double* __restrict__ b, double (&qa)[4], double (&qb)[4]) {
@@ -461,7 +459,7 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
     }
     const int own = w * kOwnRows + l;
     const bool owner = w < W && l < kOwnRows && own < n;
-    const int a9 = l % 9, base9 = tid - a9;
+    const int a9 = l % 9, base9 = w * kWave + own_first(l);
     double m[9];
     double h[9];   // the owner's row of its camera's diagonal block
     double r = 0, p = 0, z = 0;
@@ -506,7 +504,7 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             double z0 = 0, z1 = 0, z2 = 0;
 #pragma unroll
-            for (int b = 0; b < 9; b += 3) {   // (lane 63 reads its neighbours' entries against m = 0)
+            for (int b = 0; b < 9; b += 3) {   // (lane 63 reads the last camera's against m = 0)
                 z0 += m[b] * r_s[base9 + b];
                 z1 += m[b + 1] * r_s[base9 + b + 1];
                 z2 += m[b + 2] * r_s[base9 + b + 2];

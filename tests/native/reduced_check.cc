@@ -159,7 +159,19 @@ static void check_pays() {
     CHECK(reduced_pays(counts(5, 500, 2'000, 3'000), GBA_FP64, o));
 }
 
+// The residual exchange of the one-workgroup PCG stays among the entries that
+// the wavefront's row owners have written, for every lane.
+static void check_exchange() {
+    CHECK(kOwnRows == 63);
+    for (int l = 0; l < kWave; ++l) {
+        const int first = own_first(l);
+        CHECK(first >= 0 && first + 8 < kOwnRows && first % 9 == 0);
+        CHECK(l >= kOwnRows || (first <= l && l < first + 9));
+    }
+}
+
 int main() {
+    check_exchange();
     // the arguments of a recorded iteration's kernels without the explicit systems' part
     CHECK(sizeof(KernelGraph) <= 848 && sizeof(DeviceGraph) > sizeof(KernelGraph));
     check_point_side();
