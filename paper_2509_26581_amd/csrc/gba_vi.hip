@@ -19,6 +19,7 @@
 #include "gba_autodiff.h"
 #include "gba_device.h"
 #include "gba_vi_order.h"
+#include "gba_vi_rule.h"
 
 namespace gba {
 namespace vi {
@@ -515,7 +516,7 @@ struct VIDev {
     const int* kslot;      // [M] point-order slot of each keyframe-order observation
     const int* kinv;       // [Mp] and back
     const int* kfoff;      // [K + 1] keyframe-order range of each keyframe
-    int* nrow;             // [K + 1]
+    int* nrow;             // [K + 2] (the last: observations far from their workgroup's keyframes)
     int* nitem;            // [K + 1] first pair of each keyframe
     int* ncol;             // [nnz]
     int* noff;             // [nnz] first pair of each block (later keyframes; the others unused)
@@ -1541,8 +1542,26 @@ __global__ __launch_bounds__(1024) void k_vi_pattern_scan(VIDev d) {
     }
     if (tid == 0) {
         d.nrow[d.K] = nb;
+        d.nrow[d.K + 1] = 0;
         d.nitem[d.K] = ni;
     }
+}
+
+// The observations outside their workgroup's window of keyframes in the
+// implicit product (k_vi_schur_pts adds those to q one by one), into
+// nrow[K + 1].
+__global__ __launch_bounds__(kFuseBlock) void k_vi_far(VIDev d) {
+    __shared__ int kmin_w[kFuseBlock / 64];
+    const long long i = blockIdx.x * (long long)kFuseBlock + threadIdx.x;
+    const bool valid = i < d.Mp && d.qpt[i] >= 0;
+    const int k = valid ? d.qkf[i] : 0x7fffffff;
+    int km = k;
+    for (int off = 32; off > 0; off >>= 1) km = min(km, __shfl_xor(km, off, 64));
+    if ((threadIdx.x & 63) == 0) kmin_w[threadIdx.x >> 6] = km;
+    __syncthreads();
+    for (int w = 0; w < kFuseBlock / 64; ++w) km = min(km, kmin_w[w]);
+    const uint64_t far = __ballot(valid && k - km >= kKfWin);
+    if ((threadIdx.x & 63) == 0 && far) atomicAdd(d.nrow + d.K + 1, __popcll(far));
 }
 
 // V_kk' = -sum W_a C^-1 W_b^T over the block's pairs, stored at (k, k') and,
@@ -2827,15 +2846,13 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         d.nlslot = (long long)hlslot.size();
     }
     // The visual blocks of S explicitly: when no keyframe observes a point
-    // twice (the diagonal blocks are then exact), tracks are short enough
-    // that forming them (about 20 ps a pair and step) stays below a few
-    // implicit products (about 20 ps an observation and PCG iteration), and a
-    // keyframe's counts fit in LDS.
+    // twice (the diagonal blocks are then exact), a keyframe's counts fit in
+    // LDS, the pairs of observations can be listed, and vi_blocks_pay says so.
     bool explicit_s = schur && M > 0 && !twice && pairs > 0 && pairs <= 16 * M && K <= 16000;
     if (explicit_s) {
         (void)hipFuncSetAttribute((const void*)k_vi_s_pcg_one, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   144 * kOneKf * (kOneKf - 1));
-        if (!B.up(&d.nrow, no_in, (size_t)K + 1) || !B.up(&d.nitem, no_in, (size_t)K + 1) ||
+        if (!B.up(&d.nrow, no_in, (size_t)K + 2) || !B.up(&d.nitem, no_in, (size_t)K + 1) ||
             !B.up(&d.items, (const int2*)nullptr, (size_t)pairs) || !B.up(&d.ad, (const double*)nullptr, 225 * (size_t)K) ||
             !B.up(&d.cb, (const double*)nullptr, 225 * (size_t)(K - 1)) ||
             !B.up(&d.cbt, (const double*)nullptr, 225 * (size_t)(K - 1)))
@@ -2845,9 +2862,15 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         const int lds = K * (int)sizeof(int);
         hipLaunchKernelGGL(k_vi_pattern<false>, dim3(K), dim3(256), lds, nullptr, d);
         hipLaunchKernelGGL(k_vi_pattern_scan, dim3(1), dim3(1024), 0, nullptr, d);
+        hipLaunchKernelGGL(k_vi_far, dim3((unsigned)((Mp + kFuseBlock - 1) / kFuseBlock)), dim3(kFuseBlock), 0, nullptr, d);
+        int nf[2] = {0, 0};
         if (hipGetLastError() != hipSuccess ||
-            hipMemcpy(&d.nnz, d.nrow + K, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess)
+            hipMemcpy(nf, d.nrow + K, 2 * sizeof(int), hipMemcpyDeviceToHost) != hipSuccess)
             return GBA_ERR_HIP;
+        d.nnz = nf[0];
+        explicit_s = vi_blocks_pay(M, pairs, d.nnz, nf[1], o.pcg_max_iters);
+    }
+    if (explicit_s) {
         if (!B.up(&d.ncol, (const int*)nullptr, (size_t)d.nnz) || !B.up(&d.noff, (const int*)nullptr, (size_t)d.nnz) ||
             !B.up(&d.nkf, (const int*)nullptr, (size_t)d.nnz) ||
             !B.up(&d.vblk, (const double*)nullptr, 36 * (size_t)d.nnz))

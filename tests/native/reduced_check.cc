@@ -8,6 +8,7 @@
 #include <random>
 
 #include "gba_host.hip"
+#include "gba_vi_rule.h"
 
 namespace gba {
 #define GBA_STUB(name, ...)                                        \
@@ -159,6 +160,22 @@ static void check_pays() {
     CHECK(reduced_pays(counts(5, 500, 2'000, 3'000), GBA_FP64, o));
 }
 
+// Keyframe blocks: formed for windowed visibility and for scattered visibility
+// of few blocks an observation, not where an iteration's blocks are more than
+// the observations they replace, nor for a handful of iterations.
+static void check_vi_blocks() {
+    const auto pay = vi::vi_blocks_pay;
+    for (int its : {50, 100, 4000}) {
+        CHECK(pay(32'000, 112'000, 3'540, 0, its));              // 60 keyframes
+        CHECK(pay(2'070'000, 7'000'000, 24'000, 0, its));        // 2,000, windowed
+        CHECK(pay(400'000, 1'400'000, 938'000, 380'000, its));   // 1,000, at random
+        CHECK(!pay(400'000, 1'400'000, 2'400'000, 390'000, its));   // 3,000, at random
+        CHECK(!pay(240'000, 360'000, 528'000, 0, its));          // 12,000, few points
+    }
+    CHECK(pay(32'000, 112'000, 3'540, 0, 1));
+    CHECK(!pay(2'070'000, 7'000'000, 24'000, 0, 1));
+}
+
 // The residual exchange of the one-workgroup PCG stays among the entries that
 // the wavefront's row owners have written, for every lane.
 static void check_exchange() {
@@ -172,6 +189,7 @@ static void check_exchange() {
 
 int main() {
     check_exchange();
+    check_vi_blocks();
     // the arguments of a recorded iteration's kernels without the explicit systems' part
     CHECK(sizeof(KernelGraph) <= 848 && sizeof(DeviceGraph) > sizeof(KernelGraph));
     check_point_side();
