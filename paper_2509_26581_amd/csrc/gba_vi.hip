@@ -18,6 +18,7 @@
 #include "gba.h"
 #include "gba_autodiff.h"
 #include "gba_device.h"
+#include "gba_vi_bufs.h"
 #include "gba_vi_order.h"
 #include "gba_vi_rule.h"
 
@@ -2476,46 +2477,6 @@ __global__ __launch_bounds__(256) void k_vi_step(VIDev d, const double* __restri
 // ------------------------------------------------------------------ C ABI
 namespace {
 
-// Device buffers of one call, carved from a few allocations (an allocation
-// and its release cost 20-200 us each; a solve takes about 50 buffers) and
-// released on every return path.
-struct DevBufs {
-    std::vector<void*> chunks;
-    char* at = nullptr;
-    size_t left = 0, next, bytes = 0;
-    explicit DevBufs(size_t expect) : next(expect) {}
-    DevBufs(const DevBufs&) = delete;
-    DevBufs& operator=(const DevBufs&) = delete;
-    ~DevBufs() {
-        for (void* q : chunks) (void)hipFree(q);
-    }
-    template <typename T>
-    bool up(T** dst, const T* src, size_t n) {
-        const size_t need = (n * sizeof(T) + 16 + 255) & ~(size_t)255;
-        if (need > left) {
-            const size_t size = std::max(need, next);
-            void* q = nullptr;
-            if (hipMalloc(&q, size) != hipSuccess) {
-                // the expected size may be more than what is left needs
-                const bool ok = size > need && hipMalloc(&q, need) == hipSuccess;
-                (void)hipGetLastError();   // a failed allocation is the caller's to handle
-                if (!ok) return false;
-                left = need;
-            } else {
-                left = size;
-            }
-            chunks.push_back(q);
-            bytes += left;
-            at = (char*)q;
-            next = std::max<size_t>(next / 8, 1 << 20);
-        }
-        *dst = (T*)at;
-        at += need;
-        left -= need;
-        return !src || n == 0 || hipMemcpy(*dst, src, n * sizeof(T), hipMemcpyHostToDevice) == hipSuccess;
-    }
-};
-
 // A recorded run of PCG steps of one solve (its stream is only captured on).
 struct StepGraph {
     hipStream_t stream = nullptr;
@@ -2563,7 +2524,7 @@ gba_status gba_vi_preintegrate(int device, int n, const int64_t* sample_off, con
     const size_t ns = (size_t)sample_off[n];
     if (ns > 0 && (!gyro || !acc)) return GBA_ERR_INVALID_ARG;
     if (hipSetDevice(device) != hipSuccess) return GBA_ERR_HIP;
-    DevBufs b(sizeof(double) * (6 * ns + (gba::vi::kPreStride + 8) * (size_t)n) + 8192);
+    gba::vi::DevBufs b(sizeof(double) * (6 * ns + (gba::vi::kPreStride + 8) * (size_t)n) + 8192);
     long long* doff = nullptr;
     double *dg = nullptr, *da = nullptr, *db = nullptr, *dout = nullptr;
     if (!b.up(&doff, (const long long*)sample_off, (size_t)n + 1) || !b.up(&dg, gyro, 3 * ns) ||
@@ -2584,7 +2545,7 @@ gba_status gba_vi_eval_inertial(int device, int n_kf, const double* states, cons
     const int n = n_kf > 1 ? n_kf - 1 : 0;
     if (n == 0) return GBA_OK;
     if (hipSetDevice(device) != hipSuccess) return GBA_ERR_HIP;
-    DevBufs b(sizeof(double) * (15 + gba::vi::kPreStride + 225) * (size_t)n_kf + 8192);
+    gba::vi::DevBufs b(sizeof(double) * (15 + gba::vi::kPreStride + 225) * (size_t)n_kf + 8192);
     double *ds = nullptr, *dp = nullptr, *dr = nullptr, *dj = nullptr;
     if (!b.up(&ds, states, 15 * (size_t)n_kf) || !b.up(&dp, pre, (size_t)gba::vi::kPreStride * n) ||
         !b.up(&dr, (const double*)nullptr, 9 * (size_t)n) || !b.up(&dj, (const double*)nullptr, 216 * (size_t)n))
@@ -2608,7 +2569,7 @@ gba_status gba_vi_eval_stereo(int device, int n_kf, const double* states, int64_
     for (int64_t e = 0; e < n_obs; ++e)
         if (kf[e] < 0 || kf[e] >= n_kf || pt[e] < 0 || pt[e] >= n_pts) return GBA_ERR_UNKNOWN_ID;
     if (hipSetDevice(device) != hipSuccess) return GBA_ERR_HIP;
-    DevBufs b(sizeof(double) * (15 * (size_t)n_kf + 3 * (size_t)n_pts + 35 * (size_t)n_obs) + 8192);
+    gba::vi::DevBufs b(sizeof(double) * (15 * (size_t)n_kf + 3 * (size_t)n_pts + 35 * (size_t)n_obs) + 8192);
     double *ds = nullptr, *dpts = nullptr, *dobs = nullptr, *dr = nullptr, *dj = nullptr;
     long long *dkf = nullptr, *dpt = nullptr;
     if (!b.up(&ds, states, 15 * (size_t)n_kf) || !b.up(&dpts, pts, 3 * (size_t)n_pts) ||
@@ -2669,9 +2630,13 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
     const int K = P.n_kf;
     const long long N = P.n_pts, M = P.n_obs, n = 15LL * K + 3 * N;
     const bool f32 = o.precision == GBA_MIXED_FP32;
-    // one allocation for nearly everything (about this much, see below)
-    DevBufs B((size_t)(8.0 * (8200.0 * K + 46.0 * N) + (double)M * (170.0 + (schur ? (f32 ? 4.0 : 8.0) * 37 : 32.0)) +
-                       (1 << 20)));
+    // one allocation for nearly everything: what is taken below in doubles a
+    // keyframe and a point and bytes an observation (5 % pads), and for the
+    // explicit blocks the pairs of a mean track and 20 blocks a keyframe
+    const double track = N > 0 ? (double)M / (double)N : 0.0;
+    const double per_obs = 76.0 + (schur ? (f32 ? 4.0 : 8.0) * 37 : 34.0);
+    const double blocks = schur ? 300.0 * K * std::min(20.0, (double)K) + 8.0 * 0.65 * M * std::max(0.0, track - 1.0) : 0.0;
+    gba::vi::DevBufs B((size_t)(8.0 * (1950.0 * K + 61.0 * N) + (double)M * per_obs + blocks + (1 << 20)));
     VIDev d{};
     d.K = K;
     d.N = N;
@@ -2696,7 +2661,7 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         int per = 256;
         while (per < 4096 && (items / per + 1LL) * nb > (1 << 22)) per *= 2;
         const int nblk = (int)((items + (long long)per - 1) / per);
-        if (!B.up(&counts, no_in, (size_t)nblk * nb) || !B.up(&total, no_in, (size_t)nb)) return false;
+        if (!B.scratch(&counts, no_in, (size_t)nblk * nb) || !B.scratch(&total, no_in, (size_t)nb)) return false;
         int left = items;
         const int* in = no_in;
         for (int p = 0; p < passes; ++p) {
@@ -2731,12 +2696,12 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         const double* raw = nullptr;
         int *kf = nullptr, *pt = nullptr, *first = nullptr, *cnt = nullptr, *cntn = nullptr, *renum = nullptr,
             *at = nullptr, *used = nullptr, *flag = nullptr, *tmp = nullptr;
-        if (!B.up((long long**)&kf64, (const long long*)P.kf, (size_t)M) ||
-            !B.up((long long**)&pt64, (const long long*)P.pt, (size_t)M) ||
-            !B.up((double**)&raw, P.obs, 3 * (size_t)M) || !B.up(&kf, no_in, (size_t)M) || !B.up(&pt, no_in, (size_t)M) ||
-            !B.up(&first, no_in, (size_t)N) || !B.up(&cnt, no_in, (size_t)N) || !B.up(&cntn, no_in, (size_t)N) ||
-            !B.up(&renum, no_in, (size_t)N) || !B.up(&used, no_in, (size_t)N) || !B.up(&flag, no_in, 1) ||
-            !B.up(&tmp, no_in, (size_t)std::max(N, M)))
+        if (!B.scratch((long long**)&kf64, (const long long*)P.kf, (size_t)M) ||
+            !B.scratch((long long**)&pt64, (const long long*)P.pt, (size_t)M) ||
+            !B.scratch((double**)&raw, P.obs, 3 * (size_t)M) || !B.scratch(&kf, no_in, (size_t)M) || !B.scratch(&pt, no_in, (size_t)M) ||
+            !B.scratch(&first, no_in, (size_t)N) || !B.scratch(&cnt, no_in, (size_t)N) || !B.scratch(&cntn, no_in, (size_t)N) ||
+            !B.scratch(&renum, no_in, (size_t)N) || !B.scratch(&used, no_in, (size_t)N) || !B.scratch(&flag, no_in, 1) ||
+            !B.scratch(&tmp, no_in, (size_t)std::max(N, M)))
             return GBA_ERR_OOM;
         std::vector<int> hcnt((size_t)N), hat((size_t)N + 1, 0);
         int h = 0;
@@ -2772,12 +2737,13 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         int *qe = nullptr, *qs = nullptr, *qkf = nullptr, *qpt = nullptr, *key = nullptr, *dkf = nullptr, *dpt = nullptr,
             *ks = nullptr, *ko = nullptr;
         double *qobs = nullptr, *obs = nullptr;
-        if (!B.up(&at, (const int*)hat.data(), (size_t)N) || !B.up(&qe, no_in, (size_t)Mp) ||
-            !B.up(&qs, no_in, (size_t)Mp) || !B.up(&qkf, no_in, (size_t)Mp + 1) || !B.up(&qpt, no_in, (size_t)Mp + 1) ||
+        // (the kept ones first: they may open a chunk, and scratch stays behind)
+        if (!B.up(&qkf, no_in, (size_t)Mp + 1) || !B.up(&qpt, no_in, (size_t)Mp + 1) ||
             !B.up(&key, no_in, (size_t)Mp) || !B.up(&qobs, (const double*)nullptr, 3 * (size_t)Mp + 1) ||
             !B.up(&dkf, no_in, (size_t)M + 1) || !B.up(&dpt, no_in, (size_t)M + 1) ||
             !B.up(&obs, (const double*)nullptr, 3 * (size_t)M + 1) || !B.up(&ks, no_in, (size_t)M) ||
-            !B.up(&ko, no_in, (size_t)K + 1))
+            !B.up(&ko, no_in, (size_t)K + 1) || !B.scratch(&at, (const int*)hat.data(), (size_t)N) ||
+            !B.scratch(&qe, no_in, (size_t)Mp) || !B.scratch(&qs, no_in, (size_t)Mp))
             return GBA_ERR_OOM;
         if (M > 0) {
             hipLaunchKernelGGL(k_vo_fill, grid(Mp + 1), blk, 0, nullptr, Mp + 1, qpt, -1);
@@ -2804,6 +2770,7 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         d.kinv = key;
         d.kfoff = ko;
     }
+    B.drop_scratch();
     if (!B.up(&d.st, (const double*)nullptr, kSt * (size_t)K) ||
         !B.up(&d.st_c, (const double*)nullptr, kSt * (size_t)K) ||
         !B.up(&d.info, (const double*)nullptr, 81 * (size_t)(K - 1)) ||

@@ -5,10 +5,41 @@
 
 #include <cmath>
 #include <cstdio>
+#include <cstdlib>
+#include <cstring>
 #include <random>
 
 #include "gba_host.hip"
 #include "gba_vi_rule.h"
+
+// the buffers' allocations and copies, on the host
+#include <map>
+static std::map<char*, size_t> g_blocks;
+static size_t g_limit = ~(size_t)0;
+static hipError_t host_malloc(void** p, size_t n) {
+    if (n > g_limit) return hipErrorOutOfMemory;
+    *p = std::aligned_alloc(256, (n + 255) & ~(size_t)255);
+    g_blocks[(char*)*p] = n;
+    return hipSuccess;
+}
+static hipError_t host_free(void* p) {
+    g_blocks.erase((char*)p);
+    std::free(p);
+    return hipSuccess;
+}
+static hipError_t host_copy(void* d, const void* s, size_t n, hipMemcpyKind) {
+    std::memcpy(d, s, n);
+    return hipSuccess;
+}
+#define hipMalloc host_malloc
+#define hipFree host_free
+#define hipMemcpy host_copy
+#define hipGetLastError() hipSuccess
+#include "gba_vi_bufs.h"
+#undef hipMalloc
+#undef hipFree
+#undef hipMemcpy
+#undef hipGetLastError
 
 namespace gba {
 #define GBA_STUB(name, ...)                                        \
@@ -176,6 +207,47 @@ static void check_vi_blocks() {
     CHECK(!pay(2'070'000, 7'000'000, 24'000, 0, 1));
 }
 
+// Buffers of a call: 256-byte aligned, inside an allocation, disjoint while they
+// live; scratch memory is reused after it is dropped, whatever the expected size
+// and also where allocations of the expected size fail.
+static void check_buffers() {
+    std::mt19937_64 rng(7);
+    for (int it = 0; it < 400; ++it) {
+        g_limit = it % 4 == 3 ? 20'000 : ~(size_t)0;   // larger allocations fail
+        {
+            vi::DevBufs b(1 + rng() % 200'000);
+            struct Live {
+                char* p;
+                size_t n;
+                bool scratch;
+            };
+            std::vector<Live> live;
+            std::vector<char> src(12'000, 'x');
+            for (int k = 0; k < 60; ++k) {
+                if (rng() % 12 == 0) {
+                    b.drop_scratch();
+                    live.erase(std::remove_if(live.begin(), live.end(), [](const Live& l) { return l.scratch; }),
+                               live.end());
+                    continue;
+                }
+                char* p = nullptr;
+                const size_t n = rng() % 12'000;
+                const bool scratch = rng() % 3 == 0, copy = rng() % 2 == 0;
+                CHECK(scratch ? b.scratch(&p, copy ? src.data() : nullptr, n)
+                              : b.up(&p, copy ? src.data() : nullptr, n));
+                CHECK((uintptr_t)p % 256 == 0);
+                auto blk = g_blocks.upper_bound(p);
+                CHECK(blk != g_blocks.begin());
+                --blk;
+                CHECK(p + n <= blk->first + blk->second);
+                for (const Live& l : live) CHECK(p + n <= l.p || l.p + l.n <= p || n == 0 || l.n == 0);
+                live.push_back({p, n, scratch});
+            }
+        }
+        CHECK(g_blocks.empty());
+    }
+}
+
 // The residual exchange of the one-workgroup PCG stays among the entries that
 // the wavefront's row owners have written, for every lane.
 static void check_exchange() {
@@ -190,6 +262,7 @@ static void check_exchange() {
 int main() {
     check_exchange();
     check_vi_blocks();
+    check_buffers();
     // the arguments of a recorded iteration's kernels without the explicit systems' part
     CHECK(sizeof(KernelGraph) <= 848 && sizeof(DeviceGraph) > sizeof(KernelGraph));
     check_point_side();
