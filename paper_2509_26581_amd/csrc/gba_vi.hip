@@ -2649,11 +2649,11 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         return err == hipSuccess;
     };
     const int* no_in = nullptr;
-    // items sorted by key (0 .. nkeys - 1, stable; negative keys left out),
-    // 12 bits a pass; tmp: as many items.  A workgroup places its items 64 at
+    // items (of in, or 0, 1, ...) sorted by key (0 .. nkeys - 1, stable; negative
+    // keys left out), 12 bits a pass; tmp: as many items.  A workgroup places its items 64 at
     // a time in order, so short arrays are cut finer (109 us at 17,000 items
     // with 4096 each), as far as the counts stay within 4M.
-    auto sort_by = [&](int items, int kept, const int* key, int nkeys, int* out, int* tmp) {
+    auto sort_by = [&](const int* in, int items, int kept, const int* key, int nkeys, int* out, int* tmp) {
         int passes = 1;
         while (((nkeys - 1) >> (kSortBits * passes)) > 0) ++passes;
         int *counts = nullptr, *total = nullptr;
@@ -2663,7 +2663,6 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         const int nblk = (int)((items + (long long)per - 1) / per);
         if (!B.scratch(&counts, no_in, (size_t)nblk * nb) || !B.scratch(&total, no_in, (size_t)nb)) return false;
         int left = items;
-        const int* in = no_in;
         for (int p = 0; p < passes; ++p) {
             int* to = (passes - 1 - p) % 2 == 0 ? out : tmp;
             const int nbl = (int)((left + (long long)per - 1) / per), shift = kSortBits * p;
@@ -2714,7 +2713,7 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
             // ids that are not there end the call before they index anything
             if (!chk() || hipMemcpy(&h, flag, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess) return GBA_ERR_HIP;
             if (h != 0) return GBA_ERR_UNKNOWN_ID;
-            if (!sort_by((int)N, (int)N, first, K + 1, pt_old, tmp)) return GBA_ERR_HIP;
+            if (!sort_by(no_in, (int)N, (int)N, first, K + 1, pt_old, tmp)) return GBA_ERR_HIP;
             hipLaunchKernelGGL(k_vo_points, grid(N), blk, 0, nullptr, (int)N, (const int*)pt_old, (const int*)cnt,
                                (const double*)Xraw, renum, cntn, d.X);
             if (!chk() || hipMemcpy(hcnt.data(), cntn, sizeof(int) * N, hipMemcpyDeviceToHost) != hipSuccess)
@@ -2751,9 +2750,25 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
                                (const int*)at, used, qe, qpt);
             hipLaunchKernelGGL(k_vo_rank, grid(Mp), blk, 0, nullptr, Mp, (const int*)qpt, (const int*)at,
                                (const int*)cntn, (const int*)kf, (const int*)qe, qs);
+            if (!hlong.empty()) {
+                const int nl = (int)hlslot.size();
+                std::vector<int> hof((size_t)N, -1);
+                for (size_t q = 0; q < hlong.size(); ++q) hof[(size_t)hlong[q]] = (int)q;
+                int *of = nullptr, *key_kf = nullptr, *key_pt = nullptr, *by_kf = nullptr, *sorted = nullptr, *slot = nullptr;
+                if (!B.scratch(&of, (const int*)hof.data(), (size_t)N) || !B.scratch(&key_kf, no_in, (size_t)M) ||
+                    !B.scratch(&key_pt, no_in, (size_t)M) || !B.scratch(&by_kf, no_in, (size_t)nl) ||
+                    !B.scratch(&sorted, no_in, (size_t)nl) || !B.scratch(&slot, (const int*)hlslot.data(), (size_t)nl))
+                    return GBA_ERR_OOM;
+                hipLaunchKernelGGL(k_vo_long_keys, grid(M), blk, 0, nullptr, M, (const int*)kf, (const int*)pt,
+                                   (const int*)renum, (const int*)of, key_kf, key_pt);
+                if (!sort_by(no_in, (int)M, nl, key_kf, K, by_kf, tmp) ||
+                    !sort_by(by_kf, nl, nl, key_pt, (int)hlong.size(), sorted, tmp))
+                    return GBA_ERR_HIP;
+                hipLaunchKernelGGL(k_vo_long_place, grid(nl), blk, 0, nullptr, nl, (const int*)sorted, (const int*)slot, qs);
+            }
             hipLaunchKernelGGL(k_vo_slots, grid(Mp), blk, 0, nullptr, Mp, (const int*)qs, (const int*)qpt,
                                (const int*)kf, raw, qkf, key, qobs, flag);
-            if (!sort_by((int)Mp, (int)M, key, K, ks, tmp)) return GBA_ERR_HIP;
+            if (!sort_by(no_in, (int)Mp, (int)M, key, K, ks, tmp)) return GBA_ERR_HIP;
             hipLaunchKernelGGL(k_vo_kf, grid(M), blk, 0, nullptr, (int)M, K, (const int*)ks, (const int*)qkf,
                                (const int*)qpt, (const double*)qobs, dkf, dpt, obs, key, ko);
             if (!chk() || hipMemcpy(&h, flag, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess) return GBA_ERR_HIP;

@@ -154,8 +154,9 @@ __global__ __launch_bounds__(256) void k_vo_place(long long n, const int* __rest
     qpt[s] = j;
 }
 
-// each run by keyframe, then input order: a slot's place is the number of
-// smaller ones in its run
+// each run of at most 64 observations by keyframe, then input order: a slot's
+// place is the number of smaller ones in its run (the work grows with the square
+// of a run: longer ones are sorted, k_vo_long_keys)
 __global__ __launch_bounds__(256) void k_vo_rank(long long np, const int* __restrict__ qpt, const int* __restrict__ at,
                                                 const int* __restrict__ cnt, const int* __restrict__ kf,
                                                 const int* __restrict__ qe, int* __restrict__ qs) {
@@ -166,6 +167,7 @@ __global__ __launch_bounds__(256) void k_vo_rank(long long np, const int* __rest
         qs[i] = -1;
         return;
     }
+    if (cnt[j] > 64) return;   // k_vo_long_place's
     const int lo = at[j], hi = lo + cnt[j], e = qe[i], k = kf[e];
     int r = 0;
     for (int u = lo; u < hi; ++u) {
@@ -173,6 +175,27 @@ __global__ __launch_bounds__(256) void k_vo_rank(long long np, const int* __rest
         r += (m < k || (m == k && f < e)) ? 1 : 0;
     }
     qs[lo + r] = e;
+}
+
+// The observations of the longer runs are sorted by keyframe, then by point
+// (both stable, so a run ends by keyframe, then input order).  keys: an
+// observation's keyframe and its point's number among the long ones, -1 for the
+// others; long_of: that number per point (-1: not long)
+__global__ __launch_bounds__(256) void k_vo_long_keys(long long n, const int* __restrict__ kf, const int* __restrict__ pt,
+                                                     const int* __restrict__ renum, const int* __restrict__ long_of,
+                                                     int* __restrict__ key_kf, int* __restrict__ key_pt) {
+    const long long e = blockIdx.x * 256LL + threadIdx.x;
+    if (e >= n) return;
+    const int l = long_of[renum[pt[e]]];
+    key_kf[e] = l < 0 ? -1 : kf[e];
+    key_pt[e] = l;
+}
+
+// sorted observations to the slots of the long runs (in the same order)
+__global__ __launch_bounds__(256) void k_vo_long_place(int n, const int* __restrict__ sorted, const int* __restrict__ slot,
+                                                      int* __restrict__ qs) {
+    const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (i < n) qs[slot[i]] = sorted[i];
 }
 
 // the point-order arrays; twice is set when a keyframe observes a point more
