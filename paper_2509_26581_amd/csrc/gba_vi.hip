@@ -2625,7 +2625,14 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
         !(o.min_diag > 0.0) || !(o.max_diag >= o.min_diag))
         return GBA_ERR_INVALID_ARG;
     if (P.n_pts == 0 && P.n_obs > 0) return GBA_ERR_UNKNOWN_ID;
-    if (hipSetDevice(device) != hipSuccess) return GBA_ERR_HIP;
+    // Unknown ids are found on the device; where the call ends before that, they
+    // are looked for here and name its status as they do otherwise.
+    auto refuse = [&](gba_status st) {
+        for (int64_t e = 0; e < P.n_obs; ++e)
+            if (P.kf[e] < 0 || P.kf[e] >= P.n_kf || P.pt[e] < 0 || P.pt[e] >= P.n_pts) return (gba_status)GBA_ERR_UNKNOWN_ID;
+        return st;
+    };
+    if (hipSetDevice(device) != hipSuccess) return refuse(GBA_ERR_HIP);
     const bool schur = o.solver == GBA_SOLVER_SCHUR;
     const int K = P.n_kf;
     const long long N = P.n_pts, M = P.n_obs, n = 15LL * K + 3 * N;
@@ -2685,7 +2692,7 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
     if (!B.up(&s15, P.states, 15 * (size_t)K) || !B.up(&pre, P.pre, (size_t)kPreStride * (K - 1)) ||
         !B.up(&Xraw, P.pts, 3 * (size_t)N) || !B.up(&d.X, (const double*)nullptr, 3 * (size_t)N) ||
         !B.up(&d.X_c, (const double*)nullptr, 3 * (size_t)N + 1) || !B.up(&pt_old, no_in, (size_t)N + 1))
-        return GBA_ERR_OOM;
+        return refuse(GBA_ERR_OOM);
     {
         // The orders, on the device (gba_vi_order.h).  Points are renumbered
         // by the first keyframe that observes them (stable; unobserved points
@@ -2701,7 +2708,7 @@ gba_status gba_vi_solve(int device, const gba_vi_problem* prob, int max_iters, d
             !B.scratch(&first, no_in, (size_t)N) || !B.scratch(&cnt, no_in, (size_t)N) || !B.scratch(&cntn, no_in, (size_t)N) ||
             !B.scratch(&renum, no_in, (size_t)N) || !B.scratch(&used, no_in, (size_t)N) || !B.scratch(&flag, no_in, 1) ||
             !B.scratch(&tmp, no_in, (size_t)std::max(N, M)))
-            return GBA_ERR_OOM;
+            return refuse(GBA_ERR_OOM);
         std::vector<int> hcnt((size_t)N), hat((size_t)N + 1, 0);
         int h = 0;
         hipLaunchKernelGGL(k_vo_fill, dim3(1), blk, 0, nullptr, 1LL, flag, 0);
