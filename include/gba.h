@@ -113,7 +113,9 @@ typedef struct gba_options {
                                   |r_k| > ratio * min_m<=k |r_m|; <= 0 or Inf
                                   disables (default: disabled)               */
     int precond;               /* gba_precond (BLOCK_JACOBI)                 */
-    int timing;                /* 1: time phases with HIP events (0)         */
+    int timing;                /* 1: time phases with HIP events (0).  The
+                                  solve is the same; its launches are not
+                                  replayed from recorded graphs             */
     int accumulation;          /* camera-side sums of the Schur products:
                                   GBA_ACC_AUTO (default): one point-major pass
                                   with per-workgroup LDS partials when one
@@ -159,7 +161,8 @@ typedef struct gba_options {
                                   blocks), so it changes nothing there.  (0)  */
     int pcg_schedule;          /* how the PCG iterations of a damped step are
                                   launched: GBA_PCG_CHUNKED = chunks of
-                                  iterations (three kernels each) replayed as
+                                  iterations (product, reduction and update;
+                                  small problems fuse the last two) replayed as
                                   HIP graphs, the host checking the PCG state
                                   between chunks; GBA_PCG_PERSISTENT = one
                                   cooperative kernel runs every iteration of
@@ -172,8 +175,16 @@ typedef struct gba_options {
                                   grid barrier costs every workgroup a
                                   device-scope L2 write-back and invalidation,
                                   more than the graph's launch gaps it
-                                  replaces).  Per-phase timing (`timing`)
-                                  always launches chunks.                     */
+                                  replaces), and where it pays on the reduced
+                                  camera system S formed explicitly once a
+                                  step (GBA_ACC_AUTO, Schur solver, block
+                                  Jacobi, no camera that observes a point
+                                  twice): up to 28 cameras the whole PCG is one
+                                  workgroup's single launch, above (one
+                                  problem, up to 248 cameras) the chunks'
+                                  product is one on S and their update a second
+                                  kernel.  A given schedule keeps the point
+                                  passes.                                     */
     int jacobian;              /* GBA_JACOBIAN_ANALYTIC (0): closed-form edge
                                   Jacobians (Sec. IV-B); GBA_JACOBIAN_AUTODIFF:
                                   forward-mode automatic differentiation
@@ -230,7 +241,9 @@ typedef struct gba_report {
     double ms_precond;
     double ms_pcg;
     double ms_other;
-    double ms_matvec;          /* summed duration of the matvec kernels      */
+    double ms_matvec;          /* summed duration of the matvec kernels (0
+                                  with matvec_count 0 where the whole PCG is
+                                  one launch)                                */
     int matvec_count;
     int reserved_i;
     size_t workspace_bytes;    /* device bytes held by the graph             */
@@ -349,16 +362,21 @@ gba_status gba_eval_normal_equations(gba_graph* g, double* hcc, double* bc,
                                      double* hpp, double* bp);
 
 /* gba_eval_step: one damped step at the current parameters and damping
- * lambda, computed as the hot path does (point elimination, PCG on the
- * reduced camera system with the options' settings, back-substitution):
- * dcam[n_cams x 9], dpt[n_pts x 3]; *pcg_iters receives the PCG count. */
+ * lambda (point elimination, PCG on the reduced camera system with the
+ * options' settings, back-substitution): dcam[n_cams x 9], dpt[n_pts x 3];
+ * *pcg_iters receives the PCG count.  In FP64 it is computed as gba_solve does.
+ * In the mixed modes the PCG products are always the point passes, also where
+ * gba_solve forms S explicitly (pcg_schedule): an iterate short of convergence
+ * is defined there only to FP32 rounding times the conditioning (about 5e-5 of
+ * a step at tolerance 1e-6), and this call keeps the one it has always shown. */
 gba_status gba_eval_step(gba_graph* g, double lambda, double* dcam, double* dpt,
                          int* pcg_iters);
 
 /* gba_time_matvec (measurement): linearise at the current parameters, form
  * the damped reduced camera system at `lambda` as gba_eval_step does, run one
- * PCG iteration, then run `launches` Schur products (the PCG hot loop's
- * dominant kernel, with the iteration's stop decision it takes first) back to
+ * PCG iteration, then run `launches` Schur products by the point passes (the
+ * PCG hot loop's dominant kernel where S is not formed explicitly, with the
+ * iteration's stop decision it takes first) back to
  * back on the graph's stream between two HIP events; *avg_us receives the
  * average duration of one product in microseconds.  The parameters are not
  * changed. */
@@ -586,9 +604,10 @@ typedef struct gba_vi_options {
     double min_diag, max_diag; /* clip of the damping diagonal (1e-6, 1e32)  */
     int precision;             /* GBA_FP64 (default), or GBA_MIXED_FP32: the
                                   per-observation array the PCG products
-                                  stream (W = J_k^T J_p in the Schur form, the
-                                  whitened 3 x 9 stereo J in the whole-system
-                                  form) stored in FP32, all arithmetic and
+                                  stream (W = J_k^T J_p in the Schur form; in
+                                  the whole-system form, which makes the stereo
+                                  J from the point in the camera, its whitening
+                                  factor) stored in FP32, all arithmetic and
                                   every other array FP64                     */
     int reserved1;
     double pcg_rejection_ratio;/* stop PCG and keep the best iterate when

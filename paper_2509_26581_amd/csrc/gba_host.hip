@@ -907,9 +907,10 @@ gba_status batch_damped_step(Batch& b, const gba_options& o, const Tuning& tune,
     if (timing) HIP_OR(msg, hipEventRecord(tm->ev[1], s));
     // explicit reduced systems: S, and the whole PCG of those problems in one
     // launch; with no other problem in the batch the trial runs to its end
-    // without a host check (phase timing and a forced schedule keep the
-    // launched iterations, the identity preconditioner has no diagonal blocks)
-    const bool reduced = d.xs_on && block_jacobi && !timing && o.pcg_schedule == GBA_PCG_AUTO &&
+    // without a host check (a forced schedule keeps the launched iterations,
+    // the identity preconditioner has no diagonal blocks; phase timing takes
+    // the same path as none)
+    const bool reduced = d.xs_on && block_jacobi && o.pcg_schedule == GBA_PCG_AUTO &&
                          !b.launched_products && (b.P > 1 || reduced_pays(b.plan.one, d.mode, o));
     const bool wide = reduced && d.xs_wide;
     if (!reduced || !d.xs_all || wide) HIP_OR(msg, launch_pcg_init(d, s, o.pcg_tol, o.pcg_tol_relative));
@@ -922,12 +923,28 @@ gba_status batch_damped_step(Batch& b, const gba_options& o, const Tuning& tune,
             HIP_OR(msg, launch_pcg_reduced(d, s, o.pcg_tol, o.pcg_tol_relative, o.pcg_max_iters,
                                            o.pcg_rejection_ratio));
     }
-    if (reduced && d.xs_all && !wide) {
+    // back-substitution, the candidate's cost and the trial's sums, and the
+    // phase times
+    auto finish_trial = [&]() -> gba_status {
+        if (timing) HIP_OR(msg, hipEventRecord(tm->ev[2], s));
         HIP_OR(msg, launch_backsub(d, s));
         HIP_OR(msg, launch_cost(d, s, d.cam_c, d.pt_c));
         HIP_OR(msg, launch_finish(d, s));
-        return read_scal(b, msg);
-    }
+        if (timing) HIP_OR(msg, hipEventRecord(tm->ev[3], s));
+        gba_status st = read_scal(b, msg);
+        if (st != GBA_OK) return st;
+        if (timing) {
+            float a = 0.f, c = 0.f, e = 0.f;
+            HIP_OR(msg, hipEventElapsedTime(&a, tm->ev[0], tm->ev[1]));
+            HIP_OR(msg, hipEventElapsedTime(&c, tm->ev[1], tm->ev[2]));
+            HIP_OR(msg, hipEventElapsedTime(&e, tm->ev[2], tm->ev[3]));
+            tm->ms_phase[1] += a;
+            tm->ms_phase[2] += c;
+            tm->ms_phase[3] += e;
+        }
+        return GBA_OK;
+    };
+    if (reduced && d.xs_all && !wide) return finish_trial();
     // one cooperative launch for every PCG iteration (the trial then runs to
     // its end without a host check), or chunks of launched iterations
     bool persistent = false;
@@ -1055,23 +1072,7 @@ gba_status batch_damped_step(Batch& b, const gba_options& o, const Tuning& tune,
         if (all_done) break;
     }
     b.last_pcg_iters = last_iters;
-    if (timing) HIP_OR(msg, hipEventRecord(tm->ev[2], s));
-    HIP_OR(msg, launch_backsub(d, s));
-    HIP_OR(msg, launch_cost(d, s, d.cam_c, d.pt_c));
-    HIP_OR(msg, launch_finish(d, s));
-    if (timing) HIP_OR(msg, hipEventRecord(tm->ev[3], s));
-    gba_status st = read_scal(b, msg);
-    if (st != GBA_OK) return st;
-    if (timing) {
-        float a = 0.f, c = 0.f, e = 0.f;
-        HIP_OR(msg, hipEventElapsedTime(&a, tm->ev[0], tm->ev[1]));
-        HIP_OR(msg, hipEventElapsedTime(&c, tm->ev[1], tm->ev[2]));
-        HIP_OR(msg, hipEventElapsedTime(&e, tm->ev[2], tm->ev[3]));
-        tm->ms_phase[1] += a;
-        tm->ms_phase[2] += c;
-        tm->ms_phase[3] += e;
-    }
-    return GBA_OK;
+    return finish_trial();
 }
 
 gba_status batch_time_matvec(Batch& b, const gba_options& o, int launches, double* ms,

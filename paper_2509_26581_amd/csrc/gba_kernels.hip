@@ -2492,8 +2492,10 @@ hipError_t launch_pcg_iter(const DeviceGraph& g, hipStream_t s, double min_diag,
                            int max_iters, double ratio, hipEvent_t ev0, hipEvent_t ev1) {
     if (g.nc == 0) return hipSuccess;
     if (g.xs_rows) {   // on the explicit reduced system: product and update
+        if (ev0) (void)hipEventRecord(ev0, s);
         hipError_t e = launch_reduced_product(g, s, max_iters, ratio);
         if (e != hipSuccess) return e;
+        if (ev1) (void)hipEventRecord(ev1, s);
         if (g.mode == kModeFP64)
             hipLaunchKernelGGL(k_pcg_apply_s<double>, dim3(g.dc_cam.nblk), dim3(kPcgBlock), 0, s, g, g.xs_rows);
         else

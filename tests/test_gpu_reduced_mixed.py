@@ -81,3 +81,27 @@ def test_points_with_nearly_parallel_rays():
     a, b = reps
     assert a.accepted == b.accepted == 1 and a.pcg_iters_total == b.pcg_iters_total == 6
     assert abs(a.final_cost - b.final_cost) <= 1e-2 * b.final_cost
+
+
+@pytest.mark.parametrize("precision", [gba.GBA_FP64, gba.GBA_MIXED_FP32, gba.GBA_MIXED_BF16])
+@pytest.mark.parametrize("n_cams,n_pts", [(12, 800), (60, 3000)])
+def test_timing_takes_the_same_path(n_cams, n_pts, precision):
+    # phase timing observes the solve that runs without it: the same iterates
+    # to rounding (1e-12; 1e-6 where vectors are FP32)
+    sc = synth.make_scene("small", seed=2, n_cams=n_cams, n_pts=n_pts, layout="sphere")
+    got = []
+    for timing in (0, 1):
+        g = gba.Graph.from_arrays(sc.cams0, sc.pts0, sc.cam_idx, sc.pt_idx, sc.obs, loss=gba.GBA_LOSS_HUBER,
+                                  delta=1.0, precision=precision,
+                                  options=gba.options(pcg_max_iters=30, pcg_tol=1e-4, timing=timing))
+        rep = g.solve(4)
+        got.append((g.cameras(), g.points(), rep.pcg_iters_total))
+        if timing:
+            assert rep.ms_pcg > 0.0 and rep.ms_precond > 0.0 and rep.ms_other > 0.0
+            # one launch up to 28 cameras (no products of their own), else one a step
+            assert rep.matvec_count == 0 if n_cams <= 28 else rep.matvec_count >= rep.pcg_iters_total
+        g.close()
+    assert got[0][2] == got[1][2]
+    scale = 1e-12 if precision == gba.GBA_FP64 else 1e-6
+    for a, b in zip(got[0][:2], got[1][:2]):
+        assert np.linalg.norm(a - b) <= scale * np.linalg.norm(b)
