@@ -179,11 +179,13 @@ typedef struct gba_options {
                                   camera system S formed explicitly once a
                                   step (GBA_ACC_AUTO, Schur solver, block
                                   Jacobi, no camera that observes a point
-                                  twice): up to 28 cameras the whole PCG is one
-                                  workgroup's single launch, above (one
-                                  problem, up to 248 cameras) the chunks'
-                                  product is one on S and their update a second
-                                  kernel.  A given schedule keeps the point
+                                  twice): up to 28 cameras (mixed modes: 32,
+                                  and 56 where several problems share a batch)
+                                  the whole PCG is one workgroup's single
+                                  launch, above (one problem, up to 248
+                                  cameras; mixed 348) the chunks' product is
+                                  one on S and their update a second kernel.
+                                  A given schedule keeps the point
                                   passes.                                     */
     int jacobian;              /* GBA_JACOBIAN_ANALYTIC (0): closed-form edge
                                   Jacobians (Sec. IV-B); GBA_JACOBIAN_AUTODIFF:

@@ -46,7 +46,7 @@ struct ImageCounts {
 
 // Whether a problem's explicit reduced system is formed (see gba_host.hip)
 struct Tuning;
-bool reduced_rule(const ImageCounts& n, const Tuning& tune);
+bool reduced_rule(const ImageCounts& n, const Tuning& tune, int precision);
 bool reduced_wide_rule(const ImageCounts& n, const Tuning& tune, int precision);
 // Whether forming it pays under these options (one of the rules above holds)
 bool reduced_pays(const ImageCounts& n, int precision, const gba_options& o);

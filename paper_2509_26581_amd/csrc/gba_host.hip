@@ -254,12 +254,14 @@ gba_status make_image(const HostProblem& h, HostImage& img, std::string& msg) {
 // The explicit reduced system (gba_reduced.hip): when the camera sums are
 // left to the library, the points are eliminated, no camera observes a point
 // twice (the rank bitmaps hold one edge per camera and point) and S has at
-// most kReducedMax rows.  A launched PCG iteration takes 14-16 us for small
+// most reduced_max rows.  A launched PCG iteration takes 14-16 us for small
 // problems whatever their size; one workgroup's iteration on S takes 1.6 us at
-// 12 cameras, 4.4 at 18 and 6.6 at 28 (S then comes from the L2 in part).  Past
-// 28 cameras one CU's reads of S set the pace: at 32, 40 and 48 cameras whole
-// solves are 1.0, 0.85 and 0.73 times as fast as with launched iterations,
-// where launched iterations on S (below) make them 1.4 to 1.7 times as fast.
+// 12 cameras, 4.4 at 18 and 6.6 at 28 (FP64: S then comes from the L2 in part).
+// Past 28 cameras one CU's reads of S set the pace: in FP64, whole solves at 32,
+// 40 and 48 cameras are 1.0, 0.85 and 0.73 times as fast as with launched
+// iterations.  The mixed modes read half the bytes: served requests of 29, 40,
+// 48 and 56 keyframes are 2.2, 1.7, 1.4 and 1.25 times as fast as with launched
+// iterations.  A single problem has launched iterations on S as well (below).
 // A block of S is one workgroup's walk over its first camera's edges, 6.5 ns
 // (mixed) to 8 ns (FP64) an edge, so few cameras with many edges are bounded
 // too: four-trial solves at 2,000, 10,000, 16,000 and 24,000 edges a camera are
@@ -267,26 +269,29 @@ gba_status make_image(const HostProblem& h, HostImage& img, std::string& msg) {
 // (2.9-3.6, 1.9-2.7, 1.6-2.6 and 1.2-2.4 with about 25), and with one free
 // camera, whose step takes one iteration, 1.2-1.5 at 2,000, 1.0-1.2 at 5,000 and
 // 0.8-1.0 at 10,000 (0.2 at 200,000).
-bool reduced_rule(const ImageCounts& n, const Tuning& tune) {
+bool reduced_rule(const ImageCounts& n, const Tuning& tune, int precision) {
     if (tune.accumulation != GBA_ACC_AUTO || tune.deterministic || tune.solver == GBA_SOLVER_FULL) return false;
-    return n.nc > 0 && n.ne > 0 && n.n_runs == n.ne && 9 * n.nc <= kReducedMax &&
+    return n.nc > 0 && n.ne > 0 && n.n_runs == n.ne && 9 * n.nc <= reduced_max(precision) &&
            n.cam_edges <= (n.free_cams > 1 ? 20'000 : 5'000);
 }
 
 // The same for a single larger problem, whose launched PCG iterations then
-// multiply by S instead of taking the point pass and its reduction.  Whole
-// solves (8 trials of about 35 iterations, mixed FP32 and FP64) against the
+// multiply by S instead of taking the point pass and its reduction.  From 29
+// (mixed: 33) cameras on that is faster than one workgroup: mixed, whole solves
+// of 1,600 to 25,600 points, one workgroup and launched, 1.49-1.76 and 1.46-1.80
+// ms at 32 cameras, 1.85-2.03 and 1.54-1.91 at 40, 2.14-2.69 and 1.75-2.09 at 48.
+// Whole solves (8 trials of about 35 iterations, mixed FP32 and FP64) against the
 // point passes: 1.5 and 1.6 times as fast at 60 and 90 cameras, 1.4 and 1.5 at
-// 130, 1.3 and 1.4 at 203, 1.13 and 1.2 at 240, 0.95 and 0.98 at 300: S is read
-// in every iteration, FP64 in every mode, so it is bounded to 40 MB (248
-// cameras).  Forming it takes about 60 ps (mixed) and 120 ps (FP64) a pair of a
+// 130, 1.3 and 1.4 at 203, 1.25 and 1.25 at 240, 1.2 and 0.98 at 300, mixed 1.1
+// at 340: S is read in every iteration, so it is bounded to 40 MB (248 cameras,
+// mixed 348).  Forming it takes about 60 ps (mixed) and 120 ps (FP64) a pair of a
 // point's edges and step (FP64, 260 cameras, 2M pairs: no gain left), so the
 // pairs are bounded too.
 bool reduced_wide_rule(const ImageCounts& n, const Tuning& tune, int precision) {
     if (tune.accumulation != GBA_ACC_AUTO || tune.deterministic || tune.solver == GBA_SOLVER_FULL) return false;
-    if (n.nc <= 0 || n.ne <= 0 || n.n_runs != n.ne || 9 * n.nc <= kReducedMax) return false;
+    if (n.nc <= 0 || n.ne <= 0 || n.n_runs != n.ne || n.nc <= (precision == GBA_FP64 ? 28 : 32)) return false;
     const long long word = precision == GBA_FP64 ? 8 : 4;
-    return 9LL * n.nc * reduced_ld(9 * n.nc) * (long long)sizeof(double) <= 40'000'000 && n.pairs * word <= 12'000'000;
+    return 9LL * n.nc * reduced_ld(9 * n.nc) * word <= 40'000'000 && n.pairs * word <= 12'000'000;
 }
 
 // S pays when forming it takes no longer than a step's PCG iterations save.
@@ -305,9 +310,9 @@ bool reduced_pays(const ImageCounts& n, int precision, const gba_options& o) {
     if (o.pcg_tol_relative && o.pcg_tol > 0.0) its = std::min(its, std::max(1.0, -4.0 * std::log10(o.pcg_tol)));
     const bool f64 = precision == GBA_FP64;
     const double ne = n.ne;
-    if (9 * n.nc <= kReducedMax) return 0.008 * n.cam_edges <= 50.0 + 12.0 * its;
+    if (!n.wide) return 0.008 * n.cam_edges <= 50.0 + 12.0 * its;
     const double form = 8.0 + (f64 ? 150e-6 : 60e-6) * ne + (f64 ? 130e-6 : 65e-6) * (double)n.pairs;
-    const double s_mb = 9.0 * n.nc * reduced_ld(9 * n.nc) * sizeof(double) * 1e-6;
+    const double s_mb = 9.0 * n.nc * reduced_ld(9 * n.nc) * (f64 ? 8e-6 : 4e-6);
     const double saved = (f64 ? 15.0 : 12.0) + (f64 ? 30e-6 : 17e-6) * ne - std::max(4.0, s_mb / 5.2);
     return form <= its * saved;
 }
@@ -596,7 +601,7 @@ size_t layout_union(const UnionPlan& u, int precision, void* base, DeviceGraph* 
         L.add(d.xs_off, sizeof(long long) * P);
         L.add(d.xs_rank_off, sizeof(long long) * P);
         L.add(d.prob_pt_off, sizeof(int) * (P + 1));
-        L.add(d.xs_S, sizeof(double) * (size_t)u.xs_total);
+        L.add(d.xs_S, tsz * (size_t)u.xs_total);
         L.add(d.xs_diag, sizeof(double) * 45 * NC);
         L.add(d.xs_rank, sizeof(RankWord) * (size_t)u.xs_rank_total);
         if (u.xs_wide) {
@@ -709,8 +714,8 @@ gba_status build_batch(const std::vector<const HostProblem*>& probs, int precisi
     for (int p = 0; p < P; ++p) {
         gba_status st = make_image(*probs[p], imgs[p], msg);
         if (st != GBA_OK) return st;
-        imgs[p].n.reduced = reduced_rule(imgs[p].n, tune);
         imgs[p].n.wide = P == 1 && reduced_wide_rule(imgs[p].n, tune, precision);
+        imgs[p].n.reduced = !imgs[p].n.wide && reduced_rule(imgs[p].n, tune, precision);
         counts[p] = &imgs[p].n;
     }
     gba_status st = plan_union(counts, tune, dev, precision, b.plan, msg);

@@ -42,10 +42,10 @@ __host__ __device__ constexpr int sym3(int r, int c) {
 }
 
 // The explicit reduced system of small problems (gba_reduced.hip), whose PCG
-// is one workgroup's: at most kReducedMax unknowns (two row wavefronts of 128
-// rows; half of S then sits in the CU's registers), columns padded to whole
-// wavefronts.
-constexpr int kReducedMax = 256;
+// is one workgroup's: at most this many unknowns (two row wavefronts of 128
+// rows in FP64, four in the mixed modes, whose S is FP32), columns padded to
+// whole wavefronts.
+constexpr int reduced_max(int precision) { return precision == 0 ? 256 : 512; }
 __host__ __device__ constexpr int reduced_ld(int n) { return (n + kWave - 1) / kWave * kWave; }
 constexpr int kEdgeRec = 32;   // entries of an edge's record (DeviceGraph::xs_edge)
 // out = J_p Hpp^-1 (2 x 3); h: the inverse's upper triangle (00 01 02 11 12 22)
@@ -284,7 +284,8 @@ struct DeviceGraph : KernelGraph {
     const long long* xs_off;       // [P] offset of S in xs_S (entries), negative: products stay implicit
     const long long* xs_rank_off;  // [P] offset of the rank bitmaps in xs_rank
     const int* prob_pt_off;        // [P + 1] point range of each problem
-    double* xs_S;             // per problem a dense symmetric matrix, columns of reduced_ld(9 nc_p)
+    void* xs_S;               // per problem a dense symmetric matrix (block type), columns of
+                              // reduced_ld(9 nc_p)
     double* xs_diag;          // [nc][45] diagonal blocks of S (zero in xs_S)
     RankWord* xs_rank;        // per problem [nc_p][rank_words(np_p)]
     // xs_wide: the common points of every camera pair i < k, by i nc + k:

@@ -545,15 +545,15 @@ __global__ __launch_bounds__(64) void k_cam_finalize(DeviceGraph g, double min_d
     // an explicit reduced system's diagonal block (a fixed camera's stays
     // zero: its residual and preconditioner are)
     const long long xs = g.xs_on ? g.xs_off[g.cam_prob[i]] : -1;
-    double* S = nullptr;
+    T* S = nullptr;
     int ld = 0;
     if (xs >= 0) {
         const int c0 = g.prob_cam_off[g.cam_prob[i]];
         ld = reduced_ld(9 * (g.prob_cam_off[g.cam_prob[i] + 1] - c0));
-        S = g.xs_S + xs + (size_t)(9 * (i - c0)) * ld + 9 * (i - c0);
+        S = (T*)g.xs_S + xs + (size_t)(9 * (i - c0)) * ld + 9 * (i - c0);
     }
     if (S) {
-        for (int e = k; e < 81; e += 64) S[(size_t)(e / 9) * ld + e % 9] = 0.0;
+        for (int e = k; e < 81; e += 64) S[(size_t)(e / 9) * ld + e % 9] = (T)0;
         if (fixed && k < 45) g.xs_diag[45 * (size_t)i + k] = 0.0;
     }
     if (fixed || !block_jacobi) {

@@ -138,7 +138,7 @@ __global__ __launch_bounds__(256) void k_reduced_blocks(DeviceGraph g) {
     const int p0 = g.prob_pt_off[prob], nw = rank_words(g.prob_pt_off[prob + 1] - p0);
     const int n = 9 * nc, ld = reduced_ld(n);
     const int q0 = cam_edge_begin(g, a), q1 = cam_edge_begin(g, a + 1);
-    double* __restrict__ S = g.xs_S + off;
+    T* __restrict__ S = (T*)g.xs_S + off;
     int* qa = qa_s[w];
     int* qb = qb_s[w];
     for (int k = i + 1 + (int)blockIdx.y; k < nc; k += (int)gridDim.y) {   // uniform
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256) void k_reduced_blocks(DeviceGraph g) {
         for (int v = 0; v < kRegsOut; ++v) red[w][v * kWave + rev6(l)] = acc[v];
         __syncthreads();
         for (int u = (int)threadIdx.x; u < kSums; u += (int)blockDim.x) {
-            const double sum = -((red[0][u] + red[1][u]) + (red[2][u] + red[3][u]));
+            const T sum = (T)(-((red[0][u] + red[1][u]) + (red[2][u] + red[3][u])));
             const int row = 9 * i + u / 9, col = 9 * k + u % 9;
             S[(size_t)col * ld + row] = sum;
             S[(size_t)row * ld + col] = sum;
@@ -365,14 +365,14 @@ __global__ __launch_bounds__(256) void k_reduced_pairs(DeviceGraph g) {
     group_sum_scatter<kLanes>(acc);   // sum u in lane group_rev(u % kLanes), register u / kLanes
     if (m0 == m1) return;
     const int ld = reduced_ld(9 * g.nc);
-    double* __restrict__ S = g.xs_S;
+    T* __restrict__ S = (T*)g.xs_S;
 #pragma unroll
     for (int v = 0; v < (kSums + kLanes - 1) / kLanes; ++v) {
         const int u = v * kLanes + group_rev<kLanes>(l);
         if (u < kSums) {
             const int row = 9 * i + u / 9, col = 9 * k + u % 9;
-            S[(size_t)col * ld + row] = -acc[v];
-            S[(size_t)row * ld + col] = -acc[v];
+            S[(size_t)col * ld + row] = (T)-acc[v];
+            S[(size_t)row * ld + col] = (T)-acc[v];
         }
     }
 }
@@ -384,14 +384,15 @@ __global__ __launch_bounds__(256) void k_reduced_pairs(DeviceGraph g) {
 // registers (the rest are read from the L2 every iteration); the direction is
 // read from LDS four columns at a time, each value used for two rows, which
 // balances the LDS reads (2 cycles a value and wavefront) with the products.
-// S, the products, their sums and the vectors are FP64 in every mode; the
-// mixed modes have FP32 where the launched iterations have it in what goes in
-// and out (right-hand side, preconditioner, solution).  With S and its sums in
-// FP32 a damped step of five cameras with 16,000 common points was four times as
-// far from the FP64 one (5.7e-5 against 1.4e-5 of its norm; launched products:
+// The products, their sums and the vectors are FP64 in every mode; the mixed
+// modes have FP32 in S's off-diagonal blocks (summed in FP64; the diagonal
+// blocks stay FP64) and where the launched iterations have it in what goes in
+// and out (right-hand side, preconditioner, solution).  With FP32 sums a damped
+// step of five cameras with 16,000 common points was 5.7e-5 of its norm from the
+// FP64 one, where it is 1.8e-5 now (FP64 blocks: 1.4e-5; launched products:
 // 1.2e-4), and over 120 served requests of 5 to 40 keyframes the points of
-// whole solves were 0.94 times as far from a 64-bit solve as the launched
-// products' (geometric mean) where they are 0.88 times now.
+// whole solves are 0.90 times as far from a 64-bit solve as the launched
+// products' (geometric mean; FP64 blocks: 0.88).
 // The vectors live in the registers of the row owners (63 rows, whole
 // cameras, per wavefront, so that the preconditioner's exchange stays inside
 // a wavefront) and an iteration is three workgroup barriers: direction,
@@ -403,17 +404,18 @@ __global__ __launch_bounds__(256) void k_reduced_pairs(DeviceGraph g) {
 // takes 14.2 us (two kernels).
 // ==========================================================================
 // four columns of the product for the two rows of a lane
-__device__ __forceinline__ void fma4(const double* __restrict__ p4, const double* __restrict__ a,
-                                     const double* __restrict__ b, double (&qa)[4], double (&qb)[4]) {
+template <typename T>
+__device__ __forceinline__ void fma4(const double* __restrict__ p4, const T* __restrict__ a,
+                                     const T* __restrict__ b, double (&qa)[4], double (&qb)[4]) {
     const double4 v = *(const double4*)p4;   // 16-byte aligned: columns start at multiples of four
-    qa[0] = fma(a[0], v.x, qa[0]);
-    qb[0] = fma(b[0], v.x, qb[0]);
-    qa[1] = fma(a[1], v.y, qa[1]);
-    qb[1] = fma(b[1], v.y, qb[1]);
-    qa[2] = fma(a[2], v.z, qa[2]);
-    qb[2] = fma(b[2], v.z, qb[2]);
-    qa[3] = fma(a[3], v.w, qa[3]);
-    qb[3] = fma(b[3], v.w, qb[3]);
+    qa[0] = fma((double)a[0], v.x, qa[0]);
+    qb[0] = fma((double)b[0], v.x, qb[0]);
+    qa[1] = fma((double)a[1], v.y, qa[1]);
+    qb[1] = fma((double)b[1], v.y, qb[1]);
+    qa[2] = fma((double)a[2], v.z, qa[2]);
+    qb[2] = fma((double)b[2], v.z, qb[2]);
+    qa[3] = fma((double)a[3], v.w, qa[3]);
+    qb[3] = fma((double)b[3], v.w, qb[3]);
 }
 
 // One problem's PCG in the first kWaves wavefronts of the workgroup (the
@@ -422,7 +424,6 @@ __device__ __forceinline__ void fma4(const double* __restrict__ p4, const double
 template <typename T, int kWaves, int kR, int kRegs, bool kStream>
 __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int prob, double tol, int relative) {
     static_assert(kRegs % 4 == 0 && kWaves <= 16, "columns are taken four at a time");
-    static_assert(kR == 1 || 128 * kR >= kReducedMax, "every row has a wavefront");
     constexpr int kG = kWaves / kR, kRows = kR * 2 * kWave;
     constexpr int kOwners = (kRows + kOwnRows - 1) / kOwnRows < kWaves ? (kRows + kOwnRows - 1) / kOwnRows : kWaves;
     __shared__ __align__(32) double p_s[kRows + kRegs + 4];
@@ -440,11 +441,11 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
     // and their sums meet zeros of the direction and no owner
     const int cpg = ((n + kG - 1) / kG + 3) & ~3;
     const int cb = min(grp * cpg, (n + 3) & ~3), ce = grp < kG ? min(n, cb + cpg) : cb;
-    const double* __restrict__ S = g.xs_S + g.xs_off[prob];
+    const T* __restrict__ S = (const T*)g.xs_S + g.xs_off[prob];
     // byte offsets of the lane's rows in a column, whose address is uniform
-    const unsigned o0 = (unsigned)(min(row0, n - 1) * sizeof(double)), o1 = (unsigned)(min(row1, n - 1) * sizeof(double));
+    const unsigned o0 = (unsigned)(min(row0, n - 1) * sizeof(T)), o1 = (unsigned)(min(row1, n - 1) * sizeof(T));
     auto entry = [&](int c, unsigned o) {
-        return *(const double*)((const char*)(S + (size_t)(min(c, n - 1) * ld)) + o);
+        return *(const T*)((const char*)(S + (size_t)(min(c, n - 1) * ld)) + o);
     };
     double s0[kRegs], s1[kRegs];
 #pragma unroll
@@ -546,7 +547,7 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
                 if (cb + u < ce) fma4(p_s + cb + u, s0 + u, s1 + u, qa, qb);   // uniform per wavefront
 #pragma unroll 1
             for (int c = cb + kRegs; kStream && c < ce; c += 4) {
-                double a[4], b[4];
+                T a[4], b[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     a[u] = entry(c + u, o0);
@@ -630,15 +631,18 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
 // A problem's class follows its own size: up to 128 rows four wavefronts
 // (one per SIMD: the scalar steps between the products, which every wavefront
 // repeats, then issue once per SIMD), above that eight, with 32 columns of a
-// group of at most 64 in registers (24 and 40 were slower: 16 and 24 cameras,
-// whole solves of 4,800 points, 1.01 and 1.27, 1.05 and 1.25 ms against 0.90
-// and 1.18) and the rest streamed from the L2.  kBig: the batch holds a problem
-// above the first class.
+// group (of at most 64 up to 256 rows, of 128 to 256 above, FP32 S only) in
+// registers, as FP64 in every mode, and the rest streamed from the L2.  More or
+// fewer registers and FP32 in them were slower: FP64, 16 and 24 cameras, whole
+// solves of 4,800 points, 24 and 40 columns 1.01 and 1.27, 1.05 and 1.25 ms
+// against 0.90 and 1.18; mixed, a served request of 40 keyframes, 24, 32, 40 and
+// 48 columns 10.5, 10.2, 11.0 and 12.3 ms; of 18 keyframes, whose products then
+// convert every entry in every iteration, FP32 registers 4.9 against 2.6.  kBig:
+// the batch holds a problem above the first class.
 constexpr int kBigWaves = 8;
-
 template <typename T, bool kBig>
 __global__ __launch_bounds__(kBig ? kBigWaves * kWave : 4 * kWave) void k_pcg_reduced(DeviceGraph g, double tol,
-                                                                                     int relative) {
+                                                                                      int relative) {
     const int prob = blockIdx.x;
     if (g.xs_off[prob] < 0 || (sizeof(T) == 8) != (g.mode == kModeFP64)) return;
     const int n = 9 * (g.prob_cam_off[prob + 1] - g.prob_cam_off[prob]);
@@ -646,7 +650,8 @@ __global__ __launch_bounds__(kBig ? kBigWaves * kWave : 4 * kWave) void k_pcg_re
         if (kBig && threadIdx.x >= 4 * kWave) return;
         pcg_reduced_body<T, 4, 1, 32, false>(g, prob, tol, relative);
     } else if constexpr (kBig) {
-        pcg_reduced_body<T, kBigWaves, 2, 32, true>(g, prob, tol, relative);
+        if (n <= 4 * kWave) pcg_reduced_body<T, kBigWaves, 2, 32, true>(g, prob, tol, relative);
+        else if constexpr (sizeof(T) == 4) pcg_reduced_body<T, kBigWaves, 4, 32, true>(g, prob, tol, relative);
     }
 }
 
@@ -663,7 +668,7 @@ __global__ __launch_bounds__(kBig ? kBigWaves * kWave : 4 * kWave) void k_pcg_re
 constexpr int kReducedProductBlock = 5 * kWave;
 template <typename T>
 __global__ __launch_bounds__(kReducedProductBlock) void k_reduced_product(KernelGraph g,
-                                                                          const double* __restrict__ S,
+                                                                          const void* __restrict__ Sv,
                                                                           const double* __restrict__ D) {
     if ((sizeof(T) == 8) != (g.mode == kModeFP64)) return;
     constexpr int kWaves = 4;
@@ -704,8 +709,9 @@ __global__ __launch_bounds__(kReducedProductBlock) void k_reduced_product(Kernel
         if (l == 0) g.pq_partial[blockIdx.x] = dot;
         return;
     }
-    constexpr int kV = 2;
-    typedef double V __attribute__((ext_vector_type(kV)));
+    constexpr int kV = 16 / (int)sizeof(T);
+    typedef T V __attribute__((ext_vector_type(kV)));
+    const T* __restrict__ S = (const T*)Sv;
     double acc[kReducedRows];
 #pragma unroll
     for (int u = 0; u < kReducedRows; ++u) acc[u] = 0.0;
@@ -720,7 +726,7 @@ __global__ __launch_bounds__(kReducedProductBlock) void k_reduced_product(Kernel
                 const bool in = c + v < n;
                 const double zv = in ? (double)z[c + v] : 0.0;
 #pragma unroll
-                for (int u = 0; u < kReducedRows; ++u) acc[u] += (in ? s[u][v] : 0.0) * zv;
+                for (int u = 0; u < kReducedRows; ++u) acc[u] += (in ? (double)s[u][v] : 0.0) * zv;
             }
         }
     }
@@ -744,7 +750,8 @@ hipError_t launch_reduced_build(const DeviceGraph& g, size_t rank_total, size_t 
         hipLaunchKernelGGL(k_pair_lists<false>, grid, dim3(256), 0, s, g);
         hipLaunchKernelGGL(k_pair_scan, dim3(1), dim3(1024), 0, s, g);
         hipLaunchKernelGGL(k_pair_lists<true>, grid, dim3(256), 0, s, g);
-        const hipError_t e = launch_fill_f64(g.xs_S, 0.0, s_total, s);
+        // (an even number of FP32 entries: whole padded columns)
+        const hipError_t e = launch_fill_f64((double*)g.xs_S, 0.0, g.mode == kModeFP64 ? s_total : s_total / 2, s);
         if (e != hipSuccess) return e;
     }
     return hipGetLastError();
@@ -788,7 +795,8 @@ hipError_t launch_reduced_product(const DeviceGraph& g0, hipStream_t s, int max_
     g.pcg_ratio = ratio;
     // (one problem: its S is the whole of xs_S)
     const dim3 grid(g0.xs_rows), block(kReducedProductBlock);
-    const double *S = g0.xs_S, *D = g0.xs_diag;
+    const void* S = g0.xs_S;
+    const double* D = g0.xs_diag;
     if (g.mode == kModeFP64) hipLaunchKernelGGL(k_reduced_product<double>, grid, block, 0, s, g, S, D);
     else hipLaunchKernelGGL(k_reduced_product<float>, grid, block, 0, s, g, S, D);
     return hipGetLastError();

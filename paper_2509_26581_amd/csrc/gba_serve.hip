@@ -744,7 +744,7 @@ gba_status gba_server_submit(gba_server* s, const gba_problem* q, uint64_t* tick
         // the explicit reduced system only where the request fits the budget
         // with it (decided by the request alone, so that its arithmetic does
         // not depend on its batch mates)
-        r->counts.reduced = reduced_rule(r->counts, s->tune) &&
+        r->counts.reduced = reduced_rule(r->counts, s->tune, s->cfg.precision) &&
                             reduced_pays(r->counts, s->cfg.precision, s->cfg.options);
         need = r->lay.bytes + s->union_bytes_for(one);
         if (need > s->cfg.hbm_budget_bytes && r->counts.reduced) {

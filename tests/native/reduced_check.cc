@@ -132,9 +132,10 @@ static void check_point_side() {
     }
 }
 
-// Which problems take which form: one workgroup's PCG up to 28 cameras,
-// launched iterations on S above (the one-workgroup form is the slower one
-// there), the launched products where S or its forming costs too much.
+// Which problems take which form: one workgroup's PCG up to 28 cameras (FP64)
+// or 56 (mixed), for a single problem of more than 28 or 32 launched iterations
+// on S (the one-workgroup form is the slower one there), the launched products
+// where S or its forming costs too much.
 static ImageCounts counts(int nc, int np, int ne, long long pairs) {
     ImageCounts n;
     n.free_cams = nc - 1;
@@ -148,16 +149,17 @@ static ImageCounts counts(int nc, int np, int ne, long long pairs) {
 static void check_rules() {
     const Tuning t;
     for (int prec : {GBA_FP64, GBA_MIXED_FP32, GBA_MIXED_BF16})
-        for (int nc = 2; nc <= 300; ++nc) {
+        for (int nc = 2; nc <= 400; ++nc) {
             const ImageCounts n = counts(nc, 20 * nc, 100 * nc, 200 * nc);
-            CHECK(reduced_rule(n, t) == (nc <= 28));
-            CHECK(reduced_wide_rule(n, t, prec) == (nc > 28 && nc <= 248));
+            CHECK(reduced_rule(n, t, prec) == (nc <= (prec == GBA_FP64 ? 28 : 56)));
+            CHECK(reduced_wide_rule(n, t, prec) ==
+                  (prec == GBA_FP64 ? nc > 28 && nc <= 248 : nc > 32 && nc <= 348));
         }
     // few cameras with many edges: forming S would cost more than the PCG
     for (int nc : {2, 3, 8, 28})
         for (int per : {1'000, 4'000, 6'000, 19'000, 21'000, 200'000}) {
             const ImageCounts n = counts(nc, per, nc * per, per);
-            CHECK(reduced_rule(n, t) == (per <= (nc == 2 ? 5'000 : 20'000)));
+            CHECK(reduced_rule(n, t, GBA_FP64) == (per <= (nc == 2 ? 5'000 : 20'000)));
         }
 }
 
@@ -172,6 +174,7 @@ static void check_pays() {
     for (int prec : {GBA_FP64, GBA_MIXED_FP32})
         for (int k = 0; k < 3; ++k) {
             ImageCounts n = counts(nc[k], 1'000, ne[k], pairs[k]);
+            n.wide = true;
             o.pcg_max_iters = 100;
             o.pcg_tol = 1e-6;
             CHECK(reduced_pays(n, prec, o));

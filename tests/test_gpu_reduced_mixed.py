@@ -1,7 +1,7 @@
 """Mixed modes on the explicit reduced camera system: its sums, products and
 vectors are FP64 (the launched products' camera sums are too), so a step's
-error against the FP64 mode is that of the FP32 inputs (stored Jacobians,
-point inverses, right-hand side)."""
+error against the FP64 mode is that of what is stored in FP32 (Jacobians,
+point inverses, off-diagonal blocks of S, right-hand side)."""
 import numpy as np
 import pytest
 
@@ -45,6 +45,32 @@ def test_sums_over_many_common_points(n_cams, n_pts):
     err = [np.linalg.norm(_cam_step(sc, gba.GBA_MIXED_FP32, acc, 12) - want)
            for acc in (gba.GBA_ACC_AUTO, gba.GBA_ACC_LDS)]
     assert err[0] <= 0.2 * err[1], err
+
+
+@pytest.mark.parametrize("precision", [gba.GBA_MIXED_FP32, gba.GBA_MIXED_BF16])
+def test_served_requests_of_one_workgroup(precision):
+    # the edges of the classes (14, 28 and 56 keyframes) and of a row wavefront
+    # in one batch; the bound is the mixed policy's own on solutions
+    reqs = []
+    for n in (14, 15, 28, 29, 42, 43, 56, 57):
+        sc = synth.make_scene("small", seed=n, n_cams=n, n_pts=40 * n, layout="sphere")
+        fixed = np.zeros(n, bool)
+        fixed[0] = True
+        reqs.append({"cams": sc.cams0, "pts": sc.pts0, "cam_idx": sc.cam_idx, "pt_idx": sc.pt_idx, "uv": sc.obs,
+                     "cam_fixed": fixed, "max_iters": 1})
+    got = []
+    for acc in (gba.GBA_ACC_AUTO, gba.GBA_ACC_LDS):
+        s = gba.Server(precision=precision, budget_bytes=1 << 30, max_slots=8, pcg_max_iters=4, pcg_tol=0.0,
+                       initial_lambda=1e-3, accumulation=acc)
+        try:
+            got.append([s.poll(t) for t in [s.submit(r) for r in reqs]])
+        finally:
+            s.close()
+    for r, a, b in zip(reqs, *got):
+        assert a["report"]["accepted"] == b["report"]["accepted"] == 1
+        assert a["report"]["pcg_iters_total"] == b["report"]["pcg_iters_total"] == 4
+        for k in ("cams", "pts"):
+            assert np.linalg.norm(a[k] - b[k]) <= 1e-3 * np.linalg.norm(b[k] - r[k])
 
 
 def test_points_with_nearly_parallel_rays():
