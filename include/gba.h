@@ -179,7 +179,9 @@ typedef struct gba_options {
                                   camera system S formed explicitly once a
                                   step (GBA_ACC_AUTO, Schur solver, block
                                   Jacobi, no camera that observes a point
-                                  twice): up to 28 cameras (mixed modes: 32,
+                                  twice; mixed modes: every point observed
+                                  by three cameras, since the place of one on
+                                  two near-parallel rays follows rounding): up to 28 cameras (mixed modes: 32,
                                   and 56 where several problems share a batch)
                                   the whole PCG is one workgroup's single
                                   launch, above (one problem, up to 248

@@ -42,6 +42,7 @@ struct ImageCounts {
     long long pairs = 0;    // pairs of edges of one point
     int free_cams = 0;      // cameras that are not fixed
     int cam_edges = 0;      // edges of the camera with the most
+    int min_views = 0;      // edges of the point with the fewest (of those with edges)
 };
 
 // Whether a problem's explicit reduced system is formed (see gba_host.hip)

@@ -157,6 +157,7 @@ gba_status make_image(const HostProblem& h, HostImage& img, std::string& msg) {
             const int c = cnt[j + 1] - cnt[j];
             if (c == 0) continue;
             img.n.pairs += (long long)c * (c - 1) / 2;
+            img.n.min_views = img.n.min_views == 0 ? c : std::min(img.n.min_views, c);
             if (c > kTileEdges) {
                 if (cur > 0) {
                     img.tile_off.push_back(img.tile_off.back() + cur);
@@ -251,10 +252,24 @@ gba_status make_image(const HostProblem& h, HostImage& img, std::string& msg) {
 }
 
 // ---------------------------------------------------------------- planning
+// In the mixed modes S is formed only where every point has three edges.  Where
+// two nearly parallel rays are all there is, a point runs off along them, and in
+// FP32 its place then follows the rounding of every camera step: on whole solves
+// the two forms, and any two orders of the launched products' own sums, end up
+// 1e-5 to 0.5 of the points' norm apart, each as far from a 64-bit solve (2 of
+// 16 scenes of 203 cameras, 30,011 points and tracks of two and more; 5 of 16
+// bursts of 48 local requests, whose tracks are two to ten; of 20 scenes of 8 to
+// 192 cameras none differ by more than 1e-8).  Such solves keep the launched
+// products' results.
+static bool rays_fix_points(const ImageCounts& n, int precision) {
+    return precision == GBA_FP64 || n.min_views >= 3;
+}
+
 // The explicit reduced system (gba_reduced.hip): when the camera sums are
 // left to the library, the points are eliminated, no camera observes a point
-// twice (the rank bitmaps hold one edge per camera and point) and S has at
-// most reduced_max rows.  A launched PCG iteration takes 14-16 us for small
+// twice (the rank bitmaps hold one edge per camera and point), S has at most
+// reduced_max rows and the mode's rounding leaves the points where they are
+// (above).  A launched PCG iteration takes 14-16 us for small
 // problems whatever their size; one workgroup's iteration on S takes 1.6 us at
 // 12 cameras, 4.4 at 18 and 6.6 at 28 (FP64: S then comes from the L2 in part).
 // Past 28 cameras one CU's reads of S set the pace: in FP64, whole solves at 32,
@@ -271,6 +286,7 @@ gba_status make_image(const HostProblem& h, HostImage& img, std::string& msg) {
 // 0.8-1.0 at 10,000 (0.2 at 200,000).
 bool reduced_rule(const ImageCounts& n, const Tuning& tune, int precision) {
     if (tune.accumulation != GBA_ACC_AUTO || tune.deterministic || tune.solver == GBA_SOLVER_FULL) return false;
+    if (!rays_fix_points(n, precision)) return false;
     return n.nc > 0 && n.ne > 0 && n.n_runs == n.ne && 9 * n.nc <= reduced_max(precision) &&
            n.cam_edges <= (n.free_cams > 1 ? 20'000 : 5'000);
 }
@@ -289,6 +305,7 @@ bool reduced_rule(const ImageCounts& n, const Tuning& tune, int precision) {
 // pairs are bounded too.
 bool reduced_wide_rule(const ImageCounts& n, const Tuning& tune, int precision) {
     if (tune.accumulation != GBA_ACC_AUTO || tune.deterministic || tune.solver == GBA_SOLVER_FULL) return false;
+    if (!rays_fix_points(n, precision)) return false;
     if (n.nc <= 0 || n.ne <= 0 || n.n_runs != n.ne || n.nc <= (precision == GBA_FP64 ? 28 : 32)) return false;
     const long long word = precision == GBA_FP64 ? 8 : 4;
     return 9LL * n.nc * reduced_ld(9 * n.nc) * word <= 40'000'000 && n.pairs * word <= 12'000'000;

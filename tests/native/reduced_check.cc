@@ -140,6 +140,7 @@ static ImageCounts counts(int nc, int np, int ne, long long pairs) {
     ImageCounts n;
     n.free_cams = nc - 1;
     n.cam_edges = ne / nc;
+    n.min_views = 3;
     n.nc = nc;
     n.np = np;
     n.ne = n.n_runs = ne;
@@ -154,6 +155,13 @@ static void check_rules() {
             CHECK(reduced_rule(n, t, prec) == (nc <= (prec == GBA_FP64 ? 28 : 56)));
             CHECK(reduced_wide_rule(n, t, prec) ==
                   (prec == GBA_FP64 ? nc > 28 && nc <= 248 : nc > 32 && nc <= 348));
+        }
+    // points of two rays: FP64 only
+    for (int prec : {GBA_FP64, GBA_MIXED_FP32, GBA_MIXED_BF16})
+        for (int nc : {10, 60, 200}) {
+            ImageCounts n = counts(nc, 20 * nc, 100 * nc, 200 * nc);
+            n.min_views = 2;
+            CHECK((reduced_rule(n, t, prec) || reduced_wide_rule(n, t, prec)) == (prec == GBA_FP64));
         }
     // few cameras with many edges: forming S would cost more than the PCG
     for (int nc : {2, 3, 8, 28})

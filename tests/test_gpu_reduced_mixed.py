@@ -74,7 +74,7 @@ def test_served_requests_of_one_workgroup(precision):
 
 
 def test_points_with_nearly_parallel_rays():
-    # Half of the points are seen by two cameras a 25,000th of the depth apart
+    # Half of the points are seen by three cameras a 25,000th of the depth apart
     # only, at a damping of 1e-6: their inverse blocks are known to a few per
     # cent in FP32 (the launched products' two orders give costs 5e-4 apart).
     # The off-diagonal blocks hold the same inverses as the diagonal ones, so
@@ -84,16 +84,17 @@ def test_points_with_nearly_parallel_rays():
     n_cams, n_pts = 60, 4000
     sc = synth.make_scene("small", seed=5, n_cams=n_cams, n_pts=n_pts, layout="sphere")
     cams = sc.cams_true.copy()
-    cams[1::2] = cams[::2]
-    cams[1::2, 3:6] += rng.normal(0.0, 1e-3, (n_cams // 2, 3))
-    first = 2 * rng.integers(n_cams // 2, size=n_pts // 2)
-    ci = [np.stack([first, first + 1], 1).ravel()]
+    for k in (1, 2):
+        cams[k::3] = cams[::3]
+        cams[k::3, 3:6] += rng.normal(0.0, 1e-3, (n_cams // 3, 3))
+    first = 3 * rng.integers(n_cams // 3, size=n_pts // 2)
+    ci = [np.stack([first, first + 1, first + 2], 1).ravel()]
     ci += [rng.choice(n_cams, 6, replace=False) for _ in range(n_pts - n_pts // 2)]
     ci = np.concatenate(ci)
-    pi = np.repeat(np.arange(n_pts), np.where(np.arange(n_pts) < n_pts // 2, 2, 6))
+    pi = np.repeat(np.arange(n_pts), np.where(np.arange(n_pts) < n_pts // 2, 3, 6))
     X = rng.uniform(-5.0, 5.0, (n_pts, 3))
     uv = camera.residuals(cams, X, ci, pi, np.zeros((len(ci), 2))) + rng.normal(0.0, 0.5, (len(ci), 2))
-    d = np.repeat(rng.normal(0.0, 1e-3, (n_cams // 2, 3)), 2, axis=0)
+    d = np.repeat(rng.normal(0.0, 1e-3, (n_cams // 3, 3)), 3, axis=0)
     cams0, pts0 = cams.copy(), X + rng.normal(0.0, 1e-2, X.shape)
     cams0[:, 3:6] += d
     reps = []
