@@ -177,6 +177,11 @@ struct Batch {
     bool use_graphs = false;
     bool pcg_warm = false;          // one eager chunk ran (kernel attributes set)
     hipStream_t cap_stream = nullptr;   // capture only (the null stream cannot be captured)
+    // the one-workgroup PCGs of a batch that has other problems too, beside
+    // those problems' launched iterations
+    hipStream_t side = nullptr;
+    hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    hipError_t ensure_side();
     struct PcgGraph {
         hipGraphExec_t exec = nullptr;
         int iters = 0, max_iters = 0;

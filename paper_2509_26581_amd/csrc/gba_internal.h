@@ -399,6 +399,7 @@ hipError_t launch_reduced_form(const DeviceGraph& g, hipStream_t s);
 constexpr int kReducedRows = 8;
 inline int reduced_row_blocks(int n) { return (n + kReducedRows - 1) / kReducedRows; }
 hipError_t launch_reduced_product(const DeviceGraph& g, hipStream_t s, int max_iters, double reject_ratio);
+hipError_t launch_pcg_reduced_mark(const DeviceGraph& g, hipStream_t s);
 hipError_t launch_pcg_reduced(const DeviceGraph& g, hipStream_t s, double tol, int relative, int max_iters,
                               double reject_ratio);
 hipError_t launch_backsub(const DeviceGraph& g, hipStream_t s);

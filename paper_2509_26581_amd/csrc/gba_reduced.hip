@@ -802,6 +802,22 @@ hipError_t launch_reduced_product(const DeviceGraph& g0, hipStream_t s, int max_
     return hipGetLastError();
 }
 
+// The problems with a one-workgroup PCG are stopped ones to launched iterations
+// that run beside it (their decision reads `done` alone, which stays nonzero).
+__global__ __launch_bounds__(64) void k_pcg_reduced_mark(DeviceGraph g) {
+    const int prob = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (prob >= g.n_probs || g.xs_off[prob] < 0) return;
+    g.pcg[prob].done = 1;
+    g.pcg[prob].act = 0;
+    g.pcg_dec[prob].act = 0;
+}
+
+hipError_t launch_pcg_reduced_mark(const DeviceGraph& g, hipStream_t s) {
+    if (!g.xs_on) return hipSuccess;
+    hipLaunchKernelGGL(k_pcg_reduced_mark, dim3((g.n_probs + 63) / 64), dim3(64), 0, s, g);
+    return hipGetLastError();
+}
+
 hipError_t launch_pcg_reduced(const DeviceGraph& g0, hipStream_t s, double tol, int relative, int max_iters,
                               double ratio) {
     if (!g0.xs_on) return hipSuccess;
