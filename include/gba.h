@@ -180,8 +180,11 @@ typedef struct gba_options {
                                   step (GBA_ACC_AUTO, Schur solver, block
                                   Jacobi, no camera that observes a point
                                   twice; mixed modes: every point observed
-                                  by three cameras, since the place of one on
-                                  two near-parallel rays follows rounding): up to 28 cameras (mixed modes: 32,
+                                  by three cameras, or at most 20 cameras and
+                                  the rays of a point of two at least 0.57
+                                  degrees apart at the start, since the place
+                                  of one on two near-parallel rays follows
+                                  rounding): up to 28 cameras (mixed modes: 32,
                                   and 56 where several problems share a batch)
                                   the whole PCG is one workgroup's single
                                   launch, above (one problem, up to 248

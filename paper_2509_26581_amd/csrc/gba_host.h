@@ -33,6 +33,8 @@ struct HostProblem {
     bool any_free() const;
 };
 
+constexpr int kRayCams = 20;
+
 // Counts of one problem's image.
 struct ImageCounts {
     int nc = 0, np = 0, ne = 0, n_tiles = 0, n_runs = 0, n_chunks = 0;
@@ -43,6 +45,9 @@ struct ImageCounts {
     int free_cams = 0;      // cameras that are not fixed
     int cam_edges = 0;      // edges of the camera with the most
     int min_views = 0;      // edges of the point with the fewest (of those with edges)
+    // up to kRayCams cameras: least squared sine between the rays of a point of
+    // two edges, at the parameters the image was made from (1: no such point)
+    double ray_sin2 = 1.0;
 };
 
 // Whether a problem's explicit reduced system is formed (see gba_host.hip)

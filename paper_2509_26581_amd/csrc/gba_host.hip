@@ -128,6 +128,28 @@ Timers::~Timers() {
 }
 
 // ---------------------------------------------------------------- images
+// Centre -R^T t of a camera (rotation vector, translation first).
+static void camera_centre(const double* cam, double* c) {
+    const double w2 = cam[0] * cam[0] + cam[1] * cam[1] + cam[2] * cam[2], th = std::sqrt(w2);
+    const double a = th > 1e-8 ? std::sin(th) / th : 1.0, b = th > 1e-8 ? (1.0 - std::cos(th)) / w2 : 0.5;
+    const double *w = cam, *t = cam + 3;
+    const double wt = w[0] * t[0] + w[1] * t[1] + w[2] * t[2];
+    // R^T t = t - a (w x t) + b (w x (w x t))
+    const double x[3] = {w[1] * t[2] - w[2] * t[1], w[2] * t[0] - w[0] * t[2], w[0] * t[1] - w[1] * t[0]};
+    for (int k = 0; k < 3; ++k) c[k] = -(t[k] - a * x[k] + b * (w[k] * wt - w2 * t[k]));
+}
+
+// Squared sine of the angle at X between the rays from two centres (0 for
+// coinciding or non-finite ones).
+static double ray_sin2(const double* X, const double* c1, const double* c2) {
+    const double u[3] = {X[0] - c1[0], X[1] - c1[1], X[2] - c1[2]};
+    const double v[3] = {X[0] - c2[0], X[1] - c2[1], X[2] - c2[2]};
+    const double x[3] = {u[1] * v[2] - u[2] * v[1], u[2] * v[0] - u[0] * v[2], u[0] * v[1] - u[1] * v[0]};
+    const double n = (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]) * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+    const double s = (x[0] * x[0] + x[1] * x[1] + x[2] * x[2]) / n;
+    return s > 0.0 ? s : 0.0;
+}
+
 gba_status make_image(const HostProblem& h, HostImage& img, std::string& msg) {
     img = HostImage{};
     const int nc = h.nc(), np = h.np();
@@ -164,12 +186,21 @@ gba_status make_image(const HostProblem& h, HostImage& img, std::string& msg) {
     // tiles of whole points (<= 64 edges) or one long point
     img.tile_off.push_back(0);
     {
+        std::vector<double> centre;
+        if (nc <= kRayCams) {
+            centre.resize(3 * (size_t)nc);
+            for (int i = 0; i < nc; ++i) camera_centre(&h.cam_params[9 * (size_t)i], &centre[3 * (size_t)i]);
+        }
         int cur = 0;
         for (int j = 0; j < np; ++j) {
             const int c = cnt[j + 1] - cnt[j];
             if (c == 0) continue;
             img.n.pairs += (long long)c * (c - 1) / 2;
             img.n.min_views = img.n.min_views == 0 ? c : std::min(img.n.min_views, c);
+            if (c == 2 && nc <= kRayCams)
+                img.n.ray_sin2 = std::min(img.n.ray_sin2,
+                                          ray_sin2(&h.pt_params[3 * (size_t)j], &centre[3 * (size_t)img.e_cam[cnt[j]]],
+                                                   &centre[3 * (size_t)img.e_cam[cnt[j] + 1]]));
             if (c > kTileEdges) {
                 if (cur > 0) {
                     img.tile_off.push_back(img.tile_off.back() + cur);
@@ -264,17 +295,24 @@ gba_status make_image(const HostProblem& h, HostImage& img, std::string& msg) {
 }
 
 // ---------------------------------------------------------------- planning
-// In the mixed modes S is formed only where every point has three edges.  Where
-// two nearly parallel rays are all there is, a point runs off along them, and in
-// FP32 its place then follows the rounding of every camera step: on whole solves
-// the two forms, and any two orders of the launched products' own sums, end up
-// 1e-5 to 0.5 of the points' norm apart, each as far from a 64-bit solve (2 of
-// 16 scenes of 203 cameras, 30,011 points and tracks of two and more; 5 of 16
-// bursts of 48 local requests, whose tracks are two to ten; of 20 scenes of 8 to
-// 192 cameras none differ by more than 1e-8).  Such solves keep the launched
+// In the mixed modes S is formed only where the points' places don't hang on
+// rounding.  Where two nearly parallel rays are all there is, a point runs off
+// along them, and in FP32 its place then follows the rounding of every camera
+// step: on whole solves the two forms, and any two orders of the launched
+// products' own sums, end up 1e-5 to 0.5 of the points' norm apart, each as far
+// from a 64-bit solve (2 of 16 scenes of 203 cameras, 30,011 points and tracks of
+// two and more; 5 of 16 bursts of 48 local requests of 5 to 40 keyframes and
+// tracks of two to ten).  So every point has three edges (52 solves of 7 to 273
+// cameras: at most 6e-9 apart), or there are at most kRayCams cameras and the
+// rays of every point of two edges are 0.57 degrees apart, squared sine 1e-4, at
+// the start (of 266 requests of up to 20 keyframes six had points that ran off,
+// which began at 2.6e-6 to 8.5e-5; 78% of such requests pass, and 64 that do end
+// at most 6e-7 apart; windows of more keyframes end a trial's PCG at its limit
+// and are 1e-5 apart without such points).  Other solves keep the launched
 // products' results.
 static bool rays_fix_points(const ImageCounts& n, int precision) {
-    return precision == GBA_FP64 || n.min_views >= 3;
+    if (precision == GBA_FP64 || n.min_views >= 3) return true;
+    return n.min_views == 2 && n.nc <= kRayCams && n.ray_sin2 >= 1e-4;
 }
 
 // The explicit reduced system (gba_reduced.hip): when the camera sums are
@@ -948,13 +986,11 @@ gba_status batch_damped_step(Batch& b, const gba_options& o, const Tuning& tune,
                          !b.launched_products && (b.P > 1 || reduced_pays(b.plan.one, d.mode, o));
     const bool wide = reduced && d.xs_wide;
     if (!reduced || !d.xs_all || wide) HIP_OR(msg, launch_pcg_init(d, s, o.pcg_tol, o.pcg_tol_relative));
-    if (reduced) {
-        if (!b.reduced_built)
-            HIP_OR(msg, launch_reduced_build(d, (size_t)b.plan.xs_rank_total, (size_t)b.plan.xs_total, s));
+    if (reduced && !b.reduced_built) {
+        HIP_OR(msg, launch_reduced_build(d, (size_t)b.plan.xs_rank_total, (size_t)b.plan.xs_total, s));
         b.reduced_built = true;
-        HIP_OR(msg, launch_reduced_form(d, s));
     }
-    // In a batch with other problems the one-workgroup PCGs run beside those
+    // In a batch with other problems S is formed and its PCGs run beside those
     // problems' launched iterations, which take them for stopped: each leaves
     // most of the CUs idle and is a chain of its own.  (One after the other, 12
     // FP64 requests of 5 to 40 keyframes took 39.8 ms, 36.2 with launched
@@ -968,6 +1004,7 @@ gba_status batch_damped_step(Batch& b, const gba_options& o, const Tuning& tune,
         HIP_OR(msg, hipStreamWaitEvent(b.side, b.ev_fork, 0));
         rs = b.side;
     }
+    if (reduced) HIP_OR(msg, launch_reduced_form(d, rs));
     if (reduced && !wide)
         HIP_OR(msg, launch_pcg_reduced(d, rs, o.pcg_tol, o.pcg_tol_relative, o.pcg_max_iters,
                                        o.pcg_rejection_ratio));

@@ -156,19 +156,71 @@ static void check_rules() {
             CHECK(reduced_wide_rule(n, t, prec) ==
                   (prec == GBA_FP64 ? nc > 28 && nc <= 248 : nc > 32 && nc <= 348));
         }
-    // points of two rays: FP64 only
+    // points of two rays in the mixed modes: few cameras and rays apart only;
+    // of one ray never
     for (int prec : {GBA_FP64, GBA_MIXED_FP32, GBA_MIXED_BF16})
-        for (int nc : {10, 60, 200}) {
-            ImageCounts n = counts(nc, 20 * nc, 100 * nc, 200 * nc);
-            n.min_views = 2;
-            CHECK((reduced_rule(n, t, prec) || reduced_wide_rule(n, t, prec)) == (prec == GBA_FP64));
-        }
+        for (int nc : {10, 20, 21, 60, 200})
+            for (int views : {1, 2})
+                for (double sin2 : {0.0, 0.9e-4, 1.1e-4}) {
+                    ImageCounts n = counts(nc, 20 * nc, 100 * nc, 200 * nc);
+                    n.min_views = views;
+                    n.ray_sin2 = sin2;
+                    CHECK((reduced_rule(n, t, prec) || reduced_wide_rule(n, t, prec)) ==
+                          (prec == GBA_FP64 || (views == 2 && nc <= 20 && sin2 > 1e-4)));
+                }
     // few cameras with many edges: forming S would cost more than the PCG
     for (int nc : {2, 3, 8, 28})
         for (int per : {1'000, 4'000, 6'000, 19'000, 21'000, 200'000}) {
             const ImageCounts n = counts(nc, per, nc * per, per);
             CHECK(reduced_rule(n, t, GBA_FP64) == (per <= (nc == 2 ? 5'000 : 20'000)));
         }
+}
+
+// The rays' least squared sine and the fewest views, as an image counts them.
+static void check_rays() {
+    // cameras at known centres, turned arbitrarily: t = -R c
+    std::mt19937_64 rng(2);
+    std::normal_distribution<double> nrm;
+    for (int it = 0; it < 200; ++it) {
+        HostProblem h;
+        const double off[2] = {std::pow(10.0, -3.0 + 3.0 * (it / 200.0)), 5.0};
+        const double centre[3][3] = {{0, 0, 0}, {off[0], 0, 0}, {0, off[1], 0}};
+        for (auto& c : centre) {
+            const double w[3] = {it ? nrm(rng) : 0.0, it ? nrm(rng) : 0.0, it ? nrm(rng) : 0.0};
+            const double th = std::sqrt(w[0] * w[0] + w[1] * w[1] + w[2] * w[2]);
+            const double k[3] = {th ? w[0] / th : 1, th ? w[1] / th : 0, th ? w[2] / th : 0};
+            const double kc = k[0] * c[0] + k[1] * c[1] + k[2] * c[2];
+            const double x[3] = {k[1] * c[2] - k[2] * c[1], k[2] * c[0] - k[0] * c[2], k[0] * c[1] - k[1] * c[0]};
+            for (double v : w) h.cam_params.push_back(v);
+            for (int a = 0; a < 3; ++a)
+                h.cam_params.push_back(-(c[a] * std::cos(th) + x[a] * std::sin(th) + k[a] * kc * (1 - std::cos(th))));
+            for (double v : {500.0, 0.0, 0.0}) h.cam_params.push_back(v);
+            h.cam_fixed.push_back(0);
+        }
+        const double pts[3][3] = {{0, 0, 10}, {0, 0, 10}, {1, 1, 8}};
+        for (auto& p : pts) {
+            for (double v : p) h.pt_params.push_back(v);
+            h.pt_fixed.push_back(0);
+        }
+        // point 0: cameras 0 and 1; point 1: 0 and 2; point 2: all (not counted)
+        const int ec[] = {1, 0, 2, 0, 0, 1, 2}, ep[] = {0, 0, 1, 1, 2, 2, 2};
+        for (int e = 0; e < 7; ++e) {
+            h.e_cam.push_back(ec[e]);
+            h.e_pt.push_back(ep[e]);
+            h.e_uv.push_back(0.0);
+            h.e_uv.push_back(0.0);
+            h.e_active.push_back(1);
+        }
+        h.cam_init = h.cam_params;
+        h.pt_init = h.pt_params;
+        HostImage img;
+        std::string msg;
+        CHECK(make_image(h, img, msg) == GBA_OK);
+        const double least = off[0] < off[1] ? off[0] : off[1];
+        const double want = least * least / (least * least + 100.0);
+        CHECK(img.n.min_views == 2);
+        CHECK(std::fabs(img.n.ray_sin2 - want) <= 1e-9 * want + 1e-20);
+    }
 }
 
 // S is formed where a step's iterations pay for it: not at a small iteration
@@ -278,6 +330,7 @@ int main() {
     CHECK(sizeof(KernelGraph) <= 848 && sizeof(DeviceGraph) > sizeof(KernelGraph));
     check_point_side();
     check_rules();
+    check_rays();
     check_pays();
     if (g_fail) {
         std::fprintf(stderr, "%d checks failed\n", g_fail);
