@@ -324,9 +324,10 @@ static bool rays_fix_points(const ImageCounts& n, int precision) {
 // 12 cameras, 4.4 at 18 and 6.6 at 28 (FP64: S then comes from the L2 in part).
 // Past 28 cameras one CU's reads of S set the pace: in FP64, whole solves at 32,
 // 40 and 48 cameras are 1.0, 0.85 and 0.73 times as fast as with launched
-// iterations.  The mixed modes read half the bytes: served requests of 29, 40,
-// 48 and 56 keyframes are 2.2, 1.7, 1.4 and 1.25 times as fast as with launched
-// iterations.  A single problem has launched iterations on S as well (below).
+// iterations.  The mixed modes read half the bytes: requests of 18, 29, 40 and
+// 56 cameras with three-view tracks (100 points a camera) are 2.6, 1.7, 1.4 and
+// 1.1 times as fast as with launched iterations.  A single problem has launched
+// iterations on S as well (below).
 // A block of S is one workgroup's walk over its first camera's edges, 6.5 ns
 // (mixed) to 8 ns (FP64) an edge, so few cameras with many edges are bounded
 // too: four-trial solves at 2,000, 10,000, 16,000 and 24,000 edges a camera are

@@ -635,9 +635,9 @@ __device__ __forceinline__ void pcg_reduced_body(const DeviceGraph& g, const int
 // registers, as FP64 in every mode, and the rest streamed from the L2.  More or
 // fewer registers and FP32 in them were slower: FP64, 16 and 24 cameras, whole
 // solves of 4,800 points, 24 and 40 columns 1.01 and 1.27, 1.05 and 1.25 ms
-// against 0.90 and 1.18; mixed, a served request of 40 keyframes, 24, 32, 40 and
-// 48 columns 10.5, 10.2, 11.0 and 12.3 ms; of 18 keyframes, whose products then
-// convert every entry in every iteration, FP32 registers 4.9 against 2.6.  kBig:
+// against 0.90 and 1.18; mixed, whole solves of a window of 40 cameras, 24, 32,
+// 40 and 48 columns 10.5, 10.2, 11.0 and 12.3 ms; of 18 cameras, whose products
+// then convert every entry in every iteration, FP32 registers 4.9 against 2.6.  kBig:
 // the batch holds a problem above the first class.
 constexpr int kBigWaves = 8;
 template <typename T, bool kBig>
